@@ -124,7 +124,8 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         e = hipMalloc(&m->sp, sizeof(float) * m->sp_count());
         if (e == hipSuccess) e = hipMalloc(&m->sp_x, sizeof(uint16_t) * 3 * m->sp_xs());
     }
-    if (e == hipSuccess) e = hipMalloc(&m->wx, sizeof(uint16_t) * 6 * m->wx_stride());
+    // below width 64 no product has a K that the split-bfloat16 kernels take
+    if (e == hipSuccess && d.width >= 64) e = hipMalloc(&m->wx, sizeof(uint16_t) * 6 * m->wx_stride());
     if (e != hipSuccess) {
         (void)hipFree(m->w);
         if (m->tab) (void)hipFree(m->tab);
@@ -311,7 +312,7 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
             b.gUV = a.take<float>(n * 6 * F);
             b.gphi = a.take<float>(n * 3 * F);
             b.gh1 = a.take<float>(n * F);
-            const int64_t maxNK = std::max<int64_t>({3 * F * F, HC * F, 2 * F * F});
+            const int64_t maxNK = std::max<int64_t>({3 * F * F, HC * F, 3 * F * S});
             b.chunk_part = a.take<float>(int64_t(cdiv(3 * n, kChunk) + 1) * maxNK);
             b.mp_part = a.take<float>(int64_t(mp_blocks(int(n), int(F))) * 3 * F * (m->desc.n_rbf + 1));
             b.filt_sum = a.take<float>(3 * F * (m->desc.n_rbf + 1));
@@ -514,13 +515,13 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
             // differentiate the table; the embedding gets the pass-through
             // adjoint of s plus the perceptron path.
             const int S = m->desc.n_species;
-            launch_emb_grad(n, 3 * F, S, mg.species, b.gphi, b.gphi_tab, s);
+            launch_emb_grad(n, 3 * F, S, mg.species, b.gphi, b.gphi_tab, b.chunk_part, kChunk, s);
             gemm_wgrad(S, 3 * F, F, b.gphi_tab, 3 * F, b.z_tab, F, dtheta + lo.W2, b.chunk_part, kChunk, false, s);
             colsum(S, 3 * F, b.gphi_tab, 3 * F, dtheta + lo.b2, b.chunk_part, kChunk, false, s);
             gemm_gw(S, 3 * F, F, b.gphi_tab, 3 * F, m->p(lo.W2), b.gh1_tab, F, EPI_DSILU, b.h1_tab, F, false, s);
             gemm_wgrad(S, F, F, b.gh1_tab, F, m->p(m->off_emb), F, dtheta + lo.W1, b.chunk_part, kChunk, false, s);
             colsum(S, F, b.gh1_tab, F, dtheta + lo.b1, b.chunk_part, kChunk, false, s);
-            launch_emb_grad(n, F, S, mg.species, b.gs2, dtheta + m->off_emb, s);
+            launch_emb_grad(n, F, S, mg.species, b.gs2, dtheta + m->off_emb, b.chunk_part, kChunk, s);
             gemm_gw(S, F, F, b.gh1_tab, F, m->p(lo.W1), dtheta + m->off_emb, F, EPI_NONE, nullptr, 0, true, s);
         }
         return;
@@ -995,12 +996,14 @@ __global__ void __launch_bounds__(256) k_force_mse(int64_t count, const float* _
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
-__global__ void k_sum_parts(int nparts, const double* __restrict__ part, int64_t count, double* __restrict__ loss) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int k = 0; k < nparts; ++k) s += part[k];
-        *loss = s / double(count);
-    }
+// one wavefront: lane l adds parts l, l + 64, ..., then a fixed tree
+__global__ void __launch_bounds__(64) k_sum_parts(int nparts, const double* __restrict__ part, int64_t count,
+                                                  double* __restrict__ loss) {
+    double s = 0.0;
+    for (int k = threadIdx.x; k < nparts; k += 64) s += part[k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) *loss = s / double(count);
 }
 }  // namespace nnp
 

@@ -155,16 +155,38 @@ __global__ void __launch_bounds__(256) k_rep_sum(const int64_t* __restrict__ rep
     if (threadIdx.x == 0) out[r] = red[0];
 }
 
-// Per-species column sums: out[t][f] = sum over atoms of species t of x[i][f]
-// (fixed order), for the adjoints of per-species tables.
-__global__ void k_emb_grad(int n, int F, int S, const int* __restrict__ species, const float* __restrict__ gs0,
-                           float* __restrict__ gemb) {
-    const int t = blockIdx.x;  // species
-    for (int f = threadIdx.x; f < F; f += blockDim.x) {
-        float acc = 0.f;
-        for (int i = 0; i < n; ++i)
-            if (species[i] == t) acc += gs0[int64_t(i) * F + f];
-        gemb[t * F + f] = acc;
+// Per-species column sums over a chunk of rows, for the adjoints of
+// per-species tables: part[c][t][f] = sum over atoms of species t of x[i][f],
+// i in chunk c; launch_reduce_chunks adds the chunks (both in fixed order).
+// One block per chunk and 32 columns: thread (row group, column) walks every
+// eighth row of the chunk, reads of a row group being contiguous.  Bound by
+// the one read of x; one thread per (species, column) walking all rows was a
+// serial chain of n loads (4.95 ms per launch for 24,576 rows; with this kernel
+// and the reductions of gemm.hip a distillation step of those rows went from
+// 12.4 to 0.97 ms).
+__global__ void __launch_bounds__(256) k_emb_grad_part(int n, int F, int S, int chunk, const int* __restrict__ species,
+                                                       const float* __restrict__ x, float* __restrict__ part) {
+    __shared__ float red[8][8][32];  // row group, species, column
+    const int col = threadIdx.x & 31, rg = threadIdx.x >> 5;
+    const int f = blockIdx.x * 32 + col;
+    const int i0 = blockIdx.y * chunk, i1 = min(n, i0 + chunk);
+    float acc[8] = {};
+    if (f < F) {
+        for (int i = i0 + rg; i < i1; i += 8) {
+            const int sp = species[i];
+            const float v = x[int64_t(i) * F + f];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] += sp == t ? v : 0.f;
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) red[rg][t][col] = acc[t];
+    __syncthreads();
+    if (rg < S && f < F) {  // row group rg now adds species rg (S <= 8)
+        float s = 0.f;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) s += red[g][rg][col];
+        part[(int64_t(blockIdx.y) * S + rg) * F + f] = s;
     }
 }
 
@@ -966,9 +988,14 @@ void launch_rep_sum(int n_rep, const int64_t* rep_start, const float* x, double*
     k_rep_sum<<<n_rep, 256, 0, st>>>(rep_start, x, out);
     NNP_LAUNCH_CHECK();
 }
-void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, hipStream_t st) {
-    k_emb_grad<<<S, 128, 0, st>>>(n, F, S, species, gs0, gemb);
+void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,
+                     hipStream_t st) {
+    if (n <= 0) return;
+    const int nch = cdiv(n, chunk);
+    k_emb_grad_part<<<dim3(cdiv(F, 32), nch), 256, 0, st>>>(n, F, S, chunk, species, gs0, scratch);
     NNP_LAUNCH_CHECK();
+    const int64_t cnt = int64_t(S) * F;
+    launch_reduce_chunks(cnt, nch, scratch, cnt, gemb, false, st);
 }
 void launch_head_fwd(const MpGeom& mg, const float* QK, const float* Vh, float* F, bool accum, hipStream_t st,
                      float* vir_set, float* vir_add) {

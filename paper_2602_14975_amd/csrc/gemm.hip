@@ -638,13 +638,40 @@ void launch_transpose(int rows, int cols, const float* src, float* dst, hipStrea
 
 // Weight adjoint dW[N][K] += sum_m G[m][n] X[m][k], deterministic: chunks of
 // rows write partials that k_reduce_chunks adds in chunk order.
-__global__ void k_reduce_chunks(int64_t count, int nchunks, const float* __restrict__ part, int64_t stride,
-                                float* __restrict__ out, int accum) {
-    int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= count) return;
+// Sixteen row groups per output (thread (group, output)) so that the chain of
+// dependent adds is nchunks / 16 long: up to 1,536 partials of 864 outputs
+// made a chain of one load per chunk (65 us per launch).
+constexpr int kRedGroups = 16, kRedCols = 32;
+__global__ void __launch_bounds__(kRedGroups* kRedCols)
+k_reduce_chunks(int64_t count, int nchunks, const float* __restrict__ part, int64_t stride, float* __restrict__ out,
+                int accum) {
+    __shared__ float red[kRedGroups][kRedCols];
+    const int col = threadIdx.x % kRedCols, g = threadIdx.x / kRedCols;
+    const int64_t t = int64_t(blockIdx.x) * kRedCols + col;
     float s = 0.f;
-    for (int c = 0; c < nchunks; ++c) s += part[int64_t(c) * stride + t];
+    if (t < count) {
+        int c = g;
+        // four loads in flight, added in the same order as one at a time
+        for (; c + 3 * kRedGroups < nchunks; c += 4 * kRedGroups) {
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = part[int64_t(c + k * kRedGroups) * stride + t];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s += v[k];
+        }
+        for (; c < nchunks; c += kRedGroups) s += part[int64_t(c) * stride + t];
+    }
+    red[g][col] = s;
+    __syncthreads();
+    if (g != 0 || t >= count) return;
+    for (int k = 1; k < kRedGroups; ++k) s += red[k][col];
     out[t] = accum ? out[t] + s : s;
+}
+
+void launch_reduce_chunks(int64_t count, int nchunks, const float* part, int64_t stride, float* out, bool accum,
+                          hipStream_t s) {
+    k_reduce_chunks<<<cdiv(count, kRedCols), kRedGroups * kRedCols, 0, s>>>(count, nchunks, part, stride, out, accum);
+    NNP_LAUNCH_CHECK();
 }
 
 void gemm_wgrad(int M, int N, int K, const float* G, int ldg, const float* X, int ldx, float* dW, float* scratch,
@@ -659,19 +686,26 @@ void gemm_wgrad(int M, int N, int K, const float* G, int ldg, const float* X, in
     dim3 grid(cdiv(N, TM), cdiv(K, TN), nch);
     gemm_dispatch(g, grid, s);
     int64_t cnt = int64_t(N) * K;
-    k_reduce_chunks<<<cdiv(cnt, 256), 256, 0, s>>>(cnt, nch, scratch, cnt, dW, accum);
-    NNP_LAUNCH_CHECK();
+    launch_reduce_chunks(cnt, nch, scratch, cnt, dW, accum, s);
 }
 
-// Column sums db[n] (+)= sum_m G[m][n] in fixed order (chunks of rows).
-__global__ void k_colsum_partial(int M, int N, const float* __restrict__ G, int ldg, int chunk,
-                                 float* __restrict__ part) {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    int c = blockIdx.y;
-    if (n >= N) return;
-    int m0 = c * chunk, m1 = min(M, m0 + chunk);
+// Column sums db[n] (+)= sum_m G[m][n] in fixed order (chunks of rows; within
+// a chunk eight row groups of every eighth row).
+__global__ void __launch_bounds__(256) k_colsum_partial(int M, int N, const float* __restrict__ G, int ldg, int chunk,
+                                                        float* __restrict__ part) {
+    __shared__ float red[8][32];
+    const int col = threadIdx.x & 31, rg = threadIdx.x >> 5;
+    const int n = blockIdx.x * 32 + col;
+    const int c = blockIdx.y;
+    const int m0 = c * chunk, m1 = min(M, m0 + chunk);
     float s = 0.f;
-    for (int m = m0; m < m1; ++m) s += G[int64_t(m) * ldg + n];
+    if (n < N)
+        for (int m = m0 + rg; m < m1; m += 8) s += G[int64_t(m) * ldg + n];
+    red[rg][col] = s;
+    __syncthreads();
+    if (rg != 0 || n >= N) return;
+#pragma unroll
+    for (int g = 1; g < 8; ++g) s += red[g][col];
     part[int64_t(c) * N + n] = s;
 }
 
@@ -679,20 +713,14 @@ void colsum(int M, int N, const float* G, int ldg, float* db, float* scratch, in
             hipStream_t s) {
     if (M <= 0) return;
     int nch = cdiv(M, chunk);
-    k_colsum_partial<<<dim3(cdiv(N, 64), nch), 64, 0, s>>>(M, N, G, ldg, chunk, scratch);
-    k_reduce_chunks<<<cdiv(N, 256), 256, 0, s>>>(N, nch, scratch, N, db, accum);
+    k_colsum_partial<<<dim3(cdiv(N, 32), nch), 256, 0, s>>>(M, N, G, ldg, chunk, scratch);
     NNP_LAUNCH_CHECK();
+    launch_reduce_chunks(N, nch, scratch, N, db, accum, s);
 }
 
 }  // namespace nnp
 
 namespace nnp {
-void launch_reduce_chunks(int64_t count, int nchunks, const float* part, int64_t stride, float* out, bool accum,
-                          hipStream_t s) {
-    k_reduce_chunks<<<cdiv(count, 256), 256, 0, s>>>(count, nchunks, part, stride, out, accum);
-    NNP_LAUNCH_CHECK();
-}
-
 // [rows][K + 1] (filter weights then bias per row) -> Wr [rows][K], br [rows]
 __global__ void k_split_filter_grad(int rows, int K, const float* __restrict__ sum, float* __restrict__ dWr,
                                     float* __restrict__ dbr) {

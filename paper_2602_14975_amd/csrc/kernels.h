@@ -194,7 +194,11 @@ void launch_readout(int n, int F, int S, const float* z, const float* wo, const 
                     hipStream_t st, const int* perm = nullptr);
 void launch_readout_bwd(int n, int F, const float* ao, const float* wo, float* gao, hipStream_t st);
 void launch_rep_sum(int n_rep, const int64_t* rep_start, const float* x, double* out, hipStream_t st);
-void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, hipStream_t st);
+// scratch: cdiv(n, chunk) x S x F floats
+void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,
+                     hipStream_t st);
+void launch_reduce_chunks(int64_t count, int nchunks, const float* part, int64_t stride, float* out, bool accum,
+                          hipStream_t s);
 // vir_set / vir_add ([n] or nullptr): per owner i, sum_j F_ij . r_ij (its
 // share of the NPT virial proxy), written / added to
 void launch_head_fwd_rec(const MpGeom& mg, const int* cnt, const NcEdge* rec, const float* QK, const float* Vh,

@@ -7,7 +7,11 @@
 namespace nnp {
 
 constexpr int kMaxLayers = 4;
-constexpr int kChunk = 2048;  // rows per partial sum in weight adjoints
+// rows per partial sum in weight adjoints: the outputs are small (at most a
+// few 64 x 64 tiles), so the chunks of rows are what fills the chip.  24,576
+// frames' rows: 96 chunks; with 2,048 rows, 12 to 36 blocks per product took
+// 53 us each and the column sums 100 us.
+constexpr int kChunk = 256;
 
 struct LayerOff {
     int64_t W1, b1, W2, b2, Wr, br, U, V, M1, m1, M2, m2;
@@ -124,8 +128,6 @@ struct RespaBuf {
 
 void launch_reverse(int n, const int* run, const int* status, const int* offsets, const int* nbr, int* rev,
                     hipStream_t s);
-void launch_reduce_chunks(int64_t count, int nchunks, const float* part, int64_t stride, float* out, bool accum,
-                          hipStream_t s);
 struct CallScratch;
 size_t call_scratch_bytes(const Model* cons, const Model* nc, int64_t n, int32_t n_rep, int64_t E);
 void check_system(const nnp_system* sys);
