@@ -124,8 +124,11 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         e = hipMalloc(&m->sp, sizeof(float) * m->sp_count());
         if (e == hipSuccess) e = hipMalloc(&m->sp_x, sizeof(uint16_t) * 3 * m->sp_xs());
     }
-    // below width 64 no product has a K that the split-bfloat16 kernels take
-    if (e == hipSuccess && d.width >= 64) e = hipMalloc(&m->wx, sizeof(uint16_t) * 6 * m->wx_stride());
+    // width 64: products of K = 2F (below, no product has a K that the split
+    // kernel takes; width 128 has the per-atom blocks)
+    if (e == hipSuccess && d.width == 64) e = hipMalloc(&m->wx, sizeof(uint16_t) * 6 * m->wx_stride());
+    if (e == hipSuccess && d.kind == NNP_MODEL_CONS && d.width == 128)
+        e = hipMalloc(&m->wf, sizeof(uint16_t) * m->frag_count());
     if (e != hipSuccess) {
         (void)hipFree(m->w);
         if (m->tab) (void)hipFree(m->tab);
@@ -135,11 +138,13 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         if (m->wx) (void)hipFree(m->wx);
         if (m->sp) (void)hipFree(m->sp);
         if (m->sp_x) (void)hipFree(m->sp_x);
+        if (m->wf) (void)hipFree(m->wf);
         delete m;
         set_error(std::string("model set-up: ") + hipGetErrorString(e));
         return NNP_EDEVICE;
     }
     try {
+        if (m->wf) atom_block_setup();
         m->refresh_tables(nullptr);
         NNP_HIP(hipStreamSynchronize(nullptr));
     } catch (...) {
@@ -151,6 +156,7 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         if (m->wx) (void)hipFree(m->wx);
         if (m->sp) (void)hipFree(m->sp);
         if (m->sp_x) (void)hipFree(m->sp_x);
+        if (m->wf) (void)hipFree(m->wf);
         delete m;
         throw;
     }
@@ -169,6 +175,7 @@ extern "C" void nnp_model_destroy(nnp_model* model) {
     if (m->wx) (void)hipFree(m->wx);
     if (m->sp) (void)hipFree(m->sp);
     if (m->sp_x) (void)hipFree(m->sp_x);
+    if (m->wf) (void)hipFree(m->wf);
     delete m;
 }
 
@@ -256,18 +263,19 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
     b.phi_tab = m->phi_tab();
     b.gphi_tab = a.take<float>(S * 3 * F);
     b.gh1_tab = a.take<float>(S * F);
+    const int64_t nt = (n + 31) / 32 * 32;  // whole tiles of the per-atom blocks
     for (int l = 0; l < L; ++l) {
         LayerBuf& lb = b.layer[l];
-        lb.h1 = a.take<float>(n * F);
+        lb.h1 = a.take<float>(nt * F);
         lb.zphi = a.take<float>(n * F);
         lb.phi = a.take<float>(n * 3 * F);
         lb.smid = a.take<float>(n * F);
         lb.vmid = a.take<float>(n * 3 * F);
-        lb.UV = a.take<float>(n * 6 * F);
+        lb.UV = a.take<float>(nt * 6 * F);
         lb.X = a.take<float>(n * 2 * F);
-        lb.a1 = a.take<float>(n * F);
+        lb.a1 = a.take<float>(nt * F);
         lb.z = a.take<float>(n * F);
-        lb.pqo = a.take<float>(n * 3 * F);
+        lb.pqo = a.take<float>(nt * 3 * F);
     }
     if (m->desc.kind == NNP_MODEL_CONS) {
         b.ao = a.take<float>(n * F);
@@ -353,6 +361,32 @@ void Model::refresh_tables(hipStream_t s) {
         tr(ll.M1, F, 2 * F);
         tr(ll.M2, 3 * F, F);
     }
+    if (wf) {
+        for (int l = 0; l < n_layers(); ++l) {
+            const LayerOff& ll = loff[l];
+            PackFrags P{};
+            int c = 0;
+            auto add = [&](int64_t off, int id, int tr) {
+                P.m[c++] = {p(off), frag(l, id), kFragRows[id], kFragK[id], tr};
+            };
+            add(ll.U, kUV, 0);
+            add(ll.M1, kM1, 0);
+            add(ll.M2, kM2, 0);
+            add(ll.W1, kW1, 0);
+            add(ll.W2, kW2, 0);
+            add(ll.U, kUt, 1);
+            add(ll.V, kVt, 1);
+            add(ll.M1, kM1t, 1);
+            add(ll.M2, kM2t, 1);
+            add(ll.W1, kW1t, 1);
+            add(ll.W2, kW2t, 1);
+            launch_pack_frags(P, c, frag_pieces(), s);
+        }
+        PackFrags P{};
+        P.m[0] = {p(off_Wo), frag_Wo(false), F, F, 0};
+        P.m[1] = {p(off_Wo), frag_Wo(true), F, F, 1};
+        launch_pack_frags(P, 2, frag_pieces(), s);
+    }
     if (desc.kind == NNP_MODEL_CONS) {
         tr(off_Wo, F, F);
     } else {
@@ -375,8 +409,14 @@ static bool species_sum_on(const Model* m, const MpGeom& mg, const ModelBuf& b) 
     return m->sp && b.sp && mg.ecnt && message_mx_active(m->desc.width, m->desc.n_rbf, 0) && species_sum_active();
 }
 
+// Width-128 conservative models run everything between two message steps in
+// one kernel each way (atom_block.hip) unless the older dense kernels were
+// selected.
+static bool atom_blocks_on(const Model* m) { return m->wf && dense_auto(); }
+
 void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, ModelBuf& b, hipStream_t s) {
     const int n = int(sys.n_atoms);
+    const bool blocks = atom_blocks_on(m);
     const int F = m->desc.width, K = m->desc.n_rbf, S = m->desc.n_species;
     const int cut = m->desc.kind == NNP_MODEL_CONS ? 0 : 1;
     for (int l = 0; l < m->n_layers(); ++l) {
@@ -393,10 +433,13 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
             a.phi_tab = b.phi_tab;
             a.emb = m->p(m->off_emb);
         } else {
-            gemm_xwt(n, F, F, b.s[l], F, m->p(lo.W1), m->p(lo.b1), lb.zphi, F, EPI_SILU, lb.h1, F, false, s,
-                     m->bf16(), m->px(lo.W1), m->wx_stride());
-            gemm_xwt(n, 3 * F, F, lb.zphi, F, m->p(lo.W2), m->p(lo.b2), lb.phi, 3 * F, EPI_NONE, nullptr, 0, false,
-                     s, m->bf16(), m->px(lo.W2), m->wx_stride());
+            if (!blocks) {
+                gemm_xwt(n, F, F, b.s[l], F, m->p(lo.W1), m->p(lo.b1), lb.zphi, F, EPI_SILU, lb.h1, F, false, s,
+                         m->bf16(), m->px(lo.W1), m->wx_stride());
+                gemm_xwt(n, 3 * F, F, lb.zphi, F, m->p(lo.W2), m->p(lo.b2), lb.phi, 3 * F, EPI_NONE, nullptr, 0,
+                         false, s, m->bf16(), m->px(lo.W2), m->wx_stride());
+            }
+            a.pv_ready = blocks;  // written with phi by the previous layer's block
             a.s_in = b.s[l];
             a.v_in = b.v[l];
             a.phi = lb.phi;
@@ -423,6 +466,47 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
         } else {
             launch_message_fwd(F, K, cut, mg, a, s);
         }
+        if (blocks) {
+            const bool last = l + 1 == m->n_layers();
+            AtomFwd f{};
+            f.n = n;
+            f.smid = lb.smid;
+            f.vmid = lb.vmid;
+            f.U = m->frag(l, Model::kUV);
+            f.M1 = m->frag(l, Model::kM1);
+            f.M2 = m->frag(l, Model::kM2);
+            f.m1 = m->p(lo.m1);
+            f.m2 = m->p(lo.m2);
+            f.UV = lb.UV;
+            f.a1 = lb.a1;
+            f.pqo = lb.pqo;
+            if (!last) {
+                const LayerOff& ln = m->loff[l + 1];
+                LayerBuf& nb = b.layer[l + 1];
+                f.W1 = m->frag(l + 1, Model::kW1);
+                f.W2 = m->frag(l + 1, Model::kW2);
+                f.b1 = m->p(ln.b1);
+                f.b2 = m->p(ln.b2);
+                f.h1 = nb.h1;
+                f.phi = nb.phi;
+                f.pv = nb.pv;
+                f.s_out = b.s[l + 1];
+                f.v_out = b.v[l + 1];
+            } else {
+                f.W1 = m->frag_Wo(false);
+                f.W2 = m->frag_Wo(true);
+                f.b1 = m->p(m->off_bo);
+                f.wo = m->p(m->off_wo);
+                f.beta = m->p(m->off_beta);
+                f.species = sys.species;
+                f.n_species = S;
+                f.Ei = b.Ei;
+                f.perm = mg.perm;
+                f.s_out = b.gs;
+            }
+            launch_atom_fwd(f, last, m->bf16(), s);
+            continue;
+        }
         gemm_xwt(3 * n, 2 * F, F, lb.vmid, F, m->p(lo.U), nullptr, lb.UV, 2 * F, EPI_NONE, nullptr, 0, false, s,
                  m->bf16(), m->px(lo.U), m->wx_stride());
         launch_build_x(n, F, lb.smid, lb.UV, lb.X, s);
@@ -434,7 +518,9 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
     }
 }
 
-// Reverse of one embedding layer.  In: gs, gv = adjoints of the layer
+// Reverse of one embedding layer.  With the per-atom blocks, layer l takes
+// the adjoints as the message reverse of layer l + 1 left them (gs2, gv2,
+// gphi; the last layer: gs) and leaves its own there.  Otherwise: in: gs, gv = adjoints of the layer
 // output.  Out: gs, gv = adjoints of the layer input (buffers swapped).
 // With `dtheta`, the weight adjoints of the layer are written too.
 // With gv_zero, the adjoint of the layer's vector output is zero (the last
@@ -447,10 +533,33 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     const LayerOff& lo = m->loff[l];
     LayerBuf& lb = b.layer[l];
     const bool wg = dtheta != nullptr;
-    launch_update_combine_bwd(n, F, lb.UV, lb.pqo, b.gs, gv_zero ? nullptr : b.gv, b.gpqo, b.gUV, s);
-    if (wg) {
-        gemm_wgrad(n, 3 * F, F, b.gpqo, 3 * F, lb.z, F, dtheta + lo.M2, b.chunk_part, kChunk, false, s);
-        colsum(n, 3 * F, b.gpqo, 3 * F, dtheta + lo.m2, b.chunk_part, kChunk, false, s);
+    const bool blocks = !wg && atom_blocks_on(m);
+    if (blocks) {
+        AtomBwd f{};
+        f.n = n;
+        f.gs_in = gv_zero ? b.gs : b.gs2;
+        if (!gv_zero) {
+            f.gv_in = b.gv2;
+            f.gphi = b.gphi;
+            f.h1 = b.layer[l + 1].h1;
+            f.W2t = m->frag(l + 1, Model::kW2t);
+            f.W1t = m->frag(l + 1, Model::kW1t);
+        }
+        f.UV = lb.UV;
+        f.pqo = lb.pqo;
+        f.a1 = lb.a1;
+        f.M2t = m->frag(l, Model::kM2t);
+        f.M1t = m->frag(l, Model::kM1t);
+        f.Ut = m->frag(l, Model::kUt);
+        f.Vt = m->frag(l, Model::kVt);
+        f.gs_out = b.gs2;
+        f.gv_out = b.gv;
+        launch_atom_bwd(f, gv_zero, m->bf16(), s);
+    } else {
+        launch_update_combine_bwd(n, F, lb.UV, lb.pqo, b.gs, gv_zero ? nullptr : b.gv, b.gpqo, b.gUV, s);
+        if (wg) {
+            gemm_wgrad(n, 3 * F, F, b.gpqo, 3 * F, lb.z, F, dtheta + lo.M2, b.chunk_part, kChunk, false, s);
+            colsum(n, 3 * F, b.gpqo, 3 * F, dtheta + lo.m2, b.chunk_part, kChunk, false, s);
     }
     gemm_gwt(m, lo.M2, n, 3 * F, F, b.gpqo, 3 * F, b.ga1, F, EPI_DSILU, lb.a1, F, false, s);
     if (wg) {
@@ -461,6 +570,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     launch_norm_bwd(n, F, b.gs, b.gX, lb.X, lb.UV, b.gs2, b.gUV, s);  // gs2 = g_smid
     if (wg) gemm_wgrad(3 * n, 2 * F, F, b.gUV, 2 * F, lb.vmid, F, dtheta + lo.U, b.chunk_part, kChunk, false, s);
     gemm_gwt(m, lo.U, 3 * n, 2 * F, F, b.gUV, 2 * F, b.gv, F, EPI_NONE, nullptr, 0, !gv_zero, s);  // gv = g_vmid
+    }
     MpBwd a{};
     a.gsm = b.gs2;
     a.gvm = b.gv;
@@ -526,6 +636,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         }
         return;
     }
+    if (blocks) return;  // the rest comes with the block of the layer below
     if (wg) {
         gemm_wgrad(n, 3 * F, F, b.gphi, 3 * F, lb.zphi, F, dtheta + lo.W2, b.chunk_part, kChunk, false, s);
         colsum(n, 3 * F, b.gphi, 3 * F, dtheta + lo.b2, b.chunk_part, kChunk, false, s);
@@ -581,13 +692,18 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     }
     embed_forward(m, sys, mg, b, s);
     const int L = m->n_layers();
-    gemm_xwt(n, F, F, b.s[L], F, m->p(m->off_Wo), m->p(m->off_bo), b.zo, F, EPI_SILU, b.ao, F, false, s, m->bf16(),
-             m->px(m->off_Wo), m->wx_stride());
-    launch_readout(n, F, m->desc.n_species, b.zo, m->p(m->off_wo), m->p(m->off_beta), sys.species, b.Ei, s, perm);
+    const bool blocks = atom_blocks_on(m);  // the last forward block then includes the readout
+    if (!blocks) {
+        gemm_xwt(n, F, F, b.s[L], F, m->p(m->off_Wo), m->p(m->off_bo), b.zo, F, EPI_SILU, b.ao, F, false, s, m->bf16(),
+                 m->px(m->off_Wo), m->wx_stride());
+        launch_readout(n, F, m->desc.n_species, b.zo, m->p(m->off_wo), m->p(m->off_beta), sys.species, b.Ei, s, perm);
+    }
     if (energy) launch_rep_sum(sys.n_rep, t.rep_start, b.Ei, energy, s);
     if (!forces) return;
-    launch_readout_bwd(n, F, b.ao, m->p(m->off_wo), b.gs2, s);
-    gemm_gwt(m, m->off_Wo, n, F, F, b.gs2, F, b.gs, F, EPI_NONE, nullptr, 0, false, s);
+    if (!blocks) {
+        launch_readout_bwd(n, F, b.ao, m->p(m->off_wo), b.gs2, s);
+        gemm_gwt(m, m->off_Wo, n, F, F, b.gs2, F, b.gs, F, EPI_NONE, nullptr, 0, false, s);
+    }
     for (int l = L - 1; l >= 0; --l) layer_backward(m, l, mg, b, forces, l != L - 1, nullptr, s, vir, l == L - 1);
 }
 

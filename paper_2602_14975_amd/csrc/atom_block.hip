@@ -1,0 +1,706 @@
+// The per-atom work between two message steps of a width-128 conservative
+// model as one kernel each way (forward: update block, then the next layer's
+// phi perceptron or the readout; reverse: their adjoints), instead of one
+// launch per dense product and elementwise step.
+//
+// A block of four wavefronts owns 32 atoms.  Every product is
+//   out[feature][atom] = sum_k W[feature][k] x[atom][k]
+// on v_mfma_f32_32x32x16_bf16 with the weights as the first operand, so that
+// lane (atom a = lane % 32, half h = lane / 32) of wavefront w holds features
+// 32 w + 8 g + 4 h + q (g, q < 4) of atom a in its accumulators: four
+// consecutive features per 16-byte global access, and everything elementwise
+// between the products stays in registers, the same features for all of an
+// atom's quantities.  The inputs of a product pass through LDS as operand
+// fragments (16 bytes per lane and k-step of 16); the weights are read
+// straight from L2 in the packed order of launch_pack_frags, each fragment by
+// one wavefront of the block, a few k-steps ahead.
+//
+// FP32 models split both operands into three bfloat16 pieces and accumulate
+// the six piece products of order >= 2^-18 in float32, smallest first, as
+// k_gemm_x3 does (FP32-equivalent); BF16 models take the operands rounded to
+// bfloat16 and one product.
+//
+// What bounds it: 720 matrix instructions per wavefront and tile (23,000
+// cycles), the walk through 1 MB of packed weights per tile, and the waits
+// between the steps of a tile, at two wavefronts per SIMD.  As separate
+// launches the same work moved about 40 F floats per atom and layer through
+// memory forward and more in reverse, 28 products and 15 elementwise launches
+// per evaluation; the blocks move 24 F and are six launches.  Measured,
+// dense products and elementwise launches together, per evaluation (3
+// layers, FP32): 12,288 atoms 885 -> 352 us (blocks of 44 to 66 us); 1,536
+// atoms 460 -> 157 us (19 to 30 us each).  A whole evaluation: 1,536 atoms
+// 0.60 -> 0.36 ms, 12,288 atoms 1.80 -> 1.30 ms, 89,373 atoms 12.4 -> 9.6 ms.
+#include <algorithm>
+
+#include "common.h"
+#include "kernels.h"
+
+namespace nnp {
+
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kF = 128;
+constexpr int kTile = 32;        // atoms per block
+constexpr int kFrag = 1024;      // bytes of one operand fragment (64 lanes x 16)
+constexpr int kKsF = kF / 16;    // k-steps of one width
+// LDS of a block: three regions, each the fragments of F inputs of its atoms
+// (or room to turn one 4 KB slice per wavefront around); 72 KB at three
+// pieces: two blocks per CU
+constexpr int region_bytes(int NP) { return NP == 1 ? 16 * kFrag : kKsF * NP * kFrag; }
+constexpr int lds_bytes(int NP) { return 3 * region_bytes(NP); }
+
+// Four floats as NP bfloat16 pieces (round to nearest of what the previous
+// pieces leave), two packed words per piece.
+template <int NP>
+__device__ __forceinline__ void split4(const f32x4_t& x, uint2 (&o)[NP]) {
+    f32x2_t r0{x.x, x.y}, r1{x.z, x.w};
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        o[p].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(r0, bf16x2_t));
+        o[p].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(r1, bf16x2_t));
+        if (p + 1 < NP) {  // exact differences
+            r0 -= f32x2_t{__uint_as_float(o[p].x << 16), __uint_as_float(o[p].x & 0xFFFF0000u)};
+            r1 -= f32x2_t{__uint_as_float(o[p].y << 16), __uint_as_float(o[p].y & 0xFFFF0000u)};
+        }
+    }
+}
+
+// A lane's 16 values of one 32-feature slice, element 4 g + q = feature
+// 32 w + 8 g + 4 h + q of its atom.
+struct Slice {
+    f32x4_t v[4];
+    __device__ __forceinline__ float operator[](int i) const { return v[i >> 2][i & 3]; }
+};
+
+// Global memory through buffer descriptors: a uniform base, a uniform offset
+// and one 32-bit lane offset per row stride, so that addresses take no
+// vector registers (plain pointers cost these kernels about 60), and rows
+// past the last atom are read as zero and not stored.
+struct Buf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Buf(const void* p, uint32_t bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000)) {}
+    __device__ __forceinline__ u32x4_t load(uint32_t lane_off, uint32_t off) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0);
+    }
+    // The whole offset in the lane's register: with part of it in an SGPR the
+    // compiler leaves no wait between a 16-byte store and the next vector
+    // instruction that writes its data registers, and this GPU needs one (the
+    // last lanes then stored the new value of the first register).
+    __device__ __forceinline__ void store(const u32x4_t& v, uint32_t off) const {
+        __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+    }
+};
+
+// This lane's place in the block
+struct Lane {
+    int lane, w, a, h;
+    int64_t t0;  // first atom of the block's tile
+    int rows;    // atoms of the tile
+    int i;       // this lane's atom
+    bool on;
+    __device__ __forceinline__ Lane(int n) {
+        lane = threadIdx.x & 63;
+        w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        a = lane & 31;
+        h = lane >> 5;
+        t0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * kTile;
+        i = int(t0) + a;
+        on = i < n;
+        rows = min(kTile, n - int(t0));
+    }
+};
+
+// Row-major float32 of C rows per atom, row width ld: the lane's slice at
+// column c0 of row c of its atom.
+template <int C, int ld>
+__device__ __forceinline__ Slice load_slice(const float* p, int c, int c0, const Lane& L) {
+    const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
+    const uint32_t lo = uint32_t(L.a * (C * ld * 4) + 16 * L.h), o = uint32_t((c * ld + c0 + 32 * L.w) * 4);
+    Slice s;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + 32 * g));
+    return s;
+}
+// The slice into row-major rows, turned around through 4 KB of LDS (`turn`,
+// this wavefront's own) so that eight lanes write the 128 bytes of a row
+// together: written as held, 16 bytes per lane and row, a store took about
+// 100 cycles and the stores a third of the kernel.
+template <int C, int ld>
+__device__ __forceinline__ void store_slice(float* p, int c, int c0, const Lane& L, const Slice& s, char* turn) {
+    const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
+    wave_sync_lds();
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4_t*>(turn + L.a * 128 + ((2 * g + L.h) ^ (L.a & 7)) * 16) = s.v[g];
+    wave_sync_lds();
+    const int row = L.lane >> 3, q = L.lane & 7;
+    const uint32_t lo = uint32_t(row * (C * ld * 4) + 16 * q + (c * ld + c0 + 32 * L.w) * 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)  // rows 8 k + row: the same swizzle
+        b.store(*reinterpret_cast<const u32x4_t*>(turn + (8 * k + row) * 128 + (q ^ row) * 16),
+                lo + 8 * k * (C * ld * 4));
+}
+// Quantities that only these kernels exchange are kept in lane order: slice
+// `c` (of C) of the tile's wavefront w, 1 KB per group of four features.
+// Rows past the last atom are part of the buffers.
+template <int C>
+__device__ __forceinline__ void keep_slice(float* p, int c, const Lane& L, const Slice& s) {
+    const Buf b(p + L.t0 * (C * kF), uint32_t(kTile * C * kF * 4));
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        b.store(__builtin_bit_cast(u32x4_t, s.v[g]), uint32_t(16 * L.lane + ((c * 4 + L.w) * 4 + g) * 1024));
+}
+template <int C>
+__device__ __forceinline__ Slice kept_slice(const float* p, int c, const Lane& L) {
+    const Buf b(p + L.t0 * (C * kF), uint32_t(kTile * C * kF * 4));
+    Slice s;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.lane, uint32_t(((c * 4 + L.w) * 4 + g) * 1024)));
+    return s;
+}
+// kF per-feature constants (biases)
+__device__ __forceinline__ Slice load_feat(const float* p, const Lane& L) {
+    const Buf b(p, kF * 4);
+    Slice s;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.h, uint32_t(128 * L.w + 32 * g)));
+    return s;
+}
+
+// The slice as operand fragments: features 32 w .. 32 w + 31 are k-steps
+// 2 w and 2 w + 1 of the fragment array at `buf` (k-step base ks0).  Within
+// these 32, half h of k-step j holds features 16 h + 8 j .. + 7, as in
+// k_gemm_x3.
+template <int NP>
+__device__ __forceinline__ void put_slice(char* buf, int ks0, const Lane& L, const Slice& s) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        uint2 o[NP];
+        split4<NP>(s.v[g], o);
+        char* d = buf + (ks0 + 2 * L.w + (g & 1)) * (NP * kFrag) + ((g >> 1) * 32 + L.a) * 16 + 8 * L.h;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2*>(d + p * kFrag) = o[p];
+    }
+}
+
+// Packed weights of one matrix [N][K] (launch_pack_frags): piece p, 16-byte
+// unit ((n / 16) K/8 + k / 8) 16 + n % 16 holds W[n][8 (k/8) .. + 7].
+// A ring of D k-steps of the fragments of NT row tiles of 32.
+template <int NP, int NT, int KS, int D>
+struct Weights {
+    static constexpr uint32_t kRow = 1024 * KS;  // bytes of a row tile of 32 per piece
+    Buf b;
+    uint32_t ps, off, step, lo;  // bytes: piece, first row tile, row tile step; lane
+    bf16x8_t r[D][NT][NP];
+    // mat: the matrix's pieces, N its rows; row tiles t0, t0 + step, ...
+    __device__ __forceinline__ Weights(const uint16_t* mat, int N, int t0, int st, const Lane& L)
+        : b(mat, uint32_t(N) * (KS * 32 * NP)), ps(uint32_t(N) * (KS * 32)), off(t0 * kRow), step(st * kRow),
+          lo(uint32_t(((L.a >> 4) * 2 * KS + 2 * L.h) * 16 + (L.a & 15)) * 16u) {
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d) load(d, d);
+    }
+    // k-step ks into ring slot d (past the last k-step: unused data, bounded
+    // by the descriptor)
+    __device__ __forceinline__ void load(int ks, int d) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                r[d][t][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + t * step + p * ps + (ks >> 1) * 1024 + (ks & 1) * 256));
+    }
+};
+
+// acc[t][b] += W_t x_b over all k-steps; x_b's fragments at buf + b * stride.
+// The loads of k-step ks + D - 1 are issued before the products of ks and held
+// there (left alone, the compiler sinks each load to its use and the chain
+// waits for L2 at every k-step).  A loop over rings of D k-steps rather than
+// straight-line code: a block walks through its code once, so that code is
+// fetched as slowly as data.
+// KN: k-steps taken (the first of the matrix's KS).
+//
+// FP32 models: where registers allow, the products of the leading pieces are
+// summed apart from the five small ones (in `sep`, added by the caller's
+// fold), so that a sum is rounded once instead of six times per k-step at
+// its full size.
+// BF16 models: the sums of k_gemm_x3 bit for bit (its odd k-steps apart in
+// `sep` where it keeps two accumulators, `two`): operands are rounded to
+// bfloat16 after every product, and another order would flip some.
+template <int NP, int NT, int NB, int KN, int KS, int D>
+__device__ __forceinline__ void product(floatx16 (&acc)[NT][NB], floatx16 (&sep)[NT][NB], Weights<NP, NT, KS, D>& W,
+                                        const char* buf, int stride, const Lane& L, bool two) {
+    static_assert(KN % D == 0 && D % 2 == 0 && KN <= KS, "whole rings");
+    constexpr bool kApart = NP == 3 && NT <= 2 && NT * NB <= 3;
+    constexpr int XD = NB == 1 ? 2 : 1;  // k-steps of x fragments held
+    const char* bl = buf + L.lane * 16;
+    bf16x8_t x[XD][NB][NP];
+    auto load_x = [&](int ks, int d) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                x[d][b][p] = *reinterpret_cast<const bf16x8_t*>(bl + b * stride + (ks * NP + p) * kFrag);
+    };
+    if (XD == 2) load_x(0, 0);
+    auto step = [&](int ks, int d, floatx16(&c)[NT][NB]) {
+        W.load(ks + D - 1, (d + D - 1) % D);
+        if (XD == 1) load_x(ks, 0);
+        else load_x(min(ks + 1, KN - 1), (d + 1) % 2);
+        __builtin_amdgcn_sched_barrier(0);
+        const auto& w = W.r[d];
+        const auto& y = x[d % XD];
+#define NNP_TERM(ACC, PX, PW)                                                         \
+    _Pragma("unroll") for (int t = 0; t < NT; ++t) _Pragma("unroll") for (int b = 0; b < NB; ++b) ACC[t][b] = \
+        __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t][PW], y[b][PX], ACC[t][b], 0, 0, 0);
+        if constexpr (NP == 3) {
+            auto& small = kApart ? sep : c;
+            NNP_TERM(small, 2, 0)
+            NNP_TERM(small, 0, 2)
+            NNP_TERM(small, 1, 1)
+            NNP_TERM(small, 1, 0)
+            NNP_TERM(small, 0, 1)
+        }
+        NNP_TERM(c, 0, 0)
+#undef NNP_TERM
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (NP == 3 || !two) {
+#pragma unroll 1
+        for (int k0 = 0; k0 < KN; k0 += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) step(k0 + d, d, acc);
+    } else {
+#pragma unroll 1
+        for (int k0 = 0; k0 < KN; k0 += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) step(k0 + d, d, d % 2 ? sep : acc);
+    }
+}
+
+// Whether k_gemm_x3 sums odd k-steps apart in the product [M][N] of K = 128
+// (for other K it always does): where it gives a block 32 columns, i.e. where
+// 64 would leave fewer than 512 blocks.
+__device__ __forceinline__ bool two_sums(int64_t M, int N) { return (M + 127) / 128 * (N / 64) < 512; }
+
+template <int NT, int NB>
+__device__ __forceinline__ void fold(floatx16 (&acc)[NT][NB], const floatx16 (&sep)[NT][NB]) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[t][b] += sep[t][b];
+}
+// acc = W x
+template <int NP, int NT, int NB, int KN, int KS, int D>
+__device__ __forceinline__ void product(floatx16 (&acc)[NT][NB], Weights<NP, NT, KS, D>& W, const char* buf,
+                                        int stride, const Lane& L, bool two) {
+    floatx16 sep[NT][NB] = {};
+    product<NP, NT, NB, KN>(acc, sep, W, buf, stride, L, two);
+    if (NP == 1 || (NT <= 2 && NT * NB <= 3)) fold(acc, sep);
+}
+
+// Biases (or what else is added to a product): in FP32 models the sums start
+// from them, in BF16 models they are added last, as in k_gemm_x3.
+template <int NP>
+__device__ __forceinline__ floatx16 start_at(const Slice& b) {
+    floatx16 c = {};
+    if (NP > 1) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c[e] = b[e];
+    }
+    return c;
+}
+__device__ __forceinline__ Slice as_slice(const floatx16& c) {
+    Slice s;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s.v[e >> 2][e & 3] = c[e];
+    return s;
+}
+template <int NP>
+__device__ __forceinline__ Slice end_with(const floatx16& c, const Slice& b) {
+    Slice s = as_slice(c);
+    if (NP == 1) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) s.v[g] += b.v[g];
+    }
+    return s;
+}
+
+// ---------------------------------------------------------------- forward --
+// smid, vmid (the message step's outputs) -> update block -> s, v; then
+//   LAST = false: phi = W2 silu(W1 s + b1) + b2 of the next layer, and
+//                 phi_b v for its message kernels;
+//   LAST = true:  the readout, the atomic energy and the adjoint of s of the
+//                 energy (v is not used past the last layer: not formed).
+// Kept for the reverse: U v and V v, the M1 pre-activation, q and o (LAST: q
+// alone), the W1 pre-activation.
+template <int NP, bool LAST>
+__global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ float epart[LAST ? 4 : 1][kTile];
+    constexpr int CB = region_bytes(NP);
+    const Lane L(A.n);
+    // free while the rows of s and v (turn) and the outputs (turn2) are written
+    char* turn = lds + CB + L.w * (4 * kFrag);
+    char* turn2 = lds + 2 * CB + L.w * (4 * kFrag);
+    {
+        Slice v0[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v0[c] = load_slice<3, kF>(A.vmid, c, 0, L);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c]);
+    }
+    const Slice s0 = load_slice<1, kF>(A.smid, 0, 0, L);
+
+    // U v, V v: row tiles w (U) and 4 + w (V) of the adjacent matrices
+    floatx16 uv[2][3] = {};
+    {
+        Weights<NP, 2, kKsF, 2> W(A.U, 2 * kF, L.w, 4, L);
+        __syncthreads();
+        product<NP, 2, 3, kKsF>(uv, W, lds, CB, L, two_sums(3 * int64_t(A.n), 2 * kF));
+    }
+    Slice nrm, dot;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = 4 * g + q;
+            float nn = 1e-8f, dd = 0.f;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                nn = fmaf(uv[1][c][e], uv[1][c][e], nn);
+                dd = fmaf(uv[0][c][e], uv[1][c][e], dd);
+            }
+            nrm.v[g][q] = sqrtf(nn);
+            dot.v[g][q] = dd;
+        }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            keep_slice<6>(A.UV, 2 * c + m, L, as_slice(uv[m][c]));
+    // [s; |V v|] (k-steps 0..15), then M1; its output behind them (16..23)
+    Slice z;
+    {
+        const Slice m1 = load_feat(A.m1, L);
+        floatx16 acc[1][1] = {{start_at<NP>(m1)}};
+        Weights<NP, 1, 2 * kKsF, 4> W(A.M1, kF, L.w, 1, L);
+        __syncthreads();  // the vector fragments are read
+        put_slice<NP>(lds, 0, L, s0);
+        put_slice<NP>(lds, kKsF, L, nrm);
+        __syncthreads();
+        product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L, true);
+        const Slice a1 = end_with<NP>(acc[0][0], m1);
+        keep_slice<1>(A.a1, 0, L, a1);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) z.v[e >> 2][e & 3] = silu(a1[e]);
+    }
+    put_slice<NP>(lds + 2 * CB, 0, L, z);
+    // p, q, o
+    constexpr int NQ = LAST ? 2 : 3;
+    Slice s1;
+    Slice v1[3];
+    {
+        floatx16 acc[NQ][1];
+        Slice m2[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) {
+            m2[c] = load_feat(A.m2 + c * kF, L);
+            acc[c][0] = start_at<NP>(m2[c]);
+        }
+        Weights<NP, NQ, kKsF, 2> W(A.M2, 3 * kF, L.w, 4, L);
+        __syncthreads();
+        product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L, two_sums(A.n, 3 * kF));
+        Slice h[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) h[c] = end_with<NP>(acc[c][0], m2[c]);
+#pragma unroll
+        for (int c = 1; c < NQ; ++c) keep_slice<3>(A.pqo, c, L, h[c]);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s1.v[e >> 2][e & 3] = fmaf(h[1][e], dot[e], s0[e] + h[0][e]);
+        if constexpr (!LAST) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                // v and U v are read again rather than held over the products
+                // (96 registers)
+                const Slice v0 = load_slice<3, kF>(A.vmid, c, 0, L);
+                const Slice u = kept_slice<6>(A.UV, 2 * c, L);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v1[c].v[e >> 2][e & 3] = fmaf(h[NQ - 1][e], u[e], v0[e]);
+                store_slice<3, kF>(A.v_out, c, 0, L, v1[c], turn);
+            }
+        }
+    }
+    // the s fragments of M1 are read (the barrier before M2's product)
+    put_slice<NP>(lds, 0, L, s1);
+    const Slice b1 = load_feat(A.b1, L);
+    floatx16 acc1[1][1] = {{start_at<NP>(b1)}};
+    Weights<NP, 1, kKsF, 4> W1(A.W1, kF, L.w, 1, L);
+    __syncthreads();
+    product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L, two_sums(A.n, kF));
+    const Slice h1 = end_with<NP>(acc1[0][0], b1);
+    if constexpr (!LAST) {
+        keep_slice<1>(A.h1, 0, L, h1);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
+        put_slice<NP>(lds + CB, 0, L, z);
+        floatx16 acc[3][1];
+        Slice b2[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            b2[c] = load_feat(A.b2 + c * kF, L);
+            acc[c][0] = start_at<NP>(b2[c]);
+        }
+        Weights<NP, 3, kKsF, 2> W2(A.W2, 3 * kF, L.w, 4, L);
+        __syncthreads();
+        product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L, two_sums(A.n, 3 * kF));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const Slice ph = end_with<NP>(acc[c][0], b2[c]);
+            store_slice<1, 3 * kF>(A.phi, 0, c * kF, L, ph, turn2);
+            if (c == 1 && A.pv) {
+#pragma unroll
+                for (int al = 0; al < 3; ++al) {
+                    Slice t;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) t.v[g] = ph.v[g] * v1[al].v[g];
+                    store_slice<3, kF>(A.pv, al, 0, L, t, turn2);
+                }
+            }
+        }
+        store_slice<1, kF>(A.s_out, 0, 0, L, s1, turn2);
+    } else {
+        // E_i = wo . silu(h1) + beta[t_i]; adjoint of s: Wo^T (wo silu'(h1))
+        const Slice wo = load_feat(A.wo, L);
+        float e0 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            e0 = fmaf(wo[e], silu(h1[e]), e0);
+            z.v[e >> 2][e & 3] = wo[e] * silu_grad(h1[e]);
+        }
+        e0 += __shfl_xor(e0, 32, 64);
+        if (L.h == 0) epart[L.w][L.a] = e0;
+        put_slice<NP>(lds + CB, 0, L, z);
+        Weights<NP, 1, kKsF, 4> W2(A.W2, kF, L.w, 1, L);
+        __syncthreads();
+        if (L.w == 0 && L.h == 0 && L.on) {
+            const int io = A.perm ? min(max(A.perm[L.i], 0), A.n - 1) : L.i;
+            const float sum = (epart[0][L.a] + epart[1][L.a]) + (epart[2][L.a] + epart[3][L.a]);
+            A.Ei[io] = sum + A.beta[min(max(A.species[L.i], 0), A.n_species - 1)];
+        }
+        floatx16 acc[1][1] = {};
+        product<NP, 1, 1, kKsF>(acc, W2, lds + CB, 0, L, two_sums(A.n, kF));
+        store_slice<1, kF>(A.s_out, 0, 0, L, as_slice(acc[0][0]), turn2);
+    }
+}
+
+// ---------------------------------------------------------------- reverse --
+// Adjoints of (s, v) after a layer -> adjoints of its message step's outputs
+// (gs_out of smid, gv_out of vmid).
+//   TOP = false: the adjoint of s is first completed from that of the next
+//     layer's phi, gs = gs_in + W1^T (silu'(h1) W2^T gphi); gs_in is the
+//     adjoint that passes that layer's message step by.
+//   TOP = true (the last layer): gs_in is the adjoint of s, that of v is zero.
+template <int NP, bool TOP>
+__global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
+    extern __shared__ __align__(16) char lds[];
+    constexpr int CB = region_bytes(NP);
+    const Lane L(A.n);
+    char* turn = lds + CB + L.w * (4 * kFrag);
+    Slice gs = load_slice<1, kF>(A.gs_in, 0, 0, L);
+    if constexpr (!TOP) {
+        Weights<NP, 1, 3 * kKsF, 4> W(A.W2t, kF, L.w, 1, L);
+        const Slice h1 = kept_slice<1>(A.h1, 0, L);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            put_slice<NP>(lds, c * kKsF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L));
+        __syncthreads();
+        floatx16 acc[1][1] = {};
+        product<NP, 1, 1, 3 * kKsF>(acc, W, lds, 0, L, true);
+        Weights<NP, 1, kKsF, 4> W1(A.W1t, kF, L.w, 1, L);
+        Slice g;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) g.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(h1[e]);
+        __syncthreads();
+        put_slice<NP>(lds, 0, L, g);
+        __syncthreads();
+        floatx16 acc1[1][1] = {{start_at<NP>(gs)}};
+        product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L, two_sums(A.n, kF));
+        gs = end_with<NP>(acc1[0][0], gs);
+    }
+    // adjoints of p, q (and o): gs, gs (U v . V v), sum gv U v
+    Slice gsq, o, dot, go;
+    floatx16 gv[1][3];
+    {
+        constexpr int KN = (TOP ? 2 : 3) * kKsF;
+        Weights<NP, 1, 3 * kKsF, 4> W(A.M2t, kF, L.w, 1, L);
+        const Slice q = kept_slice<3>(A.pqo, 1, L);
+        if constexpr (!TOP) o = kept_slice<3>(A.pqo, 2, L);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) gsq.v[g] = gs.v[g] * q.v[g];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const Slice u = kept_slice<6>(A.UV, 2 * c, L), v = kept_slice<6>(A.UV, 2 * c + 1, L);
+            if constexpr (TOP) gv[0][c] = floatx16{};
+            else gv[0][c] = start_at<3>(load_slice<3, kF>(A.gv_in, c, 0, L));
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float d = c ? dot[e] : 0.f;
+                dot.v[e >> 2][e & 3] = fmaf(u[e], v[e], d);
+                if constexpr (!TOP) {
+                    const float t = c ? go[e] : 0.f;
+                    go.v[e >> 2][e & 3] = fmaf(gv[0][c][e], u[e], t);
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) dot.v[g] = gs.v[g] * dot.v[g];
+        if constexpr (!TOP) __syncthreads();  // W1's input is read
+        put_slice<NP>(lds, 0, L, gs);
+        put_slice<NP>(lds, kKsF, L, dot);
+        if constexpr (!TOP) put_slice<NP>(lds, 2 * kKsF, L, go);
+        const Slice a1 = kept_slice<1>(A.a1, 0, L);
+        __syncthreads();
+        floatx16 acc[1][1] = {};
+        product<NP, 1, 1, KN>(acc, W, lds, 0, L, true);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dot.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(a1[e]);
+    }
+    // M1^T: adjoints of s (added to gs) and of |V v|
+    Slice gn;
+    {
+        Weights<NP, 2, kKsF, 2> W(A.M1t, 2 * kF, L.w, 4, L);
+        __syncthreads();
+        put_slice<NP>(lds, 0, L, dot);
+        __syncthreads();
+        floatx16 acc[2][1] = {{start_at<NP>(gs)}, {floatx16{}}};
+        product<NP, 2, 1, kKsF>(acc, W, lds, 0, L, two_sums(A.n, 2 * kF));
+        gn = as_slice(acc[1][0]);
+        store_slice<1, kF>(A.gs_out, 0, 0, L, end_with<NP>(acc[0][0], gs), turn);
+    }
+    // adjoints of U v and V v, one after the other through the same regions;
+    // BF16 models add gv last (g_vmid = gv + [gU gV] [U; V])
+    floatx16 sums[1][3], sep[1][3] = {};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sums[0][c] = NP == 1 ? floatx16{} : gv[0][c];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        Weights<NP, 1, kKsF, 4> W(m ? A.Vt : A.Ut, kF, L.w, 1, L);
+        __syncthreads();
+        Slice nn;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const Slice v = kept_slice<6>(A.UV, 2 * c + 1, L);
+            Slice t;
+            if (m == 0) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    nn.v[e >> 2][e & 3] = fmaf(v[e], v[e], c ? nn[e] : 1e-8f);
+                    t.v[e >> 2][e & 3] = TOP ? gsq[e] * v[e] : fmaf(gsq[e], v[e], gv[0][c][e] * o[e]);
+                }
+            } else {
+                const Slice u = kept_slice<6>(A.UV, 2 * c, L);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) t.v[e >> 2][e & 3] = fmaf(gn[e], v[e], gsq[e] * u[e]);
+            }
+            put_slice<NP>(lds + c * CB, 0, L, t);
+        }
+        if (m == 0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) gn.v[e >> 2][e & 3] = gn[e] / sqrtf(nn[e]);
+        }
+        __syncthreads();
+        product<NP, 1, 3, kKsF>(sums, sep, W, lds, CB, L, true);
+    }
+    fold(sums, sep);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        store_slice<3, kF>(A.gv_out, c, 0, L, end_with<NP>(sums[0][c], as_slice(gv[0][c])), turn);
+}
+
+// ---------------------------------------------------------- weight packing --
+// One 16-byte unit (eight k of one row) per thread and matrix: dst piece p,
+// unit ((n / 16) K/8 + k8) 16 + n % 16.  With `tr` the matrix is the
+// transpose of the stored one ([K][N] row-major).
+__global__ void __launch_bounds__(256) k_pack_frags(PackFrags P, int np) {
+    const PackFrags::Mat m = P.m[blockIdx.y];
+    const int k8n = m.K / 8;
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= m.N * k8n) return;
+    const int n = (t / (16 * k8n)) * 16 + t % 16, k8 = (t / 16) % k8n;
+    __bf16* dst = reinterpret_cast<__bf16*>(m.dst) + int64_t(t) * 8;
+    const int64_t ps = int64_t(m.N) * m.K;
+    for (int q = 0; q < 8; ++q) {
+        const int k = 8 * k8 + q;
+        float x = m.tr ? m.src[int64_t(k) * m.N + n] : m.src[int64_t(n) * m.K + k];
+        for (int p = 0; p < np; ++p) {
+            const __bf16 b = __bf16(x);
+            dst[p * ps + q] = b;
+            x -= float(b);
+        }
+    }
+}
+
+template <typename K, typename Args>
+void launch_block(K kern, const Args& a, int np, hipStream_t s) {
+    kern<<<cdiv(a.n, kTile), 256, lds_bytes(np), s>>>(a);
+    NNP_LAUNCH_CHECK();
+}
+
+// more than 64 KB of dynamic LDS: raise the limit of each instance once per
+// device (the first call of a process on it; an idempotent setting)
+template <typename K>
+void raise_lds(K kern, int np) {
+    NNP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                lds_bytes(np)));
+}
+
+}  // namespace
+
+void launch_pack_frags(const PackFrags& P, int count, int np, hipStream_t s) {
+    int most = 0;
+    for (int k = 0; k < count; ++k) most = std::max(most, P.m[k].N * P.m[k].K / 8);
+    k_pack_frags<<<dim3(cdiv(most, 256), count), 256, 0, s>>>(P, np);
+    NNP_LAUNCH_CHECK();
+}
+
+void atom_block_setup() {
+    raise_lds(k_atom_fwd<3, false>, 3);
+    raise_lds(k_atom_fwd<3, true>, 3);
+    raise_lds(k_atom_bwd<3, false>, 3);
+    raise_lds(k_atom_bwd<3, true>, 3);
+}
+
+void launch_atom_fwd(const AtomFwd& a, bool last, bool bf16, hipStream_t s) {
+    if (a.n <= 0) return;
+    ScopedTimer timer("gemm", s);
+    if (bf16) {
+        if (last) launch_block(k_atom_fwd<1, true>, a, 1, s);
+        else launch_block(k_atom_fwd<1, false>, a, 1, s);
+    } else {
+        if (last) launch_block(k_atom_fwd<3, true>, a, 3, s);
+        else launch_block(k_atom_fwd<3, false>, a, 3, s);
+    }
+}
+
+void launch_atom_bwd(const AtomBwd& a, bool top, bool bf16, hipStream_t s) {
+    if (a.n <= 0) return;
+    ScopedTimer timer("gemm", s);
+    if (bf16) {
+        if (top) launch_block(k_atom_bwd<1, true>, a, 1, s);
+        else launch_block(k_atom_bwd<1, false>, a, 1, s);
+    } else {
+        if (top) launch_block(k_atom_bwd<3, true>, a, 3, s);
+        else launch_block(k_atom_bwd<3, false>, a, 3, s);
+    }
+}
+
+}  // namespace nnp

@@ -2,8 +2,8 @@
 //
 // C(m, n) = epi( sum_k A(m, k) B(k, n) + bias(n) ) with strided operands.
 // Two kernel families:
-//  * k_gemm_x3 (the products X W^T of the force evaluation, K of 128, 256 or
-//    384): bfloat16 matrix cores, FP32 models through operands split into
+//  * k_gemm_x3 (the products X W^T of the force evaluation with K of 128 or
+//    256 that are not part of the per-atom blocks): bfloat16 matrix cores, FP32 models through operands split into
 //    three bfloat16 pieces, BF16 models through rounded operands;
 //  * k_gemm / k_gemm_rk (other shapes, the weight adjoints G^T X by chunks
 //    of rows, and everything when the older kernels are selected): float32
@@ -464,12 +464,13 @@ __global__ void __launch_bounds__(256) k_gemm_x3(GemmArgs g) {
 }
 
 // Shapes and alignment the split-bfloat16 kernel assumes: k contiguous in A
-// with 16-byte aligned rows, K one of 128, 256, 384, N a multiple of 32, the
+// with 16-byte aligned rows, K = 128 (width-64 models; the first layer by
+// species) or 256 (the latter with many species, float32-equivalent only), N a multiple of 32, the
 // weight pieces present and 16-byte aligned (for BF16 models only the
 // first piece, the rounded weights, is read).
 static bool x3_ok(const GemmArgs& g) {
     return g.Bx && g.chunk_rows == 0 && g.sak == 1 && g.sam % 4 == 0 &&
-           (g.K == 128 || g.K == 256 || g.K == 384) && g.N % 32 == 0 && g.bxs % 8 == 0 &&
+           (g.K == 128 || (g.K == 256 && !g.bf16)) && g.N % 32 == 0 && g.bxs % 8 == 0 &&
            (reinterpret_cast<uintptr_t>(g.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.Bx) & 15) == 0;
 }
 
@@ -482,14 +483,11 @@ static void x3_launch(const GemmArgs& g, hipStream_t stream) {
     const dim3 grid(x3_blocks(g, wide ? 2 : 1));
     if (g.bf16) {  // BF16 models: the rounded operands, one product
         if (wide) k_gemm_x3<2, 128, 4, 1><<<grid, 256, 0, stream>>>(g);
-        else if (g.K == 128) k_gemm_x3<1, 128, 4, 1><<<grid, 256, 0, stream>>>(g);
-        else if (g.K == 256) k_gemm_x3<1, 256, 4, 1><<<grid, 256, 0, stream>>>(g);
-        else k_gemm_x3<1, 384, 4, 1><<<grid, 256, 0, stream>>>(g);
+        else k_gemm_x3<1, 128, 4, 1><<<grid, 256, 0, stream>>>(g);
     } else {
         if (wide) k_gemm_x3<2, 128, 4, 3><<<grid, 256, 0, stream>>>(g);
         else if (g.K == 128) k_gemm_x3<1, 128, 4, 3><<<grid, 256, 0, stream>>>(g);
-        else if (g.K == 256) k_gemm_x3<1, 256, 4, 3><<<grid, 256, 0, stream>>>(g);
-        else k_gemm_x3<1, 384, 4, 3><<<grid, 256, 0, stream>>>(g);
+        else k_gemm_x3<1, 256, 4, 3><<<grid, 256, 0, stream>>>(g);
     }
 }
 
@@ -513,6 +511,7 @@ void launch_split3(const float* src, int64_t count, uint16_t* dst, int64_t piece
 
 static std::atomic<int> g_dense_mode{0};
 void set_dense_mode(int mode) { g_dense_mode.store(mode); }
+bool dense_auto() { return g_dense_mode.load() == 0; }
 
 // Operands qualify for k_gemm_rk when k is contiguous in both, K and the row
 // strides are multiples of 4 and the bases 16-byte aligned.

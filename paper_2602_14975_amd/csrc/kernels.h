@@ -137,6 +137,51 @@ bool gemm_x3_split(int M, int N, int K, const float* X, int ldx, const uint16_t*
                    int64_t wx_stride, int m_split, float* out, int ldo, hipStream_t s);
 void gemm_xwt_f32_split(int M, int N, int K, const float* X, int ldx, const float* W, const float* W2, int m_split,
                         float* out, int ldo, hipStream_t s);
+// ------------------------------------------- per-atom blocks (width 128) --
+// Matrices as operand fragments of the per-atom blocks (atom_block.hip).
+struct PackFrags {
+    static constexpr int kMax = 12;
+    struct Mat {
+        const float* src;  // [N][K] row-major, or [K][N] with tr
+        uint16_t* dst;     // np pieces of N * K
+        int N, K, tr;
+    } m[kMax];
+};
+void launch_pack_frags(const PackFrags& P, int count, int np, hipStream_t s);
+// Once per device before the first launch of a block.
+void atom_block_setup();
+
+// Forward block after a message step: update block, then the next layer's
+// phi perceptron (last = false) or the readout with the energy's adjoint of
+// s (last = true: W1 = Wo, b1 = bo, W2 = Wo transposed, s_out = the adjoint).
+struct AtomFwd {
+    int n;
+    const float *smid, *vmid;
+    const uint16_t *U, *M1, *M2, *W1, *W2;  // packed; U is [U; V]
+    const float *m1, *m2, *b1, *b2;
+    float *UV, *a1, *pqo, *s_out, *v_out, *h1, *phi, *pv;
+    // last
+    const float *wo, *beta;
+    const int* species;
+    int n_species;
+    float* Ei;
+    const int* perm;
+};
+void launch_atom_fwd(const AtomFwd& a, bool last, bool bf16, hipStream_t s);
+// Reverse block before a message step's reverse: with top = false the next
+// layer's phi adjoint first (gphi, h1, W2t, W1t), then the update block's.
+// UV, pqo, a1 and h1 in the order the forward block left them (rows padded to
+// a multiple of 32); packed matrices transposed.
+struct AtomBwd {
+    int n;
+    const float *gs_in, *gv_in, *gphi, *h1, *UV, *pqo, *a1;
+    const uint16_t *W2t, *W1t, *M2t, *M1t, *Ut, *Vt;
+    float *gs_out, *gv_out;
+};
+void launch_atom_bwd(const AtomBwd& a, bool top, bool bf16, hipStream_t s);
+// Whether the matrix-core dense kernels are selected (nnp_set_dense_kernels).
+bool dense_auto();
+
 // dst[p * piece_stride + e] = piece p (hi, mid, lo) of src[e] as bfloat16
 void launch_split3(const float* src, int64_t count, uint16_t* dst, int64_t piece_stride, hipStream_t s);
 // 0: FP32 products on split-bfloat16 matrix cores where the shapes allow

@@ -49,6 +49,7 @@ struct MpGeom {
 };
 
 struct MpFwd {
+    bool pv_ready;  // pv already holds phi_b * v_in
     const float *s_in, *v_in, *phi, *Wr, *br;
     float *s_out, *v_out;
     // first layer: inputs are s = emb[t], v = 0, and phi = phi_tab[t] per species

@@ -812,7 +812,8 @@ void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, cons
         set_error("matrix-core message step: no phi_b * v buffer");
         throw Fail{NNP_EINVAL};
     }
-    k_phib_v<<<cdiv(int64_t(mg.n) * (kMxF / 4), 256), 256, 0, s>>>(mg.n, a.phi, a.v_in, a.pv);
+    if (!a.pv_ready)
+        k_phib_v<<<cdiv(int64_t(mg.n) * (kMxF / 4), 256), 256, 0, s>>>(mg.n, a.phi, a.v_in, a.pv);
     launch_mx(t, k_message_fwd_mx<false>, mg.n, s, mg, a);
 }
 
