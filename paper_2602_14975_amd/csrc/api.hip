@@ -416,7 +416,7 @@ static bool atom_blocks_on(const Model* m) { return m->wf && dense_auto(); }
 
 void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, ModelBuf& b, hipStream_t s) {
     const int n = int(sys.n_atoms);
-    const bool blocks = atom_blocks_on(m);
+    const bool blocks = b.blocks;
     const int F = m->desc.width, K = m->desc.n_rbf, S = m->desc.n_species;
     const int cut = m->desc.kind == NNP_MODEL_CONS ? 0 : 1;
     for (int l = 0; l < m->n_layers(); ++l) {
@@ -533,7 +533,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     const LayerOff& lo = m->loff[l];
     LayerBuf& lb = b.layer[l];
     const bool wg = dtheta != nullptr;
-    const bool blocks = !wg && atom_blocks_on(m);
+    const bool blocks = b.blocks;
     if (blocks) {
         AtomBwd f{};
         f.n = n;
@@ -678,6 +678,7 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     const int F = m->desc.width;
     MpGeom mg = make_geom(m, sys, geom, nl);
     mg.perm = perm;
+    b.blocks = atom_blocks_on(m);
     if (b.ecnt && message_mx_active(F, m->desc.n_rbf, 0)) {
         // the edges within the cutoff, prepared once for all six message launches
         // (with the first layer by neighbour species, its edge sums in the same pass)
@@ -692,7 +693,7 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     }
     embed_forward(m, sys, mg, b, s);
     const int L = m->n_layers();
-    const bool blocks = atom_blocks_on(m);  // the last forward block then includes the readout
+    const bool blocks = b.blocks;  // the last forward block then includes the readout
     if (!blocks) {
         gemm_xwt(n, F, F, b.s[L], F, m->p(m->off_Wo), m->p(m->off_bo), b.zo, F, EPI_SILU, b.ao, F, false, s, m->bf16(),
                  m->px(m->off_Wo), m->wx_stride());

@@ -109,6 +109,7 @@ struct ModelBuf {
     float* s[kMaxLayers + 1];
     float* v[kMaxLayers + 1];
     LayerBuf layer[kMaxLayers];
+    bool blocks = false;  // this evaluation runs the per-atom blocks (set once at its start)
     float *ao = nullptr, *zo = nullptr, *Ei = nullptr;
     float *QK = nullptr, *Vh = nullptr, *gQK = nullptr, *gVh = nullptr;
     float *gs = nullptr, *gs2 = nullptr, *gv = nullptr, *gv2 = nullptr, *gpqo = nullptr, *ga1 = nullptr,
