@@ -116,7 +116,7 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
     e = hipMemcpy(m->w, w32.data(), sizeof(float) * m->n_weights, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&m->tab, sizeof(float) * 5 * d.n_species * d.width);
     if (e == hipSuccess && d.kind == NNP_MODEL_NC && d.width <= 32)
-        e = hipMalloc(&m->ncw, sizeof(float) * nc_image_count(d.width));
+        e = hipMalloc(&m->ncw, sizeof(float) * nc_pack_count(d.width));
     if (e == hipSuccess) e = hipMalloc(&m->wT, sizeof(float) * m->n_weights);
     if (e == hipSuccess) e = hipMalloc(&m->mxs, sizeof(float) * 2 * kMaxLayers);
     if (e == hipSuccess && d.kind == NNP_MODEL_CONS && species_sum_shape(d.width, d.n_rbf, 0, d.n_species)) {
@@ -337,7 +337,7 @@ void Model::refresh_tables(hipStream_t s) {
     const LayerOff& lo = loff[0];
     gemm_xwt(S, F, F, p(off_emb), F, p(lo.W1), p(lo.b1), z_tab(), F, EPI_SILU, h1_tab(), F, false, s, bf16());
     gemm_xwt(S, 3 * F, F, z_tab(), F, p(lo.W2), p(lo.b2), phi_tab(), 3 * F, EPI_NONE, nullptr, 0, false, s, bf16());
-    if (ncw) pack_nc_weights(F, p(lo.U), p(lo.M1), p(lo.M2), p(off_Wq), p(off_WV), bf16(), ncw, s);
+    if (ncw) nc_pack_weights(F, p(lo.U), p(lo.M1), p(lo.M2), p(off_Wq), p(off_WV), bf16(), ncw, s);
     if (sp) {
         launch_sp_tables(F, S, p(lo.Wr), p(lo.br), phi_tab(), p(off_emb), sp, sp + 2 * int64_t(F) * sp_ep, s);
         launch_split3(sp, sp_count(), sp_x, sp_xs(), s);
@@ -719,33 +719,19 @@ void nc_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const n
     const int HC = 2 * (m->desc.n_s + m->desc.n_l) * m->desc.n_c;
     MpGeom mg = make_geom(m, sys, geom, nl);
     mg.perm = perm;
-    if (F <= 32) {
-        // inference: species-table perceptron, message, then one fused kernel
-        // for the update block and the projections (no intermediates kept)
-        const int K = m->desc.n_rbf, S = m->desc.n_species;
+    if (m->ncw) {
+        // inference: species-table perceptron, then message, update block and
+        // projections in one kernel (no intermediates kept); the pair head
+        // reads the edges it leaves as records (no second pair rule)
+        const bool records = b.nc_edges && nl.capacity <= b.nc_edge_cap;
         const LayerOff& lo = m->loff[0];
-        LayerBuf& lb = b.layer[0];
-        MpFwd a{};
-        a.Wr = m->p(lo.Wr);
-        a.br = m->p(lo.br);
-        a.s_out = lb.smid;
-        a.v_out = lb.vmid;
-        a.species = sys.species;
-        a.phi_tab = b.phi_tab;
-        a.emb = m->p(m->off_emb);
-        // the pair head then reads the edges as records (no second pair rule)
-        const bool records = b.nc_edges && nl.capacity <= b.nc_edge_cap && K == 8 && m->desc.n_s == 8;
-        if (records) {
-            a.edge_out = b.nc_edges;
-            a.edge_cnt = b.nc_ecnt;
-        }
-        launch_message_fwd(F, K, 1, mg, a, s);
-        NcUpdateArgs u{n, lb.smid, lb.vmid, m->ncw, m->p(lo.m1), m->p(lo.m2), b.QK, b.Vh};
-        if (m->ncw && launch_nc_update_proj(u, F, m->bf16(), s)) {
-            if (records) launch_head_fwd_rec(mg, b.nc_ecnt, b.nc_edges, b.QK, b.Vh, forces, false, s, vir_set, vir_add);
-            else launch_head_fwd(mg, b.QK, b.Vh, forces, false, s, vir_set, vir_add);
-            return;
-        }
+        launch_nc_embed(mg,
+                        {m->p(lo.Wr), m->p(lo.br), b.phi_tab, m->p(m->off_emb), m->ncw, m->p(lo.m1), m->p(lo.m2),
+                         records ? b.nc_edges : nullptr, records ? b.nc_ecnt : nullptr, b.QK, b.Vh},
+                        F, m->bf16(), s);
+        if (records) launch_head_fwd_rec(mg, b.nc_ecnt, b.nc_edges, b.QK, b.Vh, forces, false, s, vir_set, vir_add);
+        else launch_head_fwd(mg, b.QK, b.Vh, forces, false, s, vir_set, vir_add);
+        return;
     }
     embed_forward(m, sys, mg, b, s);
     gemm_xwt(n, HC, F, b.s[1], F, m->p(m->off_Wq), nullptr, b.QK, HC, EPI_NONE, nullptr, 0, false, s, m->bf16(),

@@ -2,9 +2,6 @@
 // the non-conservative pair head (paper, Methods: q_ih, k_ih, c_ijh, F_ij,
 // F_i = sum_j (F_ij - F_ji)).  The dense contractions around them run in
 // gemm.hip; the edge loops of the embedding in mp.hip.
-#include <algorithm>
-#include <atomic>
-
 #include "common.h"
 #include "kernels.h"
 #include "mp_edge.h"
@@ -674,323 +671,6 @@ __global__ void __launch_bounds__(64) k_head_bwd(MpGeom mg, const float* __restr
         const int h = lane / 3, a = lane % 3;
         gVh[(int64_t(i) * 3 + a) * kNl + h] = gv_acc;
     }
-}
-
-// ------------------------------------------------- fused NC update block --
-// Update block of the one-layer NC embedding followed by its q/k and vector
-// projections, for widths F <= 32: one lane per feature column of two atoms
-// (each weight read from LDS serves both).
-// The model keeps an LDS image of these weights (pack_nc_weights: one row
-// per output, rows padded by four floats, rounded for BF16 models), so
-// staging is a straight 16-byte copy; a lane then reads four consecutive k
-// of its output's row per 16-byte LDS read (the padding puts the rows of
-// neighbouring lanes in different banks), the per-atom inputs as broadcast
-// 16-byte reads, and the block walks over groups of atoms.  Every sum runs
-// over k in increasing order.  With BF16, weights and every perceptron input
-// are rounded to bfloat16 and products accumulate in float32, as in the MFMA
-// GEMMs of the general path.
-__device__ __forceinline__ float bf16_round(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return __uint_as_float(u & 0xFFFF0000u);
-}
-
-// floats of the packed image: rows of U;V (2F), M2 (3F), W_qk (HC) and W_V
-// (n_l) of pitch F + 4, rows of M1 (F) of pitch 2F + 4
-// atoms per lane and block pass of k_nc_update_proj
-constexpr int kNcAtomsPerLane = 2;
-
-constexpr int64_t nc_image_floats(int F) {
-    return int64_t(5 * F + 2 * kH * kNc + kNl) * (F + 4) + int64_t(F) * (2 * F + 4);
-}
-
-template <int F, bool BF16>
-__global__ void __launch_bounds__(256) k_nc_update_proj(NcUpdateArgs a) {
-    constexpr int HC = 2 * kH * kNc;  // q and k outputs
-    constexpr int GPB = 256 / F;      // lane groups per block
-    constexpr int NA = kNcAtomsPerLane;
-    constexpr int APB = NA * GPB;     // atoms per block pass
-    constexpr int QPL = HC / F;       // q/k outputs per lane
-    static_assert(HC % F == 0, "q/k outputs split evenly over the lanes of an atom");
-    constexpr int P1 = F + 4, P2 = 2 * F + 4;
-    extern __shared__ float lds[];
-    float* UV = lds;                   // [2F][P1]  outputs of U, then of V
-    float* M1 = UV + 2 * F * P1;       // [F][P2]
-    float* M2 = M1 + F * P2;           // [3F][P1]
-    float* Q = M2 + 3 * F * P1;        // [HC][P1]
-    float* WV = Q + HC * P1;           // [kNl][P1]
-    float* m1 = WV + kNl * P1;         // [F]
-    float* m2 = m1 + F;                // [3F]
-    float* work = m2 + 3 * F;          // per atom: sm[F], vm[3F], x[2F], z[F], so[F], vo[3F]
-    auto rnd = [](float x) { return BF16 ? bf16_round(x) : x; };
-    auto ld4 = [](const float* p) { return *reinterpret_cast<const float4*>(p); };
-    constexpr int NW = int(nc_image_floats(F));
-    static_assert(NW % 4 == 0, "image of whole 16-byte units");
-    {
-        // every load issued before the first store: one round trip per block
-        constexpr int U = (NW / 4 + 255) / 256;
-        float4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            v[u] = reinterpret_cast<const float4*>(a.wt)[min(int(threadIdx.x) + u * 256, NW / 4 - 1)];
-        const float b1 = a.m1[threadIdx.x % F], b2 = a.m2[threadIdx.x % (3 * F)];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int idx = threadIdx.x + u * 256;
-            if (idx < NW / 4) reinterpret_cast<float4*>(lds)[idx] = v[u];
-        }
-        if (threadIdx.x < F) m1[threadIdx.x] = b1;
-        if (threadIdx.x < 3 * F) m2[threadIdx.x] = b2;
-    }
-    // lane (g, f) takes feature f of atoms base + g + u GPB, u < NA: every
-    // weight read from LDS serves NA atoms
-    const int g = threadIdx.x / F, f = threadIdx.x % F;
-    float *sm[NA], *vm[NA], *x[NA], *z[NA], *so[NA], *vo[NA];
-#pragma unroll
-    for (int u = 0; u < NA; ++u) {
-        sm[u] = work + (g + u * GPB) * 11 * F;
-        vm[u] = sm[u] + F;
-        x[u] = vm[u] + 3 * F;
-        z[u] = x[u] + 2 * F;
-        so[u] = z[u] + F;
-        vo[u] = so[u] + F;
-    }
-    const int n = a.n;
-    for (int base = blockIdx.x * APB; base < n; base += gridDim.x * APB) {
-        __syncthreads();  // weights staged / previous pass done with the work rows
-        // the work rows hold perceptron inputs as the products read them
-        // (rounded once here for BF16 models); the lane keeps its own
-        // columns of s and v unrounded for the residual sums
-        float s_own[NA], v_own[NA][3];
-#pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            const int i = base + g + u * GPB;
-            const bool act = i < n;
-            s_own[u] = act ? a.smid[int64_t(i) * F + f] : 0.f;
-            sm[u][f] = rnd(s_own[u]);
-#pragma unroll
-            for (int al = 0; al < 3; ++al) {
-                v_own[u][al] = act ? a.vmid[(int64_t(i) * 3 + al) * F + f] : 0.f;
-                vm[u][al * F + f] = rnd(v_own[u][al]);
-            }
-        }
-        __syncthreads();
-        float Uv[NA][3] = {}, Vv[NA][3] = {};
-        {
-            const float* ur = UV + f * P1;
-            const float* vr = UV + (F + f) * P1;
-#pragma unroll 2
-            for (int k = 0; k < F; k += 4) {
-                const float4 uw = ld4(ur + k);
-                const float4 vw = ld4(vr + k);
-#pragma unroll
-                for (int u = 0; u < NA; ++u)
-#pragma unroll
-                    for (int al = 0; al < 3; ++al) {
-                        const float4 vk = ld4(vm[u] + al * F + k);
-                        Uv[u][al] = fmaf(uw.x, vk.x, Uv[u][al]);
-                        Vv[u][al] = fmaf(vw.x, vk.x, Vv[u][al]);
-                        Uv[u][al] = fmaf(uw.y, vk.y, Uv[u][al]);
-                        Vv[u][al] = fmaf(vw.y, vk.y, Vv[u][al]);
-                        Uv[u][al] = fmaf(uw.z, vk.z, Uv[u][al]);
-                        Vv[u][al] = fmaf(vw.z, vk.z, Vv[u][al]);
-                        Uv[u][al] = fmaf(uw.w, vk.w, Uv[u][al]);
-                        Vv[u][al] = fmaf(vw.w, vk.w, Vv[u][al]);
-                    }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            float nn = 1e-8f;
-#pragma unroll
-            for (int al = 0; al < 3; ++al) nn = fmaf(Vv[u][al], Vv[u][al], nn);
-            x[u][f] = sm[u][f];
-            x[u][F + f] = rnd(sqrtf(nn));
-        }
-        __syncthreads();
-        {
-            float a1[NA];
-#pragma unroll
-            for (int u = 0; u < NA; ++u) a1[u] = m1[f];
-            const float* wr = M1 + f * P2;
-#pragma unroll 4
-            for (int k = 0; k < 2 * F; k += 4) {
-                const float4 w = ld4(wr + k);
-#pragma unroll
-                for (int u = 0; u < NA; ++u) {
-                    const float4 xv = ld4(x[u] + k);
-                    a1[u] = fmaf(w.x, xv.x, a1[u]);
-                    a1[u] = fmaf(w.y, xv.y, a1[u]);
-                    a1[u] = fmaf(w.z, xv.z, a1[u]);
-                    a1[u] = fmaf(w.w, xv.w, a1[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NA; ++u) z[u][f] = rnd(silu(a1[u]));
-        }
-        __syncthreads();
-        float pq[NA][3];
-#pragma unroll
-        for (int u = 0; u < NA; ++u)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) pq[u][c] = m2[c * F + f];
-#pragma unroll 2
-        for (int k = 0; k < F; k += 4) {
-            float4 zk[NA];
-#pragma unroll
-            for (int u = 0; u < NA; ++u) zk[u] = ld4(z[u] + k);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float4 w = ld4(M2 + (c * F + f) * P1 + k);
-#pragma unroll
-                for (int u = 0; u < NA; ++u) {
-                    pq[u][c] = fmaf(w.x, zk[u].x, pq[u][c]);
-                    pq[u][c] = fmaf(w.y, zk[u].y, pq[u][c]);
-                    pq[u][c] = fmaf(w.z, zk[u].z, pq[u][c]);
-                    pq[u][c] = fmaf(w.w, zk[u].w, pq[u][c]);
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            const float dot = Uv[u][0] * Vv[u][0] + Uv[u][1] * Vv[u][1] + Uv[u][2] * Vv[u][2];
-            so[u][f] = rnd(s_own[u] + pq[u][0] + pq[u][1] * dot);
-#pragma unroll
-            for (int al = 0; al < 3; ++al) vo[u][al * F + f] = rnd(v_own[u][al] + pq[u][2] * Uv[u][al]);
-        }
-        __syncthreads();
-        {
-            // q/k outputs f + q F, q < QPL, of every atom of the lane: one
-            // read of each input chunk serves all of them
-            float acc[NA][QPL] = {};
-#pragma unroll 2
-            for (int k = 0; k < F; k += 4) {
-                float4 sv[NA];
-#pragma unroll
-                for (int u = 0; u < NA; ++u) sv[u] = ld4(so[u] + k);
-#pragma unroll
-                for (int q = 0; q < QPL; ++q) {
-                    const float4 w = ld4(Q + (f + q * F) * P1 + k);
-#pragma unroll
-                    for (int u = 0; u < NA; ++u) {
-                        acc[u][q] = fmaf(w.x, sv[u].x, acc[u][q]);
-                        acc[u][q] = fmaf(w.y, sv[u].y, acc[u][q]);
-                        acc[u][q] = fmaf(w.z, sv[u].z, acc[u][q]);
-                        acc[u][q] = fmaf(w.w, sv[u].w, acc[u][q]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NA; ++u) {
-                const int i = base + g + u * GPB;
-                if (i < n) {
-#pragma unroll
-                    for (int q = 0; q < QPL; ++q) a.QK[int64_t(i) * HC + f + q * F] = acc[u][q];
-                }
-            }
-        }
-        if (f < 3 * kNl) {
-            const int h = f / 3, al = f % 3;
-            const float* wr = WV + h * P1;
-            float acc[NA] = {};
-#pragma unroll 2
-            for (int k = 0; k < F; k += 4) {
-                const float4 w = ld4(wr + k);
-#pragma unroll
-                for (int u = 0; u < NA; ++u) {
-                    const float4 vv = ld4(vo[u] + al * F + k);
-                    acc[u] = fmaf(w.x, vv.x, acc[u]);
-                    acc[u] = fmaf(w.y, vv.y, acc[u]);
-                    acc[u] = fmaf(w.z, vv.z, acc[u]);
-                    acc[u] = fmaf(w.w, vv.w, acc[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NA; ++u) {
-                const int i = base + g + u * GPB;
-                if (i < n) a.Vh[(int64_t(i) * 3 + al) * kNl + h] = acc[u];
-            }
-        }
-    }
-}
-
-// The LDS image of k_nc_update_proj, element (row o, column k) of each
-// segment = W[o][k] (zero in the padding), rounded for BF16 models.
-__global__ void k_pack_nc(int F, const float* __restrict__ UV, const float* __restrict__ M1,
-                          const float* __restrict__ M2, const float* __restrict__ Wqk, const float* __restrict__ WV,
-                          int bf16, float* __restrict__ out) {
-    constexpr int HC = 2 * kH * kNc;
-    const int P1 = F + 4, P2 = 2 * F + 4;
-    const int64_t total = nc_image_floats(F);
-    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    int64_t r = t;
-    float v = 0.f;
-    if (r < 2 * F * P1) {
-        const int o = int(r / P1), k = int(r % P1);
-        if (k < F) v = UV[int64_t(o) * F + k];
-    } else if ((r -= 2 * F * P1) < int64_t(F) * P2) {
-        const int o = int(r / P2), k = int(r % P2);
-        if (k < 2 * F) v = M1[int64_t(o) * 2 * F + k];
-    } else if ((r -= int64_t(F) * P2) < 3 * F * P1) {
-        const int o = int(r / P1), k = int(r % P1);
-        if (k < F) v = M2[int64_t(o) * F + k];
-    } else if ((r -= 3 * F * P1) < int64_t(HC) * P1) {
-        const int o = int(r / P1), k = int(r % P1);
-        if (k < F) v = Wqk[int64_t(o) * F + k];
-    } else {
-        r -= int64_t(HC) * P1;
-        const int o = int(r / P1), k = int(r % P1);
-        if (k < F) v = WV[int64_t(o) * F + k];
-    }
-    out[t] = bf16 ? bf16_round(v) : v;
-}
-
-void pack_nc_weights(int F, const float* UV, const float* M1, const float* M2, const float* Wqk, const float* WV,
-                     bool bf16, float* out, hipStream_t st) {
-    const int64_t total = nc_image_floats(F);
-    k_pack_nc<<<cdiv(total, 256), 256, 0, st>>>(F, UV, M1, M2, Wqk, WV, bf16 ? 1 : 0, out);
-    NNP_LAUNCH_CHECK();
-}
-
-size_t nc_update_lds_bytes(int F) {
-    return sizeof(float) *
-           (size_t(nc_image_floats(F)) + size_t(F + 3 * F) + size_t(kNcAtomsPerLane) * size_t(256 / F) * 11 * F);
-}
-
-int64_t nc_image_count(int F) { return nc_image_floats(F); }
-
-bool launch_nc_update_proj(const NcUpdateArgs& a, int F, bool bf16, hipStream_t st) {
-    if (a.n <= 0) return true;
-    const size_t lds = nc_update_lds_bytes(F);
-    const int blocks = std::min(cdiv(a.n, kNcAtomsPerLane * (256 / F)), 512);
-    ScopedTimer timer("nc_update", st);
-    // more than 64 KB of dynamic LDS at F = 32: raise each instance's limit
-    // once (flag per width and precision)
-    static std::atomic<bool> raised[6];
-    const int slot = (F == 32 ? 0 : F == 16 ? 1 : 2) * 2 + (bf16 ? 1 : 0);
-    auto launch = [&](void (*kernel)(NcUpdateArgs)) {
-        if (!raised[slot].load()) {
-            NNP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-            raised[slot].store(true);
-        }
-        kernel<<<blocks, 256, lds, st>>>(a);
-    };
-    if (F == 32) {
-        if (bf16) launch(k_nc_update_proj<32, true>);
-        else launch(k_nc_update_proj<32, false>);
-    } else if (F == 16) {
-        if (bf16) launch(k_nc_update_proj<16, true>);
-        else launch(k_nc_update_proj<16, false>);
-    } else if (F == 8) {
-        if (bf16) launch(k_nc_update_proj<8, true>);
-        else launch(k_nc_update_proj<8, false>);
-    } else {
-        return false;
-    }
-    NNP_LAUNCH_CHECK();
-    return true;
 }
 
 // ------------------------------------------------------------------- host --

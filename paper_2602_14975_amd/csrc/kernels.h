@@ -253,21 +253,21 @@ void launch_head_fwd(const MpGeom& mg, const float* QK, const float* Vh, float* 
 void launch_head_bwd(const MpGeom& mg, const float* QK, const float* Vh, const float* gF, float* gQK, float* gVh,
                      hipStream_t st);
 
-struct NcUpdateArgs {
-    int n;
-    const float *smid, *vmid;                          // message outputs [n][F], [n][3][F]
-    const float *wt, *m1, *m2;                          // packed weights (pack_nc_weights), biases
-    float *QK, *Vh;                                    // [n][2 H n_c], [n][3][n_l]
+// Embedding of NC models of width 8, 16 or 32: message step, update block and
+// q/k/V projections in one kernel (nc_embed.hip).
+struct NcEmbedArgs {
+    const float *Wr, *br, *phi_tab, *emb;  // filter, phi per species [S][3F], embedding [S][F]
+    const float *wt, *m1, *m2;             // packed weights (nc_pack_weights), biases
+    NcEdge* edge_out;                      // or nullptr: edge records at the owner's list positions
+    int* edge_cnt;                         // or nullptr: edges per atom
+    float *QK, *Vh;                        // [n][2 H n_c], [n][3][n_l]
 };
-// Fused update block + q/k/V projections of the NC embedding (widths <= 32);
-// returns false when the width is not supported by the fused kernel.
-bool launch_nc_update_proj(const NcUpdateArgs& a, int F, bool bf16, hipStream_t st);
-// LDS image of U|V, M1, M2, W_qk and W_V for k_nc_update_proj: one row per
-// output, rows padded by four floats (rounded to bfloat16 when bf16);
-// nc_image_count(F) floats
-void pack_nc_weights(int F, const float* UV, const float* M1, const float* M2, const float* Wqk, const float* WV,
-                     bool bf16, float* out, hipStream_t st);
-int64_t nc_image_count(int F);
+void launch_nc_embed(const MpGeom& mg, const NcEmbedArgs& a, int F, bool bf16, hipStream_t s);
+// U|V, M1, M2, W_qk and W_V as its matrix operands (rounded to bfloat16 when
+// bf16); nc_pack_count(F) floats
+void nc_pack_weights(int F, const float* UV, const float* M1, const float* M2, const float* Wqk, const float* WV,
+                     bool bf16, float* out, hipStream_t s);
+int64_t nc_pack_count(int F);
 
 // -------------------------------------------------------------- integrator
 struct BaoaArgs {

@@ -37,8 +37,8 @@ struct Model {
     float* z_tab() const { return tab + int64_t(desc.n_species) * desc.width; }
     float* phi_tab() const { return tab + 2 * int64_t(desc.n_species) * desc.width; }
     // NC models of width <= 32: the update-block and projection weights
-    // (UV, M1, M2, W_qk, W_V) as the LDS image of the fused update kernel
-    // (pack_nc_weights), BF16-rounded for BF16 models; refreshed with the
+    // (UV, M1, M2, W_qk, W_V) as operands of the embedding kernel
+    // (nc_pack_weights), BF16-rounded for BF16 models; refreshed with the
     // tables.
     float* ncw = nullptr;
     // A mirror of the weight vector in which every matrix that input adjoints

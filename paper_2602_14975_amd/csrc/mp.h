@@ -15,7 +15,7 @@ struct EdgeRec {
     float ir;       // 1 / r
 };
 
-// One NC edge within the cutoff as the NC message step leaves it for the
+// One NC edge within the cutoff as the NC embedding leaves it for the
 // pair head (list order within each owner's row): neighbour, r, unit vector
 // and the envelope-weighted Bessel values B_h(r) u(r / rc), float32.
 struct NcEdge {
@@ -62,11 +62,6 @@ struct MpFwd {
     // matrix-core forward of layers past the first, read there and by the
     // reverse in place of phi_b and v_in; ignored elsewhere
     float* pv;
-    // NC forward (vector kernel, F <= 64): when set, the edges within the
-    // cutoff are also written as records at off[i] + rank (rank among the
-    // atom's edges within the cutoff), with their count per atom
-    NcEdge* edge_out;
-    int* edge_cnt;
 };
 
 struct MpBwd {

@@ -14,7 +14,6 @@ struct EdgeSlot {
     float fc, dfc;  // f(r), f'(r)
     float u[3];
     float ir;       // 1 / r
-    float r;        // NC forward only: r in float32
     int j, t;       // neighbour, neighbour species
 };
 
