@@ -127,8 +127,10 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
     // width 64: products of K = 2F (below, no product has a K that the split
     // kernel takes; width 128 has the per-atom blocks)
     if (e == hipSuccess && d.width == 64) e = hipMalloc(&m->wx, sizeof(uint16_t) * 6 * m->wx_stride());
-    if (e == hipSuccess && d.kind == NNP_MODEL_CONS && d.width == 128)
+    if (e == hipSuccess && d.kind == NNP_MODEL_CONS && d.width == 128) {
         e = hipMalloc(&m->wf, sizeof(uint16_t) * m->frag_count());
+        if (e == hipSuccess) e = hipMalloc(&m->mxf, sizeof(uint4) * filter_operand_units() * m->n_layers());
+    }
     if (e != hipSuccess) {
         (void)hipFree(m->w);
         if (m->tab) (void)hipFree(m->tab);
@@ -139,6 +141,7 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         if (m->sp) (void)hipFree(m->sp);
         if (m->sp_x) (void)hipFree(m->sp_x);
         if (m->wf) (void)hipFree(m->wf);
+        if (m->mxf) (void)hipFree(m->mxf);
         delete m;
         set_error(std::string("model set-up: ") + hipGetErrorString(e));
         return NNP_EDEVICE;
@@ -157,6 +160,7 @@ extern "C" nnp_status nnp_model_create(const nnp_model_desc* desc, nnp_model** o
         if (m->sp) (void)hipFree(m->sp);
         if (m->sp_x) (void)hipFree(m->sp_x);
         if (m->wf) (void)hipFree(m->wf);
+        if (m->mxf) (void)hipFree(m->mxf);
         delete m;
         throw;
     }
@@ -176,6 +180,7 @@ extern "C" void nnp_model_destroy(nnp_model* model) {
     if (m->sp) (void)hipFree(m->sp);
     if (m->sp_x) (void)hipFree(m->sp_x);
     if (m->wf) (void)hipFree(m->wf);
+    if (m->mxf) (void)hipFree(m->mxf);
     delete m;
 }
 
@@ -355,6 +360,7 @@ void Model::refresh_tables(hipStream_t s) {
     for (int l = 0; l < n_layers(); ++l) {
         const LayerOff& ll = loff[l];
         launch_filter_scale(3 * F * (desc.n_rbf + 1), p(ll.Wr), mxs + 2 * l, s);  // Wr, then br
+        if (mxf) launch_filter_operands(p(ll.Wr), p(ll.br), mx_scale(l), mxf + l * filter_operand_units(), s);
         tr(ll.W1, F, F);
         tr(ll.W2, 3 * F, F);
         tr(ll.U, 2 * F, F);
@@ -426,6 +432,7 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
         a.Wr = m->p(lo.Wr);
         a.br = m->p(lo.br);
         a.mx_scale = m->mx_scale(l);
+        a.mx_filter = m->mx_filter(l);
         a.s_out = lb.smid;
         a.v_out = lb.vmid;
         if (l == 0) {
@@ -577,6 +584,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     a.Wr = m->p(lo.Wr);
     a.br = m->p(lo.br);
     a.mx_scale = m->mx_scale(l);
+    a.mx_filter = m->mx_filter(l);
     a.gphi = b.gphi;
     a.gv_in = b.gv2;
     a.force = force;

@@ -221,6 +221,10 @@ void launch_sp_bwd(const MpGeom& mg, int S, const float* P0, const float* P2, fl
 void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, const ScopedTimer& t);
 void launch_message_bwd_mx(const MpGeom& mg, const MpBwd& a, hipStream_t s, const ScopedTimer& t);
 void launch_filter_scale(int count, const float* Wr, float* out, hipStream_t s);
+// Filter operands of one layer in the order the matrix-core message kernels
+// read them (filter_operand_units() units of 16 bytes), after its scale.
+int64_t filter_operand_units();
+void launch_filter_operands(const float* Wr, const float* br, const float* scale, uint4* out, hipStream_t s);
 void launch_message_fwd(int F, int K, int cut, const MpGeom& mg, const MpFwd& a, hipStream_t s);
 void launch_message_bwd(int F, int K, int cut, const MpGeom& mg, const MpBwd& a, bool geo, bool wgrad,
                         hipStream_t s);

@@ -60,6 +60,10 @@ struct Model {
     // matrix-core message kernels, and its inverse.
     float* mxs = nullptr;
     const float* mx_scale(int l) const { return mxs + 2 * l; }
+    // Width-128 conservative models: the filter operands of those kernels,
+    // per layer.
+    uint4* mxf = nullptr;
+    const uint4* mx_filter(int l) const { return mxf ? mxf + l * filter_operand_units() : nullptr; }
     // Conservative models of the matrix-core message shape: the first
     // layer's tables by neighbour species (launch_sp_tables), T [2][F][ep]
     // then TT [2][pp][F] (species_sum_pitches), and the same split into

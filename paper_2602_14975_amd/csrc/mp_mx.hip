@@ -20,9 +20,18 @@
 // e_k(r) f(r) and their r-derivatives (float32) already split into FP16
 // pairs.
 //
-// Message kernels: blocks take four atoms in turn with four wavefronts, one
-// per block of 32 features; the wavefronts do not synchronise except once
-// per block in the reverse, to add their force shares.  An atom's edges are
+// Message kernels: blocks take one or two atoms in turn with four wavefronts,
+// one per block of 32 features, which share the staged edges.  The reverse is
+// bound by its vector arithmetic (34 operations per edge and feature, 59 % of
+// its time at 12,288 atoms) and by the rows it gathers through L1 (9 loads
+// per edge and feature, about half of it), the forward by the gathers; what
+// remains is the chain product -> gather -> sums of a batch with three
+// wavefronts per SIMD to hide it.  Held out of that chain: the filter operands
+// (laid out with the weights, in LDS during the kernel), the list rows of the
+// block's atoms (in registers), the sums over lanes (no LDS).  At 12,288 atoms
+// these took the forward from 155 to 137 us and the reverse from 255 to 246,
+// at 1,536 atoms, with fewer atoms to a block, from 31 to 21 and from 48 to
+// 32.  An atom's edges are
 // consumed in batches of fixed size (32 forward, 16 reverse) in list order,
 // so the batch an edge falls into depends only on its rank among the atom's
 // edges within the cutoff: results do not depend on the list radius.
@@ -49,7 +58,7 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kMxF = 128, kMxK = 16, kMxWaves = 4, kMxAtoms = 4;
+constexpr int kMxF = 128, kMxK = 16, kMxWaves = 4, kMxAtoms = 2;
 // forward: edges of a lane whose loads are issued together (eight: 40
 // loads in flight per lane, within three wavefronts per SIMD)
 constexpr int kFwdGroup = 8;
@@ -81,37 +90,56 @@ __device__ __forceinline__ floatx16_t mma3(const half4_t& ab, const half4_t& bb,
     return c;
 }
 
-__device__ __forceinline__ void load8(const float* p, float* x) {
-    const float4 a = *reinterpret_cast<const float4*>(p);
-    const float4 b = *reinterpret_cast<const float4*>(p + 4);
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-}
-
-// This lane's B fragments: rows 8h..8h+7 of column f of the scaled filter
-// weights of each channel, split; and the bias operand of each channel (a
-// 32x32x8 product): rows 0..2 of column f hold (b_hi, b_hi, b_lo) of the
+// A lane's filter operands: of each channel the B fragments (rows 8h..8h+7 of
+// column f of the scaled filter weights, split) and the bias operand (a
+// 32x32x8 product: rows 0..2 of column f hold (b_hi, b_hi, b_lo) of the
 // scaled bias, the other rows zero, so that with A rows (c_hi, c_lo, c_hi,
 // 0, ...) of a per-edge factor c one product gives c b at FP32-equivalent
-// precision.
-__device__ __forceinline__ void load_filter(const float* Wr, const float* br, float sc, int f, int h, half8_t* bh,
-                                            half8_t* bl, half4_t* bb) {
-#pragma unroll
+// precision).  They are functions of the weights: k_filter_operands lays
+// them out once per weight change as pieces bh[0..2], bl[0..2], then bb[0],
+// bb[1] and bb[2] (8 bytes each) in pieces 6 and 7, [wavefront][piece][lane]
+// of 16 bytes, the order in which the kernels read them (into registers, or
+// into LDS as they are).
+constexpr int kFiltPieces = 8;
+
+__device__ __forceinline__ half8_t as_half8(const uint4& u) { return __builtin_bit_cast(half8_t, u); }
+
+__device__ __forceinline__ void load_channel(const uint4* fl, int p, half8_t& bh, half8_t& bl, half4_t& bb) {
+    bh = as_half8(fl[p * 64]);
+    bl = as_half8(fl[(3 + p) * 64]);
+    const uint4 q = fl[(6 + p / 2) * 64];
+    bb = __builtin_bit_cast(half4_t, p % 2 == 0 ? make_uint2(q.x, q.y) : make_uint2(q.z, q.w));
+}
+
+// one thread per lane of the message kernels' four wavefronts
+__global__ void __launch_bounds__(64 * kMxWaves) k_filter_operands(const float* Wr, const float* br,
+                                                                   const float* scale, uint4* out) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int h = lane >> 5, f = w * 32 + (lane & 31);
+    const float sc = scale[0];
+    uint4* fl = out + w * kFiltPieces * 64 + lane;
+    uint2 bias[3];
     for (int p = 0; p < 3; ++p) {
         float x[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) x[q] = Wr[(p * kMxF + f) * kMxK + 8 * h + q] * sc;
-        split8(x, bh[p], bl[p]);
+        half8_t hi, lo;
+        split8(x, hi, lo);
+        fl[p * 64] = __builtin_bit_cast(uint4, hi);
+        fl[(3 + p) * 64] = __builtin_bit_cast(uint4, lo);
         const float b = br[p * kMxF + f] * sc;
         const _Float16 b_hi = static_cast<_Float16>(b);
         const _Float16 b_lo = static_cast<_Float16>(b - static_cast<float>(b_hi));
-        bb[p] = half4_t{};
+        half4_t bb{};
         if (h == 0) {
-            bb[p][0] = b_hi;
-            bb[p][1] = b_hi;
-            bb[p][2] = b_lo;
+            bb[0] = b_hi;
+            bb[1] = b_hi;
+            bb[2] = b_lo;
         }
+        bias[p] = __builtin_bit_cast(uint2, bb);
     }
+    fl[6 * 64] = make_uint4(bias[0].x, bias[0].y, bias[1].x, bias[1].y);
+    fl[7 * 64] = make_uint4(bias[2].x, bias[2].y, 0u, 0u);
 }
 
 // The A operand of the bias product for a row whose per-edge factor is c
@@ -128,13 +156,30 @@ __device__ __forceinline__ half4_t bias_rows(float c, int h) {
     return a;
 }
 
-__device__ __forceinline__ half8_t as_half8(const uint4& u) { return __builtin_bit_cast(half8_t, u); }
-
 // A float at a 32-bit byte offset from a wavefront-uniform base: the
 // neighbour-row gathers then take one 32-bit multiply-add per edge for
 // their address, and the quantities of a row differ by immediate offsets.
 __device__ __forceinline__ float ld_off(const float* base, uint32_t byte_off) {
     return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);
+}
+
+// Sums over the wavefront in the order of a butterfly 32, 16, 8, 4, 2, 1 (the
+// same bits), by lane swaps and row rotations instead of trips through LDS:
+// once the pairs 8 lanes apart are added a row repeats every 8 lanes, so that
+// a rotation by 4 meets the lane 4 apart, and so on.
+__device__ __forceinline__ float add_half(float x) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+template <int N>
+__device__ __forceinline__ float add_rotated(float x) {  // row_ror:N
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float butterfly_sum(float x) {
+    x = add_half(x);
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(x))));
 }
 
 // ---------------------------------------------------------- edge preparation
@@ -303,20 +348,34 @@ __device__ __forceinline__ void store_piece(BatchBuf<BATCH>& b, const uint4& v) 
     if (threadIdx.x < BatchBuf<BATCH>::N) reinterpret_cast<uint4*>(&b)[threadIdx.x] = v;
 }
 
-// The block's batches in processing order: atoms i0 .. i0 + kMxAtoms - 1
-// (those below n), each atom's edges in batches of BATCH.  Returns the list
-// position and size of the batch after batch b0 of atom ai (ai = -1: the
-// first batch), or nb = 0 when there is none.
+// The rows of the block's atoms i0 .. end - 1: lane a holds the list start and
+// the edge count of atom i0 + a (none past the last atom), read once; a row is
+// then a lane read with no trip to memory (as scalar loads where a batch ends,
+// they took a tenth of the reverse).
+struct Rows {
+    int off, cnt, atoms;
+    __device__ __forceinline__ Rows(const MpGeom& mg, int i0, int per) : atoms(min(per, mg.n - i0)) {
+        const int lane = threadIdx.x & 63;
+        off = lane < atoms ? mg.off[i0 + lane] : 0;
+        cnt = lane < atoms ? mg.ecnt[i0 + lane] : 0;
+    }
+    __device__ __forceinline__ int count(int ai) const { return __builtin_amdgcn_readlane(cnt, ai); }
+    __device__ __forceinline__ int start(int ai) const { return __builtin_amdgcn_readlane(off, ai); }
+};
+
+// The block's batches in processing order, each atom's edges in batches of
+// BATCH.  Returns the list position and size of the batch after batch b0 of
+// atom ai (ai = -1: the first batch), or nb = 0 when there is none.
 struct NextBatch {
     int p0, nb;
 };
 
 template <int BATCH>
-__device__ __forceinline__ NextBatch next_batch(const MpGeom& mg, int i0, int ai, int b0, int cnt) {
-    if (ai >= 0 && b0 + BATCH < cnt) return {mg.off[i0 + ai] + b0 + BATCH, min(BATCH, cnt - b0 - BATCH)};
-    for (int a2 = ai + 1; a2 < kMxAtoms && i0 + a2 < mg.n; ++a2) {
-        const int c2 = mg.ecnt[i0 + a2];
-        if (c2 > 0) return {mg.off[i0 + a2], min(BATCH, c2)};
+__device__ __forceinline__ NextBatch next_batch(const Rows& rows, int ai, int b0, int cnt) {
+    if (ai >= 0 && b0 + BATCH < cnt) return {rows.start(ai) + b0 + BATCH, min(BATCH, cnt - b0 - BATCH)};
+    for (int a2 = ai + 1; a2 < rows.atoms; ++a2) {
+        const int c2 = rows.count(a2);
+        if (c2 > 0) return {rows.start(a2), min(BATCH, c2)};
     }
     return {0, 0};
 }
@@ -332,18 +391,24 @@ struct FwdAcc {
 // of a partial batch reads the batch's first edge and contributes nothing).
 template <bool L0>
 __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, const BatchBuf<32>& buf, int nb, int f,
-                                          int h, const half8_t* bh, const half8_t* bl, const half4_t* bb,
-                                          FwdAcc& acc) {
+                                          int h, const uint4* fl, FwdAcc& acc) {
     constexpr int F = kMxF, E = 16;
     const EdgeRec* rec = buf.rec;
     const int r = threadIdx.x & 31;  // A row: edge r (zero past nb: staged as zeros)
     const half8_t ah = as_half8(buf.a[r][h]), al = as_half8(buf.a[r][2 + h]);
     const half4_t ab = bias_rows(rec[r].fc, h);
     // w = Wr (e f) + b f of every channel
-    const floatx16_t wa = mma3(ab, bb[0], ah, al, bh[0], bl[0]);
+    half8_t bh, bl;
+    half4_t bb;
+    load_channel(fl, 0, bh, bl, bb);
+    const floatx16_t wa = mma3(ab, bb, ah, al, bh, bl);
     floatx16_t wb = {};
-    if (!L0) wb = mma3(ab, bb[1], ah, al, bh[1], bl[1]);  // the first layer's vector input is zero
-    const floatx16_t wc = mma3(ab, bb[2], ah, al, bh[2], bl[2]);
+    if (!L0) {  // the first layer's vector input is zero
+        load_channel(fl, 1, bh, bl, bb);
+        wb = mma3(ab, bb, ah, al, bh, bl);
+    }
+    load_channel(fl, 2, bh, bl, bb);
+    const floatx16_t wc = mma3(ab, bb, ah, al, bh, bl);
     const uint32_t fo = uint32_t(f) * 4u;
 #pragma unroll
     for (int g0 = 0; g0 < E; g0 += kFwdGroup) {
@@ -392,7 +457,7 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
 }
 
 template <bool L0>
-__global__ void __launch_bounds__(64 * kMxWaves, 2) k_message_fwd_mx(MpGeom mg, MpFwd a) {
+__global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_fwd_mx(MpGeom mg, MpFwd a, int per) {
     constexpr int F = kMxF, BATCH = 32;
     __shared__ __align__(16) BatchBuf<BATCH> buf[2];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -404,31 +469,33 @@ __global__ void __launch_bounds__(64 * kMxWaves, 2) k_message_fwd_mx(MpGeom mg, 
         for (int t = threadIdx.x; t < mg.n_species * 3 * F; t += blockDim.x) ptab_s[t] = a.phi_tab[t];
         __syncthreads();
     }
-    const float sc = a.mx_scale[0], isc = a.mx_scale[1];
-    half8_t bh[3], bl[3];
-    half4_t bb[3];
-    load_filter(a.Wr, a.br, sc, f, h, bh, bl, bb);
-    const int i0 = xcd_block(blockIdx.x, gridDim.x) * kMxAtoms;
-    NextBatch nx = next_batch<BATCH>(mg, i0, -1, 0, 0);
+    const float isc = a.mx_scale[1];
+    __shared__ __align__(16) uint4 filt_s[kMxWaves][kFiltPieces][64];
+    uint4* fl = &filt_s[w][0][lane];
+#pragma unroll
+    for (int p = 0; p < kFiltPieces; ++p) fl[p * 64] = a.mx_filter[(w * kFiltPieces + p) * 64 + lane];
+    wave_sync_lds();
+    const int i0 = xcd_block(blockIdx.x, gridDim.x) * per;
+    const Rows rows(mg, i0, per);
+    NextBatch nx = next_batch<BATCH>(rows, -1, 0, 0);
     uint4 piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
     int k = 0;  // batches of the block so far (LDS buffer parity)
-    for (int ai = 0; ai < kMxAtoms; ++ai) {
+    for (int ai = 0; ai < rows.atoms; ++ai) {
         const int i = i0 + ai;
-        if (i >= n) break;
-        const int cnt = mg.ecnt[i];
+        const int cnt = rows.count(ai);
         FwdAcc acc{};
         for (int b0 = 0; b0 < cnt; b0 += BATCH, ++k) {
             BatchBuf<BATCH>& b = buf[k & 1];
             store_piece(b, piece);
             __syncthreads();  // the batch is staged; the other buffer's batch is done
-            nx = next_batch<BATCH>(mg, i0, ai, b0, cnt);
+            nx = next_batch<BATCH>(rows, ai, b0, cnt);
             piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
-            fwd_batch<L0>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, bh, bl, bb, acc);
+            fwd_batch<L0>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, fl, acc);
         }
         // both halves of the wavefront hold partial sums of feature f
-        acc.s += __shfl_xor(acc.s, 32, 64);
+        acc.s = add_half(acc.s);
 #pragma unroll
-        for (int al = 0; al < 3; ++al) acc.v[al] += __shfl_xor(acc.v[al], 32, 64);
+        for (int al = 0; al < 3; ++al) acc.v[al] = add_half(acc.v[al]);
         if (h == 0) {
             const int ti = L0 ? min(max(a.species[i], 0), mg.n_species - 1) : 0;
             const float si = L0 ? a.emb[ti * F + f] : a.s_in[int64_t(i) * F + f];
@@ -460,30 +527,6 @@ struct Owner {
 struct BwdAcc {
     float gph0, gph2, GV[3], S1[3], T1, T2[3], vir;
 };
-
-// The split filter operands of a lane in LDS: pieces bh[0..2], bl[0..2],
-// then bb[0], bb[1] and bb[2] (8 bytes each) in pieces 6 and 7, each piece
-// at stride 64 (one lane's) so that a wavefront reads 1 KB contiguously.
-constexpr int kFiltPieces = 8;
-
-__device__ __forceinline__ void store_filter(uint4* fl, const half8_t* bh, const half8_t* bl, const half4_t* bb) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        fl[p * 64] = __builtin_bit_cast(uint4, bh[p]);
-        fl[(3 + p) * 64] = __builtin_bit_cast(uint4, bl[p]);
-    }
-    const uint2 b0 = __builtin_bit_cast(uint2, bb[0]), b1 = __builtin_bit_cast(uint2, bb[1]),
-                b2 = __builtin_bit_cast(uint2, bb[2]);
-    fl[6 * 64] = make_uint4(b0.x, b0.y, b1.x, b1.y);
-    fl[7 * 64] = make_uint4(b2.x, b2.y, 0u, 0u);
-}
-
-__device__ __forceinline__ void load_channel(const uint4* fl, int p, half8_t& bh, half8_t& bl, half4_t& bb) {
-    bh = as_half8(fl[p * 64]);
-    bl = as_half8(fl[(3 + p) * 64]);
-    const uint4 q = fl[(6 + p / 2) * 64];
-    bb = __builtin_bit_cast(half4_t, p % 2 == 0 ? make_uint2(q.x, q.y) : make_uint2(q.z, q.w));
-}
 
 // The neighbour rows one group of edges needs (phi_b of the neighbour
 // enters only as phi_b v_n, read as one product; phi, pv and the vector
@@ -636,7 +679,7 @@ __device__ __forceinline__ void bwd_batch(const MpBwd& a, const float* ptab, con
 }
 
 template <bool L0, bool VIR>
-__global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, MpBwd a) {
+__global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, MpBwd a, int per) {
     constexpr int F = kMxF, BATCH = 16;
     __shared__ __align__(16) BatchBuf<BATCH> buf[2];
     __shared__ float fpart[kMxAtoms][kMxWaves][4];
@@ -656,10 +699,16 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
     uint4* fl = L0 ? nullptr : &filt_s[L0 ? 0 : w][0][lane];
     half8_t bh[3], bl[3];
     half4_t bb[3];
-    load_filter(a.Wr, a.br, sc, f, h, bh, bl, bb);
-    if constexpr (!L0) {
-        store_filter(fl, bh, bl, bb);
-        wave_sync_lds();
+    {
+        const uint4* src = a.mx_filter + w * kFiltPieces * 64 + lane;
+        if constexpr (L0) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) load_channel(src, p, bh[p], bl[p], bb[p]);
+        } else {
+#pragma unroll
+            for (int p = 0; p < kFiltPieces; ++p) fl[p * 64] = src[p * 64];
+            wave_sync_lds();
+        }
     }
     float bf[3] = {};  // the scaled biases, for the first layer's per-edge work
     if constexpr (L0) {
@@ -667,14 +716,14 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
         for (int p = 0; p < 3; ++p) bf[p] = a.br[p * F + f] * sc;
     }
     const int blk = xcd_block(blockIdx.x, gridDim.x);
-    const int i0 = blk * kMxAtoms;
-    NextBatch nx = next_batch<BATCH>(mg, i0, -1, 0, 0);
+    const int i0 = blk * per;
+    const Rows rows(mg, i0, per);
+    NextBatch nx = next_batch<BATCH>(rows, -1, 0, 0);
     uint4 piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
     int k = 0;  // batches of the block so far (LDS buffer parity)
-    for (int ai = 0; ai < kMxAtoms; ++ai) {
+    for (int ai = 0; ai < rows.atoms; ++ai) {
         const int i = i0 + ai;
-        if (i >= n) break;
-        const int cnt = mg.ecnt[i];
+        const int cnt = rows.count(ai);
         Owner o{};
         {
             const int ti = L0 ? min(max(a.species[i], 0), mg.n_species - 1) : 0;
@@ -694,7 +743,7 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
             BatchBuf<BATCH>& b = buf[k & 1];
             store_piece(b, piece);
             __syncthreads();  // the batch is staged; the other buffer's batch is done
-            nx = next_batch<BATCH>(mg, i0, ai, b0, cnt);
+            nx = next_batch<BATCH>(rows, ai, b0, cnt);
             piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
             bwd_batch<L0, VIR>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, fl, bh, bl, bb, bf, o, acc);
         }
@@ -703,14 +752,14 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
         float fs[3];
 #pragma unroll
         for (int al = 0; al < 3; ++al) fs[al] = fmaf(o.gv[al], acc.T1, fmaf(-o.ph[2], acc.T2[al], acc.S1[al]));
-        acc.gph0 += __shfl_xor(acc.gph0, 32, 64);
-        acc.gph2 += __shfl_xor(acc.gph2, 32, 64);
+        acc.gph0 = add_half(acc.gph0);
+        acc.gph2 = add_half(acc.gph2);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) acc.GV[p] += __shfl_xor(acc.GV[p], 32, 64);
+        for (int p = 0; p < 3; ++p) acc.GV[p] = add_half(acc.GV[p]);
         const float gph[3] = {acc.gph0, fmaf(o.v[2], acc.GV[2], fmaf(o.v[1], acc.GV[1], o.v[0] * acc.GV[0])),
                               acc.gph2};
-        const float fx = group_sum<64>(fs[0]), fy = group_sum<64>(fs[1]), fz = group_sum<64>(fs[2]);
-        const float vr = VIR ? group_sum<64>(acc.vir) : 0.f;
+        const float fx = butterfly_sum(fs[0]), fy = butterfly_sum(fs[1]), fz = butterfly_sum(fs[2]);
+        const float vr = VIR ? butterfly_sum(acc.vir) : 0.f;
         if (lane == 0) {
             fpart[ai][w][0] = fx;
             fpart[ai][w][1] = fy;
@@ -735,10 +784,10 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
     // the force (and virial share) of each atom of the block: the feature
     // blocks' shares in a fixed order
     const int t = threadIdx.x;
-    if (t < 4 * kMxAtoms) {
+    if (t < 4 * rows.atoms) {
         const int ai = t / 4, c = t % 4;
         const int i = i0 + ai;
-        if (i < n && (c < 3 || VIR)) {
+        if (c < 3 || VIR) {
             float sum = 0.f;
             for (int k = 0; k < kMxWaves; ++k) sum += fpart[ai][k][c];
             sum *= isc;
@@ -792,11 +841,25 @@ __global__ void __launch_bounds__(256) k_phib_v(int n, const float* __restrict__
     }
 }
 
+// Atoms of a block: one or two, whichever takes fewer turns (an atom's time)
+// of the 3 x 256 blocks that are in flight at once, two where that is equal
+// (half as many starts).  A block's atoms follow one another, so that with
+// fewer blocks than the chip holds the longest block is the time: reverse at
+// 192 atoms 12.6 us with one, 21.0 with two, 37 with four; at 768 21.5 / 30 /
+// 48; at 1,536 33.9 / 32.3 / 45.5 (forward 22.6 / 21.0 / 31.0); at 2,100
+// 47 / 51 / 56; at 12,288 254 / 246 / 245; at 89,373 1,822 / 1,772 / 1,785.
+// An atom's sums do not depend on it.
+int mx_atoms(int n) {
+    const int slots = 3 * 256;
+    return cdiv(n, slots) < 2 * cdiv(cdiv(n, 2), slots) ? 1 : kMxAtoms;
+}
+
 template <typename Kern, typename Args>
 void launch_mx(const ScopedTimer& t, Kern kern, int n, hipStream_t s, const MpGeom& mg, const Args& a) {
-    const dim3 grid(cdiv(n, kMxAtoms));
-    if (t.active && t.by_launch) hipExtLaunchKernelGGL(kern, grid, dim3(64 * kMxWaves), 0, s, t.a, t.b, 0, mg, a);
-    else kern<<<grid, 64 * kMxWaves, 0, s>>>(mg, a);
+    const int per = mx_atoms(n);
+    const dim3 grid(cdiv(n, per));
+    if (t.active && t.by_launch) hipExtLaunchKernelGGL(kern, grid, dim3(64 * kMxWaves), 0, s, t.a, t.b, 0, mg, a, per);
+    else kern<<<grid, 64 * kMxWaves, 0, s>>>(mg, a, per);
 }
 
 }  // namespace
@@ -844,6 +907,13 @@ void launch_edge_prep(const MpGeom& mg, int* ecnt, EdgeRec* erec, uint4* ehalf, 
 
 void launch_filter_scale(int count, const float* Wr, float* out, hipStream_t s) {
     k_filter_scale<<<1, 256, 0, s>>>(count, Wr, out);
+    NNP_LAUNCH_CHECK();
+}
+
+int64_t filter_operand_units() { return int64_t(kMxWaves) * kFiltPieces * 64; }
+
+void launch_filter_operands(const float* Wr, const float* br, const float* scale, uint4* out, hipStream_t s) {
+    k_filter_operands<<<1, 64 * kMxWaves, 0, s>>>(Wr, br, scale, out);
     NNP_LAUNCH_CHECK();
 }
 
