@@ -3,33 +3,38 @@
 // phi perceptron or the readout; reverse: their adjoints), instead of one
 // launch per dense product and elementwise step.
 //
-// A block of four wavefronts owns 32 atoms.  Every product is
+// A block of four wavefronts owns a tile of TA = 32 or 16 atoms.  Every
+// product is
 //   out[feature][atom] = sum_k W[feature][k] x[atom][k]
-// on v_mfma_f32_32x32x16_bf16 with the weights as the first operand, so that
-// lane (atom a = lane % 32, half h = lane / 32) of wavefront w holds features
-// 32 w + 8 g + 4 h + q (g, q < 4) of atom a in its accumulators: four
+// on v_mfma_f32_32x32x16_bf16 (TA = 32) or 16x16x32 (TA = 16) with the
+// weights as the first operand, so that a lane of wavefront w holds of one
+// atom the features 32 w + 8 g + 4 h + q (g, q < 4; h = lane / 32), or
+// 32 w + 16 g + 4 h + q (g < 2; h = lane / 16), in its accumulators: four
 // consecutive features per 16-byte global access, and everything elementwise
 // between the products stays in registers, the same features for all of an
 // atom's quantities.  The inputs of a product pass through LDS as operand
-// fragments (16 bytes per lane and k-step of 16); the weights are read
-// straight from L2 in the packed order of launch_pack_frags, each fragment by
-// one wavefront of the block, a few k-steps ahead.
+// fragments (16 bytes per lane and step); the weights are read straight from
+// L2 in the packed order of launch_pack_frags, each fragment by one
+// wavefront of the block, a few steps ahead.
 //
 // FP32 models split both operands into three bfloat16 pieces and accumulate
 // the six piece products of order >= 2^-18 in float32, smallest first, as
 // k_gemm_x3 does (FP32-equivalent); BF16 models take the operands rounded to
 // bfloat16 and one product.
 //
-// What bounds it: 720 matrix instructions per wavefront and tile (23,000
-// cycles), the walk through 1 MB of packed weights per tile, and the waits
-// between the steps of a tile, at two wavefronts per SIMD.  As separate
+// What bounds it: of a block alone on its CU the way of 1 MB of packed weights
+// from L2 (45 bytes a cycle of at most 64) beside 720 matrix instructions per
+// wavefront (23,000 cycles at 32 atoms, half at 16) and the elementwise work
+// of a lane; of two blocks on a CU these and the rows from memory.  While a
+// block has a CU to itself, 16 atoms take two thirds of the time of 32 (half
+// the matrix and elementwise work per lane, the same weights), beyond that
+// they read the weights twice as often: see small_tiles.  As separate
 // launches the same work moved about 40 F floats per atom and layer through
 // memory forward and more in reverse, 28 products and 15 elementwise launches
 // per evaluation; the blocks move 24 F and are six launches.  Measured,
 // dense products and elementwise launches together, per evaluation (3
 // layers, FP32): 12,288 atoms 885 -> 352 us (blocks of 44 to 66 us); 1,536
-// atoms 460 -> 157 us (19 to 30 us each).  A whole evaluation: 1,536 atoms
-// 0.60 -> 0.36 ms, 12,288 atoms 1.80 -> 1.30 ms, 89,373 atoms 12.4 -> 9.6 ms.
+// atoms 460 -> 115 us (14 to 22 us each; 19 to 30 with 32 atoms to a block).
 #include <algorithm>
 
 #include "common.h"
@@ -47,14 +52,18 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kF = 128;
-constexpr int kTile = 32;        // atoms per block
 constexpr int kFrag = 1024;      // bytes of one operand fragment (64 lanes x 16)
-constexpr int kKsF = kF / 16;    // k-steps of one width
+constexpr int kKsF = kF / 16;    // steps of a product over one width: 16 k of 32 features (TA = 32),
+                                 // or 32 k of 16 of them (TA = 16)
+template <int TA>
+constexpr int kFragsF = TA * kF / 512;  // operand fragments of one width of the tile's atoms, per piece
 // LDS of a block: three regions, each the fragments of F inputs of its atoms
-// (or room to turn one 4 KB slice per wavefront around); 72 KB at three
-// pieces: two blocks per CU
-constexpr int region_bytes(int NP) { return NP == 1 ? 16 * kFrag : kKsF * NP * kFrag; }
-constexpr int lds_bytes(int NP) { return 3 * region_bytes(NP); }
+// (or room to turn one slice per wavefront around); 72 KB at three pieces and
+// 32 atoms: two blocks per CU
+template <int NP, int TA>
+constexpr int kRegion = kFragsF<TA> * kFrag * (NP == 1 ? 2 : NP);
+template <int NP, int TA>
+constexpr int kLdsBytes = 3 * kRegion<NP, TA>;
 
 // Four floats as NP bfloat16 pieces (round to nearest of what the previous
 // pieces leave), two packed words per piece.
@@ -72,11 +81,35 @@ __device__ __forceinline__ void split4(const f32x4_t& x, uint2 (&o)[NP]) {
     }
 }
 
-// A lane's 16 values of one 32-feature slice, element 4 g + q = feature
-// 32 w + 8 g + 4 h + q of its atom.
+// A lane's values of one 32-feature slice: element 4 g + q = feature
+// 32 w + 4 H g + 4 h + q of its atom, H = 64 / TA lanes to an atom.
+template <int TA>
 struct Slice {
-    f32x4_t v[4];
+    static constexpr int H = 64 / TA, G = TA / 8;
+    f32x4_t v[G];
     __device__ __forceinline__ float operator[](int i) const { return v[i >> 2][i & 3]; }
+};
+
+// The sums of one 32-feature slice of a product, element by element those of
+// Slice: one 32 x 32 result, or two of 16 x 16.
+template <int TA>
+struct Sums;
+template <>
+struct Sums<32> {
+    floatx16 c = {};
+    __device__ __forceinline__ float operator[](int e) const { return c[e]; }
+    __device__ __forceinline__ void set(int e, float x) { c[e] = x; }
+    __device__ __forceinline__ void add(const Sums& o) { c += o.c; }
+};
+template <>
+struct Sums<16> {
+    f32x4_t c[2] = {};
+    __device__ __forceinline__ float operator[](int e) const { return c[e >> 2][e & 3]; }
+    __device__ __forceinline__ void set(int e, float x) { c[e >> 2][e & 3] = x; }
+    __device__ __forceinline__ void add(const Sums& o) {
+        c[0] += o.c[0];
+        c[1] += o.c[1];
+    }
 };
 
 // Global memory through buffer descriptors: a uniform base, a uniform offset
@@ -100,6 +133,7 @@ struct Buf {
 };
 
 // This lane's place in the block
+template <int TA>
 struct Lane {
     int lane, w, a, h;
     int64_t t0;  // first atom of the block's tile
@@ -109,84 +143,103 @@ struct Lane {
     __device__ __forceinline__ Lane(int n) {
         lane = threadIdx.x & 63;
         w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        a = lane & 31;
-        h = lane >> 5;
-        t0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * kTile;
+        a = lane % TA;
+        h = lane / TA;
+        t0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * TA;
         i = int(t0) + a;
         on = i < n;
-        rows = min(kTile, n - int(t0));
+        rows = min(TA, n - int(t0));
     }
 };
 
 // Row-major float32 of C rows per atom, row width ld: the lane's slice at
 // column c0 of row c of its atom.
-template <int C, int ld>
-__device__ __forceinline__ Slice load_slice(const float* p, int c, int c0, const Lane& L) {
+template <int C, int ld, int TA>
+__device__ __forceinline__ Slice<TA> load_slice(const float* p, int c, int c0, const Lane<TA>& L) {
     const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
     const uint32_t lo = uint32_t(L.a * (C * ld * 4) + 16 * L.h), o = uint32_t((c * ld + c0 + 32 * L.w) * 4);
-    Slice s;
+    Slice<TA> s;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + 32 * g));
+    for (int g = 0; g < s.G; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + 16 * s.H * g));
     return s;
 }
-// The slice into row-major rows, turned around through 4 KB of LDS (`turn`,
-// this wavefront's own) so that eight lanes write the 128 bytes of a row
-// together: written as held, 16 bytes per lane and row, a store took about
+// The slice into row-major rows, turned around through TA x 128 bytes of LDS
+// (`turn`, this wavefront's own) so that eight lanes write the 128 bytes of a
+// row together: written as held, 16 bytes per lane and row, a store took about
 // 100 cycles and the stores a third of the kernel.
-template <int C, int ld>
-__device__ __forceinline__ void store_slice(float* p, int c, int c0, const Lane& L, const Slice& s, char* turn) {
+template <int C, int ld, int TA>
+__device__ __forceinline__ void store_slice(float* p, int c, int c0, const Lane<TA>& L, const Slice<TA>& s,
+                                            char* turn) {
     const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
     wave_sync_lds();
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4_t*>(turn + L.a * 128 + ((2 * g + L.h) ^ (L.a & 7)) * 16) = s.v[g];
+    for (int g = 0; g < s.G; ++g)
+        *reinterpret_cast<f32x4_t*>(turn + L.a * 128 + ((s.H * g + L.h) ^ (L.a & 7)) * 16) = s.v[g];
     wave_sync_lds();
     const int row = L.lane >> 3, q = L.lane & 7;
     const uint32_t lo = uint32_t(row * (C * ld * 4) + 16 * q + (c * ld + c0 + 32 * L.w) * 4);
 #pragma unroll
-    for (int k = 0; k < 4; ++k)  // rows 8 k + row: the same swizzle
+    for (int k = 0; k < TA / 8; ++k)  // rows 8 k + row: the same swizzle
         b.store(*reinterpret_cast<const u32x4_t*>(turn + (8 * k + row) * 128 + (q ^ row) * 16),
                 lo + 8 * k * (C * ld * 4));
 }
 // Quantities that only these kernels exchange are kept in lane order: slice
 // `c` (of C) of the tile's wavefront w, 1 KB per group of four features.
 // Rows past the last atom are part of the buffers.
-template <int C>
-__device__ __forceinline__ void keep_slice(float* p, int c, const Lane& L, const Slice& s) {
-    const Buf b(p + L.t0 * (C * kF), uint32_t(kTile * C * kF * 4));
+template <int C, int TA>
+__device__ __forceinline__ void keep_slice(float* p, int c, const Lane<TA>& L, const Slice<TA>& s) {
+    const Buf b(p + L.t0 * (C * kF), uint32_t(TA * C * kF * 4));
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-        b.store(__builtin_bit_cast(u32x4_t, s.v[g]), uint32_t(16 * L.lane + ((c * 4 + L.w) * 4 + g) * 1024));
+    for (int g = 0; g < s.G; ++g)
+        b.store(__builtin_bit_cast(u32x4_t, s.v[g]), uint32_t(16 * L.lane + ((c * 4 + L.w) * s.G + g) * 1024));
 }
-template <int C>
-__device__ __forceinline__ Slice kept_slice(const float* p, int c, const Lane& L) {
-    const Buf b(p + L.t0 * (C * kF), uint32_t(kTile * C * kF * 4));
-    Slice s;
+template <int C, int TA>
+__device__ __forceinline__ Slice<TA> kept_slice(const float* p, int c, const Lane<TA>& L) {
+    const Buf b(p + L.t0 * (C * kF), uint32_t(TA * C * kF * 4));
+    Slice<TA> s;
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.lane, uint32_t(((c * 4 + L.w) * 4 + g) * 1024)));
+    for (int g = 0; g < s.G; ++g)
+        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.lane, uint32_t(((c * 4 + L.w) * s.G + g) * 1024)));
     return s;
 }
 // kF per-feature constants (biases)
-__device__ __forceinline__ Slice load_feat(const float* p, const Lane& L) {
+template <int TA>
+__device__ __forceinline__ Slice<TA> load_feat(const float* p, const Lane<TA>& L) {
     const Buf b(p, kF * 4);
-    Slice s;
+    Slice<TA> s;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.h, uint32_t(128 * L.w + 32 * g)));
+    for (int g = 0; g < s.G; ++g)
+        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.h, uint32_t(128 * L.w + 16 * s.H * g)));
     return s;
 }
 
-// The slice as operand fragments: features 32 w .. 32 w + 31 are k-steps
-// 2 w and 2 w + 1 of the fragment array at `buf` (k-step base ks0).  Within
-// these 32, half h of k-step j holds features 16 h + 8 j .. + 7, as in
-// k_gemm_x3.
-template <int NP>
-__device__ __forceinline__ void put_slice(char* buf, int ks0, const Lane& L, const Slice& s) {
+// The slice as operand fragments.  Its 32 features are four groups of eight
+// k, G0..G3; the products of a sum are chained in the order of k_gemm_x3,
+// (G0 G2) (G1 G3) of one 32 after the other:
+//   TA = 32: steps 2 w and 2 w + 1 hold (G0 G2) and (G1 G3), one half each;
+//   TA = 16: fragment w holds G0 G2 G1 G3 in its quarters: one 16x16x32
+//     product gives the bits of the two 32x32x16 ones chained (measured on
+//     random operands: no result differs; any other order of the quarters
+//     does).  With `two` (BF16 models, sums of odd steps apart) fragments
+//     2 v and 2 v + 1 hold (G0 G2) and (G1 G3) of wavefronts 2 v and 2 v + 1.
+// `at`: first fragment at `buf` (widths before this one).
+template <int NP, int TA>
+__device__ __forceinline__ void put_slice(char* buf, int at, const Lane<TA>& L, const Slice<TA>& s, bool two) {
+    const bool apart = NP == 1 && two;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < s.G; ++g) {
         uint2 o[NP];
         split4<NP>(s.v[g], o);
-        char* d = buf + (ks0 + 2 * L.w + (g & 1)) * (NP * kFrag) + ((g >> 1) * 32 + L.a) * 16 + 8 * L.h;
+        int frag, unit;
+        if (TA == 32) {
+            frag = 2 * L.w + (g & 1);
+            unit = (g >> 1) * 32 + L.a;
+        } else {
+            const int half = L.h >> 1;  // group 2 g + half of the slice
+            frag = apart ? (L.w & 2) + half : L.w;
+            unit = (apart ? 2 * (L.w & 1) + g : 2 * half + g) * 16 + L.a;
+        }
+        char* d = buf + (at + frag) * (NP * kFrag) + unit * 16 + 8 * (L.h & 1);
 #pragma unroll
         for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2*>(d + p * kFrag) = o[p];
     }
@@ -194,141 +247,173 @@ __device__ __forceinline__ void put_slice(char* buf, int ks0, const Lane& L, con
 
 // Packed weights of one matrix [N][K] (launch_pack_frags): piece p, 16-byte
 // unit ((n / 16) K/8 + k / 8) 16 + n % 16 holds W[n][8 (k/8) .. + 7].
-// A ring of D k-steps of the fragments of NT row tiles of 32.
-template <int NP, int NT, int KS, int D>
+// A ring of D steps of the fragments of NT slices of 32 rows.  Step ks: TA =
+// 32: k-step ks of all 32 rows; TA = 16: k-step ks / 2 (of 32 k) of 16 of the
+// rows, the first or the second by ks % 2; the k of both as in put_slice.
+template <int NP, int NT, int KS, int D, int TA>
 struct Weights {
-    static constexpr uint32_t kRow = 1024 * KS;  // bytes of a row tile of 32 per piece
+    static constexpr uint32_t kRow = 1024 * KS;  // bytes of a slice of 32 rows per piece
     Buf b;
-    uint32_t ps, off, step, lo;  // bytes: piece, first row tile, row tile step; lane
+    uint32_t ps, off, step, lo;  // bytes: piece, first slice, slice step; lane
+    bool apart;
     bf16x8_t r[D][NT][NP];
-    // mat: the matrix's pieces, N its rows; row tiles t0, t0 + step, ...
-    __device__ __forceinline__ Weights(const uint16_t* mat, int N, int t0, int st, const Lane& L)
+    // mat: the matrix's pieces, N its rows; slices t0, t0 + step, ...
+    __device__ __forceinline__ Weights(const uint16_t* mat, int N, int t0, int st, const Lane<TA>& L, bool two)
         : b(mat, uint32_t(N) * (KS * 32 * NP)), ps(uint32_t(N) * (KS * 32)), off(t0 * kRow), step(st * kRow),
-          lo(uint32_t(((L.a >> 4) * 2 * KS + 2 * L.h) * 16 + (L.a & 15)) * 16u) {
+          apart(NP == 1 && two) {
+        if (TA == 32) {
+            lo = uint32_t(((L.a >> 4) * 2 * KS + 2 * L.h) * 16 + (L.a & 15)) * 16u;
+        } else {
+            const int q = L.h;  // quarter of the fragment
+            lo = uint32_t((apart ? 4 * (q >> 1) + 2 * (q & 1) : 2 * (q & 1) + (q >> 1)) * 16 + L.a) * 16u;
+        }
 #pragma unroll
         for (int d = 0; d < D - 1; ++d) load(d, d);
     }
-    // k-step ks into ring slot d (past the last k-step: unused data, bounded
-    // by the descriptor)
+    // step ks into ring slot d (past the last step: unused data, bounded by
+    // the descriptor)
     __device__ __forceinline__ void load(int ks, int d) {
+        const int k32 = ks >> 1, odd = ks & 1;
+        const uint32_t at = TA == 32 ? k32 * 1024 + odd * 256
+                                     : odd * (512 * KS) + (apart ? (k32 >> 1) * 2048 + (k32 & 1) * 256 : k32 * 1024);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                r[d][t][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + t * step + p * ps + (ks >> 1) * 1024 + (ks & 1) * 256));
+                r[d][t][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + t * step + p * ps + at));
     }
 };
 
-// acc[t][b] += W_t x_b over all k-steps; x_b's fragments at buf + b * stride.
-// The loads of k-step ks + D - 1 are issued before the products of ks and held
+// Steps of weights held (eight and four with TA = 16 were 2 to 5 % slower)
+template <int NP, int NT, int TA>
+constexpr int kDepth = NT == 1 || (NP == 1 && TA == 16) ? 4 : 2;
+
+// acc[t][b] += W_t x_b over all steps; x_b's fragments at buf + b * stride.
+// The loads of step ks + D - 1 are issued before the products of ks and held
 // there (left alone, the compiler sinks each load to its use and the chain
-// waits for L2 at every k-step).  A loop over rings of D k-steps rather than
+// waits for L2 at every step).  A loop over turns of a few steps rather than
 // straight-line code: a block walks through its code once, so that code is
 // fetched as slowly as data.
-// KN: k-steps taken (the first of the matrix's KS).
+// KN: steps taken (the first of the matrix's KS).
 //
 // FP32 models: where registers allow, the products of the leading pieces are
 // summed apart from the five small ones (in `sep`, added by the caller's
 // fold), so that a sum is rounded once instead of six times per k-step at
 // its full size.
-// BF16 models: the sums of k_gemm_x3 bit for bit (its odd k-steps apart in
-// `sep` where it keeps two accumulators, `two`): operands are rounded to
+// BF16 models: the sums of k_gemm_x3 bit for bit (its odd k-steps of 16 apart
+// in `sep` where it keeps two accumulators, `two`): operands are rounded to
 // bfloat16 after every product, and another order would flip some.
-template <int NP, int NT, int NB, int KN, int KS, int D>
-__device__ __forceinline__ void product(floatx16 (&acc)[NT][NB], floatx16 (&sep)[NT][NB], Weights<NP, NT, KS, D>& W,
-                                        const char* buf, int stride, const Lane& L, bool two) {
-    static_assert(KN % D == 0 && D % 2 == 0 && KN <= KS, "whole rings");
-    constexpr bool kApart = NP == 3 && NT <= 2 && NT * NB <= 3;
-    constexpr int XD = NB == 1 ? 2 : 1;  // k-steps of x fragments held
+template <int NP, int NT, int NB, int TA>
+constexpr bool kApart = NP == 3 && (TA == 16 || (NT <= 2 && NT * NB <= 3));
+
+template <int NP, int NT, int NB, int KN, int KS, int D, int TA>
+__device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Sums<TA> (&sep)[NT][NB],
+                                        Weights<NP, NT, KS, D, TA>& W, const char* buf, int stride,
+                                        const Lane<TA>& L) {
+    constexpr int XS = TA == 32 ? 1 : 2;   // steps that share the fragments of x
+    constexpr int XD = NB == 1 ? 2 : 1;    // fragments of x held
+    constexpr int R = D > 2 * XS ? D : 2 * XS;  // steps of a turn: whole rings of weights and of x
+    static_assert(KN % R == 0 && R % D == 0 && KN <= KS, "whole rings");
     const char* bl = buf + L.lane * 16;
     bf16x8_t x[XD][NB][NP];
-    auto load_x = [&](int ks, int d) {
+    auto load_x = [&](int k, int d) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                x[d][b][p] = *reinterpret_cast<const bf16x8_t*>(bl + b * stride + (ks * NP + p) * kFrag);
+                x[d][b][p] = *reinterpret_cast<const bf16x8_t*>(bl + b * stride + (k * NP + p) * kFrag);
     };
     if (XD == 2) load_x(0, 0);
-    auto step = [&](int ks, int d, floatx16(&c)[NT][NB]) {
+    auto step = [&](int ks, int d, Sums<TA>(&c)[NT][NB]) {
         W.load(ks + D - 1, (d + D - 1) % D);
-        if (XD == 1) load_x(ks, 0);
-        else load_x(min(ks + 1, KN - 1), (d + 1) % 2);
-        __builtin_amdgcn_sched_barrier(0);
-        const auto& w = W.r[d];
-        const auto& y = x[d % XD];
-#define NNP_TERM(ACC, PX, PW)                                                         \
-    _Pragma("unroll") for (int t = 0; t < NT; ++t) _Pragma("unroll") for (int b = 0; b < NB; ++b) ACC[t][b] = \
-        __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t][PW], y[b][PX], ACC[t][b], 0, 0, 0);
-        if constexpr (NP == 3) {
-            auto& small = kApart ? sep : c;
-            NNP_TERM(small, 2, 0)
-            NNP_TERM(small, 0, 2)
-            NNP_TERM(small, 1, 1)
-            NNP_TERM(small, 1, 0)
-            NNP_TERM(small, 0, 1)
+        if (d % XS == 0) {
+            if (XD == 1) load_x(ks / XS, 0);
+            else load_x(min(ks / XS + 1, KN / XS - 1), (d / XS + 1) % 2);
         }
-        NNP_TERM(c, 0, 0)
-#undef NNP_TERM
+        __builtin_amdgcn_sched_barrier(0);
+        const auto& w = W.r[d % D];
+        const auto& y = x[(d / XS) % XD];
+        auto term = [&](Sums<TA>(&to)[NT][NB], int px, int pw) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    if constexpr (TA == 32)
+                        to[t][b].c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t][pw], y[b][px], to[t][b].c, 0, 0, 0);
+                    else
+                        to[t][b].c[d % 2] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][pw], y[b][px], to[t][b].c[d % 2], 0, 0, 0);
+                }
+        };
+        if constexpr (NP == 3) {
+            auto& small = kApart<NP, NT, NB, TA> ? sep : c;
+            term(small, 2, 0);
+            term(small, 0, 2);
+            term(small, 1, 1);
+            term(small, 1, 0);
+            term(small, 0, 1);
+        }
+        term(c, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
-    if (NP == 3 || !two) {
+    if (NP == 3 || !W.apart) {
 #pragma unroll 1
-        for (int k0 = 0; k0 < KN; k0 += D)
+        for (int k0 = 0; k0 < KN; k0 += R)
 #pragma unroll
-            for (int d = 0; d < D; ++d) step(k0 + d, d, acc);
+            for (int d = 0; d < R; ++d) step(k0 + d, d, acc);
     } else {
 #pragma unroll 1
-        for (int k0 = 0; k0 < KN; k0 += D)
+        for (int k0 = 0; k0 < KN; k0 += R)
 #pragma unroll
-            for (int d = 0; d < D; ++d) step(k0 + d, d, d % 2 ? sep : acc);
+            for (int d = 0; d < R; ++d) step(k0 + d, d, (d / XS) % 2 ? sep : acc);
     }
 }
 
 // Whether k_gemm_x3 sums odd k-steps apart in the product [M][N] of K = 128
 // (for other K it always does): where it gives a block 32 columns, i.e. where
 // 64 would leave fewer than 512 blocks.
-__device__ __forceinline__ bool two_sums(int64_t M, int N) { return (M + 127) / 128 * (N / 64) < 512; }
+__host__ __device__ __forceinline__ bool two_sums(int64_t M, int N) { return (M + 127) / 128 * (N / 64) < 512; }
 
-template <int NT, int NB>
-__device__ __forceinline__ void fold(floatx16 (&acc)[NT][NB], const floatx16 (&sep)[NT][NB]) {
+template <int NT, int NB, int TA>
+__device__ __forceinline__ void fold(Sums<TA> (&acc)[NT][NB], const Sums<TA> (&sep)[NT][NB]) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[t][b] += sep[t][b];
+        for (int b = 0; b < NB; ++b) acc[t][b].add(sep[t][b]);
 }
 // acc = W x
-template <int NP, int NT, int NB, int KN, int KS, int D>
-__device__ __forceinline__ void product(floatx16 (&acc)[NT][NB], Weights<NP, NT, KS, D>& W, const char* buf,
-                                        int stride, const Lane& L, bool two) {
-    floatx16 sep[NT][NB] = {};
-    product<NP, NT, NB, KN>(acc, sep, W, buf, stride, L, two);
-    if (NP == 1 || (NT <= 2 && NT * NB <= 3)) fold(acc, sep);
+template <int NP, int NT, int NB, int KN, int KS, int D, int TA>
+__device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Weights<NP, NT, KS, D, TA>& W, const char* buf,
+                                        int stride, const Lane<TA>& L) {
+    Sums<TA> sep[NT][NB];
+    product<NP, NT, NB, KN>(acc, sep, W, buf, stride, L);
+    if (NP == 1 || kApart<NP, NT, NB, TA>) fold(acc, sep);
 }
 
 // Biases (or what else is added to a product): in FP32 models the sums start
 // from them, in BF16 models they are added last, as in k_gemm_x3.
-template <int NP>
-__device__ __forceinline__ floatx16 start_at(const Slice& b) {
-    floatx16 c = {};
+template <int NP, int TA>
+__device__ __forceinline__ Sums<TA> start_at(const Slice<TA>& b) {
+    Sums<TA> c;
     if (NP > 1) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) c[e] = b[e];
+        for (int e = 0; e < 4 * b.G; ++e) c.set(e, b[e]);
     }
     return c;
 }
-__device__ __forceinline__ Slice as_slice(const floatx16& c) {
-    Slice s;
+template <int TA>
+__device__ __forceinline__ Slice<TA> as_slice(const Sums<TA>& c) {
+    Slice<TA> s;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s.v[e >> 2][e & 3] = c[e];
+    for (int e = 0; e < 4 * s.G; ++e) s.v[e >> 2][e & 3] = c[e];
     return s;
 }
-template <int NP>
-__device__ __forceinline__ Slice end_with(const floatx16& c, const Slice& b) {
-    Slice s = as_slice(c);
+template <int NP, int TA>
+__device__ __forceinline__ Slice<TA> end_with(const Sums<TA>& c, const Slice<TA>& b) {
+    Slice<TA> s = as_slice(c);
     if (NP == 1) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) s.v[g] += b.v[g];
+        for (int g = 0; g < s.G; ++g) s.v[g] += b.v[g];
     }
     return s;
 }
@@ -341,34 +426,35 @@ __device__ __forceinline__ Slice end_with(const floatx16& c, const Slice& b) {
 //                 energy (v is not used past the last layer: not formed).
 // Kept for the reverse: U v and V v, the M1 pre-activation, q and o (LAST: q
 // alone), the W1 pre-activation.
-template <int NP, bool LAST>
+template <int NP, int TA, bool LAST>
 __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     extern __shared__ __align__(16) char lds[];
-    __shared__ float epart[LAST ? 4 : 1][kTile];
-    constexpr int CB = region_bytes(NP);
-    const Lane L(A.n);
+    __shared__ float epart[LAST ? 4 : 1][TA];
+    constexpr int CB = kRegion<NP, TA>, FF = kFragsF<TA>, E = TA / 2;
+    const Lane<TA> L(A.n);
+    const bool two_uv = two_sums(3 * int64_t(A.n), 2 * kF), two_3 = two_sums(A.n, 3 * kF), two_1 = two_sums(A.n, kF);
     // free while the rows of s and v (turn) and the outputs (turn2) are written
-    char* turn = lds + CB + L.w * (4 * kFrag);
-    char* turn2 = lds + 2 * CB + L.w * (4 * kFrag);
+    char* turn = lds + CB + L.w * (TA * 128);
+    char* turn2 = lds + 2 * CB + L.w * (TA * 128);
     {
-        Slice v0[3];
+        Slice<TA> v0[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) v0[c] = load_slice<3, kF>(A.vmid, c, 0, L);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c]);
+        for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c], two_uv);
     }
-    const Slice s0 = load_slice<1, kF>(A.smid, 0, 0, L);
+    const Slice<TA> s0 = load_slice<1, kF>(A.smid, 0, 0, L);
 
     // U v, V v: row tiles w (U) and 4 + w (V) of the adjacent matrices
-    floatx16 uv[2][3] = {};
+    Sums<TA> uv[2][3];
     {
-        Weights<NP, 2, kKsF, 2> W(A.U, 2 * kF, L.w, 4, L);
+        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.U, 2 * kF, L.w, 4, L, two_uv);
         __syncthreads();
-        product<NP, 2, 3, kKsF>(uv, W, lds, CB, L, two_sums(3 * int64_t(A.n), 2 * kF));
+        product<NP, 2, 3, kKsF>(uv, W, lds, CB, L);
     }
-    Slice nrm, dot;
+    Slice<TA> nrm, dot;
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < E / 4; ++g)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = 4 * g + q;
@@ -387,90 +473,90 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
         for (int m = 0; m < 2; ++m)
             keep_slice<6>(A.UV, 2 * c + m, L, as_slice(uv[m][c]));
     // [s; |V v|] (k-steps 0..15), then M1; its output behind them (16..23)
-    Slice z;
+    Slice<TA> z;
     {
-        const Slice m1 = load_feat(A.m1, L);
-        floatx16 acc[1][1] = {{start_at<NP>(m1)}};
-        Weights<NP, 1, 2 * kKsF, 4> W(A.M1, kF, L.w, 1, L);
+        const Slice<TA> m1 = load_feat(A.m1, L);
+        Sums<TA> acc[1][1] = {{start_at<NP, TA>(m1)}};
+        Weights<NP, 1, 2 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M1, kF, L.w, 1, L, true);
         __syncthreads();  // the vector fragments are read
-        put_slice<NP>(lds, 0, L, s0);
-        put_slice<NP>(lds, kKsF, L, nrm);
+        put_slice<NP>(lds, 0, L, s0, true);
+        put_slice<NP>(lds, FF, L, nrm, true);
         __syncthreads();
-        product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L, true);
-        const Slice a1 = end_with<NP>(acc[0][0], m1);
+        product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L);
+        const Slice<TA> a1 = end_with<NP, TA>(acc[0][0], m1);
         keep_slice<1>(A.a1, 0, L, a1);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) z.v[e >> 2][e & 3] = silu(a1[e]);
+        for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(a1[e]);
     }
-    put_slice<NP>(lds + 2 * CB, 0, L, z);
+    put_slice<NP>(lds + 2 * CB, 0, L, z, two_3);
     // p, q, o
     constexpr int NQ = LAST ? 2 : 3;
-    Slice s1;
-    Slice v1[3];
+    Slice<TA> s1;
+    Slice<TA> v1[3];
     {
-        floatx16 acc[NQ][1];
-        Slice m2[NQ];
+        Sums<TA> acc[NQ][1];
+        Slice<TA> m2[NQ];
 #pragma unroll
         for (int c = 0; c < NQ; ++c) {
             m2[c] = load_feat(A.m2 + c * kF, L);
-            acc[c][0] = start_at<NP>(m2[c]);
+            acc[c][0] = start_at<NP, TA>(m2[c]);
         }
-        Weights<NP, NQ, kKsF, 2> W(A.M2, 3 * kF, L.w, 4, L);
+        Weights<NP, NQ, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, 4, L, two_3);
         __syncthreads();
-        product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L, two_sums(A.n, 3 * kF));
-        Slice h[NQ];
+        product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L);
+        Slice<TA> h[NQ];
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) h[c] = end_with<NP>(acc[c][0], m2[c]);
+        for (int c = 0; c < NQ; ++c) h[c] = end_with<NP, TA>(acc[c][0], m2[c]);
 #pragma unroll
         for (int c = 1; c < NQ; ++c) keep_slice<3>(A.pqo, c, L, h[c]);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s1.v[e >> 2][e & 3] = fmaf(h[1][e], dot[e], s0[e] + h[0][e]);
+        for (int e = 0; e < E; ++e) s1.v[e >> 2][e & 3] = fmaf(h[1][e], dot[e], s0[e] + h[0][e]);
         if constexpr (!LAST) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 // v and U v are read again rather than held over the products
                 // (96 registers)
-                const Slice v0 = load_slice<3, kF>(A.vmid, c, 0, L);
-                const Slice u = kept_slice<6>(A.UV, 2 * c, L);
+                const Slice<TA> v0 = load_slice<3, kF>(A.vmid, c, 0, L);
+                const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v1[c].v[e >> 2][e & 3] = fmaf(h[NQ - 1][e], u[e], v0[e]);
+                for (int e = 0; e < E; ++e) v1[c].v[e >> 2][e & 3] = fmaf(h[NQ - 1][e], u[e], v0[e]);
                 store_slice<3, kF>(A.v_out, c, 0, L, v1[c], turn);
             }
         }
     }
     // the s fragments of M1 are read (the barrier before M2's product)
-    put_slice<NP>(lds, 0, L, s1);
-    const Slice b1 = load_feat(A.b1, L);
-    floatx16 acc1[1][1] = {{start_at<NP>(b1)}};
-    Weights<NP, 1, kKsF, 4> W1(A.W1, kF, L.w, 1, L);
+    put_slice<NP>(lds, 0, L, s1, two_1);
+    const Slice<TA> b1 = load_feat(A.b1, L);
+    Sums<TA> acc1[1][1] = {{start_at<NP, TA>(b1)}};
+    Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1, kF, L.w, 1, L, two_1);
     __syncthreads();
-    product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L, two_sums(A.n, kF));
-    const Slice h1 = end_with<NP>(acc1[0][0], b1);
+    product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
+    const Slice<TA> h1 = end_with<NP, TA>(acc1[0][0], b1);
     if constexpr (!LAST) {
         keep_slice<1>(A.h1, 0, L, h1);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
-        put_slice<NP>(lds + CB, 0, L, z);
-        floatx16 acc[3][1];
-        Slice b2[3];
+        for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
+        put_slice<NP>(lds + CB, 0, L, z, two_3);
+        Sums<TA> acc[3][1];
+        Slice<TA> b2[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             b2[c] = load_feat(A.b2 + c * kF, L);
-            acc[c][0] = start_at<NP>(b2[c]);
+            acc[c][0] = start_at<NP, TA>(b2[c]);
         }
-        Weights<NP, 3, kKsF, 2> W2(A.W2, 3 * kF, L.w, 4, L);
+        Weights<NP, 3, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, 4, L, two_3);
         __syncthreads();
-        product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L, two_sums(A.n, 3 * kF));
+        product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const Slice ph = end_with<NP>(acc[c][0], b2[c]);
+            const Slice<TA> ph = end_with<NP, TA>(acc[c][0], b2[c]);
             store_slice<1, 3 * kF>(A.phi, 0, c * kF, L, ph, turn2);
             if (c == 1 && A.pv) {
 #pragma unroll
                 for (int al = 0; al < 3; ++al) {
-                    Slice t;
+                    Slice<TA> t;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) t.v[g] = ph.v[g] * v1[al].v[g];
+                    for (int g = 0; g < E / 4; ++g) t.v[g] = ph.v[g] * v1[al].v[g];
                     store_slice<3, kF>(A.pv, al, 0, L, t, turn2);
                 }
             }
@@ -478,25 +564,39 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
         store_slice<1, kF>(A.s_out, 0, 0, L, s1, turn2);
     } else {
         // E_i = wo . silu(h1) + beta[t_i]; adjoint of s: Wo^T (wo silu'(h1))
-        const Slice wo = load_feat(A.wo, L);
-        float e0 = 0.f;
+        const Slice<TA> wo = load_feat(A.wo, L);
+        Slice<TA> y;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            e0 = fmaf(wo[e], silu(h1[e]), e0);
+        for (int e = 0; e < E; ++e) {
+            y.v[e >> 2][e & 3] = silu(h1[e]);
             z.v[e >> 2][e & 3] = wo[e] * silu_grad(h1[e]);
         }
-        e0 += __shfl_xor(e0, 32, 64);
-        if (L.h == 0) epart[L.w][L.a] = e0;
-        put_slice<NP>(lds + CB, 0, L, z);
-        Weights<NP, 1, kKsF, 4> W2(A.W2, kF, L.w, 1, L);
+        // The sum over the slice in one order for both tiles: the groups of
+        // four features 0, 2, 4, 6 and 1, 3, 5, 7, then the two sums.  With
+        // 16 atoms groups 0 and 4 (1 and 5) are in one lane, 2 and 6 (3 and
+        // 7) in the lane 32 further, and the sum goes to and fro.
+        float e0 = 0.f;
+#pragma unroll
+        for (int g = 0; g < E / 4; ++g) {
+#pragma unroll
+            for (int r = 0; r < 32 / TA; ++r) {
+                if (TA == 16 && (g || r)) e0 = __shfl_xor(e0, 32, 64);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e0 = fmaf(wo.v[g][q], y.v[g][q], e0);
+            }
+        }
+        e0 += __shfl_xor(e0, TA, 64);
+        if (L.h == (TA == 32 ? 0 : 2)) epart[L.w][L.a] = e0;
+        put_slice<NP>(lds + CB, 0, L, z, two_1);
+        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W2(A.W2, kF, L.w, 1, L, two_1);
         __syncthreads();
         if (L.w == 0 && L.h == 0 && L.on) {
             const int io = A.perm ? min(max(A.perm[L.i], 0), A.n - 1) : L.i;
             const float sum = (epart[0][L.a] + epart[1][L.a]) + (epart[2][L.a] + epart[3][L.a]);
             A.Ei[io] = sum + A.beta[min(max(A.species[L.i], 0), A.n_species - 1)];
         }
-        floatx16 acc[1][1] = {};
-        product<NP, 1, 1, kKsF>(acc, W2, lds + CB, 0, L, two_sums(A.n, kF));
+        Sums<TA> acc[1][1];
+        product<NP, 1, 1, kKsF>(acc, W2, lds + CB, 0, L);
         store_slice<1, kF>(A.s_out, 0, 0, L, as_slice(acc[0][0]), turn2);
     }
 }
@@ -508,50 +608,51 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
 //     layer's phi, gs = gs_in + W1^T (silu'(h1) W2^T gphi); gs_in is the
 //     adjoint that passes that layer's message step by.
 //   TOP = true (the last layer): gs_in is the adjoint of s, that of v is zero.
-template <int NP, bool TOP>
+template <int NP, int TA, bool TOP>
 __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
     extern __shared__ __align__(16) char lds[];
-    constexpr int CB = region_bytes(NP);
-    const Lane L(A.n);
-    char* turn = lds + CB + L.w * (4 * kFrag);
-    Slice gs = load_slice<1, kF>(A.gs_in, 0, 0, L);
+    constexpr int CB = kRegion<NP, TA>, FF = kFragsF<TA>, E = TA / 2;
+    const Lane<TA> L(A.n);
+    const bool two_1 = two_sums(A.n, kF), two_2 = two_sums(A.n, 2 * kF);
+    char* turn = lds + CB + L.w * (TA * 128);
+    Slice<TA> gs = load_slice<1, kF>(A.gs_in, 0, 0, L);
     if constexpr (!TOP) {
-        Weights<NP, 1, 3 * kKsF, 4> W(A.W2t, kF, L.w, 1, L);
-        const Slice h1 = kept_slice<1>(A.h1, 0, L);
+        Weights<NP, 1, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.W2t, kF, L.w, 1, L, true);
+        const Slice<TA> h1 = kept_slice<1>(A.h1, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            put_slice<NP>(lds, c * kKsF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L));
+            put_slice<NP>(lds, c * FF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L), true);
         __syncthreads();
-        floatx16 acc[1][1] = {};
-        product<NP, 1, 1, 3 * kKsF>(acc, W, lds, 0, L, true);
-        Weights<NP, 1, kKsF, 4> W1(A.W1t, kF, L.w, 1, L);
-        Slice g;
+        Sums<TA> acc[1][1];
+        product<NP, 1, 1, 3 * kKsF>(acc, W, lds, 0, L);
+        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1t, kF, L.w, 1, L, two_1);
+        Slice<TA> g;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) g.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(h1[e]);
+        for (int e = 0; e < E; ++e) g.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(h1[e]);
         __syncthreads();
-        put_slice<NP>(lds, 0, L, g);
+        put_slice<NP>(lds, 0, L, g, two_1);
         __syncthreads();
-        floatx16 acc1[1][1] = {{start_at<NP>(gs)}};
-        product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L, two_sums(A.n, kF));
-        gs = end_with<NP>(acc1[0][0], gs);
+        Sums<TA> acc1[1][1] = {{start_at<NP, TA>(gs)}};
+        product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
+        gs = end_with<NP, TA>(acc1[0][0], gs);
     }
     // adjoints of p, q (and o): gs, gs (U v . V v), sum gv U v
-    Slice gsq, o, dot, go;
-    floatx16 gv[1][3];
+    Slice<TA> gsq, o, dot, go;
+    Sums<TA> gv[1][3];
     {
         constexpr int KN = (TOP ? 2 : 3) * kKsF;
-        Weights<NP, 1, 3 * kKsF, 4> W(A.M2t, kF, L.w, 1, L);
-        const Slice q = kept_slice<3>(A.pqo, 1, L);
+        Weights<NP, 1, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M2t, kF, L.w, 1, L, true);
+        const Slice<TA> q = kept_slice<3>(A.pqo, 1, L);
         if constexpr (!TOP) o = kept_slice<3>(A.pqo, 2, L);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) gsq.v[g] = gs.v[g] * q.v[g];
+        for (int g = 0; g < E / 4; ++g) gsq.v[g] = gs.v[g] * q.v[g];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const Slice u = kept_slice<6>(A.UV, 2 * c, L), v = kept_slice<6>(A.UV, 2 * c + 1, L);
-            if constexpr (TOP) gv[0][c] = floatx16{};
-            else gv[0][c] = start_at<3>(load_slice<3, kF>(A.gv_in, c, 0, L));
+            const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L), v = kept_slice<6>(A.UV, 2 * c + 1, L);
+            if constexpr (TOP) gv[0][c] = Sums<TA>{};
+            else gv[0][c] = start_at<3, TA>(load_slice<3, kF>(A.gv_in, c, 0, L));
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const float d = c ? dot[e] : 0.f;
                 dot.v[e >> 2][e & 3] = fmaf(u[e], v[e], d);
                 if constexpr (!TOP) {
@@ -561,69 +662,69 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
             }
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) dot.v[g] = gs.v[g] * dot.v[g];
+        for (int g = 0; g < E / 4; ++g) dot.v[g] = gs.v[g] * dot.v[g];
         if constexpr (!TOP) __syncthreads();  // W1's input is read
-        put_slice<NP>(lds, 0, L, gs);
-        put_slice<NP>(lds, kKsF, L, dot);
-        if constexpr (!TOP) put_slice<NP>(lds, 2 * kKsF, L, go);
-        const Slice a1 = kept_slice<1>(A.a1, 0, L);
+        put_slice<NP>(lds, 0, L, gs, true);
+        put_slice<NP>(lds, FF, L, dot, true);
+        if constexpr (!TOP) put_slice<NP>(lds, 2 * FF, L, go, true);
+        const Slice<TA> a1 = kept_slice<1>(A.a1, 0, L);
         __syncthreads();
-        floatx16 acc[1][1] = {};
-        product<NP, 1, 1, KN>(acc, W, lds, 0, L, true);
+        Sums<TA> acc[1][1];
+        product<NP, 1, 1, KN>(acc, W, lds, 0, L);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dot.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(a1[e]);
+        for (int e = 0; e < E; ++e) dot.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(a1[e]);
     }
     // M1^T: adjoints of s (added to gs) and of |V v|
-    Slice gn;
+    Slice<TA> gn;
     {
-        Weights<NP, 2, kKsF, 2> W(A.M1t, 2 * kF, L.w, 4, L);
+        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.M1t, 2 * kF, L.w, 4, L, two_2);
         __syncthreads();
-        put_slice<NP>(lds, 0, L, dot);
+        put_slice<NP>(lds, 0, L, dot, two_2);
         __syncthreads();
-        floatx16 acc[2][1] = {{start_at<NP>(gs)}, {floatx16{}}};
-        product<NP, 2, 1, kKsF>(acc, W, lds, 0, L, two_sums(A.n, 2 * kF));
+        Sums<TA> acc[2][1] = {{start_at<NP, TA>(gs)}, {Sums<TA>{}}};
+        product<NP, 2, 1, kKsF>(acc, W, lds, 0, L);
         gn = as_slice(acc[1][0]);
-        store_slice<1, kF>(A.gs_out, 0, 0, L, end_with<NP>(acc[0][0], gs), turn);
+        store_slice<1, kF>(A.gs_out, 0, 0, L, end_with<NP, TA>(acc[0][0], gs), turn);
     }
     // adjoints of U v and V v, one after the other through the same regions;
     // BF16 models add gv last (g_vmid = gv + [gU gV] [U; V])
-    floatx16 sums[1][3], sep[1][3] = {};
+    Sums<TA> sums[1][3], sep[1][3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) sums[0][c] = NP == 1 ? floatx16{} : gv[0][c];
+    for (int c = 0; c < 3; ++c) sums[0][c] = NP == 1 ? Sums<TA>{} : gv[0][c];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-        Weights<NP, 1, kKsF, 4> W(m ? A.Vt : A.Ut, kF, L.w, 1, L);
+        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(m ? A.Vt : A.Ut, kF, L.w, 1, L, true);
         __syncthreads();
-        Slice nn;
+        Slice<TA> nn;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const Slice v = kept_slice<6>(A.UV, 2 * c + 1, L);
-            Slice t;
+            const Slice<TA> v = kept_slice<6>(A.UV, 2 * c + 1, L);
+            Slice<TA> t;
             if (m == 0) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
+                for (int e = 0; e < E; ++e) {
                     nn.v[e >> 2][e & 3] = fmaf(v[e], v[e], c ? nn[e] : 1e-8f);
                     t.v[e >> 2][e & 3] = TOP ? gsq[e] * v[e] : fmaf(gsq[e], v[e], gv[0][c][e] * o[e]);
                 }
             } else {
-                const Slice u = kept_slice<6>(A.UV, 2 * c, L);
+                const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) t.v[e >> 2][e & 3] = fmaf(gn[e], v[e], gsq[e] * u[e]);
+                for (int e = 0; e < E; ++e) t.v[e >> 2][e & 3] = fmaf(gn[e], v[e], gsq[e] * u[e]);
             }
-            put_slice<NP>(lds + c * CB, 0, L, t);
+            put_slice<NP>(lds + c * CB, 0, L, t, true);
         }
         if (m == 0) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) gn.v[e >> 2][e & 3] = gn[e] / sqrtf(nn[e]);
+            for (int e = 0; e < E; ++e) gn.v[e >> 2][e & 3] = gn[e] / sqrtf(nn[e]);
         }
         __syncthreads();
-        product<NP, 1, 3, kKsF>(sums, sep, W, lds, CB, L, true);
+        product<NP, 1, 3, kKsF>(sums, sep, W, lds, CB, L);
     }
     fold(sums, sep);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-        store_slice<3, kF>(A.gv_out, c, 0, L, end_with<NP>(sums[0][c], as_slice(gv[0][c])), turn);
+        store_slice<3, kF>(A.gv_out, c, 0, L, end_with<NP, TA>(sums[0][c], as_slice(gv[0][c])), turn);
 }
 
 // ---------------------------------------------------------- weight packing --
@@ -649,18 +750,41 @@ __global__ void __launch_bounds__(256) k_pack_frags(PackFrags P, int np) {
     }
 }
 
-template <typename K, typename Args>
-void launch_block(K kern, const Args& a, int np, hipStream_t s) {
-    kern<<<cdiv(a.n, kTile), 256, lds_bytes(np), s>>>(a);
+template <int NP, int TA, typename K, typename Args>
+void launch_block(K kern, const Args& a, hipStream_t s) {
+    kern<<<cdiv(a.n, TA), 256, kLdsBytes<NP, TA>, s>>>(a);
     NNP_LAUNCH_CHECK();
 }
 
 // more than 64 KB of dynamic LDS: raise the limit of each instance once per
 // device (the first call of a process on it; an idempotent setting)
 template <typename K>
-void raise_lds(K kern, int np) {
+void raise_lds(K kern) {
     NNP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                lds_bytes(np)));
+                                kLdsBytes<3, 32>));
+}
+
+// 16 atoms to a block or 32.  Measured (reverse / forward of a middle layer,
+// us): FP32, 1,536 atoms 21.6 / 20.5 with 16 against 30.5 / 27.7 with 32;
+// 4,096: 27 / 27 against 33 / 31; 5,121: 36 / 35 against 36 / 35; 6,144:
+// 39 / 41 against 39 / 40; 12,288: 69 / 72 against 66 / 66.  BF16, a third of
+// the weights: 1,536 15.6 / 14.6 against 21.8 / 20.3; 8,192 28 / 33 against
+// 33 / 34; 12,288 39 / 48 against 43 / 43.  BF16 results are the same bits
+// with both.  FP32 ones are not (the order of the six piece products): they
+// change tiles where k_gemm_x3 changed its number of sums for the widest of
+// these products, close to where the two are equal, so that replicas give the
+// same bits alone and packed up to the same total as with it.
+bool small_tiles(int n, bool bf16) { return bf16 ? n <= 2 * 256 * 16 : two_sums(3 * int64_t(n), 2 * kF); }
+
+template <int NP, int TA>
+void launch_fwd(const AtomFwd& a, bool last, hipStream_t s) {
+    if (last) launch_block<NP, TA>(k_atom_fwd<NP, TA, true>, a, s);
+    else launch_block<NP, TA>(k_atom_fwd<NP, TA, false>, a, s);
+}
+template <int NP, int TA>
+void launch_bwd(const AtomBwd& a, bool top, hipStream_t s) {
+    if (top) launch_block<NP, TA>(k_atom_bwd<NP, TA, true>, a, s);
+    else launch_block<NP, TA>(k_atom_bwd<NP, TA, false>, a, s);
 }
 
 }  // namespace
@@ -673,34 +797,24 @@ void launch_pack_frags(const PackFrags& P, int count, int np, hipStream_t s) {
 }
 
 void atom_block_setup() {
-    raise_lds(k_atom_fwd<3, false>, 3);
-    raise_lds(k_atom_fwd<3, true>, 3);
-    raise_lds(k_atom_bwd<3, false>, 3);
-    raise_lds(k_atom_bwd<3, true>, 3);
+    raise_lds(k_atom_fwd<3, 32, false>);
+    raise_lds(k_atom_fwd<3, 32, true>);
+    raise_lds(k_atom_bwd<3, 32, false>);
+    raise_lds(k_atom_bwd<3, 32, true>);
 }
 
 void launch_atom_fwd(const AtomFwd& a, bool last, bool bf16, hipStream_t s) {
     if (a.n <= 0) return;
     ScopedTimer timer("gemm", s);
-    if (bf16) {
-        if (last) launch_block(k_atom_fwd<1, true>, a, 1, s);
-        else launch_block(k_atom_fwd<1, false>, a, 1, s);
-    } else {
-        if (last) launch_block(k_atom_fwd<3, true>, a, 3, s);
-        else launch_block(k_atom_fwd<3, false>, a, 3, s);
-    }
+    if (small_tiles(a.n, bf16)) bf16 ? launch_fwd<1, 16>(a, last, s) : launch_fwd<3, 16>(a, last, s);
+    else bf16 ? launch_fwd<1, 32>(a, last, s) : launch_fwd<3, 32>(a, last, s);
 }
 
 void launch_atom_bwd(const AtomBwd& a, bool top, bool bf16, hipStream_t s) {
     if (a.n <= 0) return;
     ScopedTimer timer("gemm", s);
-    if (bf16) {
-        if (top) launch_block(k_atom_bwd<1, true>, a, 1, s);
-        else launch_block(k_atom_bwd<1, false>, a, 1, s);
-    } else {
-        if (top) launch_block(k_atom_bwd<3, true>, a, 3, s);
-        else launch_block(k_atom_bwd<3, false>, a, 3, s);
-    }
+    if (small_tiles(a.n, bf16)) bf16 ? launch_bwd<1, 16>(a, top, s) : launch_bwd<3, 16>(a, top, s);
+    else bf16 ? launch_bwd<1, 32>(a, top, s) : launch_bwd<3, 32>(a, top, s);
 }
 
 }  // namespace nnp
