@@ -230,18 +230,19 @@ void carve_tables(Arena& a, int32_t n_rep, SysTables& t) {
     t.o_step = a.take<uint64_t>(1);
 }
 
-// Uploads the replica tables of `sys` (pageable copies are staged by the
-// runtime before hipMemcpyAsync returns).
-RepGeom upload_tables(const nnp_system& sys, SysTables& t, hipStream_t s, std::vector<double>& host_scratch) {
+// The replica tables of `sys`.  Device code takes the box of a single replica
+// from the geometry and its atoms' range from n: the tables of one replica are
+// sent only where `always` (the integrator, whose kernels read and write them).
+RepGeom upload_tables(const nnp_system& sys, SysTables& t, Uploads& up, bool always = false) {
     const int R = sys.n_rep;
-    host_scratch.assign(size_t(2 * R), 0.0);
-    for (int r = 0; r < R; ++r) {
-        host_scratch[r] = sys.box[r];
-        host_scratch[R + r] = 1.0 / sys.box[r];
+    if (R > 1 || always) {
+        static thread_local std::vector<double> inv;  // reused: no host allocation once grown
+        inv.resize(size_t(R));
+        for (int r = 0; r < R; ++r) inv[r] = 1.0 / sys.box[r];
+        up.add(t.rep_start, sys.rep_start, sizeof(int64_t) * (R + 1));
+        up.add(t.box, sys.box, sizeof(double) * R);
+        up.add(t.inv_box, inv.data(), sizeof(double) * R);
     }
-    NNP_HIP(hipMemcpyAsync(t.rep_start, sys.rep_start, sizeof(int64_t) * (R + 1), hipMemcpyHostToDevice, s));
-    NNP_HIP(hipMemcpyAsync(t.box, host_scratch.data(), sizeof(double) * R, hipMemcpyHostToDevice, s));
-    NNP_HIP(hipMemcpyAsync(t.inv_box, host_scratch.data() + R, sizeof(double) * R, hipMemcpyHostToDevice, s));
     RepGeom g{};
     g.rep_of_atom = R > 1 ? sys.rep_of_atom : nullptr;
     g.box = t.box;
@@ -249,6 +250,12 @@ RepGeom upload_tables(const nnp_system& sys, SysTables& t, hipStream_t s, std::v
     g.rep_start = t.rep_start;
     g.box0 = sys.box[0];
     g.inv0 = 1.0 / sys.box[0];
+    return g;
+}
+RepGeom upload_tables(const nnp_system& sys, SysTables& t, hipStream_t s, bool always = false) {
+    Uploads up(s);
+    const RepGeom g = upload_tables(sys, t, up, always);
+    up.flush();
     return g;
 }
 
@@ -707,7 +714,7 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
                  m->px(m->off_Wo), m->wx_stride());
         launch_readout(n, F, m->desc.n_species, b.zo, m->p(m->off_wo), m->p(m->off_beta), sys.species, b.Ei, s, perm);
     }
-    if (energy) launch_rep_sum(sys.n_rep, t.rep_start, b.Ei, energy, s);
+    if (energy) launch_rep_sum(sys.n_rep, t.rep_start, n, b.Ei, energy, s);
     if (!forces) return;
     if (!blocks) {
         launch_readout_bwd(n, F, b.ao, m->p(m->off_wo), b.gs2, s);
@@ -860,19 +867,19 @@ extern "C" nnp_status nnp_neighbors(const nnp_system* sys, nnp_nlist* nl, void* 
     carve_tables(a, sys->n_rep, t);
     NbrScratch nb;
     carve_nbr_scratch(a, sys->n_atoms, sys->n_rep, nb);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, t, s, hs);
-    CellPlan plan = plan_cells(*sys, nl->cutoff);
-    upload_cell_plan(plan, nb, s);
-    NNP_HIP(hipMemsetAsync(nb.status, 0, sizeof(int) * 8, s));
-    launch_set_flag(t.flags, 1, s);
+    const CellPlan plan = plan_cells(*sys, nl->cutoff);
+    const int run = 1;
+    Uploads up(s);
+    RepGeom g = upload_tables(*sys, t, up);
+    up.add(nb.status, nullptr, sizeof(int) * 8);
+    up.add(t.flags, &run, sizeof(int));
+    upload_cell_plan(plan, nb, up, s);
     launch_build(int(sys->n_atoms), sys->pos, g, plan, nb, t.flags, nl->cutoff, nl->capacity, nl->offsets,
                  nl->nbr, nl->rev, nullptr, s);
     int host_status[8];
-    int total = 0;
     NNP_HIP(hipMemcpyAsync(host_status, nb.status, sizeof(host_status), hipMemcpyDeviceToHost, s));
-    NNP_HIP(hipMemcpyAsync(&total, nb.tmp_off + sys->n_atoms, sizeof(int), hipMemcpyDeviceToHost, s));
     NNP_HIP(hipStreamSynchronize(s));
+    const int total = host_status[4];
     nl->n_edges = total;
     NNP_REQUIRE(host_status[2] == 0, NNP_EROWLIMIT, "a neighbour row exceeds the 1024-entry limit of the builder");
     NNP_REQUIRE(host_status[0] == 0, NNP_ECAPACITY,
@@ -905,8 +912,7 @@ extern "C" nnp_status nnp_cons_energy_forces(const nnp_model* cons, const nnp_sy
     Arena a(ws, ws_bytes);
     CallScratch c;
     carve_all(a, m, nullptr, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, c.t, s, hs);
+    RepGeom g = upload_tables(*sys, c.t, s);
     cons_eval(m, *sys, g, c.t, *nl, c.cons, energy, forces, s);
     NNP_API_END
 }
@@ -924,10 +930,9 @@ extern "C" nnp_status nnp_cons_virial(const nnp_model* cons, const nnp_system* s
     Arena a(ws, ws_bytes);
     CallScratch c;
     carve_all(a, m, nullptr, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, c.t, s, hs);
+    RepGeom g = upload_tables(*sys, c.t, s);
     cons_eval(m, *sys, g, c.t, *nl, c.cons, energy, forces, s, c.cons.vir);
-    launch_rep_sum(sys->n_rep, c.t.rep_start, c.cons.vir, virial, s);
+    launch_rep_sum(sys->n_rep, c.t.rep_start, sys->n_atoms, c.cons.vir, virial, s);
     NNP_API_END
 }
 
@@ -943,10 +948,9 @@ extern "C" nnp_status nnp_nc_virial(const nnp_model* nc, const nnp_system* sys, 
     Arena a(ws, ws_bytes);
     CallScratch c;
     carve_all(a, nullptr, m, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, c.t, s, hs);
+    RepGeom g = upload_tables(*sys, c.t, s);
     nc_eval(m, *sys, g, *nl, c.nc, forces, s, c.nc.vir, nullptr);
-    launch_rep_sum(sys->n_rep, c.t.rep_start, c.nc.vir, virial, s);
+    launch_rep_sum(sys->n_rep, c.t.rep_start, sys->n_atoms, c.nc.vir, virial, s);
     NNP_API_END
 }
 
@@ -962,8 +966,7 @@ extern "C" nnp_status nnp_nc_forces(const nnp_model* nc, const nnp_system* sys, 
     Arena a(ws, ws_bytes);
     CallScratch c;
     carve_all(a, nullptr, m, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, c.t, s, hs);
+    RepGeom g = upload_tables(*sys, c.t, s);
     nc_eval(m, *sys, g, *nl, c.nc, forces, s);
     NNP_API_END
 }
@@ -1030,8 +1033,7 @@ extern "C" nnp_status nnp_nc_forces_noalloc(const nnp_model* nc, const nnp_syste
     SysTables t;
     ModelBuf b;
     carve_nc_only(a, m, sys->n_atoms, sys->n_rep, t, b);
-    static thread_local std::vector<double> hs;  // reused: no host allocation once grown
-    RepGeom g = upload_tables(*sys, t, s, hs);
+    RepGeom g = upload_tables(*sys, t, s);
     nc_eval(m, *sys, g, *nl, b, forces, s);
     NNP_API_END
 }
@@ -1049,8 +1051,7 @@ extern "C" nnp_status nnp_nc_weight_grad(const nnp_model* nc, const nnp_system* 
     Arena a(ws, ws_bytes);
     CallScratch c;
     carve_all(a, nullptr, m, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), true, c);
-    std::vector<double> hs;
-    RepGeom g = upload_tables(*sys, c.t, s, hs);
+    RepGeom g = upload_tables(*sys, c.t, s);
     nc_wgrad(m, *sys, g, *nl, c.nc, dl_df, dl_dtheta, s);
     NNP_API_END
 }
@@ -1302,16 +1303,15 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
     for (int r = 0; r < R; ++r)
         dis_chunks = std::max<int>(dis_chunks, cdiv(st->sys.rep_start[r + 1] - st->sys.rep_start[r], kDisChunk));
     double* inner_energy = c.inner_energy;
-    std::vector<double> hs;
-    RepGeom g = upload_tables(st->sys, c.t, s, hs);
-    NNP_HIP(hipMemcpyAsync(c.t.seed, seeds, sizeof(uint64_t) * R, hipMemcpyHostToDevice, s));
-    NNP_HIP(hipMemcpyAsync(c.t.stream, streams, sizeof(uint64_t) * R, hipMemcpyHostToDevice, s));
-    NNP_HIP(hipMemcpyAsync(c.t.step_base, step_base, sizeof(uint64_t) * R, hipMemcpyHostToDevice, s));
-    launch_set_u64(c.t.o_step, 0, s);  // O-steps since the start of the call, advanced by the kicks
+    Uploads up(s);
+    RepGeom g = upload_tables(st->sys, c.t, up, true);
+    up.add(c.t.seed, seeds, sizeof(uint64_t) * R);
+    up.add(c.t.stream, streams, sizeof(uint64_t) * R);
+    up.add(c.t.step_base, step_base, sizeof(uint64_t) * R);
+    up.add(c.t.o_step, nullptr, sizeof(uint64_t));  // O-steps since the start of the call, advanced by the kicks
     const double rc_cons = cons->desc.cutoff + p->skin;
     const double rc_nc = mts ? nc->desc.cutoff + p->skin : 0.0;
-    CellPlan plan = plan_cells(st->sys, rc_cons);
-    upload_cell_plan(plan, c.nb, s);
+    const CellPlan plan = plan_cells(st->sys, rc_cons);
     // flags: [0] rebuild trigger, [4] stale-list flag of the predictive mode, [5..6]
     // displacement record, [8..10] fast-force list status, [12] rewind trip;
     // nb.status: conservative list
@@ -1320,10 +1320,11 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
     int* stale = c.t.flags + 4;
     unsigned* maxd2 = reinterpret_cast<unsigned*>(c.t.flags + 5);
     int* nc_status = c.t.flags + 8;
-    NNP_HIP(hipMemsetAsync(c.t.flags, 0, sizeof(int) * 16, s));
-    NNP_HIP(hipMemsetAsync(c.t.rep_bad, 0, sizeof(int) * R, s));
-    NNP_HIP(hipMemsetAsync(c.nb.status, 0, sizeof(int) * 8, s));
-    NNP_HIP(hipMemsetAsync(c.t.rebuilds, 0, sizeof(long long), s));
+    up.add(c.t.flags, nullptr, sizeof(int) * 16);
+    up.add(c.t.rep_bad, nullptr, sizeof(int) * R);
+    up.add(c.nb.status, nullptr, sizeof(int) * 8);
+    up.add(c.t.rebuilds, nullptr, sizeof(long long));
+    upload_cell_plan(plan, c.nb, up, s);
     NNP_HIP(hipMemsetAsync(c.spare_off, 0, sizeof(int) * (size_t(n) + 1), s));  // empty rows until a spare build
 
     nnp_nlist lc = st->nl_cons, ln = st->nl_nc;
@@ -1525,7 +1526,7 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
         launch_baoa(ba, s);
         rebuild_if_flagged();
         eval_cons();
-        if (want_vir) launch_rep_sum(R, c.t.rep_start, c.cons.vir, st->virial, s);
+        if (want_vir) launch_rep_sum(R, c.t.rep_start, n, c.cons.vir, st->virial, s);
         launch_kick(n, st->vel, st->mass, st->f_cons, nullptr, 0.5 * dt, s, c.t.o_step);
         offset += 1;
         st->step += 1;
@@ -1586,7 +1587,7 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
         if (ov) adopt_spare();
         if (want_vir) {
             launch_virial_combine(n, c.cons.vir, c.nc.vir, c.nc.vir_sum, float(1.0 / n_in), c.cons.vir_sum, s);
-            launch_rep_sum(R, c.t.rep_start, c.cons.vir_sum, st->virial, s);
+            launch_rep_sum(R, c.t.rep_start, n, c.cons.vir_sum, st->virial, s);
         }
         launch_kick(n, st->vel, st->mass, st->f_cons, st->f_nc, 0.5 * D, s);
         if (rewind) {
@@ -1779,8 +1780,7 @@ extern "C" nnp_status nnp_barostat_scr(respa_state* st, const nnp_barostat_param
     for (int r = 0; r < R; ++r)
         chunks = std::max<int>(chunks, cdiv(st->sys.rep_start[r + 1] - st->sys.rep_start[r], kKeChunk));
     double* part = a.take<double>(int64_t(R) * chunks);
-    std::vector<double> hs;
-    upload_tables(st->sys, t, s, hs);
+    upload_tables(st->sys, t, s, true);
     launch_kinetic(R, t.rep_start, n, st->pos, st->vel, st->mass, ke, nullptr, s, st->sys.rep_of_atom, part, chunks);
     const double bar = 1e5 * 6.02214076e23 * 1e-30 / 4184.0;  // kcal/mol/A^3
     ScrArgs sa{p->pressure_bar * bar, p->compressibility_per_bar / bar, p->tau_fs, p->dt_fs, p->temperature_K,

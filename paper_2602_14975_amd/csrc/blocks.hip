@@ -127,11 +127,11 @@ __global__ void k_readout_bwd(int n, int F, const float* __restrict__ ao, const 
 }
 
 // Per-replica float64 sums in a fixed order (one block per replica).
-__global__ void __launch_bounds__(256) k_rep_sum(const int64_t* __restrict__ rep_start, const float* __restrict__ x,
-                                                 double* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_rep_sum(const int64_t* __restrict__ rep_start, int64_t n,
+                                                 const float* __restrict__ x, double* __restrict__ out) {
     __shared__ double red[256];
     int r = blockIdx.x;
-    int64_t a0 = rep_start[r], a1 = rep_start[r + 1];
+    const int64_t a0 = rep_start ? rep_start[r] : 0, a1 = rep_start ? rep_start[r + 1] : n;
     double s = 0.0;
     int64_t a = a0 + threadIdx.x;
     // eight loads in flight, added in the same order as one at a time
@@ -708,8 +708,8 @@ void launch_readout_bwd(int n, int F, const float* ao, const float* wo, float* g
     k_readout_bwd<<<ew_blocks(int64_t(n) * F), 256, 0, st>>>(n, F, ao, wo, gao);
     NNP_LAUNCH_CHECK();
 }
-void launch_rep_sum(int n_rep, const int64_t* rep_start, const float* x, double* out, hipStream_t st) {
-    k_rep_sum<<<n_rep, 256, 0, st>>>(rep_start, x, out);
+void launch_rep_sum(int n_rep, const int64_t* rep_start, int64_t n, const float* x, double* out, hipStream_t st) {
+    k_rep_sum<<<n_rep, 256, 0, st>>>(n_rep > 1 ? rep_start : nullptr, n, x, out);
     NNP_LAUNCH_CHECK();
 }
 void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,

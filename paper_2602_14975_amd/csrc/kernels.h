@@ -25,17 +25,43 @@ struct ScopedTimer {
     ~ScopedTimer();
 };
 
+// Small tables from the host to the device as kernel arguments: one launch
+// for up to 12 tables of 3,840 bytes together, larger ones by pageable
+// copies.  Each pageable copy is a launch of its own behind host work: a
+// fast-force evaluation of 192 atoms took 24.9 us with its three (16.6
+// without: a single replica needs no tables), a list build of 12,288 atoms 225
+// us with its nine and the sort behind two of them (174 with one launch here,
+// the cell numbers formed on the device and one copy back).  Sources may go as
+// soon as add() returned; flush() before the first use on the stream.
+class Uploads {
+public:
+    explicit Uploads(hipStream_t s) : s_(s) {}
+    // bytes: a multiple of 4; src = nullptr: zeros
+    void add(void* dst, const void* src, size_t bytes);
+    void flush();
+    static constexpr int kPieces = 12, kWords = 960;
+    struct Args {
+        uint32_t* dst[kPieces];
+        int end[kPieces];  // last word of each piece, plus one
+        int pieces, words;
+        uint32_t data[kWords];
+    };
+
+private:
+    hipStream_t s_;
+    Args a_{};
+};
+
 // ---------------------------------------------------------------- neighbours
+// Cell numbering: the cell at lexicographic position l ((cx m + cy) m + cz)
+// of replica r is number code[base_r + l]; lex is the inverse.  Within a
+// replica the numbers follow the Morton (bit-interleaved) order of the
+// cell coordinates, so consecutive cells, and the atoms the cell order
+// puts together, form compact blocks of space.
 struct CellPlan {
     std::vector<int> m;     // cells per side per replica (1 = whole replica)
     std::vector<int> base;  // first global cell of each replica
     int n_cells = 0;
-    // Cell numbering: the cell at lexicographic position l ((cx m + cy) m + cz)
-    // of replica r is number code[base_r + l]; lex is the inverse.  Within a
-    // replica the numbers follow the Morton (bit-interleaved) order of the
-    // cell coordinates, so consecutive cells, and the atoms the cell order
-    // puts together, form compact blocks of space.
-    std::vector<int> code, lex;
 };
 
 struct NbrScratch {
@@ -47,7 +73,8 @@ struct NbrScratch {
 CellPlan plan_cells(const nnp_system& sys, double radius);
 int64_t max_cells(int64_t n_atoms, int32_t n_rep);
 void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s);
-void upload_cell_plan(const CellPlan& plan, NbrScratch& s, hipStream_t stream);
+// The plan's tables through `up` (flushed), then the cell numbers on the device
+void upload_cell_plan(const CellPlan& plan, NbrScratch& s, Uploads& up, hipStream_t stream);
 // cell_rows: rows and entries in the cell order of this list build (s.cell_atoms
 // maps them to the caller's indices, s.cell_pos holds the positions in that
 // order); each row still ascending in caller index.
@@ -242,7 +269,8 @@ void launch_norm_bwd(int n, int F, const float* gs, const float* gX, const float
 void launch_readout(int n, int F, int S, const float* z, const float* wo, const float* beta, const int* species, float* Ei,
                     hipStream_t st, const int* perm = nullptr);
 void launch_readout_bwd(int n, int F, const float* ao, const float* wo, float* gao, hipStream_t st);
-void launch_rep_sum(int n_rep, const int64_t* rep_start, const float* x, double* out, hipStream_t st);
+// rep_start = nullptr: one replica of n atoms
+void launch_rep_sum(int n_rep, const int64_t* rep_start, int64_t n, const float* x, double* out, hipStream_t st);
 // scratch: cdiv(n, chunk) x S x F floats
 void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,
                      hipStream_t st);

@@ -25,7 +25,7 @@
 // their order.  commit_order then records the permutation with the
 // positions and species in that order, once both lists are built.
 #include <algorithm>
-#include <utility>
+#include <cstring>
 
 #include "common.h"
 #include "kernels.h"
@@ -276,6 +276,7 @@ k_nbr_fill(int n, const double* __restrict__ pos, RepGeom geom, Stencil st, doub
     if (row_i >= n) return;
     const int i = cell_rows ? st.cell_atoms[row_i] : row_i;
     int total = tmp_off[n];
+    if (row_i == 0 && lane == 0) status[4] = total;
     if (status[2] != 0) return;  // a row is longer than kMaxRow: keep the previous list intact
     if (int64_t(total) > capacity) {
         if (i == 0 && lane == 0) {
@@ -514,22 +515,73 @@ __global__ void k_predict_rebuild(unsigned* maxd2, double thr, int* flag) {
 
 // ------------------------------------------------------------------- host --
 
-// Morton rank of each lexicographic cell position of an m^3 grid: the cells
-// sorted by their bit-interleaved coordinates (x, y, z bits in turn).
-static std::vector<int> morton_ranks(int m) {
-    const int n = m * m * m;
-    std::vector<std::pair<uint64_t, int>> key(n);
-    for (int l = 0; l < n; ++l) {
-        const int c[3] = {l / (m * m), (l / m) % m, l % m};
-        uint64_t code = 0;
-        for (int b = 0; b < 20; ++b)
-            for (int d = 0; d < 3; ++d) code |= uint64_t((c[d] >> b) & 1) << (3 * b + (2 - d));
-        key[l] = {code, l};
+// The cell numbers of the plan: the Morton rank of each cell among the m^3
+// cells of its replica (codes interleave x, y, z bits, x first), one thread per
+// cell.  The cells with a smaller code are counted by the first bit in which
+// they differ: for each bit set in the cell's code, those that agree above it
+// and have it clear form a box of coordinates, cut at m.  (On the host the
+// numbers took a sort per call and two more pageable copies.)
+__global__ void __launch_bounds__(256) k_cell_numbers(int R, int n_cells, const int* __restrict__ grid_m,
+                                                      const int* __restrict__ grid_base, int* __restrict__ code,
+                                                      int* __restrict__ lex) {
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= n_cells) return;
+    int r = 0, hi = R;  // the last replica whose first cell is at or before c
+    while (hi - r > 1) {
+        const int mid = (r + hi) / 2;
+        if (grid_base[mid] <= c) r = mid;
+        else hi = mid;
     }
-    std::sort(key.begin(), key.end());
-    std::vector<int> rank(n);
-    for (int k = 0; k < n; ++k) rank[key[k].second] = k;
-    return rank;
+    const int m = grid_m[r], base = grid_base[r], l = c - base;
+    const int x[3] = {l / (m * m), (l / m) % m, l % m};
+    int fixed[3] = {0, 0, 0};  // the coordinates' bits above the current one
+    int rank = 0;
+    for (int b = 31 - __clz(m); b >= 0; --b)  // m < 2^(b + 1)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if ((x[d] >> b) & 1) {
+                int cells = 1;
+#pragma unroll
+                for (int e = 0; e < 3; ++e)  // axes before d have bit b fixed, those after it free
+                    cells *= min(max(m - fixed[e], 0), 1 << (e > d ? b + 1 : b));
+                rank += cells;
+                fixed[d] |= 1 << b;
+            }
+        }
+    code[c] = base + rank;
+    lex[base + rank] = c;
+}
+
+// Uploads::flush: word t of the payload to its table
+__global__ void __launch_bounds__(256) k_put(Uploads::Args a) {
+    for (int t = threadIdx.x; t < a.words; t += 256) {
+        int p = 0, first = 0;
+        while (t >= a.end[p]) first = a.end[p++];
+        a.dst[p][t - first] = a.data[t];
+    }
+}
+
+void Uploads::add(void* dst, const void* src, size_t bytes) {
+    const int words = int(bytes / 4);
+    if (words > kWords) {
+        if (src) NNP_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s_));
+        else launch_zero(static_cast<int*>(dst), words, nullptr, s_);
+        return;
+    }
+    if (a_.words + words > kWords || a_.pieces == kPieces) flush();
+    a_.dst[a_.pieces] = static_cast<uint32_t*>(dst);
+    if (src) std::memcpy(a_.data + a_.words, src, bytes);
+    else std::memset(a_.data + a_.words, 0, bytes);
+    a_.words += words;
+    a_.end[a_.pieces++] = a_.words;
+}
+
+void Uploads::flush() {
+    if (a_.words) {
+        k_put<<<1, 256, 0, s_>>>(a_);
+        NNP_LAUNCH_CHECK();
+    }
+    a_.words = a_.pieces = 0;
 }
 
 CellPlan plan_cells(const nnp_system& sys, double radius) {
@@ -550,21 +602,6 @@ CellPlan plan_cells(const nnp_system& sys, double radius) {
         total += m * m * m;
     }
     p.n_cells = total;
-    p.code.resize(total);
-    p.lex.resize(total);
-    std::vector<int> rank;
-    int rank_m = 0;
-    for (int r = 0; r < sys.n_rep; ++r) {
-        const int m = p.m[r], b = p.base[r], nc = m * m * m;
-        if (m != rank_m) {
-            rank = morton_ranks(m);
-            rank_m = m;
-        }
-        for (int l = 0; l < nc; ++l) {
-            p.code[b + l] = b + rank[l];
-            p.lex[b + rank[l]] = b + l;
-        }
-    }
     return p;
 }
 
@@ -587,14 +624,14 @@ void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s) {
     s.status = a.take<int>(8);
 }
 
-void upload_cell_plan(const CellPlan& plan, NbrScratch& s, hipStream_t stream) {
-    NNP_HIP(hipMemcpyAsync(s.cell_code, plan.code.data(), plan.code.size() * sizeof(int), hipMemcpyHostToDevice,
-                           stream));
-    NNP_HIP(hipMemcpyAsync(s.cell_lex, plan.lex.data(), plan.lex.size() * sizeof(int), hipMemcpyHostToDevice,
-                           stream));
-    NNP_HIP(hipMemcpyAsync(s.grid_m, plan.m.data(), plan.m.size() * sizeof(int), hipMemcpyHostToDevice, stream));
-    NNP_HIP(hipMemcpyAsync(s.grid_base, plan.base.data(), plan.base.size() * sizeof(int),
-                           hipMemcpyHostToDevice, stream));
+void upload_cell_plan(const CellPlan& plan, NbrScratch& s, Uploads& up, hipStream_t stream) {
+    const int R = int(plan.m.size());
+    up.add(s.grid_m, plan.m.data(), sizeof(int) * R);
+    up.add(s.grid_base, plan.base.data(), sizeof(int) * R);
+    up.flush();
+    k_cell_numbers<<<cdiv(plan.n_cells, 256), 256, 0, stream>>>(R, plan.n_cells, s.grid_m, s.grid_base, s.cell_code,
+                                                                s.cell_lex);
+    NNP_LAUNCH_CHECK();
 }
 
 void launch_build(int n, const double* pos, const RepGeom& geom, const CellPlan& plan, NbrScratch& s,
