@@ -29,9 +29,9 @@
 // wavefronts per SIMD to hide it.  Held out of that chain: the filter operands
 // (laid out with the weights, in LDS during the kernel), the list rows of the
 // block's atoms (in registers), the sums over lanes (no LDS).  At 12,288 atoms
-// these took the forward from 155 to 137 us and the reverse from 255 to 246,
-// at 1,536 atoms, with fewer atoms to a block, from 31 to 21 and from 48 to
-// 32.  An atom's edges are
+// these took the forward from 155 to 137 us (now 129) and the reverse from 255
+// to 246, at 1,536 atoms, with fewer atoms to a block, from 31 to 21 (now 19)
+// and from 48 to 32.  An atom's edges are
 // consumed in batches of fixed size (32 forward, 16 reverse) in list order,
 // so the batch an edge falls into depends only on its rank among the atom's
 // edges within the cutoff: results do not depend on the list radius.
@@ -60,7 +60,7 @@ typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kMxF = 128, kMxK = 16, kMxWaves = 4, kMxAtoms = 2;
 // forward: edges of a lane whose loads are issued together (eight: 40
-// loads in flight per lane, within three wavefronts per SIMD)
+// loads in flight per lane, within four wavefronts per SIMD)
 constexpr int kFwdGroup = 8;
 // reverse: the same; small groups keep every variant within three
 // wavefronts per SIMD (measured: more gathers in flight per wavefront at
@@ -388,7 +388,10 @@ struct FwdAcc {
 
 // One batch of nb <= 32 edges.  The lane's 16 edges are taken kFwdGroup at
 // a time, the loads of a group issued before its arithmetic (an invalid edge
-// of a partial batch reads the batch's first edge and contributes nothing).
+// of a partial batch reads the rows of the batch's first edge and adds them
+// times a filter of exact zeros: with a branch around each edge instead the
+// edges' arithmetic could not overlap, 137 -> 129 us at 12,288 atoms, 20.7 ->
+// 19.3 at 1,536, and the reverse, short of registers, is no faster without).
 template <bool L0>
 __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, const BatchBuf<32>& buf, int nb, int f,
                                           int h, const uint4* fl, FwdAcc& acc) {
@@ -437,7 +440,6 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
         for (int g = 0; g < kFwdGroup; ++g) {
             const int q = g0 + g;
             const int te = 8 * (q / 4) + 4 * h + q % 4;
-            if (te >= nb) continue;
             const EdgeRec& s = rec[te];
             const float w_a = wa[q];
             const float c = pc[g] * wc[q];
@@ -457,7 +459,7 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
 }
 
 template <bool L0>
-__global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_fwd_mx(MpGeom mg, MpFwd a, int per) {
+__global__ void __launch_bounds__(64 * kMxWaves, 4) k_message_fwd_mx(MpGeom mg, MpFwd a, int per) {
     constexpr int F = kMxF, BATCH = 32;
     __shared__ __align__(16) BatchBuf<BATCH> buf[2];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
