@@ -33,8 +33,8 @@
 // memory forward and more in reverse, 28 products and 15 elementwise launches
 // per evaluation; the blocks move 24 F and are six launches.  Measured,
 // dense products and elementwise launches together, per evaluation (3
-// layers, FP32): 12,288 atoms 885 -> 352 us (blocks of 44 to 66 us); 1,536
-// atoms 460 -> 115 us (14 to 22 us each; 19 to 30 with 32 atoms to a block).
+// layers, FP32): 12,288 atoms 885 -> 365 us (blocks of 44 to 70 us); 1,536
+// atoms 460 -> 116 us (14 to 22 us each; 19 to 30 with 32 atoms to a block).
 #include <algorithm>
 
 #include "common.h"
@@ -390,17 +390,6 @@ __device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Weights<NP, NT,
     if (NP == 1 || kApart<NP, NT, NB, TA>) fold(acc, sep);
 }
 
-// Biases (or what else is added to a product): in FP32 models the sums start
-// from them, in BF16 models they are added last, as in k_gemm_x3.
-template <int NP, int TA>
-__device__ __forceinline__ Sums<TA> start_at(const Slice<TA>& b) {
-    Sums<TA> c;
-    if (NP > 1) {
-#pragma unroll
-        for (int e = 0; e < 4 * b.G; ++e) c.set(e, b[e]);
-    }
-    return c;
-}
 template <int TA>
 __device__ __forceinline__ Slice<TA> as_slice(const Sums<TA>& c) {
     Slice<TA> s;
@@ -408,13 +397,15 @@ __device__ __forceinline__ Slice<TA> as_slice(const Sums<TA>& c) {
     for (int e = 0; e < 4 * s.G; ++e) s.v[e >> 2][e & 3] = c[e];
     return s;
 }
-template <int NP, int TA>
-__device__ __forceinline__ Slice<TA> end_with(const Sums<TA>& c, const Slice<TA>& b) {
+// Biases, and the adjoints that pass a product by, are added to it last:
+// started from them, every partial sum is rounded at their size (forces then
+// were 1 % further off float64 than with separate products, now 1 % closer),
+// and BF16 models would not have the bits of k_gemm_x3.
+template <int TA>
+__device__ __forceinline__ Slice<TA> added(const Sums<TA>& c, const Slice<TA>& b) {
     Slice<TA> s = as_slice(c);
-    if (NP == 1) {
 #pragma unroll
-        for (int g = 0; g < s.G; ++g) s.v[g] += b.v[g];
-    }
+    for (int g = 0; g < s.G; ++g) s.v[g] += b.v[g];
     return s;
 }
 
@@ -475,15 +466,14 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     // [s; |V v|] (k-steps 0..15), then M1; its output behind them (16..23)
     Slice<TA> z;
     {
-        const Slice<TA> m1 = load_feat(A.m1, L);
-        Sums<TA> acc[1][1] = {{start_at<NP, TA>(m1)}};
+        Sums<TA> acc[1][1];
         Weights<NP, 1, 2 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M1, kF, L.w, 1, L, true);
         __syncthreads();  // the vector fragments are read
         put_slice<NP>(lds, 0, L, s0, true);
         put_slice<NP>(lds, FF, L, nrm, true);
         __syncthreads();
         product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L);
-        const Slice<TA> a1 = end_with<NP, TA>(acc[0][0], m1);
+        const Slice<TA> a1 = added(acc[0][0], load_feat(A.m1, L));
         keep_slice<1>(A.a1, 0, L, a1);
 #pragma unroll
         for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(a1[e]);
@@ -495,18 +485,12 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     Slice<TA> v1[3];
     {
         Sums<TA> acc[NQ][1];
-        Slice<TA> m2[NQ];
-#pragma unroll
-        for (int c = 0; c < NQ; ++c) {
-            m2[c] = load_feat(A.m2 + c * kF, L);
-            acc[c][0] = start_at<NP, TA>(m2[c]);
-        }
         Weights<NP, NQ, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, 4, L, two_3);
         __syncthreads();
         product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L);
         Slice<TA> h[NQ];
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) h[c] = end_with<NP, TA>(acc[c][0], m2[c]);
+        for (int c = 0; c < NQ; ++c) h[c] = added(acc[c][0], load_feat(A.m2 + c * kF, L));
 #pragma unroll
         for (int c = 1; c < NQ; ++c) keep_slice<3>(A.pqo, c, L, h[c]);
 #pragma unroll
@@ -526,30 +510,23 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     }
     // the s fragments of M1 are read (the barrier before M2's product)
     put_slice<NP>(lds, 0, L, s1, two_1);
-    const Slice<TA> b1 = load_feat(A.b1, L);
-    Sums<TA> acc1[1][1] = {{start_at<NP, TA>(b1)}};
+    Sums<TA> acc1[1][1];
     Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1, kF, L.w, 1, L, two_1);
     __syncthreads();
     product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
-    const Slice<TA> h1 = end_with<NP, TA>(acc1[0][0], b1);
+    const Slice<TA> h1 = added(acc1[0][0], load_feat(A.b1, L));
     if constexpr (!LAST) {
         keep_slice<1>(A.h1, 0, L, h1);
 #pragma unroll
         for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
         put_slice<NP>(lds + CB, 0, L, z, two_3);
         Sums<TA> acc[3][1];
-        Slice<TA> b2[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            b2[c] = load_feat(A.b2 + c * kF, L);
-            acc[c][0] = start_at<NP, TA>(b2[c]);
-        }
         Weights<NP, 3, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, 4, L, two_3);
         __syncthreads();
         product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const Slice<TA> ph = end_with<NP, TA>(acc[c][0], b2[c]);
+            const Slice<TA> ph = added(acc[c][0], load_feat(A.b2 + c * kF, L));
             store_slice<1, 3 * kF>(A.phi, 0, c * kF, L, ph, turn2);
             if (c == 1 && A.pv) {
 #pragma unroll
@@ -632,13 +609,13 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
         __syncthreads();
         put_slice<NP>(lds, 0, L, g, two_1);
         __syncthreads();
-        Sums<TA> acc1[1][1] = {{start_at<NP, TA>(gs)}};
+        Sums<TA> acc1[1][1];
         product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
-        gs = end_with<NP, TA>(acc1[0][0], gs);
+        gs = added(acc1[0][0], gs);
     }
     // adjoints of p, q (and o): gs, gs (U v . V v), sum gv U v
     Slice<TA> gsq, o, dot, go;
-    Sums<TA> gv[1][3];
+    Slice<TA> gv[3];
     {
         constexpr int KN = (TOP ? 2 : 3) * kKsF;
         Weights<NP, 1, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M2t, kF, L.w, 1, L, true);
@@ -649,15 +626,14 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L), v = kept_slice<6>(A.UV, 2 * c + 1, L);
-            if constexpr (TOP) gv[0][c] = Sums<TA>{};
-            else gv[0][c] = start_at<3, TA>(load_slice<3, kF>(A.gv_in, c, 0, L));
+            if constexpr (!TOP) gv[c] = load_slice<3, kF>(A.gv_in, c, 0, L);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const float d = c ? dot[e] : 0.f;
                 dot.v[e >> 2][e & 3] = fmaf(u[e], v[e], d);
                 if constexpr (!TOP) {
                     const float t = c ? go[e] : 0.f;
-                    go.v[e >> 2][e & 3] = fmaf(gv[0][c][e], u[e], t);
+                    go.v[e >> 2][e & 3] = fmaf(gv[c][e], u[e], t);
                 }
             }
         }
@@ -681,16 +657,14 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
         __syncthreads();
         put_slice<NP>(lds, 0, L, dot, two_2);
         __syncthreads();
-        Sums<TA> acc[2][1] = {{start_at<NP, TA>(gs)}, {Sums<TA>{}}};
+        Sums<TA> acc[2][1];
         product<NP, 2, 1, kKsF>(acc, W, lds, 0, L);
         gn = as_slice(acc[1][0]);
-        store_slice<1, kF>(A.gs_out, 0, 0, L, end_with<NP, TA>(acc[0][0], gs), turn);
+        store_slice<1, kF>(A.gs_out, 0, 0, L, added(acc[0][0], gs), turn);
     }
-    // adjoints of U v and V v, one after the other through the same regions;
-    // BF16 models add gv last (g_vmid = gv + [gU gV] [U; V])
+    // adjoints of U v and V v, one after the other through the same regions:
+    // g_vmid = gv + [gU gV] [U; V], gv (48 registers) read again at the end
     Sums<TA> sums[1][3], sep[1][3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sums[0][c] = NP == 1 ? Sums<TA>{} : gv[0][c];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(m ? A.Vt : A.Ut, kF, L.w, 1, L, true);
@@ -704,7 +678,7 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     nn.v[e >> 2][e & 3] = fmaf(v[e], v[e], c ? nn[e] : 1e-8f);
-                    t.v[e >> 2][e & 3] = TOP ? gsq[e] * v[e] : fmaf(gsq[e], v[e], gv[0][c][e] * o[e]);
+                    t.v[e >> 2][e & 3] = TOP ? gsq[e] * v[e] : fmaf(gsq[e], v[e], gv[c][e] * o[e]);
                 }
             } else {
                 const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L);
@@ -724,7 +698,8 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-        store_slice<3, kF>(A.gv_out, c, 0, L, end_with<NP, TA>(sums[0][c], as_slice(gv[0][c])), turn);
+        store_slice<3, kF>(A.gv_out, c, 0, L,
+                           TOP ? as_slice(sums[0][c]) : added(sums[0][c], load_slice<3, kF>(A.gv_in, c, 0, L)), turn);
 }
 
 // ---------------------------------------------------------- weight packing --
