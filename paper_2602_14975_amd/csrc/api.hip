@@ -297,10 +297,11 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
         b.gs2 = a.take<float>(n * F);
         b.gv = a.take<float>(n * 3 * F);
         b.gv2 = a.take<float>(n * 3 * F);
-        b.gpqo = a.take<float>(n * 3 * F);
-        b.ga1 = a.take<float>(n * F);
-        b.gX = a.take<float>(n * 2 * F);
-        b.gUV = a.take<float>(n * 6 * F);
+        b.gpqo = a.take<float>(std::max<int64_t>(n * 12 * F, m->wf && !m->bf16() ? 5 * E : 0));
+        b.edge_cap = E;
+        b.ga1 = b.gpqo + n * 3 * F;
+        b.gX = b.ga1 + n * F;
+        b.gUV = b.gX + n * 2 * F;
         b.gphi = a.take<float>(n * 3 * F);
         b.gh1 = a.take<float>(n * F);
         if (message_mx_shape(int(F), m->desc.n_rbf, 0)) {
@@ -607,6 +608,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         a.phi = lb.phi;
         a.pv = lb.pv;
         a.want_gphi = 1;
+        a.edge_f = b.edge_f;
     }
     if (l == 0 && !wg && force && species_sum_on(m, mg, b)) {
         // P_0 = g_smid T_0, P_2 = g_vmid T_2 (float32 products), then the
@@ -624,10 +626,16 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
                 gemm_xwt(3 * n, pp, F, b.gv, F, m->sp_TT(1), nullptr, P2, pp, EPI_NONE, nullptr, 0, false, s);
             }
         }
-        launch_sp_bwd(mg, m->desc.n_species, b.sp, P2, force, accum_force, vir, s);
+        if (b.edge_f) {
+            launch_sp_bwd_own(mg, m->desc.n_species, b.sp, P2, b.edge_f, accum_force, s);
+            launch_edge_force(mg, b.edge_f, force, vir, s);
+        } else {
+            launch_sp_bwd(mg, m->desc.n_species, b.sp, P2, force, accum_force, vir, s);
+        }
         return;
     }
     launch_message_bwd(F, K, cut, mg, a, force != nullptr, wg, s);
+    if (l == 1 && b.edge_f && !species_sum_on(m, mg, b)) launch_edge_force(mg, b.edge_f, force, vir, s);
     if (wg) {
         const int nb = mp_blocks(n, F);
         const int64_t cnt = int64_t(3) * F * (K + 1);
@@ -694,7 +702,18 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     MpGeom mg = make_geom(m, sys, geom, nl);
     mg.perm = perm;
     b.blocks = atom_blocks_on(m);
+    b.edge_f = nullptr;
+    b.edge_key = nullptr;
     if (b.ecnt && message_mx_active(F, m->desc.n_rbf, 0)) {
+        // FP32 models: the reverse past the first layer one message per edge
+        // (BF16 models keep the other form: with other sums the positions of
+        // a trajectory differ in the last bits, and some operands then round
+        // to other bfloat16 numbers)
+        if (b.blocks && !m->bf16()) {
+            b.edge_f = b.gpqo;
+            b.edge_key = reinterpret_cast<int*>(b.gpqo + 4 * b.edge_cap);
+        }
+        mg.edge_key = b.edge_key;
         // the edges within the cutoff, prepared once for all six message launches
         // (with the first layer by neighbour species, its edge sums in the same pass)
         if (m->sp && b.sp && species_sum_active())

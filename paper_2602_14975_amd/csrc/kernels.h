@@ -245,8 +245,12 @@ void launch_sp_tables(int F, int S, const float* Wr, const float* br, const floa
                       float* TT, hipStream_t s);
 void launch_sp_bwd(const MpGeom& mg, int S, const float* P0, const float* P2, float* force, bool accum, float* vir,
                    hipStream_t s);
+// The first layer's share of edge_f (see launch_edge_force), written or added
+void launch_sp_bwd_own(const MpGeom& mg, int S, const float* P0, const float* P2, float* edge_f, bool add,
+                       hipStream_t s);
 void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, const ScopedTimer& t);
 void launch_message_bwd_mx(const MpGeom& mg, const MpBwd& a, hipStream_t s, const ScopedTimer& t);
+void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, hipStream_t s);
 void launch_filter_scale(int count, const float* Wr, float* out, hipStream_t s);
 // Filter operands of one layer in the order the matrix-core message kernels
 // read them (filter_operand_units() units of 16 bytes), after its scale.

@@ -133,6 +133,13 @@ struct ModelBuf {
     int* ecnt = nullptr;
     EdgeRec* erec = nullptr;
     uint4* ehalf = nullptr;
+    // [E][4] feature sums of the messages past the first layer, and [E] the
+    // caller's index of each edge's neighbour (FP32 models with the per-atom
+    // blocks), in the room of gpqo, ga1, gX and gUV, which those do not use;
+    // nullptr: not used in this evaluation
+    float* edge_f = nullptr;
+    int* edge_key = nullptr;
+    int64_t edge_cap = 0;  // E
     // first layer per species: pre-activation, hidden, phi, and adjoints
     float *h1_tab = nullptr, *z_tab = nullptr, *phi_tab = nullptr, *gphi_tab = nullptr, *gh1_tab = nullptr;
 };

@@ -42,6 +42,9 @@ struct MpGeom {
     const int* ecnt;
     const EdgeRec* erec;
     const uint4* ehalf;
+    // With the prepared edges, or nullptr: the caller's index of each edge's
+    // neighbour, in which the rows ascend.
+    int* edge_key;
     // Rows in a working order (or nullptr: the caller's): the caller's index
     // of row i, under which the per-atom outputs (forces, energies, virial
     // shares) are stored.
@@ -81,6 +84,11 @@ struct MpBwd {
     const float* mx_scale;  // [2] filter-weight scale and its inverse for the matrix-core kernels, or nullptr
     const uint4* mx_filter;  // the layer's filter operands (launch_filter_operands)
     const float* pv;        // phi_b * v_in as written by the matrix-core forward (layers past the first)
+    // [list position][4] or nullptr (layers past the first): instead of
+    // forces, the feature sums of each edge's message away from its owner,
+    // written or added to with accum_force; launch_edge_force forms the
+    // forces of all layers from them
+    float* edge_f;
 };
 
 }  // namespace nnp

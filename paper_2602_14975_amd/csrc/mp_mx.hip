@@ -21,7 +21,7 @@
 // pairs.
 //
 // Message kernels: blocks take one or two atoms in turn with four wavefronts,
-// one per block of 32 features, which share the staged edges.  The reverse is
+// one per block of 32 features, which share the staged edges.  The The reverse is
 // bound by its vector arithmetic (34 operations per edge and feature, 59 % of
 // its time at 12,288 atoms) and by the rows it gathers through L1 (9 loads
 // per edge and feature, about half of it), the forward by the gathers; what
@@ -157,10 +157,11 @@ __device__ __forceinline__ half4_t bias_rows(float c, int h) {
 }
 
 // A float at a 32-bit byte offset from a wavefront-uniform base: the
-// neighbour-row gathers then take one 32-bit multiply-add per edge for
-// their address, and the quantities of a row differ by immediate offsets.
+// neighbour-row gathers then take two shift-adds per edge for their
+// addresses (rows of F and of 3F floats), and the quantities of a row differ by immediate offsets.
+template <int IMM = 0>  // added to the address, not to the offset, which might wrap
 __device__ __forceinline__ float ld_off(const float* base, uint32_t byte_off) {
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off + IMM);
 }
 
 // Sums over the wavefront in the order of a butterfly 32, 16, 8, 4, 2, 1 (the
@@ -252,6 +253,7 @@ __global__ void __launch_bounds__(256, 3) k_edge_prep(MpGeom mg, int* __restrict
             rec.u[2] = float(dz * ir);
             rec.ir = float(ir);
             erec[p] = rec;
+            if (mg.edge_key) mg.edge_key[p] = mg.perm ? mg.perm[j] : j;
             uint4* dst = ehalf + int64_t(p) * 8;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -326,22 +328,37 @@ __device__ __forceinline__ uint4 load_nt(const uint4* p) {
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// This thread's piece of every batch: what does not change from one batch to
+// the next is kept (the offsets took about 40 vector instructions a batch).
 template <int BATCH>
-__device__ __forceinline__ uint4 fetch_piece(const MpGeom& mg, int p0, int nb) {
-    using B = BatchBuf<BATCH>;
-    const int t = threadIdx.x;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    // read once per evaluation and layer: non-temporal, so that the streamed
-    // edges do not displace the neighbour rows from L2
-    if (t < B::NA) {
-        const int e = t / B::AP, q = t % B::AP;
-        if (e < nb) v = load_nt(mg.ehalf + int64_t(p0 + e) * 8 + q);
-    } else if (t < B::N) {
-        const int u = t - B::NA;
-        if (u < 2 * nb) v = load_nt(reinterpret_cast<const uint4*>(mg.erec + p0) + u);
+struct Stage {
+    const char* src;  // of list position 0
+    int edge, shift;  // the piece's edge in the batch; log2 of its array's bytes per position
+    bool head;        // the piece with the neighbour's index
+    __device__ __forceinline__ explicit Stage(const MpGeom& mg) {
+        using B = BatchBuf<BATCH>;
+        const int t = threadIdx.x, u = t - B::NA;
+        head = false;
+        if (t < B::NA) {
+            edge = t / B::AP;
+            shift = 7;
+            src = reinterpret_cast<const char*>(mg.ehalf + edge * 8 + t % B::AP);
+        } else {
+            edge = t < B::N ? u / 2 : 0x7FFFFFFF;
+            shift = 5;
+            head = u % 2 == 0;
+            src = reinterpret_cast<const char*>(mg.erec) + 16 * u;
+        }
     }
-    return v;
-}
+    // Edges past nb are zeros: their filter is zero; their neighbour is the
+    // owner, so that what their rows hold cannot reach another atom.
+    __device__ __forceinline__ uint4 fetch(int p0, int nb, int owner) const {
+        // read once per evaluation and layer: non-temporal, so that the
+        // streamed edges do not displace the neighbour rows from L2
+        if (edge < nb) return load_nt(reinterpret_cast<const uint4*>(src + (int64_t(p0) << shift)));
+        return make_uint4(head ? uint32_t(owner) : 0u, 0u, 0u, 0u);
+    }
+};
 
 template <int BATCH>
 __device__ __forceinline__ void store_piece(BatchBuf<BATCH>& b, const uint4& v) {
@@ -367,17 +384,17 @@ struct Rows {
 // BATCH.  Returns the list position and size of the batch after batch b0 of
 // atom ai (ai = -1: the first batch), or nb = 0 when there is none.
 struct NextBatch {
-    int p0, nb;
+    int p0, nb, ai;
 };
 
 template <int BATCH>
 __device__ __forceinline__ NextBatch next_batch(const Rows& rows, int ai, int b0, int cnt) {
-    if (ai >= 0 && b0 + BATCH < cnt) return {rows.start(ai) + b0 + BATCH, min(BATCH, cnt - b0 - BATCH)};
+    if (ai >= 0 && b0 + BATCH < cnt) return {rows.start(ai) + b0 + BATCH, min(BATCH, cnt - b0 - BATCH), ai};
     for (int a2 = ai + 1; a2 < rows.atoms; ++a2) {
         const int c2 = rows.count(a2);
-        if (c2 > 0) return {rows.start(a2), min(BATCH, c2)};
+        if (c2 > 0) return {rows.start(a2), min(BATCH, c2), a2};
     }
-    return {0, 0};
+    return {0, 0, 0};
 }
 
 // ------------------------------------------------------------- forward --
@@ -387,8 +404,8 @@ struct FwdAcc {
 };
 
 // One batch of nb <= 32 edges.  The lane's 16 edges are taken kFwdGroup at
-// a time, the loads of a group issued before its arithmetic (an invalid edge
-// of a partial batch reads the rows of the batch's first edge and adds them
+// a time, the loads of a group issued before its arithmetic (an edge
+// past the end of a partial batch reads the owner's rows and adds them
 // times a filter of exact zeros: with a branch around each edge instead the
 // edges' arithmetic could not overlap, 137 -> 129 us at 12,288 atoms, 20.7 ->
 // 19.3 at 1,536, and the reverse, short of registers, is no faster without).
@@ -422,18 +439,18 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
         for (int g = 0; g < kFwdGroup; ++g) {
             const int q = g0 + g;
             const int te = 8 * (q / 4) + 4 * h + q % 4;
-            const EdgeRec& s = rec[te < nb ? te : 0];
+            const EdgeRec& s = rec[te];
             if (L0) {
                 const float* phj = ptab + s.t * 3 * F + f;
                 pa[g] = phj[0];
                 pc[g] = phj[2 * F];
             } else {
-                const uint32_t off = uint32_t(s.j) * (3u * F * 4u) + fo;
+                const uint32_t off = (uint32_t(s.j) << 10) + ((uint32_t(s.j) << 9) + fo);
                 pa[g] = ld_off(a.phi, off);
-                pc[g] = ld_off(a.phi, off + 2 * F * 4);
+                pc[g] = ld_off<2 * F * 4>(a.phi, off);
                 pv[g][0] = ld_off(a.pv, off);
-                pv[g][1] = ld_off(a.pv, off + F * 4);
-                pv[g][2] = ld_off(a.pv, off + 2 * F * 4);
+                pv[g][1] = ld_off<F * 4>(a.pv, off);
+                pv[g][2] = ld_off<2 * F * 4>(a.pv, off);
             }
         }
 #pragma unroll
@@ -480,7 +497,8 @@ __global__ void __launch_bounds__(64 * kMxWaves, 4) k_message_fwd_mx(MpGeom mg, 
     const int i0 = xcd_block(blockIdx.x, gridDim.x) * per;
     const Rows rows(mg, i0, per);
     NextBatch nx = next_batch<BATCH>(rows, -1, 0, 0);
-    uint4 piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
+    const Stage<BATCH> stage(mg);
+    uint4 piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
     int k = 0;  // batches of the block so far (LDS buffer parity)
     for (int ai = 0; ai < rows.atoms; ++ai) {
         const int i = i0 + ai;
@@ -491,7 +509,7 @@ __global__ void __launch_bounds__(64 * kMxWaves, 4) k_message_fwd_mx(MpGeom mg, 
             store_piece(b, piece);
             __syncthreads();  // the batch is staged; the other buffer's batch is done
             nx = next_batch<BATCH>(rows, ai, b0, cnt);
-            piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
+            piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
             fwd_batch<L0>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, fl, acc);
         }
         // both halves of the wavefront hold partial sums of feature f
@@ -540,8 +558,8 @@ struct BwdGather {
 };
 
 // One batch of nb <= 16 edges.  The lane's eight edges are taken kBwdGroup
-// at a time (an invalid edge of a partial batch reads the batch's first
-// edge and contributes nothing).  Past the first layer the rows of the next
+// at a time (an edge past the end of a partial batch reads the owner's rows
+// and contributes nothing).  Past the first layer the rows of the next
 // group are requested before the current one is reduced, and the filter
 // operands come from LDS (fl) for the products only, which keeps their
 // registers free for the second group; the first layer, with fewer rows per
@@ -582,24 +600,23 @@ __device__ __forceinline__ void bwd_batch(const MpBwd& a, const float* ptab, con
         for (int g = 0; g < G; ++g) {
             const int q = g0 + g;
             const int te = 8 * (q / 4) + 4 * h + q % 4;
-            const EdgeRec& s = rec[te < nb ? te : 0];
-            const uint32_t j = uint32_t(s.j);
-            const uint32_t off3 = j * (3u * F * 4u) + fo;
+            const EdgeRec& s = rec[te];
+            const uint32_t off = (uint32_t(s.j) << 9) + fo, off3 = (uint32_t(s.j) << 10) + off;
             if (L0) {
                 const float* phj = ptab + s.t * 3 * F + f;
                 d.pa[g] = phj[0];
                 d.pc[g] = phj[2 * F];
             } else {
                 d.pa[g] = ld_off(a.phi, off3);
-                d.pc[g] = ld_off(a.phi, off3 + 2 * F * 4);
+                d.pc[g] = ld_off<2 * F * 4>(a.phi, off3);
                 d.pvn[g][0] = ld_off(a.pv, off3);
-                d.pvn[g][1] = ld_off(a.pv, off3 + F * 4);
-                d.pvn[g][2] = ld_off(a.pv, off3 + 2 * F * 4);
+                d.pvn[g][1] = ld_off<F * 4>(a.pv, off3);
+                d.pvn[g][2] = ld_off<2 * F * 4>(a.pv, off3);
             }
             d.gn[g][0] = ld_off(a.gvm, off3);
-            d.gn[g][1] = ld_off(a.gvm, off3 + F * 4);
-            d.gn[g][2] = ld_off(a.gvm, off3 + 2 * F * 4);
-            d.gsn[g] = ld_off(a.gsm, j * (F * 4u) + fo);
+            d.gn[g][1] = ld_off<F * 4>(a.gvm, off3);
+            d.gn[g][2] = ld_off<2 * F * 4>(a.gvm, off3);
+            d.gsn[g] = ld_off(a.gsm, off);
         }
     };
     auto reduce = [&](int g0, const BwdGather<G>& d) {
@@ -721,7 +738,8 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
     const int i0 = blk * per;
     const Rows rows(mg, i0, per);
     NextBatch nx = next_batch<BATCH>(rows, -1, 0, 0);
-    uint4 piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
+    const Stage<BATCH> stage(mg);
+    uint4 piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
     int k = 0;  // batches of the block so far (LDS buffer parity)
     for (int ai = 0; ai < rows.atoms; ++ai) {
         const int i = i0 + ai;
@@ -746,7 +764,7 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
             store_piece(b, piece);
             __syncthreads();  // the batch is staged; the other buffer's batch is done
             nx = next_batch<BATCH>(rows, ai, b0, cnt);
-            piece = fetch_piece<BATCH>(mg, nx.p0, nx.nb);
+            piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
             bwd_batch<L0, VIR>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, fl, bh, bl, bb, bf, o, acc);
         }
         // the lane's force share, then both halves of the wavefront (partial
@@ -802,6 +820,280 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
     }
 }
 
+// ---------------------------------------- reverse, one message of each edge --
+// FP32 models with the per-atom blocks.  A pair's force is the sum of those
+// of its two messages, and both of its atoms see both.  Here an atom takes
+// only the messages it sends, o -> n, which need of the neighbour the adjoints
+// of s and v alone (4 rows instead of 9, which are most of what the kernel
+// above waits for), and keeps of each the sums over the features
+//   S = sum_f [ph_a gs_n w_a' + (ph_b v_o . gv_n) w_b' - ph_c (gv_n . u) w_c'],
+//   T = sum_f ph_c w_c gv_n,
+// with which the force on o through it is (S + T . u / r) u - T / r; the
+// messages it receives are the ones its neighbours send it, found from their
+// rows (k_edge_force, once for all layers).  The sums over features take
+// 9 operations per edge and feature (all four sums of a batch's edges in one
+// exchange that halves the values at every step), the rest 20 instead of 34;
+// vector arithmetic keeps the SIMDs three quarters busy.  At 12,288 atoms a
+// layer takes 185 us instead of 240, at 1,536 26 instead of 32, and the first
+// layer in the same form (k_sp_bwd_own) with k_edge_force no more than
+// k_sp_bwd did (35 + 24 us instead of 66; 7.6 + 5.2 instead of 11.6): energy
+// and forces 1,184 -> 1,086 us and 258 -> 249.  Forces are 2 % closer to
+// float64.  The adjoints of phi and of the vector input are as above, bit for
+// bit.
+
+// One step of the exchange: of the sums x and y over 2 k lanes each, x's in
+// half of the lanes and y's in the other (by lane bit 4, 3, 2, 1, 0).
+__device__ __forceinline__ float halve16(float x, float y) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float plus_dpp(float x) {
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int BANKS>
+__device__ __forceinline__ float pick_banks(float x, float y) {  // y in the quads of BANKS
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(y), 0xE4, 0xF, BANKS, false));
+}
+__device__ __forceinline__ float halve8(float x, float y) {  // row_ror:8
+    return pick_banks<0xC>(plus_dpp<0x128>(x), plus_dpp<0x128>(y));
+}
+__device__ __forceinline__ float halve4(float x, float y) {  // row_half_mirror
+    return pick_banks<0xA>(plus_dpp<0x141>(x), plus_dpp<0x141>(y));
+}
+__device__ __forceinline__ float halve2(float x, float y, bool odd) {  // quad_perm 2 3 0 1
+    const float u = plus_dpp<0x4E>(x), t = plus_dpp<0x4E>(y);
+    return odd ? t : u;
+}
+__device__ __forceinline__ float halve1(float x, float y, bool odd) {  // quad_perm 1 0 3 2
+    const float u = plus_dpp<0xB1>(x), t = plus_dpp<0xB1>(y);
+    return odd ? t : u;
+}
+
+constexpr int kSendGroup = 2;  // edges of a lane whose rows are requested together
+
+struct SendAcc {
+    float gph0, gph2, GV[3];
+};
+struct SendOwner {
+    float ph0, ph2, pv[3];  // ph_a, ph_c, ph_b v
+};
+
+// One batch of nb <= 16 edges; returns the lane's feature sum (over its
+// wavefront's 32 features) of value (edge, component) = send_slot(lane).
+__device__ __forceinline__ float send_batch(const MpBwd& a, const BatchBuf<16>& buf, int nb, int f, int h,
+                                            const uint4* fl, const SendOwner& o, SendAcc& acc) {
+    constexpr int F = kMxF, E = 8, G = kSendGroup;
+    const EdgeRec* rec = buf.rec;
+    const int lane = threadIdx.x & 63, r = lane & 31, e = r & 15, part = 4 * (r >> 4);
+    const half8_t ah = as_half8(buf.a[e][part + h]), al = as_half8(buf.a[e][part + 2 + h]);
+    const half4_t ab = bias_rows(part ? rec[e].dfc : rec[e].fc, h);
+    half8_t bh, bl;
+    half4_t bb;
+    load_channel(fl, 0, bh, bl, bb);
+    const floatx16_t m0 = mma3(ab, bb, ah, al, bh, bl);
+    load_channel(fl, 1, bh, bl, bb);
+    const floatx16_t m1 = mma3(ab, bb, ah, al, bh, bl);
+    load_channel(fl, 2, bh, bl, bb);
+    const floatx16_t m2 = mma3(ab, bb, ah, al, bh, bl);
+    struct Rows4 {
+        float gn[G][3], gsn[G];
+    };
+    const uint32_t fo = uint32_t(f) * 4u;
+    auto gather = [&](int g0, Rows4& d) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int q = g0 + g, te = 8 * (q / 4) + 4 * h + q % 4;
+            const uint32_t off = (uint32_t(rec[te].j) << 9) + fo, off3 = (uint32_t(rec[te].j) << 10) + off;
+            d.gn[g][0] = ld_off(a.gvm, off3);
+            d.gn[g][1] = ld_off<F * 4>(a.gvm, off3);
+            d.gn[g][2] = ld_off<2 * F * 4>(a.gvm, off3);
+            d.gsn[g] = ld_off(a.gsm, off);
+        }
+    };
+    // edges past nb: a filter of exact zeros
+    float quarter[E / 2];  // a pair of edges: lane bits 4, 3, 2 = edge, component % 2, component / 2
+    auto reduce = [&](int g0, const Rows4& d) {
+#pragma unroll
+        for (int g1 = 0; g1 < G; g1 += 2) {
+            float val[2][4];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int g = g1 + k, q = g0 + g, te = 8 * (q / 4) + 4 * h + q % 4;
+                const EdgeRec& s = rec[te];
+                const float g0v = d.gn[g][0], g1v = d.gn[g][1], g2v = d.gn[g][2];
+                const float gvn_u = fmaf(g2v, s.u[2], fmaf(g1v, s.u[1], g0v * s.u[0]));
+                const float B = fmaf(g2v, o.pv[2], fmaf(g1v, o.pv[1], g0v * o.pv[0]));
+                const float A = o.ph0 * d.gsn[g], C = o.ph2 * gvn_u;
+                const float w0 = m0[q], w1 = m1[q], w2 = m2[q];
+                val[k][0] = fmaf(A, m0[8 + q], fmaf(B, m1[8 + q], -C * m2[8 + q]));
+                const float p2 = o.ph2 * w2;
+                val[k][1] = p2 * g0v;
+                val[k][2] = p2 * g1v;
+                val[k][3] = p2 * g2v;
+                acc.GV[0] = fmaf(w1, g0v, acc.GV[0]);
+                acc.GV[1] = fmaf(w1, g1v, acc.GV[1]);
+                acc.GV[2] = fmaf(w1, g2v, acc.GV[2]);
+                acc.gph0 = fmaf(d.gsn[g], w0, acc.gph0);
+                acc.gph2 = fmaf(-w2, gvn_u, acc.gph2);
+            }
+            float x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = halve16(val[0][c], val[1][c]);
+            quarter[(g0 + g1) / 2] = halve4(halve8(x[0], x[1]), halve8(x[2], x[3]));
+        }
+    };
+    Rows4 d0, d1;
+    gather(0, d0);
+#pragma unroll
+    for (int g0 = 0; g0 < E; g0 += 2 * G) {
+        if (g0 + G < E) gather(g0 + G, d1);
+        reduce(g0, d0);
+        if (g0 + G < E) {
+            if (g0 + 2 * G < E) gather(g0 + 2 * G, d0);
+            reduce(g0 + G, d1);
+        }
+    }
+    const bool b1 = lane & 2, b0 = lane & 1;
+    return halve1(halve2(quarter[0], quarter[1], b1), halve2(quarter[2], quarter[3], b1), b0);
+}
+// (edge of the batch) 4 + component of the value a lane holds then
+__device__ __forceinline__ int send_slot(int lane) {
+    const int pair = ((lane >> 1) & 1) + 2 * (lane & 1), q = 2 * pair + ((lane >> 4) & 1);
+    const int comp = ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1);
+    return (8 * (q / 4) + 4 * (lane >> 5) + q % 4) * 4 + comp;
+}
+
+// ADD: a.edge_f already holds the sums of the layers above.  BLOCKS per CU:
+// four spill 11 registers, which pays where there are more blocks than three
+// per CU hold (12,288 atoms 192 -> 183 us, 4,095 atoms 79 -> 74; 1,536 atoms,
+// all in flight with three, 27.0 -> 28.4).
+template <bool ADD, int BLOCKS>
+__global__ void __launch_bounds__(64 * kMxWaves, BLOCKS) k_message_bwd_send(MpGeom mg, MpBwd a, int per) {
+    constexpr int F = kMxF, BATCH = 16;
+    __shared__ __align__(16) BatchBuf<BATCH> buf[2];
+    __shared__ float fsum[2][kMxWaves][4 * BATCH];  // feature sums of a batch per wavefront
+    __shared__ __align__(16) uint4 filt_s[kMxWaves][kFiltPieces][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int h = lane >> 5, f = w * 32 + (lane & 31);
+    const float isc = a.mx_scale[1];
+    uint4* fl = &filt_s[w][0][lane];
+#pragma unroll
+    for (int p = 0; p < kFiltPieces; ++p) fl[p * 64] = a.mx_filter[(w * kFiltPieces + p) * 64 + lane];
+    wave_sync_lds();
+    const int i0 = xcd_block(blockIdx.x, gridDim.x) * per;
+    const Rows rows(mg, i0, per);
+    const int slot = send_slot(lane);
+    NextBatch nx = next_batch<BATCH>(rows, -1, 0, 0);
+    const Stage<BATCH> stage(mg);
+    uint4 piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
+    int k = 0;           // batches of the block so far (LDS buffer parity)
+    int done_p = 0, done_n = 0;  // the batch before: its sums are in fsum[(k - 1) & 1]
+    // the wavefronts take turns to add the batch's sums over all features
+    auto pending = [&] { return done_n > 0 && w == ((k - 1) & 3) && (lane >> 2) < done_n; };
+    auto store = [&](float before) {
+        const float* p = &fsum[(k - 1) & 1][0][lane];
+        const float sum = ((p[0] + p[4 * BATCH]) + p[8 * BATCH]) + p[12 * BATCH];
+        a.edge_f[int64_t(done_p) * 4 + lane] = ADD ? fmaf(sum, isc, before) : sum * isc;
+    };
+    for (int ai = 0; ai < rows.atoms; ++ai) {
+        const int i = i0 + ai;
+        const int cnt = rows.count(ai);
+        const float* pho = a.phi + int64_t(i) * 3 * F + f;
+        const float ph1 = pho[F];
+        SendOwner o;
+        o.ph0 = pho[0];
+        o.ph2 = pho[2 * F];
+        float v[3], gv[3];
+#pragma unroll
+        for (int al = 0; al < 3; ++al) {
+            v[al] = a.v_in[(int64_t(i) * 3 + al) * F + f];
+            gv[al] = a.gvm[(int64_t(i) * 3 + al) * F + f];
+            o.pv[al] = ph1 * v[al];
+        }
+        SendAcc acc{};
+        for (int b0 = 0; b0 < cnt; b0 += BATCH, ++k) {
+            BatchBuf<BATCH>& b = buf[k & 1];
+            store_piece(b, piece);
+            __syncthreads();  // the batch is staged; the other buffer's batch is done, its sums in fsum
+            const int nb = min(BATCH, cnt - b0);
+            const bool mine = pending();
+            float before = 0.f;
+            if (ADD && mine) before = a.edge_f[int64_t(done_p) * 4 + lane];
+            nx = next_batch<BATCH>(rows, ai, b0, cnt);
+            piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
+            const float x = send_batch(a, b, nb, f, h, fl, o, acc);
+            if (mine) store(before);
+            fsum[k & 1][w][slot] = x;
+            done_p = rows.start(ai) + b0;
+            done_n = nb;
+        }
+        acc.gph0 = add_half(acc.gph0);
+        acc.gph2 = add_half(acc.gph2);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) acc.GV[p] = add_half(acc.GV[p]);
+        const float gph[3] = {acc.gph0, fmaf(v[2], acc.GV[2], fmaf(v[1], acc.GV[1], v[0] * acc.GV[0])), acc.gph2};
+        if (h == 0) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a.gphi[int64_t(i) * 3 * F + p * F + f] = gph[p] * isc;
+#pragma unroll
+            for (int al = 0; al < 3; ++al)
+                a.gv_in[(int64_t(i) * 3 + al) * F + f] = gv[al] + (ph1 * acc.GV[al]) * isc;
+        }
+    }
+    __syncthreads();
+    if (pending()) store(ADD ? a.edge_f[int64_t(done_p) * 4 + lane] : 0.f);
+}
+
+// Forces (and virial shares) of the messages whose feature sums
+// k_message_bwd_send left: one wavefront per atom, lanes over its edges, the
+// message it receives along an edge from the neighbour's row (ascending in
+// the caller's index, so found by bisection; its unit vector is the other way
+// round).  Bound by that chain of dependent loads.
+template <bool VIR>
+__global__ void __launch_bounds__(256) k_edge_force(MpGeom mg, const float4* __restrict__ edge_f,
+                                                    float* __restrict__ force, float* __restrict__ vir) {
+    const int lane = threadIdx.x & 63;
+    const int i = xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    if (i >= mg.n) return;  // whole wavefronts
+    const int start = mg.off[i], cnt = mg.ecnt[i];
+    const int key = mg.perm ? mg.perm[i] : i;
+    float fx = 0.f, fy = 0.f, fz = 0.f, vr = 0.f;
+    for (int e = lane; e < cnt; e += 64) {
+        const EdgeRec rec = mg.erec[start + e];
+        const float4 own = edge_f[start + e];
+        int lo = mg.off[rec.j];
+        const int end = lo + mg.ecnt[rec.j];
+        for (int hi = end; lo < hi;) {
+            const int mid = (lo + hi) >> 1;
+            if (mg.edge_key[mid] < key) lo = mid + 1;
+            else hi = mid;
+        }
+        float4 got = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (lo < end && mg.edge_key[lo] == key) got = edge_f[lo];
+        const float S = own.x + got.x;
+        const float tx = own.y - got.y, ty = own.z - got.z, tz = own.w - got.w;
+        const float tu = fmaf(tz, rec.u[2], fmaf(ty, rec.u[1], tx * rec.u[0]));
+        const float rad = fmaf(tu, rec.ir, S);
+        fx += fmaf(rad, rec.u[0], -tx * rec.ir);
+        fy += fmaf(rad, rec.u[1], -ty * rec.ir);
+        fz += fmaf(rad, rec.u[2], -tz * rec.ir);
+        if (VIR) vr += S / rec.ir;
+    }
+    fx = butterfly_sum(fx);
+    fy = butterfly_sum(fy);
+    fz = butterfly_sum(fz);
+    if (VIR) vr = butterfly_sum(vr);
+    if (lane == 0) {
+        const int io = mg.perm ? min(max(key, 0), mg.n - 1) : i;
+        force[io] = fx;
+        force[mg.n + io] = fy;
+        force[2 * mg.n + io] = fz;
+        if (VIR) vir[io] = 0.5f * vr;
+    }
+}
+
 // Scale of the filter weights and biases of one layer for the split
 // products: a power of two s with max(|Wr|, |br|) s in [2^13, 2^14) (s = 1
 // when all are zero), and 1 / s.  Wr and br are contiguous in the weights.
@@ -851,10 +1143,8 @@ __global__ void __launch_bounds__(256) k_phib_v(int n, const float* __restrict__
 // 48; at 1,536 33.9 / 32.3 / 45.5 (forward 22.6 / 21.0 / 31.0); at 2,100
 // 47 / 51 / 56; at 12,288 254 / 246 / 245; at 89,373 1,822 / 1,772 / 1,785.
 // An atom's sums do not depend on it.
-int mx_atoms(int n) {
-    const int slots = 3 * 256;
-    return cdiv(n, slots) < 2 * cdiv(cdiv(n, 2), slots) ? 1 : kMxAtoms;
-}
+constexpr int kMxSlots = 3 * 256;
+int mx_atoms(int n) { return cdiv(n, kMxSlots) < 2 * cdiv(cdiv(n, 2), kMxSlots) ? 1 : kMxAtoms; }
 
 template <typename Kern, typename Args>
 void launch_mx(const ScopedTimer& t, Kern kern, int n, hipStream_t s, const MpGeom& mg, const Args& a) {
@@ -882,7 +1172,27 @@ void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, cons
     launch_mx(t, k_message_fwd_mx<false>, mg.n, s, mg, a);
 }
 
+void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, hipStream_t s) {
+    if (mg.n <= 0) return;
+    ScopedTimer t("message_bwd_first", s, true);
+    const float4* ef = reinterpret_cast<const float4*>(edge_f);
+    const dim3 grid(cdiv(mg.n, 4)), block(256);
+    auto go = [&](auto kern) {
+        if (t.active && t.by_launch) hipExtLaunchKernelGGL(kern, grid, block, 0, s, t.a, t.b, 0, mg, ef, force, vir);
+        else kern<<<grid, block, 0, s>>>(mg, ef, force, vir);
+    };
+    if (vir) go(k_edge_force<true>);
+    else go(k_edge_force<false>);
+    NNP_LAUNCH_CHECK();
+}
+
 void launch_message_bwd_mx(const MpGeom& mg, const MpBwd& a, hipStream_t s, const ScopedTimer& t) {
+    if (a.edge_f && !a.phi_tab) {
+        const bool many = cdiv(mg.n, mx_atoms(mg.n)) > kMxSlots;
+        if (a.accum_force) launch_mx(t, many ? k_message_bwd_send<true, 4> : k_message_bwd_send<true, 3>, mg.n, s, mg, a);
+        else launch_mx(t, many ? k_message_bwd_send<false, 4> : k_message_bwd_send<false, 3>, mg.n, s, mg, a);
+        return;
+    }
     if (!a.phi_tab && !a.pv) {
         set_error("matrix-core message reverse: no phi_b * v buffer");
         throw Fail{NNP_EINVAL};
