@@ -279,7 +279,8 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
     for (int l = 0; l < L; ++l) {
         LayerBuf& lb = b.layer[l];
         lb.h1 = a.take<float>(nt * F);
-        lb.zphi = a.take<float>(n * F);
+        // only the weight gradient (one layer) reads it after its own layer
+        lb.zphi = l > 0 && m->desc.kind == NNP_MODEL_CONS ? b.layer[0].zphi : a.take<float>(n * F);
         lb.phi = a.take<float>(n * 3 * F);
         lb.smid = a.take<float>(n * F);
         lb.vmid = a.take<float>(n * 3 * F);
@@ -1362,11 +1363,10 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
     }
     auto rebuild_if_flagged = [&]() {
         launch_build(n, st->pos, g, plan, c.nb, trig, rc_cons, lc.capacity, lc.offsets, lc.nbr, lc.rev, st->pos_ref,
-                     s, rows);
+                     s, rows, {st->sys.species, st->order, c.pos_rows, c.species_rows});
         if (mts)
             launch_filter(n, rows ? c.nb.cell_pos : st->pos, g, c.nb, trig, lc.offsets, lc.nbr, rc_nc, ln.capacity,
                           ln.offsets, ln.nbr, nullptr, nc_status, s, rows ? c.nb.cell_atoms : nullptr, c.nb.status);
-        if (rows) launch_commit_order(n, c.nb, trig, st->sys.species, st->order, c.pos_rows, c.species_rows, s);
         launch_finish_rebuild(trig, c.t.rebuilds, maxd2, s);
     };
     // Predictive outer steps decide on the next step's rebuild right after
@@ -1380,12 +1380,10 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
     auto build_spare_if_predicted = [&]() {
         launch_predict_rebuild(maxd2, disp_thr, trig, s);
         launch_build(n, st->pos, g, plan, c.nb, trig, rc_cons, lc.capacity, c.spare_off, c.spare_nbr, nullptr,
-                     st->pos_ref, s, rows);
+                     st->pos_ref, s, rows, {st->sys.species, c.spare_order, c.spare_pos, c.spare_species});
         launch_filter(n, rows ? c.nb.cell_pos : st->pos, g, c.nb, trig, c.spare_off, c.spare_nbr, rc_nc,
                       ln.capacity, ln.offsets, ln.nbr, nullptr, nc_status, s, rows ? c.nb.cell_atoms : nullptr,
                       c.nb.status);
-        if (rows)
-            launch_commit_order(n, c.nb, trig, st->sys.species, c.spare_order, c.spare_pos, c.spare_species, s);
     };
     auto adopt_spare = [&]() {
         launch_adopt_lists(n, trig, c.nb, c.spare_off, c.spare_nbr, lc.capacity, lc.offsets, lc.nbr,

@@ -31,7 +31,7 @@ struct ScopedTimer {
 // fast-force evaluation of 192 atoms took 24.9 us with its three (16.6
 // without: a single replica needs no tables), a list build of 12,288 atoms 225
 // us with its nine and the sort behind two of them (174 with one launch here,
-// the cell numbers formed on the device and one copy back).  Sources may go as
+// the cell numbers formed on the device and one copy back; now 141).  Sources may go as
 // soon as add() returned; flush() before the first use on the stream.
 class Uploads {
 public:
@@ -64,9 +64,20 @@ struct CellPlan {
     int n_cells = 0;
 };
 
+// Where a cell-order build that succeeds leaves the permutation (order[2n]:
+// row -> caller index, then caller index -> row) and the positions and species
+// in row order.
+struct RowOrder {
+    const int* species_in = nullptr;
+    int* order = nullptr;
+    double* pos = nullptr;
+    int* species = nullptr;
+};
+
 struct NbrScratch {
     int *grid_m, *grid_base, *cell_code, *cell_lex, *cell_of_atom, *slot_of_atom, *cell_count, *cell_start,
         *cell_atoms, *counts, *tmp_off, *status;
+    int* hits;         // [n][128] entries of each row as the count found them (cell positions)
     double* cell_pos;  // [3][n] positions in cell order
 };
 
@@ -80,7 +91,8 @@ void upload_cell_plan(const CellPlan& plan, NbrScratch& s, Uploads& up, hipStrea
 // order); each row still ascending in caller index.
 void launch_build(int n, const double* pos, const RepGeom& geom, const CellPlan& plan, NbrScratch& s, const int* run,
                   double radius, int64_t capacity, int* offsets, int* nbr, int* rev, double* pos_ref,
-                  hipStream_t stream, bool cell_rows = false);
+                  hipStream_t stream, bool cell_rows = false,
+                  const RowOrder& order = {});
 // pos: the positions in the order of the input list's rows; key (or
 // nullptr): caller's index of a row, for the reverse entries
 // src_status (or nullptr): the input list's build status; a failed build
@@ -94,11 +106,6 @@ void launch_filter(int n, const double* pos, const RepGeom& geom, NbrScratch& s,
 void launch_adopt_lists(int n, const int* run, const NbrScratch& s, const int* off_src, const int* nbr_src,
                         int64_t capacity, int* off_dst, int* nbr_dst, const int* order_src, int* order_dst,
                         const double* pos_src, double* pos_dst, const int* sp_src, int* sp_dst, hipStream_t stream);
-// After a cell-order build that succeeded: the permutation into order[2n]
-// (row -> caller index, then caller index -> row), positions and species in
-// row order.
-void launch_commit_order(int n, const NbrScratch& s, const int* run, const int* species, int* order, double* pos_m,
-                         int* species_m, hipStream_t stream);
 // pos_m / species_m (or nullptr) in row order from the caller's arrays
 void launch_gather_rows(int n, const int* order, const double* pos, const int* species, double* pos_m,
                         int* species_m, hipStream_t stream);

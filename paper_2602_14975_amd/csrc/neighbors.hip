@@ -12,8 +12,9 @@
 //   cell_fill    cell-sorted atom array
 //   nbr_count    one wavefront per atom: 27-cell stencil, float64 pair rule
 //   scan         row offsets
-//   nbr_fill     same tests, ballot compaction into LDS, rank sort so each
-//                row lists j ascending, then a coalesced row store
+//   nbr_fill     the entries the count kept (rows of up to 128; longer ones
+//                by the same tests again) into LDS, rank sort so each row
+//                lists j ascending, then a coalesced row store
 //   nbr_reverse  rev[e] for e = (i, j): position of i in row j (binary search)
 // A second list at a smaller radius is filtered from the first row by row
 // (filter_count / scan / filter_fill), which keeps row order.
@@ -22,8 +23,8 @@
 // integrator) row p belongs to the atom at position p of the cell-sorted
 // array and an entry names its neighbour by that position too; rows still
 // list the neighbours in ascending caller index, so each atom's sums keep
-// their order.  commit_order then records the permutation with the
-// positions and species in that order, once both lists are built.
+// their order.  The fill also records the permutation with the positions and
+// species in that order.
 #include <algorithm>
 #include <cstring>
 
@@ -80,8 +81,9 @@ __global__ void k_cell_assign(int n, const double* __restrict__ pos, RepGeom geo
 // stores are coalesced (element q * 1024 + t of the tile by thread t); in
 // LDS thread t owns 16 consecutive elements: wavefront prefix sums of the
 // thread totals, then the 16 wavefront totals; a carry links the tiles.
-__global__ void __launch_bounds__(1024) k_scan(int n, const int* __restrict__ in,
-                                                int* __restrict__ out, const int* __restrict__ run) {
+// clear: the input is left zero (the counters of the next build).
+__global__ void __launch_bounds__(1024) k_scan(int n, int* __restrict__ in, int* __restrict__ out,
+                                                const int* __restrict__ run, int clear) {
     if (run && *run == 0) return;
     constexpr int E = 16, TILE = 1024 * E;
     __shared__ int tile[TILE + TILE / 32];  // one padding word per 32 (thread rows of 16 words)
@@ -95,6 +97,13 @@ __global__ void __launch_bounds__(1024) k_scan(int n, const int* __restrict__ in
         for (int q = 0; q < E; ++q) {
             const int k = base + q * 1024 + t;
             g[q] = k < n ? in[min(k, n - 1)] : 0;
+        }
+        if (clear) {
+#pragma unroll
+            for (int q = 0; q < E; ++q) {
+                const int k = base + q * 1024 + t;
+                if (k < n) in[k] = 0;
+            }
         }
 #pragma unroll
         for (int q = 0; q < E; ++q) tile[at(q * 1024 + t)] = g[q];
@@ -221,10 +230,18 @@ __device__ __forceinline__ void for_candidates(const Stencil& st, int i, int r, 
     }
 }
 
-// cell_rows: row p is the atom at cell position p (else row i is atom i)
+// Entries a row may have for the fill to take them as the count found them.
+constexpr int kKeep = 128;
+
+// cell_rows: row p is the atom at cell position p (else row i is atom i).
+// The entries (their cell positions, in the order found) are kept for the
+// fill, up to kKeep of a row: found twice, the pair rule in float64 over all
+// candidates was half of the fill (12,288 atoms at 6 A, 89 entries a row: fill
+// 48 -> 16 us, count 28 -> 31).
 __global__ void __launch_bounds__(64 * kWaves)
 k_nbr_count(int n, const double* __restrict__ pos, RepGeom geom, Stencil st, double rc2,
-            const int* __restrict__ run, int* __restrict__ counts, int* __restrict__ status, int cell_rows) {
+            const int* __restrict__ run, int* __restrict__ counts, int* __restrict__ hits,
+            int* __restrict__ status, int cell_rows) {
     if (*run == 0) return;
     int lane = threadIdx.x & 63;
     const int row_i = xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6);
@@ -235,40 +252,59 @@ k_nbr_count(int n, const double* __restrict__ pos, RepGeom geom, Stencil st, dou
     geom.get(i, L, inv);
     double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
     int cnt = 0;
+    int* kept = hits + int64_t(row_i) * kKeep;
     for_candidates(st, i, r, lane, [&](int t) {
         const int j = t >= 0 ? st.cell_atoms[t] : -1;
+        bool ok = false;
         if (j >= 0 && j != i) {
             double dx, dy, dz;
-            if (pair_rule(xi, yi, zi, st.cell_pos[t], st.cell_pos[n + t], st.cell_pos[2 * n + t], L, inv, rc2, dx,
-                          dy, dz))
-                ++cnt;
+            ok = pair_rule(xi, yi, zi, st.cell_pos[t], st.cell_pos[n + t], st.cell_pos[2 * n + t], L, inv, rc2, dx, dy,
+                           dz);
         }
+        const uint64_t bal = __ballot(ok);
+        const int at = cnt + __popcll(bal & ((1ull << lane) - 1ull));
+        if (ok && at < kKeep) kept[at] = t;
+        cnt += __popcll(bal);
     });
-    float tot = wave_sum(float(cnt));
     if (lane == 0) {
-        const int c = int(tot + 0.5f);
-        counts[row_i] = c;
-        if (c > kMaxRow) status[2] = 1;  // the fill kernel cannot sort this row: build nothing
+        counts[row_i] = cnt;
+        if (cnt > kMaxRow) status[2] = 1;  // the fill kernel cannot sort this row: build nothing
     }
 }
 
-// Rank sort of `cnt` distinct keys in LDS key[] into out[] (global): the
-// entry of rank k is val[t] of the key of rank k (val = nullptr: the key).
-__device__ __forceinline__ void rank_sort_store(const int* key, const int* val, int cnt, int lane, int* out) {
-    for (int t = lane; t < cnt; t += 64) {
-        int v = key[t];
-        int rank = 0;
-        for (int u = 0; u < cnt; ++u) rank += key[u] < v;
-        out[rank] = val ? val[t] : v;
+// Rank sort of `cnt` distinct keys in LDS key[] (16-byte aligned, room for a
+// multiple of four) into out[] (global): the entry of rank k is val[t] of the
+// key of rank k (val = nullptr: the key).  Two keys of a lane against four
+// others per read.
+__device__ __forceinline__ void rank_sort_store(int* key, const int* val, int cnt, int lane, int* out) {
+    if (lane < ((4 - (cnt & 3)) & 3)) key[cnt + lane] = 0x7FFFFFFF;
+    wave_sync_lds();
+    const int4* key4 = reinterpret_cast<const int4*>(key);
+    for (int t = lane; t < cnt; t += 128) {
+        const bool second = t + 64 < cnt;
+        const int v0 = key[t], v1 = second ? key[t + 64] : 0;
+        int r0 = 0, r1 = 0;
+        for (int u = 0; u < (cnt + 3) / 4; ++u) {
+            const int4 k = key4[u];
+            r0 += (k.x < v0) + (k.y < v0) + (k.z < v0) + (k.w < v0);
+            r1 += (k.x < v1) + (k.y < v1) + (k.z < v1) + (k.w < v1);
+        }
+        out[r0] = val ? val[t] : v0;
+        if (second) out[r1] = val ? val[t + 64] : v1;
     }
 }
 
+// `order` (or nullptr; with cell_rows): also, for a build that succeeds, order[p]
+// = caller's index of row p, order[n + i] = row of atom i, and the positions
+// and species in row order for the evaluations (a failed build keeps the
+// previous order with the previous lists).
 __global__ void __launch_bounds__(64 * kWaves)
 k_nbr_fill(int n, const double* __restrict__ pos, RepGeom geom, Stencil st, double rc2,
-           const int* __restrict__ run, const int* __restrict__ tmp_off, int64_t capacity,
-           int* __restrict__ offsets, int* __restrict__ nbr, int* __restrict__ status, int cell_rows) {
+           const int* __restrict__ run, const int* __restrict__ tmp_off, const int* __restrict__ hits,
+           int64_t capacity, int* __restrict__ offsets, int* __restrict__ nbr, int* __restrict__ status,
+           int cell_rows, RowOrder order) {
     if (*run == 0) return;
-    __shared__ int rows[kWaves][kMaxRow];
+    __shared__ __align__(16) int rows[kWaves][kMaxRow];
     __shared__ int cpos[kWaves][kMaxRow];  // cell positions of the entries (cell_rows)
     int lane = threadIdx.x & 63;
     int w = threadIdx.x >> 6;
@@ -285,37 +321,51 @@ k_nbr_fill(int n, const double* __restrict__ pos, RepGeom geom, Stencil st, doub
         }
         return;
     }
-    int r = geom.rep_of_atom ? geom.rep_of_atom[i] : 0;
-    double L, inv;
-    geom.get(i, L, inv);
-    double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
+    if (order.order && lane == 0) {
+        order.order[row_i] = i;
+        order.order[n + i] = row_i;
+        order.species[row_i] = order.species_in[i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) order.pos[a * n + row_i] = st.cell_pos[a * n + row_i];
+    }
+    const int start = tmp_off[row_i], cnt = tmp_off[row_i + 1] - start;
     int fill = 0;
     int* row = rows[w];
     int* crow = cpos[w];
-    for_candidates(st, i, r, lane, [&](int t) {
-        const int j = t >= 0 ? st.cell_atoms[t] : -1;
-        bool ok = false;
-        if (j >= 0 && j != i) {
-            double dx, dy, dz;
-            ok = pair_rule(xi, yi, zi, st.cell_pos[t], st.cell_pos[n + t], st.cell_pos[2 * n + t], L, inv, rc2, dx,
-                           dy, dz);
+    if (cnt <= kKeep) {
+        fill = cnt;
+        for (int t = lane; t < cnt; t += 64) {
+            const int c = hits[int64_t(row_i) * kKeep + t];
+            row[t] = st.cell_atoms[c];
+            crow[t] = c;
         }
-        uint64_t bal = __ballot(ok);
-        int pre = __popcll(bal & ((1ull << lane) - 1ull));
-        if (ok && fill + pre < kMaxRow) {
-            row[fill + pre] = j;
-            crow[fill + pre] = t;
-        }
-        fill += __popcll(bal);
-    });
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    int start = tmp_off[row_i];
-    if (fill != tmp_off[row_i + 1] - start) {
+    } else {
+        int r = geom.rep_of_atom ? geom.rep_of_atom[i] : 0;
+        double L, inv;
+        geom.get(i, L, inv);
+        double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
+        for_candidates(st, i, r, lane, [&](int t) {
+            const int j = t >= 0 ? st.cell_atoms[t] : -1;
+            bool ok = false;
+            if (j >= 0 && j != i) {
+                double dx, dy, dz;
+                ok = pair_rule(xi, yi, zi, st.cell_pos[t], st.cell_pos[n + t], st.cell_pos[2 * n + t], L, inv, rc2, dx,
+                               dy, dz);
+            }
+            uint64_t bal = __ballot(ok);
+            int pre = __popcll(bal & ((1ull << lane) - 1ull));
+            if (ok && fill + pre < kMaxRow) {
+                row[fill + pre] = j;
+                crow[fill + pre] = t;
+            }
+            fill += __popcll(bal);
+        });
+    }
+    wave_sync_lds();
+    if (fill != cnt) {
         if (lane == 0) status[3] = 1;  // count and fill disagree (not expected)
     }
-    fill = min(fill, tmp_off[row_i + 1] - start);
+    fill = min(fill, cnt);
     if (lane == 0) {
         offsets[row_i] = start;
         if (row_i == n - 1) offsets[n] = total;
@@ -410,26 +460,6 @@ k_nbr_reverse(int n, const int* __restrict__ run, const int* __restrict__ status
     }
 }
 
-// After a successful build in cell order: order[p] = caller's index of row
-// p, order[n + i] = row of atom i, and the positions and species in row
-// order for the evaluations (a failed build keeps the previous order with
-// the previous lists).
-__global__ void k_commit_order(int n, const int* __restrict__ run, const int* __restrict__ status,
-                               const int* __restrict__ cell_atoms, const double* __restrict__ cell_pos,
-                               const int* __restrict__ species, int* __restrict__ order, double* __restrict__ pos_m,
-                               int* __restrict__ species_m) {
-    if (*run == 0 || status[0] != 0 || status[2] != 0) return;
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const int i = cell_atoms[p];
-    order[p] = i;
-    order[n + i] = p;
-    pos_m[p] = cell_pos[p];
-    pos_m[n + p] = cell_pos[n + p];
-    pos_m[2 * n + p] = cell_pos[2 * n + p];
-    species_m[p] = species[i];
-}
-
 // A list built into spare buffers (with its order and row-ordered copies)
 // replaces the one in use, once nothing reads the latter any more; only
 // after a build that ran and succeeded.
@@ -517,15 +547,17 @@ __global__ void k_predict_rebuild(unsigned* maxd2, double thr, int* flag) {
 
 // The cell numbers of the plan: the Morton rank of each cell among the m^3
 // cells of its replica (codes interleave x, y, z bits, x first), one thread per
-// cell.  The cells with a smaller code are counted by the first bit in which
+// cell; also clears the cells' member counts (each build's scan leaves them
+// cleared).  The cells with a smaller code are counted by the first bit in which
 // they differ: for each bit set in the cell's code, those that agree above it
 // and have it clear form a box of coordinates, cut at m.  (On the host the
 // numbers took a sort per call and two more pageable copies.)
 __global__ void __launch_bounds__(256) k_cell_numbers(int R, int n_cells, const int* __restrict__ grid_m,
                                                       const int* __restrict__ grid_base, int* __restrict__ code,
-                                                      int* __restrict__ lex) {
+                                                      int* __restrict__ lex, int* __restrict__ cell_count) {
     const int c = blockIdx.x * 256 + threadIdx.x;
     if (c >= n_cells) return;
+    cell_count[c] = 0;
     int r = 0, hi = R;  // the last replica whose first cell is at or before c
     while (hi - r > 1) {
         const int mid = (r + hi) / 2;
@@ -620,6 +652,7 @@ void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s) {
     s.cell_atoms = a.take<int>(n);
     s.cell_pos = a.take<double>(3 * n);
     s.counts = a.take<int>(n);
+    s.hits = a.take<int>(n * kKeep);
     s.tmp_off = a.take<int>(n + 1);
     s.status = a.take<int>(8);
 }
@@ -630,37 +663,31 @@ void upload_cell_plan(const CellPlan& plan, NbrScratch& s, Uploads& up, hipStrea
     up.add(s.grid_base, plan.base.data(), sizeof(int) * R);
     up.flush();
     k_cell_numbers<<<cdiv(plan.n_cells, 256), 256, 0, stream>>>(R, plan.n_cells, s.grid_m, s.grid_base, s.cell_code,
-                                                                s.cell_lex);
+                                                                s.cell_lex, s.cell_count);
     NNP_LAUNCH_CHECK();
 }
 
 void launch_build(int n, const double* pos, const RepGeom& geom, const CellPlan& plan, NbrScratch& s,
                   const int* run, double radius, int64_t capacity, int* offsets, int* nbr, int* rev,
-                  double* pos_ref, hipStream_t stream, bool cell_rows) {
-    launch_zero(s.cell_count, plan.n_cells + 1, run, stream);
+                  double* pos_ref, hipStream_t stream, bool cell_rows, const RowOrder& order) {
     k_cell_assign<<<cdiv(n, 256), 256, 0, stream>>>(n, pos, geom, s.grid_m, s.grid_base, s.cell_code, run,
                                                     s.cell_of_atom, s.slot_of_atom, s.cell_count, pos_ref);
-    k_scan<<<1, 1024, 0, stream>>>(plan.n_cells, s.cell_count, s.cell_start, run);
+    k_scan<<<1, 1024, 0, stream>>>(plan.n_cells, s.cell_count, s.cell_start, run, 1);
     k_cell_fill<<<cdiv(n, 256), 256, 0, stream>>>(n, run, s.cell_of_atom, s.slot_of_atom, s.cell_start,
                                                   s.cell_atoms, pos, s.cell_pos);
     Stencil st{s.grid_m, s.grid_base, s.cell_code, s.cell_lex, s.cell_of_atom, s.cell_start, s.cell_atoms, s.cell_pos};
     double rc2 = radius * radius;
     const int cr = cell_rows ? 1 : 0;
-    k_nbr_count<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, st, rc2, run, s.counts, s.status, cr);
-    k_scan<<<1, 1024, 0, stream>>>(n, s.counts, s.tmp_off, run);
+    k_nbr_count<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, st, rc2, run, s.counts, s.hits, s.status,
+                                                             cr);
+    k_scan<<<1, 1024, 0, stream>>>(n, s.counts, s.tmp_off, run, 0);
     ScopedTimer timer("nbr_fill", stream);
-    k_nbr_fill<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, st, rc2, run, s.tmp_off, capacity,
-                                                            offsets, nbr, s.status, cr);
+    k_nbr_fill<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, st, rc2, run, s.tmp_off, s.hits,
+                                                            capacity, offsets, nbr, s.status, cr,
+                                                            cell_rows ? order : RowOrder{});
     if (rev)
         k_nbr_reverse<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, run, s.status, offsets, nbr, rev,
                                                                    cell_rows ? s.cell_atoms : nullptr);
-    NNP_LAUNCH_CHECK();
-}
-
-void launch_commit_order(int n, const NbrScratch& s, const int* run, const int* species, int* order,
-                         double* pos_m, int* species_m, hipStream_t stream) {
-    k_commit_order<<<cdiv(n, 256), 256, 0, stream>>>(n, run, s.status, s.cell_atoms, s.cell_pos, species, order,
-                                                     pos_m, species_m);
     NNP_LAUNCH_CHECK();
 }
 
@@ -693,7 +720,7 @@ void launch_filter(int n, const double* pos, const RepGeom& geom, NbrScratch& s,
     double rc2 = radius * radius;
     k_filter_count<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, off_in, nbr_in, rc2, run, s.counts,
                                                                 src_status);
-    k_scan<<<1, 1024, 0, stream>>>(n, s.counts, s.tmp_off, run);
+    k_scan<<<1, 1024, 0, stream>>>(n, s.counts, s.tmp_off, run, 0);
     k_filter_fill<<<cdiv(n, kWaves), 64 * kWaves, 0, stream>>>(n, pos, geom, off_in, nbr_in, rc2, run, s.tmp_off,
                                                                capacity, offsets, nbr, status, src_status);
     if (rev)
