@@ -283,7 +283,7 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
         lb.zphi = l > 0 && m->desc.kind == NNP_MODEL_CONS ? b.layer[0].zphi : a.take<float>(n * F);
         lb.phi = a.take<float>(n * 3 * F);
         lb.smid = a.take<float>(n * F);
-        lb.vmid = a.take<float>(n * 3 * F);
+        lb.vmid = a.take<float>((l == 0 ? nt : n) * 3 * F);
         lb.UV = a.take<float>(nt * 6 * F);
         lb.X = a.take<float>(n * 2 * F);
         lb.a1 = a.take<float>(nt * F);
@@ -400,7 +400,14 @@ void Model::refresh_tables(hipStream_t s) {
         PackFrags P{};
         P.m[0] = {p(off_Wo), frag_Wo(false), F, F, 0};
         P.m[1] = {p(off_Wo), frag_Wo(true), F, F, 1};
-        launch_pack_frags(P, 2, frag_pieces(), s);
+        int c = 2;
+        if (frag_species()) {
+            for (int k = 0; k < 2; ++k) {
+                P.m[c++] = {sp_T(k), frag_T(k), F, sp_ep, 0};
+                P.m[c++] = {sp_TT(k), frag_TT(k), sp_pp, F, 0};
+            }
+        }
+        launch_pack_frags(P, c, frag_pieces(), s);
     }
     if (desc.kind == NNP_MODEL_CONS) {
         tr(off_Wo, F, F);
@@ -428,6 +435,11 @@ static bool species_sum_on(const Model* m, const MpGeom& mg, const ModelBuf& b) 
 // one kernel each way (atom_block.hip) unless the older dense kernels were
 // selected.
 static bool atom_blocks_on(const Model* m) { return m->wf && dense_auto(); }
+
+// The dense products of the first layer by species within those kernels.
+static bool species_in_blocks(const Model* m, const MpGeom& mg, const ModelBuf& b) {
+    return b.blocks && b.edge_f && m->frag_species() && species_sum_on(m, mg, b);
+}
 
 void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, ModelBuf& b, hipStream_t s) {
     const int n = int(sys.n_atoms);
@@ -461,7 +473,10 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
             a.phi = lb.phi;
             a.pv = lb.pv;
         }
-        if (l == 0 && species_sum_on(m, mg, b)) {
+        const bool fused = l == 0 && species_in_blocks(m, mg, b);
+        if (fused) {
+            // with the block
+        } else if (l == 0 && species_sum_on(m, mg, b)) {
             // s = [E | species indicator] T_0^T (T_0 holds the embedding in
             // the indicator slots), v = U T_2^T: one launch over the rows
             // [s; v] where they are adjacent (FP32-equivalent split-bfloat16
@@ -488,6 +503,13 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
             f.n = n;
             f.smid = lb.smid;
             f.vmid = lb.vmid;
+            if (fused) {
+                f.smid = b.sp;
+                f.vmid = b.sp + int64_t(n) * m->sp_ep;
+                f.T0 = m->frag_T(0);
+                f.T2 = m->frag_T(1);
+                f.v_keep = lb.vmid;
+            }
             f.U = m->frag(l, Model::kUV);
             f.M1 = m->frag(l, Model::kM1);
             f.M2 = m->frag(l, Model::kM2);
@@ -550,6 +572,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     LayerBuf& lb = b.layer[l];
     const bool wg = dtheta != nullptr;
     const bool blocks = b.blocks;
+    const bool fused = l == 0 && species_in_blocks(m, mg, b);
     if (blocks) {
         AtomBwd f{};
         f.n = n;
@@ -570,6 +593,14 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         f.Vt = m->frag(l, Model::kVt);
         f.gs_out = b.gs2;
         f.gv_out = b.gv;
+        if (fused) {
+            f.TT0 = m->frag_TT(0);
+            f.TT2 = m->frag_TT(1);
+            f.pp = m->sp_pp;
+            f.P0 = b.sp;
+            f.P2 = b.sp + int64_t(n) * F;
+            f.keep = lb.pqo;
+        }
         launch_atom_bwd(f, gv_zero, m->bf16(), s);
     } else {
         launch_update_combine_bwd(n, F, lb.UV, lb.pqo, b.gs, gv_zero ? nullptr : b.gv, b.gpqo, b.gUV, s);
@@ -611,6 +642,11 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         a.want_gphi = 1;
         a.edge_f = b.edge_f;
     }
+    if (fused) {
+        launch_sp_bwd_own(mg, m->desc.n_species, F, b.sp, b.sp + int64_t(n) * F, b.edge_f, accum_force, s);
+        launch_edge_force(mg, b.edge_f, force, vir, s);
+        return;
+    }
     if (l == 0 && !wg && force && species_sum_on(m, mg, b)) {
         // P_0 = g_smid T_0, P_2 = g_vmid T_2 (float32 products), then the
         // per-edge force shares
@@ -628,7 +664,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
             }
         }
         if (b.edge_f) {
-            launch_sp_bwd_own(mg, m->desc.n_species, b.sp, P2, b.edge_f, accum_force, s);
+            launch_sp_bwd_own(mg, m->desc.n_species, pp, b.sp, P2, b.edge_f, accum_force, s);
             launch_edge_force(mg, b.edge_f, force, vir, s);
         } else {
             launch_sp_bwd(mg, m->desc.n_species, b.sp, P2, force, accum_force, vir, s);

@@ -415,9 +415,14 @@ __device__ __forceinline__ Slice<TA> added(const Sums<TA>& c, const Slice<TA>& b
 //                 phi_b v for its message kernels;
 //   LAST = true:  the readout, the atomic energy and the adjoint of s of the
 //                 energy (v is not used past the last layer: not formed).
+//   FIRST (FP32 models, first layer by species): smid and vmid are the edge
+//   sums by species, rows E and U of 128 slots; s = T_0 E and v = T_2 U come
+//   first (v_keep: v, read again later).  As launches of their own this
+//   layer's products, here and in the reverse, took 47 us at 12,288 atoms and 16
+//   at 1,536 (more where n is not a multiple of 128); in the blocks 20 and 8.
 // Kept for the reverse: U v and V v, the M1 pre-activation, q and o (LAST: q
 // alone), the W1 pre-activation.
-template <int NP, int TA, bool LAST>
+template <int NP, int TA, bool LAST, bool FIRST>
 __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     extern __shared__ __align__(16) char lds[];
     __shared__ float epart[LAST ? 4 : 1][TA];
@@ -427,14 +432,41 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
     // free while the rows of s and v (turn) and the outputs (turn2) are written
     char* turn = lds + CB + L.w * (TA * 128);
     char* turn2 = lds + 2 * CB + L.w * (TA * 128);
+    Slice<TA> s0;
     {
         Slice<TA> v0[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) v0[c] = load_slice<3, kF>(A.vmid, c, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c], two_uv);
+        s0 = load_slice<1, kF>(A.smid, 0, 0, L);
+        if constexpr (FIRST) {
+            // v = T_2 U, then s = T_0 E, by way of the same regions
+            {
+                Sums<TA> sums[1][3];
+                Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.T2, kF, L.w, 1, L, false);
+                __syncthreads();
+                product<NP, 1, 3, kKsF>(sums, W, lds, CB, L);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) v0[c] = as_slice(sums[0][c]);
+            }
+            if constexpr (!LAST) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) keep_slice<3>(A.v_keep, c, L, v0[c]);
+            }
+            Sums<TA> sums[1][1];
+            Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.T0, kF, L.w, 1, L, false);
+            __syncthreads();  // the rows of U are read
+            put_slice<NP>(lds, 0, L, s0, false);
+#pragma unroll
+            for (int c = 1; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c], two_uv);
+            __syncthreads();
+            product<NP, 1, 1, kKsF>(sums, W, lds, 0, L);
+            s0 = as_slice(sums[0][0]);
+            __syncthreads();  // the rows of E are read
+            put_slice<NP>(lds, 0, L, v0[0], two_uv);
+        }
     }
-    const Slice<TA> s0 = load_slice<1, kF>(A.smid, 0, 0, L);
 
     // U v, V v: row tiles w (U) and 4 + w (V) of the adjacent matrices
     Sums<TA> uv[2][3];
@@ -500,7 +532,9 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
             for (int c = 0; c < 3; ++c) {
                 // v and U v are read again rather than held over the products
                 // (96 registers)
-                const Slice<TA> v0 = load_slice<3, kF>(A.vmid, c, 0, L);
+                Slice<TA> v0;
+                if constexpr (FIRST) v0 = kept_slice<3>(A.v_keep, c, L);
+                else v0 = load_slice<3, kF>(A.vmid, c, 0, L);
                 const Slice<TA> u = kept_slice<6>(A.UV, 2 * c, L);
 #pragma unroll
                 for (int e = 0; e < E; ++e) v1[c].v[e >> 2][e & 3] = fmaf(h[NQ - 1][e], u[e], v0[e]);
@@ -585,7 +619,9 @@ __global__ void __launch_bounds__(256, 2) k_atom_fwd(AtomFwd A) {
 //     layer's phi, gs = gs_in + W1^T (silu'(h1) W2^T gphi); gs_in is the
 //     adjoint that passes that layer's message step by.
 //   TOP = true (the last layer): gs_in is the adjoint of s, that of v is zero.
-template <int NP, int TA, bool TOP>
+//   BOTTOM (with FIRST): instead of gs_out and gv_out the rows P_0 and P_2 (128
+//   slots, the first pp used) that k_sp_bwd_own takes (keep: room for g_s).
+template <int NP, int TA, bool TOP, bool BOTTOM>
 __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
     extern __shared__ __align__(16) char lds[];
     constexpr int CB = kRegion<NP, TA>, FF = kFragsF<TA>, E = TA / 2;
@@ -660,7 +696,8 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
         Sums<TA> acc[2][1];
         product<NP, 2, 1, kKsF>(acc, W, lds, 0, L);
         gn = as_slice(acc[1][0]);
-        store_slice<1, kF>(A.gs_out, 0, 0, L, added(acc[0][0], gs), turn);
+        if constexpr (BOTTOM) keep_slice<3>(A.keep, 0, L, added(acc[0][0], gs));
+        else store_slice<1, kF>(A.gs_out, 0, 0, L, added(acc[0][0], gs), turn);
     }
     // adjoints of U v and V v, one after the other through the same regions:
     // g_vmid = gv + [gU gV] [U; V], gv (48 registers) read again at the end
@@ -696,10 +733,39 @@ __global__ void __launch_bounds__(256, 2) k_atom_bwd(AtomBwd A) {
     }
     fold(sums, sep);
     __syncthreads();
+    Slice<TA> gvo[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-        store_slice<3, kF>(A.gv_out, c, 0, L,
-                           TOP ? as_slice(sums[0][c]) : added(sums[0][c], load_slice<3, kF>(A.gv_in, c, 0, L)), turn);
+        gvo[c] = TOP ? as_slice(sums[0][c]) : added(sums[0][c], load_slice<3, kF>(A.gv_in, c, 0, L));
+    if constexpr (!BOTTOM) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) store_slice<3, kF>(A.gv_out, c, 0, L, gvo[c], turn);
+    } else {
+        // P_2 = T_2^T g_v, then P_0 = T_0^T g_s; wavefront w has the slots
+        // 32 w .. of the pp ones
+        const bool on = 32 * L.w < A.pp;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, gvo[c], false);
+        {
+            Sums<TA> p[1][3];
+            Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT2, A.pp, L.w, 1, L, false);
+            __syncthreads();
+            if (on) product<NP, 1, 3, kKsF>(p, W, lds, CB, L);
+            __syncthreads();  // read: region 1 is the room to turn again
+            if (on) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) store_slice<3, kF>(A.P2, c, 0, L, as_slice(p[0][c]), turn);
+            }
+        }
+        Sums<TA> p[1][1];
+        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT0, A.pp, L.w, 1, L, false);
+        put_slice<NP>(lds, 0, L, kept_slice<3>(A.keep, 0, L), false);
+        __syncthreads();
+        if (on) {
+            product<NP, 1, 1, kKsF>(p, W, lds, 0, L);
+            store_slice<1, kF>(A.P0, 0, 0, L, as_slice(p[0][0]), turn);
+        }
+    }
 }
 
 // ---------------------------------------------------------- weight packing --
@@ -753,13 +819,27 @@ bool small_tiles(int n, bool bf16) { return bf16 ? n <= 2 * 256 * 16 : two_sums(
 
 template <int NP, int TA>
 void launch_fwd(const AtomFwd& a, bool last, hipStream_t s) {
-    if (last) launch_block<NP, TA>(k_atom_fwd<NP, TA, true>, a, s);
-    else launch_block<NP, TA>(k_atom_fwd<NP, TA, false>, a, s);
+    if constexpr (NP == 3) {
+        if (a.T0) {
+            if (last) launch_block<NP, TA>(k_atom_fwd<NP, TA, true, true>, a, s);
+            else launch_block<NP, TA>(k_atom_fwd<NP, TA, false, true>, a, s);
+            return;
+        }
+    }
+    if (last) launch_block<NP, TA>(k_atom_fwd<NP, TA, true, false>, a, s);
+    else launch_block<NP, TA>(k_atom_fwd<NP, TA, false, false>, a, s);
 }
 template <int NP, int TA>
 void launch_bwd(const AtomBwd& a, bool top, hipStream_t s) {
-    if (top) launch_block<NP, TA>(k_atom_bwd<NP, TA, true>, a, s);
-    else launch_block<NP, TA>(k_atom_bwd<NP, TA, false>, a, s);
+    if constexpr (NP == 3) {
+        if (a.TT0) {
+            if (top) launch_block<NP, TA>(k_atom_bwd<NP, TA, true, true>, a, s);
+            else launch_block<NP, TA>(k_atom_bwd<NP, TA, false, true>, a, s);
+            return;
+        }
+    }
+    if (top) launch_block<NP, TA>(k_atom_bwd<NP, TA, true, false>, a, s);
+    else launch_block<NP, TA>(k_atom_bwd<NP, TA, false, false>, a, s);
 }
 
 }  // namespace
@@ -772,10 +852,14 @@ void launch_pack_frags(const PackFrags& P, int count, int np, hipStream_t s) {
 }
 
 void atom_block_setup() {
-    raise_lds(k_atom_fwd<3, 32, false>);
-    raise_lds(k_atom_fwd<3, 32, true>);
-    raise_lds(k_atom_bwd<3, 32, false>);
-    raise_lds(k_atom_bwd<3, 32, true>);
+    raise_lds(k_atom_fwd<3, 32, false, false>);
+    raise_lds(k_atom_fwd<3, 32, true, false>);
+    raise_lds(k_atom_fwd<3, 32, false, true>);
+    raise_lds(k_atom_fwd<3, 32, true, true>);
+    raise_lds(k_atom_bwd<3, 32, false, false>);
+    raise_lds(k_atom_bwd<3, 32, true, false>);
+    raise_lds(k_atom_bwd<3, 32, false, true>);
+    raise_lds(k_atom_bwd<3, 32, true, true>);
 }
 
 void launch_atom_fwd(const AtomFwd& a, bool last, bool bf16, hipStream_t s) {

@@ -194,6 +194,10 @@ struct AtomFwd {
     const uint16_t *U, *M1, *M2, *W1, *W2;  // packed; U is [U; V]
     const float *m1, *m2, *b1, *b2;
     float *UV, *a1, *pqo, *s_out, *v_out, *h1, *phi, *pv;
+    // first layer by species (FP32 models), or nullptr: packed T_0 and T_2;
+    // smid and vmid are then the rows E and U, v_keep room for v
+    const uint16_t *T0, *T2;
+    float* v_keep;
     // last
     const float *wo, *beta;
     const int* species;
@@ -211,6 +215,12 @@ struct AtomBwd {
     const float *gs_in, *gv_in, *gphi, *h1, *UV, *pqo, *a1;
     const uint16_t *W2t, *W1t, *M2t, *M1t, *Ut, *Vt;
     float *gs_out, *gv_out;
+    // first layer by species (FP32 models), or nullptr: packed transposes of
+    // T_0 and T_2 (pp rows); P0 and P2 (rows of 128) are written instead of
+    // gs_out and gv_out, keep is room for the former ([tile rows][3][F])
+    const uint16_t *TT0, *TT2;
+    int pp;
+    float *P0, *P2, *keep;
 };
 void launch_atom_bwd(const AtomBwd& a, bool top, bool bf16, hipStream_t s);
 // Whether the matrix-core dense kernels are selected (nnp_set_dense_kernels).
@@ -253,7 +263,7 @@ void launch_sp_tables(int F, int S, const float* Wr, const float* br, const floa
 void launch_sp_bwd(const MpGeom& mg, int S, const float* P0, const float* P2, float* force, bool accum, float* vir,
                    hipStream_t s);
 // The first layer's share of edge_f (see launch_edge_force), written or added
-void launch_sp_bwd_own(const MpGeom& mg, int S, const float* P0, const float* P2, float* edge_f, bool add,
+void launch_sp_bwd_own(const MpGeom& mg, int S, int pitch, const float* P0, const float* P2, float* edge_f, bool add,
                        hipStream_t s);
 void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, const ScopedTimer& t);
 void launch_message_bwd_mx(const MpGeom& mg, const MpBwd& a, hipStream_t s, const ScopedTimer& t);

@@ -94,12 +94,22 @@ struct Model {
         return o;
     }
     int64_t frag_count() const {
-        return frag_pieces() * (n_layers() * frag_prefix(kFrags) + 2 * int64_t(desc.width) * desc.width);
+        return frag_pieces() * (n_layers() * frag_prefix(kFrags) + 2 * int64_t(desc.width) * desc.width +
+                                (frag_species() ? sp_count() : 0));
     }
     uint16_t* frag(int l, int id) const { return wf + frag_pieces() * (l * frag_prefix(kFrags) + frag_prefix(id)); }
     uint16_t* frag_Wo(bool transposed) const {
         return wf + frag_pieces() * (n_layers() * frag_prefix(kFrags) +
                                      (transposed ? int64_t(desc.width) * desc.width : 0));
+    }
+    // FP32 models with up to 128 slots of species: the tables of the first
+    // layer for its blocks, T_c [F][128] and their transposes [pp][F]
+    bool frag_species() const { return sp && sp_ep == 128 && !bf16(); }
+    uint16_t* frag_T(int c) const {
+        return frag_Wo(true) + frag_pieces() * int64_t(desc.width) * (desc.width + c * sp_ep);
+    }
+    uint16_t* frag_TT(int c) const {
+        return frag_T(2) + frag_pieces() * int64_t(desc.width) * c * sp_pp;
     }
     void refresh_tables(hipStream_t s);
 };

@@ -321,18 +321,16 @@ void launch_sp_tables(int F, int S, const float* Wr, const float* br, const floa
     NNP_LAUNCH_CHECK();
 }
 
-void launch_sp_bwd_own(const MpGeom& mg, int S, const float* P0, const float* P2, float* edge_f, bool add,
+void launch_sp_bwd_own(const MpGeom& mg, int S, int pitch, const float* P0, const float* P2, float* edge_f, bool add,
                        hipStream_t s) {
     if (mg.n <= 0) return;
-    int pp, ep;
-    species_sum_pitches(S, pp, ep);
     ScopedTimer t("message_bwd_first", s, true);
     const dim3 grid(cdiv(mg.n, kSpWaves)), block(64 * kSpWaves);
     float4* ef = reinterpret_cast<float4*>(edge_f);
     auto go = [&](auto kern) {
         if (t.active && t.by_launch)
-            hipExtLaunchKernelGGL(kern, grid, block, 0, s, t.a, t.b, 0, mg, S, pp, P0, P2, ef);
-        else kern<<<grid, block, 0, s>>>(mg, S, pp, P0, P2, ef);
+            hipExtLaunchKernelGGL(kern, grid, block, 0, s, t.a, t.b, 0, mg, S, pitch, P0, P2, ef);
+        else kern<<<grid, block, 0, s>>>(mg, S, pitch, P0, P2, ef);
     };
     if (add) go(k_sp_bwd_own<true>);
     else go(k_sp_bwd_own<false>);
