@@ -4,9 +4,9 @@
 // update and the projections of an atom need nothing of its neighbours'
 // features.
 //
-// A block of four wavefronts owns 16 atoms.
-//   Messages (each wavefront its own four atoms, whose list rows are one run
-//   of entries): in chunks of 128 entries, the float64 pair rule with lanes
+// A block of eight (four up to 16 features) wavefronts owns 16 atoms.
+//   Messages (each wavefront its own two or four atoms, whose list rows are
+//   one run of entries): in chunks of 64 or 128 entries, the float64 pair rule with lanes
 //   over entries, the edges that pass compacted in list order into LDS; their
 //   radial values with lanes over edges; then lanes over features, one atom
 //   per F lanes, every edge added in list order.
@@ -17,10 +17,11 @@
 //   holds features 16 t + 4 q + i (i < 4) of atom a.  Every sum runs over k in
 //   increasing order; for BF16 models weights and inputs are rounded to
 //   bfloat16 first.
-// Bound by instruction issue of the message part.  As two kernels (message;
+// Bound by the chain of a block's steps (a block alone takes 10 us, vector
+// instructions issue a third of the time at 12,288 atoms).  As two kernels (message;
 // update with weights and inputs read from LDS for plain multiply-adds) with
 // s and v of the message step through memory, 12,288 atoms took 18.0 + 21.9
-// us; now 26.1 (192 atoms at width 16: 8.8 + 8.8 -> 9.4).
+// us; now 24.6 (192 atoms at width 16: 8.8 + 8.8 -> 8.9).
 #include "common.h"
 #include "kernels.h"
 #include "mp_edge.h"
@@ -33,8 +34,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kK = 8;                                    // Bessel functions of the filter
 constexpr int kHC = 160, kNl = 2;                        // q and k outputs, vector heads
-constexpr int kAtoms = 16, kWaves = 4, kPer = kAtoms / kWaves;
-constexpr int kChunk = 128;                              // list entries per wavefront and chunk
+constexpr int kAtoms = 16;                               // atoms of a block
 
 constexpr int pad16(int x) { return (x + 15) / 16 * 16; }
 
@@ -90,11 +90,13 @@ struct Slot {
     int t, owner, pad[2];
 };
 
-template <int F, bool BF16>
-__global__ void __launch_bounds__(64 * kWaves, 3) k_nc_embed(MpGeom mg, NcEmbedArgs A) {
+template <int F, bool BF16, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves, kWaves == 4 ? 3 : 4) k_nc_embed(MpGeom mg, NcEmbedArgs A) {
     using P = Pack<F>;
+    constexpr int kPer = kAtoms / kWaves;                // atoms of a wavefront
+    constexpr int kChunk = kWaves == 4 ? 128 : 64;       // list entries per wavefront and chunk
     constexpr int FL = F < 16 ? 16 : F;        // lanes per atom in the feature step
-    constexpr int G = 64 / FL, R = kPer / G;   // atoms at a time, rounds
+    constexpr int G = 64 / FL, R = kPer > G ? kPer / G : 1;  // atoms at a time, rounds
     constexpr int KV = pad16(F), KX = pad16(2 * F);
     __shared__ __align__(16) Slot slot_s[kWaves][kChunk];
     __shared__ __align__(16) float xs[KX * 16];       // [s; |V v|]; s alone before it
@@ -256,6 +258,7 @@ __global__ void __launch_bounds__(64 * kWaves, 3) k_nc_embed(MpGeom mg, NcEmbedA
     // s and v of the block's atoms (zero rows past the last atom and feature)
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
+        if (rr * G + g >= kPer) continue;
         const int a = w * kPer + rr * G + g, i = ib + a;
         const bool on = i < n && f < F;
         const int ti = i < n ? min(max(mg.species[i], 0), mg.n_species - 1) : 0;
@@ -427,10 +430,15 @@ void launch_nc_embed(const MpGeom& mg, const NcEmbedArgs& a, int F, bool bf16, h
     if (mg.n <= 0) return;
     ScopedTimer timer("nc_message_fwd", s);
     const int blocks = cdiv(mg.n, kAtoms);
-    auto launch = [&](void (*kernel)(MpGeom, NcEmbedArgs)) { kernel<<<blocks, 64 * kWaves, 0, s>>>(mg, a); };
-    if (F == 32) launch(bf16 ? k_nc_embed<32, true> : k_nc_embed<32, false>);
-    else if (F == 16) launch(bf16 ? k_nc_embed<16, true> : k_nc_embed<16, false>);
-    else launch(bf16 ? k_nc_embed<8, true> : k_nc_embed<8, false>);
+    // Wavefronts of a block: eight with two atoms each, where these fill their
+    // lanes (32 features): 192 atoms 12.3 -> 10.4 us, 4,095 atoms 16.8 -> 13.8,
+    // 12,288 atoms 25.1 -> 24.6.  At 16 features a wavefront takes four atoms at
+    // a time: 12,288 atoms 19.0 with four wavefronts, 21.7 with eight (192
+    // atoms 8.9 and 8.7).
+    auto launch = [&](auto kernel, int waves) { kernel<<<blocks, 64 * waves, 0, s>>>(mg, a); };
+    if (F == 32) launch(bf16 ? k_nc_embed<32, true, 8> : k_nc_embed<32, false, 8>, 8);
+    else if (F == 16) launch(bf16 ? k_nc_embed<16, true, 4> : k_nc_embed<16, false, 4>, 4);
+    else launch(bf16 ? k_nc_embed<8, true, 4> : k_nc_embed<8, false, 4>, 4);
     NNP_LAUNCH_CHECK();
 }
 
