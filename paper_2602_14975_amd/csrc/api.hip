@@ -644,7 +644,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     }
     if (fused) {
         launch_sp_bwd_own(mg, m->desc.n_species, F, b.sp, b.sp + int64_t(n) * F, b.edge_f, accum_force, s);
-        launch_edge_force(mg, b.edge_f, force, vir, s);
+        launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
         return;
     }
     if (l == 0 && !wg && force && species_sum_on(m, mg, b)) {
@@ -665,14 +665,14 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         }
         if (b.edge_f) {
             launch_sp_bwd_own(mg, m->desc.n_species, pp, b.sp, P2, b.edge_f, accum_force, s);
-            launch_edge_force(mg, b.edge_f, force, vir, s);
+            launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
         } else {
             launch_sp_bwd(mg, m->desc.n_species, b.sp, P2, force, accum_force, vir, s);
         }
         return;
     }
     launch_message_bwd(F, K, cut, mg, a, force != nullptr, wg, s);
-    if (l == 1 && b.edge_f && !species_sum_on(m, mg, b)) launch_edge_force(mg, b.edge_f, force, vir, s);
+    if (l == 1 && b.edge_f && !species_sum_on(m, mg, b)) launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
     if (wg) {
         const int nb = mp_blocks(n, F);
         const int64_t cnt = int64_t(3) * F * (K + 1);
@@ -770,7 +770,11 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
                  m->px(m->off_Wo), m->wx_stride());
         launch_readout(n, F, m->desc.n_species, b.zo, m->p(m->off_wo), m->p(m->off_beta), sys.species, b.Ei, s, perm);
     }
-    if (energy) launch_rep_sum(sys.n_rep, t.rep_start, n, b.Ei, energy, s);
+    // with the last kernel of the reverse where that is launch_edge_force
+    const RepSum es{energy ? sys.n_rep : 0, t.rep_start, n, b.Ei, energy};
+    b.energy_sum = RepSum{};
+    if (forces && b.edge_f && (L > 1 || species_sum_on(m, mg, b))) b.energy_sum = es;
+    else if (energy) launch_rep_sum(es, s);
     if (!forces) return;
     if (!blocks) {
         launch_readout_bwd(n, F, b.ao, m->p(m->off_wo), b.gs2, s);
@@ -988,7 +992,7 @@ extern "C" nnp_status nnp_cons_virial(const nnp_model* cons, const nnp_system* s
     carve_all(a, m, nullptr, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
     RepGeom g = upload_tables(*sys, c.t, s);
     cons_eval(m, *sys, g, c.t, *nl, c.cons, energy, forces, s, c.cons.vir);
-    launch_rep_sum(sys->n_rep, c.t.rep_start, sys->n_atoms, c.cons.vir, virial, s);
+    launch_rep_sum({sys->n_rep, c.t.rep_start, sys->n_atoms, c.cons.vir, virial}, s);
     NNP_API_END
 }
 
@@ -1006,7 +1010,7 @@ extern "C" nnp_status nnp_nc_virial(const nnp_model* nc, const nnp_system* sys, 
     carve_all(a, nullptr, m, sys->n_atoms, sys->n_rep, std::max<int64_t>(nl->capacity, 1), false, c);
     RepGeom g = upload_tables(*sys, c.t, s);
     nc_eval(m, *sys, g, *nl, c.nc, forces, s, c.nc.vir, nullptr);
-    launch_rep_sum(sys->n_rep, c.t.rep_start, sys->n_atoms, c.nc.vir, virial, s);
+    launch_rep_sum({sys->n_rep, c.t.rep_start, sys->n_atoms, c.nc.vir, virial}, s);
     NNP_API_END
 }
 
@@ -1579,7 +1583,7 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
         launch_baoa(ba, s);
         rebuild_if_flagged();
         eval_cons();
-        if (want_vir) launch_rep_sum(R, c.t.rep_start, n, c.cons.vir, st->virial, s);
+        if (want_vir) launch_rep_sum({R, c.t.rep_start, n, c.cons.vir, st->virial}, s);
         launch_kick(n, st->vel, st->mass, st->f_cons, nullptr, 0.5 * dt, s, c.t.o_step);
         offset += 1;
         st->step += 1;
@@ -1640,7 +1644,7 @@ nnp_status respa_run(const Model* cons, const Model* nc, respa_state* st, const 
         if (ov) adopt_spare();
         if (want_vir) {
             launch_virial_combine(n, c.cons.vir, c.nc.vir, c.nc.vir_sum, float(1.0 / n_in), c.cons.vir_sum, s);
-            launch_rep_sum(R, c.t.rep_start, n, c.cons.vir_sum, st->virial, s);
+            launch_rep_sum({R, c.t.rep_start, n, c.cons.vir_sum, st->virial}, s);
         }
         launch_kick(n, st->vel, st->mass, st->f_cons, st->f_nc, 0.5 * D, s);
         if (rewind) {

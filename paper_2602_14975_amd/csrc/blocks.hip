@@ -126,30 +126,10 @@ __global__ void k_readout_bwd(int n, int F, const float* __restrict__ ao, const 
     gao[t] = wo[t % F] * silu_grad(ao[t]);
 }
 
-// Per-replica float64 sums in a fixed order (one block per replica).
-__global__ void __launch_bounds__(256) k_rep_sum(const int64_t* __restrict__ rep_start, int64_t n,
-                                                 const float* __restrict__ x, double* __restrict__ out) {
+// Per-replica sums, one block per replica.
+__global__ void __launch_bounds__(256) k_rep_sum(RepSum a) {
     __shared__ double red[256];
-    int r = blockIdx.x;
-    const int64_t a0 = rep_start ? rep_start[r] : 0, a1 = rep_start ? rep_start[r + 1] : n;
-    double s = 0.0;
-    int64_t a = a0 + threadIdx.x;
-    // eight loads in flight, added in the same order as one at a time
-    for (; a + 7 * 256 < a1; a += 8 * 256) {
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = x[a + k * 256];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += double(v[k]);
-    }
-    for (; a < a1; a += 256) s += double(x[a]);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[r] = red[0];
+    rep_sum_block(a, blockIdx.x, red);
 }
 
 // Per-species column sums over a chunk of rows, for the adjoints of
@@ -708,8 +688,8 @@ void launch_readout_bwd(int n, int F, const float* ao, const float* wo, float* g
     k_readout_bwd<<<ew_blocks(int64_t(n) * F), 256, 0, st>>>(n, F, ao, wo, gao);
     NNP_LAUNCH_CHECK();
 }
-void launch_rep_sum(int n_rep, const int64_t* rep_start, int64_t n, const float* x, double* out, hipStream_t st) {
-    k_rep_sum<<<n_rep, 256, 0, st>>>(n_rep > 1 ? rep_start : nullptr, n, x, out);
+void launch_rep_sum(const RepSum& a, hipStream_t st) {
+    k_rep_sum<<<a.n_rep, 256, 0, st>>>(a);
     NNP_LAUNCH_CHECK();
 }
 void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,

@@ -267,7 +267,6 @@ void launch_sp_bwd_own(const MpGeom& mg, int S, int pitch, const float* P0, cons
                        hipStream_t s);
 void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, const ScopedTimer& t);
 void launch_message_bwd_mx(const MpGeom& mg, const MpBwd& a, hipStream_t s, const ScopedTimer& t);
-void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, hipStream_t s);
 void launch_filter_scale(int count, const float* Wr, float* out, hipStream_t s);
 // Filter operands of one layer in the order the matrix-core message kernels
 // read them (filter_operand_units() units of 16 bytes), after its scale.
@@ -290,8 +289,42 @@ void launch_norm_bwd(int n, int F, const float* gs, const float* gX, const float
 void launch_readout(int n, int F, int S, const float* z, const float* wo, const float* beta, const int* species, float* Ei,
                     hipStream_t st, const int* perm = nullptr);
 void launch_readout_bwd(int n, int F, const float* ao, const float* wo, float* gao, hipStream_t st);
-// rep_start = nullptr: one replica of n atoms
-void launch_rep_sum(int n_rep, const int64_t* rep_start, int64_t n, const float* x, double* out, hipStream_t st);
+// out[r] = sum of x over the atoms of replica r (rep_start is not read for a
+// single replica, of n atoms)
+struct RepSum {
+    int n_rep = 0;
+    const int64_t* rep_start = nullptr;
+    int64_t n = 0;
+    const float* x = nullptr;
+    double* out = nullptr;
+};
+void launch_rep_sum(const RepSum& a, hipStream_t st);
+// The same by the 256 threads of one block, in a fixed order.
+__device__ __forceinline__ void rep_sum_block(const RepSum& q, int r, double* red) {
+    const int64_t a0 = q.n_rep > 1 ? q.rep_start[r] : 0, a1 = q.n_rep > 1 ? q.rep_start[r + 1] : q.n;
+    double s = 0.0;
+    int64_t a = a0 + threadIdx.x;
+    // eight loads in flight, added in the same order as one at a time
+    for (; a + 7 * 256 < a1; a += 8 * 256) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = q.x[a + k * 256];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += double(v[k]);
+    }
+    for (; a < a1; a += 256) s += double(q.x[a]);
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) q.out[r] = red[0];
+}
+// Forces (and virial shares) from the feature sums of the edges' messages; in
+// the same launch also the per-replica sums `rs` (the energies).
+void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, const RepSum& rs,
+                       hipStream_t s);
 // scratch: cdiv(n, chunk) x S x F floats
 void launch_emb_grad(int n, int F, int S, const int* species, const float* gs0, float* gemb, float* scratch, int chunk,
                      hipStream_t st);

@@ -149,6 +149,7 @@ struct ModelBuf {
     // nullptr: not used in this evaluation
     float* edge_f = nullptr;
     int* edge_key = nullptr;
+    RepSum energy_sum;  // sums that launch_edge_force takes along
     int64_t edge_cap = 0;  // E
     // first layer per species: pre-activation, hidden, phi, and adjoints
     float *h1_tab = nullptr, *z_tab = nullptr, *phi_tab = nullptr, *gphi_tab = nullptr, *gh1_tab = nullptr;

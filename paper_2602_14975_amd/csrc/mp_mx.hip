@@ -1073,11 +1073,19 @@ __global__ void __launch_bounds__(64 * kMxWaves, BLOCKS) k_message_bwd_send(MpGe
 // message it receives along an edge from the neighbour's row (ascending in
 // the caller's index, so found by bisection; its unit vector is the other way
 // round).  Bound by that chain of dependent loads.
+// Blocks past the atoms': the energies of the replicas (as a launch of its
+// own, between the forward and the reverse, 4.6 us).
 template <bool VIR>
 __global__ void __launch_bounds__(256) k_edge_force(MpGeom mg, const float4* __restrict__ edge_f,
-                                                    float* __restrict__ force, float* __restrict__ vir) {
+                                                    float* __restrict__ force, float* __restrict__ vir, RepSum rs) {
+    __shared__ double red[256];
+    const int blocks = gridDim.x - rs.n_rep;
+    if (int(blockIdx.x) >= blocks) {
+        rep_sum_block(rs, blockIdx.x - blocks, red);
+        return;
+    }
     const int lane = threadIdx.x & 63;
-    const int i = xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int i = xcd_block(blockIdx.x, blocks) * 4 + (threadIdx.x >> 6);
     if (i >= mg.n) return;  // whole wavefronts
     const int start = mg.off[i], cnt = mg.ecnt[i];
     const int key = mg.perm ? mg.perm[i] : i;
@@ -1194,14 +1202,16 @@ void launch_message_fwd_mx(const MpGeom& mg, const MpFwd& a, hipStream_t s, cons
     launch_mx(t, k_message_fwd_mx<false>, mg.n, s, mg, a);
 }
 
-void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, hipStream_t s) {
+void launch_edge_force(const MpGeom& mg, const float* edge_f, float* force, float* vir, const RepSum& rs,
+                       hipStream_t s) {
     if (mg.n <= 0) return;
     ScopedTimer t("message_bwd_first", s, true);
     const float4* ef = reinterpret_cast<const float4*>(edge_f);
-    const dim3 grid(cdiv(mg.n, 4)), block(256);
+    const dim3 grid(cdiv(mg.n, 4) + rs.n_rep), block(256);
     auto go = [&](auto kern) {
-        if (t.active && t.by_launch) hipExtLaunchKernelGGL(kern, grid, block, 0, s, t.a, t.b, 0, mg, ef, force, vir);
-        else kern<<<grid, block, 0, s>>>(mg, ef, force, vir);
+        if (t.active && t.by_launch)
+            hipExtLaunchKernelGGL(kern, grid, block, 0, s, t.a, t.b, 0, mg, ef, force, vir, rs);
+        else kern<<<grid, block, 0, s>>>(mg, ef, force, vir, rs);
     };
     if (vir) go(k_edge_force<true>);
     else go(k_edge_force<false>);
