@@ -3,13 +3,12 @@
 // phi perceptron or the readout; reverse: their adjoints), instead of one
 // launch per dense product and elementwise step.
 //
-// A block owns a tile of TA = 32 atoms with four wavefronts, or of 16 with
-// eight.  Every product is
+// A block of eight wavefronts owns a tile of TA = 16 or 32 atoms.  Every
+// product is
 //   out[feature][atom] = sum_k W[feature][k] x[atom][k]
-// on v_mfma_f32_32x32x16_bf16 (TA = 32) or 16x16x32 (TA = 16) with the
-// weights as the first operand, so that a lane of wavefront w holds of one
-// atom the features 32 w + 8 g + 4 h + q (g, q < 4; h = lane / 32), or
-// 16 w + 4 h + q (h = lane / 16), in its accumulators: four consecutive
+// on v_mfma_f32_16x16x32_bf16 with the weights as the first operand, so that
+// a lane of wavefront w holds, of atoms a = lane % 16 and a + 16, the features
+// 16 w + 4 h + q (h = lane / 16, q < 4) in its accumulators: four consecutive
 // features per 16-byte global access, and everything elementwise between the
 // products stays in registers, the same features for all of an atom's
 // quantities.  The inputs of a product pass through LDS as operand
@@ -25,21 +24,25 @@
 // What bounds it: of a block alone on its CU the way of 1 MB of packed weights
 // from L2 (45 bytes a cycle of at most 64) beside 23,000 cycles (32 atoms;
 // half at 16) of matrix instructions per SIMD and the chain from one product
-// to the next; of two blocks on a CU these and the rows from memory.  While a
-// block has a CU to itself, 16 atoms take two thirds of the time of 32 (half
-// the matrix and elementwise work per lane, the same weights), beyond that
-// they read the weights twice as often: see small_tiles.  Eight wavefronts to
-// 16 atoms rather than four, each half the features: two per SIMD hide each
-// other's waits and share what is elementwise (1,536 atoms, middle layer
-// reverse / forward: FP32 22.9 / 21.2 -> 21.5 / 19.6 us, BF16 15.6 / 14.6 ->
-// 13.3 / 12.8; BF16 at 8,192 32 / 33 -> 28 / 31).  As separate
-// launches the same work moved about 40 F floats per atom and layer through
-// memory forward and more in reverse, 28 products and 15 elementwise launches
-// per evaluation; the blocks move 24 F and are six launches.  Measured,
-// dense products and elementwise launches together, per evaluation (3
-// layers, FP32): 12,288 atoms 885 -> 385 us (blocks of 43 to 79 us, the first
-// layer's species products among them); 1,536 atoms 460 -> 119 us (13 to 24
-// us each; 19 to 30 with 32 atoms to a block).
+// to the next.  With two blocks on a CU the rows from memory too: a middle
+// layer moves 204 MB at 12,288 atoms, 43 us at the rate of a copy, of 65
+// (BF16, with a sixth of the matrix work: 42), and the blocks, which start
+// together, load, compute and store at the same times.  While a block has a
+// CU to itself, 16 atoms take two thirds of the time of 32 (half the matrix
+// and elementwise work per lane, the same weights), beyond that they read the
+// weights twice as often: see small_tiles.  Eight wavefronts of 16 features
+// rather than four of 32: two (and with two blocks four) per SIMD hide each
+// other's waits.  Middle layer, reverse / forward, us, four -> eight: tiles of
+// 16, 1,536 atoms FP32 22.9 / 21.2 -> 21.5 / 19.6, BF16 15.6 / 14.6 -> 13.3 /
+// 12.8; tiles of 32 (there on 32x32x16 products, two wavefronts per SIMD),
+// FP32 6,144 41.9 / 42.7 -> 40.4 / 40.6, 12,288 71.8 / 68.4 -> 69.4 / 64.6,
+// BF16 23,700 78.5 / 80.9 -> 75.3 / 75.2.  As separate launches the same work
+// moved about 40 F floats per atom and layer through memory forward and more
+// in reverse, 28 products and 15 elementwise launches per evaluation; the
+// blocks move 24 F and are six launches.  Measured, dense products and
+// elementwise launches together, per evaluation (3 layers, FP32): 12,288
+// atoms 885 -> 378 us (blocks of 43 to 79 us, the first layer's species
+// products among them); 1,536 atoms 460 -> 119 us (13 to 24 us each).
 #include <algorithm>
 #include <numeric>
 
@@ -54,19 +57,15 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kF = 128;
 constexpr int kFrag = 1024;      // bytes of one operand fragment (64 lanes x 16)
-constexpr int kKsF = kF / 16;    // groups of 16 k of one width: a step of a product with TA = 32, half of one
-                                 // with TA = 16
+constexpr int kKsF = kF / 32;    // steps of a product over one width: 32 k each
+constexpr int kW = 8;            // wavefronts of a block
+constexpr int kWF = kF / kW;     // features of a wavefront's slice
 template <int TA>
-constexpr int kW = 128 / TA;  // wavefronts of a block
-template <int TA>
-constexpr int kWF = kF / kW<TA>;  // features of a wavefront's slice
-template <int TA>
-constexpr int kTurn = TA * kWF<TA> * 4;  // bytes of LDS that turn one slice around
+constexpr int kTurn = TA * kWF * 4;  // bytes of LDS that turn one slice around
 template <int TA>
 constexpr int kFragsF = TA * kF / 512;  // operand fragments of one width of the tile's atoms, per piece
 // LDS of a block: three regions, each the fragments of F inputs of its atoms
@@ -76,9 +75,6 @@ template <int NP, int TA>
 constexpr int kRegion = kFragsF<TA> * kFrag * (NP == 1 ? 2 : NP);
 template <int NP, int TA>
 constexpr int kLdsBytes = 3 * kRegion<NP, TA>;
-// Wavefronts per SIMD that the registers must allow: two blocks to a CU
-template <int TA>
-constexpr int kWaves = TA == 32 ? 2 : 4;
 
 // Four floats as NP bfloat16 pieces (round to nearest of what the previous
 // pieces leave), two packed words per piece.
@@ -96,32 +92,25 @@ __device__ __forceinline__ void split4(const f32x4_t& x, uint2 (&o)[NP]) {
     }
 }
 
-// A lane's values of one slice (32 or 16 features): element 4 g + q = feature
-// kWF w + 4 H g + 4 h + q of its atom, H = 64 / TA lanes to an atom.
+// A lane's values of one slice of 16 features: element 4 g + q = feature
+// 16 w + 4 h + q of atom a + 16 g.
 template <int TA>
 struct Slice {
-    static constexpr int H = 64 / TA, G = kWF<TA> / (4 * H);
+    static constexpr int G = TA / 16;
     f32x4_t v[G];
     __device__ __forceinline__ float operator[](int i) const { return v[i >> 2][i & 3]; }
 };
 
-// The sums of one slice of a product, element by element those of Slice: one
-// 32 x 32 or 16 x 16 result.
+// The sums of one slice of a product, element by element those of Slice
 template <int TA>
-struct Sums;
-template <>
-struct Sums<32> {
-    floatx16 c = {};
-    __device__ __forceinline__ float operator[](int e) const { return c[e]; }
-    __device__ __forceinline__ void set(int e, float x) { c[e] = x; }
-    __device__ __forceinline__ void add(const Sums& o) { c += o.c; }
-};
-template <>
-struct Sums<16> {
-    f32x4_t c = {};
-    __device__ __forceinline__ float operator[](int e) const { return c[e]; }
-    __device__ __forceinline__ void set(int e, float x) { c[e] = x; }
-    __device__ __forceinline__ void add(const Sums& o) { c += o.c; }
+struct Sums {
+    static constexpr int G = TA / 16;
+    f32x4_t c[G] = {};
+    __device__ __forceinline__ float operator[](int e) const { return c[e >> 2][e & 3]; }
+    __device__ __forceinline__ void add(const Sums& o) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) c[g] += o.c[g];
+    }
 };
 
 // Global memory through buffer descriptors: a uniform base, a uniform offset
@@ -150,16 +139,12 @@ struct Lane {
     int lane, w, a, h;
     int64_t t0;  // first atom of the block's tile
     int rows;    // atoms of the tile
-    int i;       // this lane's atom
-    bool on;
     __device__ __forceinline__ Lane(int n) {
         lane = threadIdx.x & 63;
         w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        a = lane % TA;
-        h = lane / TA;
+        a = lane & 15;
+        h = lane >> 4;
         t0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * TA;
-        i = int(t0) + a;
-        on = i < n;
         rows = min(TA, n - int(t0));
     }
 };
@@ -169,32 +154,31 @@ struct Lane {
 template <int C, int ld, int TA>
 __device__ __forceinline__ Slice<TA> load_slice(const float* p, int c, int c0, const Lane<TA>& L) {
     const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
-    const uint32_t lo = uint32_t(L.a * (C * ld * 4) + 16 * L.h), o = uint32_t((c * ld + c0 + kWF<TA> * L.w) * 4);
+    const uint32_t lo = uint32_t(L.a * (C * ld * 4) + 16 * L.h), o = uint32_t((c * ld + c0 + kWF * L.w) * 4);
     Slice<TA> s;
 #pragma unroll
-    for (int g = 0; g < s.G; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + 16 * s.H * g));
+    for (int g = 0; g < s.G; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + g * (16 * C * ld * 4)));
     return s;
 }
 // The slice into row-major rows, turned around through kTurn bytes of LDS
-// (`turn`, this wavefront's own) so that the lanes of a row write its 128 or
-// 64 bytes together: written as held, 16 bytes per lane and row, a store took
+// (`turn`, this wavefront's own) so that four lanes write the 64 bytes of a
+// row together: written as held, 16 bytes per lane and row, a store took
 // about 100 cycles and the stores a third of the kernel.
 template <int C, int ld, int TA>
 __device__ __forceinline__ void store_slice(float* p, int c, int c0, const Lane<TA>& L, const Slice<TA>& s,
                                             char* turn) {
-    constexpr int Q = kWF<TA> / 4, R = 64 / Q;  // lanes of a row, rows at a time
     const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
     wave_sync_lds();
 #pragma unroll
     for (int g = 0; g < s.G; ++g)
-        *reinterpret_cast<f32x4_t*>(turn + L.a * (16 * Q) + ((s.H * g + L.h) ^ (L.a & (Q - 1))) * 16) = s.v[g];
+        *reinterpret_cast<f32x4_t*>(turn + (16 * g + L.a) * 64 + (L.h ^ (L.a & 3)) * 16) = s.v[g];
     wave_sync_lds();
-    const int row = L.lane / Q, q = L.lane % Q;
-    const uint32_t lo = uint32_t(row * (C * ld * 4) + 16 * q + (c * ld + c0 + kWF<TA> * L.w) * 4);
+    const int row = L.lane >> 2, q = L.lane & 3;
+    const uint32_t lo = uint32_t(row * (C * ld * 4) + 16 * q + (c * ld + c0 + kWF * L.w) * 4);
 #pragma unroll
-    for (int k = 0; k < TA / R; ++k)  // rows R k + row: the same swizzle
-        b.store(*reinterpret_cast<const u32x4_t*>(turn + (R * k + row) * (16 * Q) + (q ^ (row & (Q - 1))) * 16),
-                lo + R * k * (C * ld * 4));
+    for (int g = 0; g < s.G; ++g)
+        b.store(*reinterpret_cast<const u32x4_t*>(turn + (16 * g + row) * 64 + (q ^ (row & 3)) * 16),
+                lo + g * (16 * C * ld * 4));
 }
 // Quantities that only these kernels exchange are kept in lane order: slice
 // `c` (of C) of the tile's wavefront w, 1 KB per group of four features.
@@ -204,7 +188,7 @@ __device__ __forceinline__ void keep_slice(float* p, int c, const Lane<TA>& L, c
     const Buf b(p + L.t0 * (C * kF), uint32_t(TA * C * kF * 4));
 #pragma unroll
     for (int g = 0; g < s.G; ++g)
-        b.store(__builtin_bit_cast(u32x4_t, s.v[g]), uint32_t(16 * L.lane + ((c * kW<TA> + L.w) * s.G + g) * 1024));
+        b.store(__builtin_bit_cast(u32x4_t, s.v[g]), uint32_t(16 * L.lane + ((c * kW + L.w) * s.G + g) * 1024));
 }
 template <int C, int TA>
 __device__ __forceinline__ Slice<TA> kept_slice(const float* p, int c, const Lane<TA>& L) {
@@ -212,7 +196,7 @@ __device__ __forceinline__ Slice<TA> kept_slice(const float* p, int c, const Lan
     Slice<TA> s;
 #pragma unroll
     for (int g = 0; g < s.G; ++g)
-        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.lane, uint32_t(((c * kW<TA> + L.w) * s.G + g) * 1024)));
+        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.lane, uint32_t(((c * kW + L.w) * s.G + g) * 1024)));
     return s;
 }
 // kF per-feature constants (biases)
@@ -220,91 +204,74 @@ template <int TA>
 __device__ __forceinline__ Slice<TA> load_feat(const float* p, const Lane<TA>& L) {
     const Buf b(p, kF * 4);
     Slice<TA> s;
+    s.v[0] = __builtin_bit_cast(f32x4_t, b.load(16 * L.h, uint32_t(4 * kWF * L.w)));
 #pragma unroll
-    for (int g = 0; g < s.G; ++g)
-        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(16 * L.h, uint32_t(4 * kWF<TA> * L.w + 16 * s.H * g)));
+    for (int g = 1; g < s.G; ++g) s.v[g] = s.v[0];
     return s;
 }
 
-// The slice as operand fragments.  32 features v (of wavefront v, or of 2 v
-// and 2 v + 1) are four groups of eight k, G0..G3; the products of a sum are
-// chained in the order of k_gemm_x3, (G0 G2) (G1 G3) of one 32 after the
-// other:
-//   TA = 32: steps 2 v and 2 v + 1 hold (G0 G2) and (G1 G3), one half each;
-//   TA = 16: fragment v holds G0 G2 G1 G3 in its quarters: one 16x16x32
-//     product gives the bits of the two 32x32x16 ones chained (measured on
-//     random operands: no result differs; any other order of the quarters
-//     does).  With `two` (BF16 models, sums of odd steps apart) fragments
-//     2 u and 2 u + 1 hold (G0 G2) and (G1 G3) of the features 2 u and 2 u + 1.
-// `at`: first fragment at `buf` (widths before this one).
+// The slice as operand fragments.  The 32 features v of wavefronts 2 v and
+// 2 v + 1 are four groups of eight k, G0..G3; the products of a sum are
+// chained in the order of k_gemm_x3, 32x32x16 products with (G0 G2) and then
+// (G1 G3).  Fragment v holds G0 G2 G1 G3 in its quarters: one 16x16x32
+// product gives the bits of those two chained (measured on random operands:
+// no result differs; any other order of the quarters does).  With `two` (BF16
+// models, sums of odd steps apart) fragments 2 u and 2 u + 1 hold (G0 G2) and
+// (G1 G3) of the features 2 u and 2 u + 1.  `at`: first fragment at `buf`
+// (widths before this one); the atoms a + 16 g of a fragment follow each
+// other.
 template <int NP, int TA>
 __device__ __forceinline__ void put_slice(char* buf, int at, const Lane<TA>& L, const Slice<TA>& s, bool two) {
     const bool apart = NP == 1 && two;
+    const int v = L.w >> 1, odd = L.w & 1, half = L.h >> 1;  // group 2 odd + half of v
+    const int frag = at + (apart ? (v & 2) + half : v);
+    const int unit = (apart ? 2 * (v & 1) + odd : 2 * half + odd) * 16 + L.a;
+    char* d = buf + frag * (s.G * NP * kFrag) + unit * 16 + 8 * (L.h & 1);
 #pragma unroll
     for (int g = 0; g < s.G; ++g) {
         uint2 o[NP];
         split4<NP>(s.v[g], o);
-        int frag, unit;
-        if (TA == 32) {
-            frag = 2 * L.w + (g & 1);
-            unit = (g >> 1) * 32 + L.a;
-        } else {
-            const int v = L.w >> 1, odd = L.w & 1, half = L.h >> 1;  // group 2 odd + half of v
-            frag = apart ? (v & 2) + half : v;
-            unit = (apart ? 2 * (v & 1) + odd : 2 * half + odd) * 16 + L.a;
-        }
-        char* d = buf + (at + frag) * (NP * kFrag) + unit * 16 + 8 * (L.h & 1);
 #pragma unroll
-        for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2*>(d + p * kFrag) = o[p];
+        for (int p = 0; p < NP; ++p) *reinterpret_cast<uint2*>(d + (g * NP + p) * kFrag) = o[p];
     }
 }
 
 // Packed weights of one matrix [N][K] (launch_pack_frags): piece p, 16-byte
 // unit ((n / 16) K/8 + k / 8) 16 + n % 16 holds W[n][8 (k/8) .. + 7].
-// A ring of D steps of the fragments of NT slices of kWF rows.  TA = 32: step
-// f is 16 k of every slice; TA = 16: 32 k of slice f % NT (a ring of whole
-// steps of three slices does not fit 128 registers: at 4,800 atoms, where two
-// blocks share CUs, the kernels took 41.7 us instead of 39.1).  The k of both
-// as in put_slice.
+// A ring of D steps of the fragments of NT slices of 16 rows: step f is 32 k,
+// those of put_slice, of slice f % NT (a ring of whole steps of three slices
+// does not fit 128 registers: at 4,800 atoms, where two blocks share CUs, the
+// kernels took 41.7 us instead of 39.1).
 template <int NP, int NT, int KS, int D, int TA>
 struct Weights {
-    static constexpr uint32_t kRow = 32 * kWF<TA> * KS;  // bytes of a slice per piece
-    static constexpr int TS = TA == 32 ? NT : 1, XS = NT / TS;  // slices of a step; steps with the same k
+    static constexpr uint32_t kRow = 64 * kWF * KS;  // bytes of a slice per piece
     Buf b;
     uint32_t ps, off, step, lo;  // bytes: piece, first slice, slice step; lane
     bool apart;
-    bf16x8_t r[D][TS][NP];
-    // mat: the matrix's pieces, N its rows; slices t0, t0 + step, ...
+    bf16x8_t r[D][NP];
+    // mat: the matrix's pieces, N its rows; slices t0, t0 + st, ...
     __device__ __forceinline__ Weights(const uint16_t* mat, int N, int t0, int st, const Lane<TA>& L, bool two)
-        : b(mat, uint32_t(N) * (KS * 32 * NP)), ps(uint32_t(N) * (KS * 32)), off(t0 * kRow), step(st * kRow),
+        : b(mat, uint32_t(N) * (KS * 64 * NP)), ps(uint32_t(N) * (KS * 64)), off(t0 * kRow), step(st * kRow),
           apart(NP == 1 && two) {
-        if (TA == 32) {
-            lo = uint32_t(((L.a >> 4) * 2 * KS + 2 * L.h) * 16 + (L.a & 15)) * 16u;
-        } else {
-            const int q = L.h;  // quarter of the fragment
-            lo = uint32_t((apart ? 4 * (q >> 1) + 2 * (q & 1) : 2 * (q & 1) + (q >> 1)) * 16 + L.a) * 16u;
-        }
+        const int q = L.h;  // quarter of the fragment
+        lo = uint32_t((apart ? 4 * (q >> 1) + 2 * (q & 1) : 2 * (q & 1) + (q >> 1)) * 16 + L.a) * 16u;
 #pragma unroll
         for (int d = 0; d < D - 1; ++d) load(d, d);
     }
     // step f into ring slot d (past the last step: unused data, bounded by
     // the descriptor)
     __device__ __forceinline__ void load(int f, int d) {
-        const int ks = f / XS;
-        uint32_t at;
-        if (TA == 32) at = (ks >> 1) * 1024 + (ks & 1) * 256;
-        else at = apart ? (ks >> 1) * 2048 + (ks & 1) * 256 : ks * 1024;
+        const int ks = f / NT;
+        const uint32_t at = apart ? (ks >> 1) * 2048 + (ks & 1) * 256 : ks * 1024;
 #pragma unroll
-        for (int t = 0; t < TS; ++t)
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-                r[d][t][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + (f % XS + t) * step + p * ps + at));
+        for (int p = 0; p < NP; ++p)
+            r[d][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + (f % NT) * step + p * ps + at));
     }
 };
 
-// Steps of weights held: with 16 atoms what 128 registers leave room for
+// Steps of weights held: what 128 registers leave room for
 template <int NP, int NT, int TA>
-constexpr int kDepth = TA == 32 ? (NT == 1 ? 4 : 2) : NP == 1 ? 4 * NT : NT == 2 ? 2 : 4;
+constexpr int kDepth = NP == 1 ? 4 * NT : NT == 2 ? 2 : TA == 16 ? 4 : 2;
 
 // acc[t][b] += W_t x_b over all steps; x_b's fragments at buf + b * stride.
 // The loads of step f + D - 1 are issued before the products of f and held
@@ -312,7 +279,7 @@ constexpr int kDepth = TA == 32 ? (NT == 1 ? 4 : 2) : NP == 1 ? 4 * NT : NT == 2
 // waits for L2 at every step).  A loop over turns of a few steps rather than
 // straight-line code: a block walks through its code once, so that code is
 // fetched as slowly as data.
-// KN: groups of 16 k taken (the first of the matrix's KS).
+// KN: steps of 32 k taken (the first of the matrix's KS).
 //
 // FP32 models: where registers allow, the products of the leading pieces are
 // summed apart from the five small ones (in `sep`, added by the caller's
@@ -328,50 +295,60 @@ template <int NP, int NT, int NB, int KN, int KS, int D, int TA>
 __device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Sums<TA> (&sep)[NT][NB],
                                         Weights<NP, NT, KS, D, TA>& W, const char* buf, int stride,
                                         const Lane<TA>& L) {
-    constexpr int XS = Weights<NP, NT, KS, D, TA>::XS, TS = NT / XS;
-    constexpr int S = KN * TA / 32 * XS;  // steps taken
-    constexpr int XD = NB == 1 ? 2 : 1;   // fragments of x held
-    constexpr int R = std::lcm(D, XD * XS);  // steps of a turn: whole rings of weights and of x
+    constexpr int G = Sums<TA>::G;
+    constexpr int S = KN * NT;                      // steps taken
+    // Fragments of x held: with 16 atoms those of all b (and of the next step
+    // where there is one b); with 32 atoms one, or with one b the two of an
+    // atom pair in turn: more do not fit (the reverse spilled 10 registers).
+    constexpr int XD = NB == 1 ? 2 : 1, XB = G > 1 ? 1 : NB;
+    constexpr int R0 = std::lcm(D, G > 1 ? NT : XD * NT);  // steps of a turn: whole rings of weights and of x,
+    constexpr int R = R0 / NT % 2 ? 2 * R0 : R0;           // an even number of k steps
     static_assert(S % R == 0 && KN <= KS, "whole rings");
     const char* bl = buf + L.lane * 16;
-    bf16x8_t x[XD][NB][NP];
-    auto load_x = [&](int k, int d) {
+    bf16x8_t x[XD][XB][NP];
+    auto load_x = [&](int k, int u, int d) {  // u: the step's b and g (16 atoms: all b)
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < XB; ++b)
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                x[d][b][p] = *reinterpret_cast<const bf16x8_t*>(bl + b * stride + (k * NP + p) * kFrag);
+                x[d][b][p] = *reinterpret_cast<const bf16x8_t*>(
+                    bl + (b + u / G) * stride + ((k * G + u % G) * NP + p) * kFrag);
     };
-    if (XD == 2) load_x(0, 0);
+    if (XD == 2) load_x(0, 0, 0);
     auto step = [&](int f, int d, Sums<TA>(&c)[NT][NB]) {
         W.load(f + D - 1, (d + D - 1) % D);
-        if (d % XS == 0) {
-            if (XD == 1) load_x(f / XS, 0);
-            else load_x(min(f / XS + 1, S / XS - 1), (d / XS + 1) % 2);
-        }
-        __builtin_amdgcn_sched_barrier(0);
         const auto& w = W.r[d % D];
-        const auto& y = x[(d / XS) % XD];
-        auto term = [&](Sums<TA>(&to)[NT][NB], int px, int pw) {
+        const int t = d % NT;
+        // the product of the pieces px of x and pw of w
+        auto term = [&](Sums<TA>(&to)[NT][NB], int u, int px, int pw) {
 #pragma unroll
-            for (int t = 0; t < TS; ++t)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    auto& o = to[d % XS + t][b].c;
-                    if constexpr (TA == 32) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t][pw], y[b][px], o, 0, 0, 0);
-                    else o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][pw], y[b][px], o, 0, 0, 0);
-                }
+            for (int b = 0; b < XB; ++b) {
+                auto& o = to[t][b + u / G].c[u % G];
+                o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[pw], x[(G > 1 ? u : d / NT) % XD][b][px], o, 0, 0, 0);
+            }
         };
-        if constexpr (NP == 3) {
-            auto& small = kApart<NP, NT, NB, TA> ? sep : c;
-            term(small, 2, 0);
-            term(small, 0, 2);
-            term(small, 1, 1);
-            term(small, 1, 0);
-            term(small, 0, 1);
+#pragma unroll
+        for (int u = 0; u < G * (NB / XB); ++u) {
+            if (G > 1) {
+                const bool last = u + 1 == G * NB;
+                if (XD == 1) load_x(f / NT, u, 0);
+                else load_x(last ? min((f + 1) / NT, KN - 1) : f / NT, last ? 0 : u + 1, (u + 1) % 2);
+            } else if (t == 0) {
+                if (XD == 1) load_x(f / NT, 0, 0);
+                else load_x(min(f / NT + 1, KN - 1), 0, (d / NT + 1) % 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NP == 3) {
+                auto& small = kApart<NP, NT, NB, TA> ? sep : c;
+                term(small, u, 2, 0);
+                term(small, u, 0, 2);
+                term(small, u, 1, 1);
+                term(small, u, 1, 0);
+                term(small, u, 0, 1);
+            }
+            term(c, u, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        term(c, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
     };
     if (NP == 3 || !W.apart) {
 #pragma unroll 1
@@ -382,7 +359,7 @@ __device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Sums<TA> (&sep)
 #pragma unroll 1
         for (int k0 = 0; k0 < S; k0 += R)
 #pragma unroll
-            for (int d = 0; d < R; ++d) step(k0 + d, d, (d / XS) % 2 ? sep : acc);
+            for (int d = 0; d < R; ++d) step(k0 + d, d, (d / NT) % 2 ? sep : acc);
     }
 }
 
@@ -440,12 +417,14 @@ __device__ __forceinline__ Slice<TA> added(const Sums<TA>& c, const Slice<TA>& b
 // Kept for the reverse: U v and V v, the M1 pre-activation, q and o (LAST: q
 // alone), the W1 pre-activation.
 template <int NP, int TA, bool LAST, bool FIRST>
-__global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A) {
+__global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
     extern __shared__ __align__(16) char lds[];
-    __shared__ float epart[LAST ? 4 : 1][TA], ehalf[LAST && TA == 16 ? 8 : 1][TA];
-    constexpr int CB = kRegion<NP, TA>, FF = kFragsF<TA>, E = 4 * Slice<TA>::G;
+    __shared__ float epart[LAST ? 4 : 1][TA], ehalf[LAST ? 8 : 1][TA];
+    constexpr int CB = kRegion<NP, TA>, E = 4 * Slice<TA>::G;
     const Lane<TA> L(A.n);
-    const bool two_uv = two_sums(3 * int64_t(A.n), 2 * kF), two_3 = two_sums(A.n, 3 * kF), two_1 = two_sums(A.n, kF);
+    // (tiles of 32 are for sizes where k_gemm_x3 had one sum in the first two)
+    const bool two_uv = TA == 16 && two_sums(3 * int64_t(A.n), 2 * kF);
+    const bool two_3 = TA == 16 && two_sums(A.n, 3 * kF), two_1 = two_sums(A.n, kF);
     // free while the rows of s and v (turn) and the outputs (turn2) are written
     char* turn = lds + CB + L.w * kTurn<TA>;
     char* turn2 = lds + 2 * CB + L.w * kTurn<TA>;
@@ -488,7 +467,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
     // U v, V v: slices w of U and of V, of the adjacent matrices
     Sums<TA> uv[2][3];
     {
-        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.U, 2 * kF, L.w, kW<TA>, L, two_uv);
+        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.U, 2 * kF, L.w, kW, L, two_uv);
         __syncthreads();
         product<NP, 2, 3, kKsF>(uv, W, lds, CB, L);
     }
@@ -519,7 +498,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
         Weights<NP, 1, 2 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M1, kF, L.w, 1, L, true);
         __syncthreads();  // the vector fragments are read
         put_slice<NP>(lds, 0, L, s0, true);
-        put_slice<NP>(lds, FF, L, nrm, true);
+        put_slice<NP>(lds, kKsF, L, nrm, true);
         __syncthreads();
         product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L);
         const Slice<TA> a1 = added(acc[0][0], load_feat(A.m1, L));
@@ -534,7 +513,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
     Slice<TA> v1[3];
     {
         Sums<TA> acc[NQ][1];
-        Weights<NP, NQ, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, kW<TA>, L, two_3);
+        Weights<NP, NQ, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, kW, L, two_3);
         __syncthreads();
         product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L);
         Slice<TA> h[NQ];
@@ -572,7 +551,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
         for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
         put_slice<NP>(lds + CB, 0, L, z, two_3);
         Sums<TA> acc[3][1];
-        Weights<NP, 3, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, kW<TA>, L, two_3);
+        Weights<NP, 3, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, kW, L, two_3);
         __syncthreads();
         product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L);
 #pragma unroll
@@ -599,41 +578,45 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
             y.v[e >> 2][e & 3] = silu(h1[e]);
             z.v[e >> 2][e & 3] = wo[e] * silu_grad(h1[e]);
         }
-        // The sum over 32 features in one order for both tiles: the groups
-        // of four 0, 2, 4, 6 and 1, 3, 5, 7, then the two sums.  With 16
-        // atoms groups 0 to 3 are in the four lanes of an atom of an even
-        // wavefront and 4 to 7 in those of the next one, which takes the two
-        // sums over and goes on.
-        auto group_sum = [&](float e0, int g) {
+        // The sum over 32 features: the groups of four 0, 2, 4, 6 and 1, 3,
+        // 5, 7, then the two sums.  Groups 0 to 3 are in the four lanes of an
+        // atom of an even wavefront and 4 to 7 in those of the next one,
+        // which takes the two sums over and goes on.
+        auto pair_sum = [&](float e0, int g) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) e0 = fmaf(wo.v[g][q], y.v[g][q], e0);
+            for (int r = 0; r < 2; ++r) {
+                if (r) e0 = __shfl_xor(e0, 32, 64);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e0 = fmaf(wo.v[g][q], y.v[g][q], e0);
+            }
             return e0;
         };
-        float e0 = 0.f;
-        if constexpr (TA == 32) {
+        if (!(L.w & 1)) {
 #pragma unroll
-            for (int g = 0; g < E / 4; ++g) e0 = group_sum(e0, g);
-            e0 += __shfl_xor(e0, 32, 64);
-            if (L.h == 0) epart[L.w][L.a] = e0;
-        } else {
-            e0 = group_sum(__shfl_xor(group_sum(0.f, 0), 32, 64), 0);
-            if (!(L.w & 1) && L.h >= 2) ehalf[L.w + L.h - 2][L.a] = e0;
+            for (int g = 0; g < E / 4; ++g) {
+                const float e0 = pair_sum(0.f, g);
+                if (L.h >= 2) ehalf[L.w + L.h - 2][16 * g + L.a] = e0;
+            }
         }
         put_slice<NP>(lds + CB, 0, L, z, two_1);
         Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W2(A.W2, kF, L.w, 1, L, two_1);
         __syncthreads();
-        if (TA == 16 && (L.w & 1)) {
-            e0 = group_sum(__shfl_xor(group_sum(ehalf[L.w - 1 + (L.h & 1)][L.a], 0), 32, 64), 0);
-            e0 += __shfl_xor(e0, 16, 64);
-            if (L.h == 2) epart[L.w >> 1][L.a] = e0;
+        if (L.w & 1) {
+#pragma unroll
+            for (int g = 0; g < E / 4; ++g) {
+                float e0 = pair_sum(ehalf[L.w - 1 + (L.h & 1)][16 * g + L.a], g);
+                e0 += __shfl_xor(e0, 16, 64);
+                if (L.h == 2) epart[L.w >> 1][16 * g + L.a] = e0;
+            }
         }
         Sums<TA> acc[1][1];
         product<NP, 1, 1, kKsF>(acc, W2, lds + CB, 0, L);
-        if (TA == 16) __syncthreads();
-        if (L.w == 0 && L.h == 0 && L.on) {
-            const int io = A.perm ? min(max(A.perm[L.i], 0), A.n - 1) : L.i;
-            const float sum = (epart[0][L.a] + epart[1][L.a]) + (epart[2][L.a] + epart[3][L.a]);
-            A.Ei[io] = sum + A.beta[min(max(A.species[L.i], 0), A.n_species - 1)];
+        __syncthreads();
+        const int r = L.lane, i = int(L.t0) + r;
+        if (L.w == 0 && r < L.rows) {
+            const int io = A.perm ? min(max(A.perm[i], 0), A.n - 1) : i;
+            const float sum = (epart[0][r] + epart[1][r]) + (epart[2][r] + epart[3][r]);
+            A.Ei[io] = sum + A.beta[min(max(A.species[i], 0), A.n_species - 1)];
         }
         store_slice<1, kF>(A.s_out, 0, 0, L, as_slice(acc[0][0]), turn2);
     }
@@ -649,9 +632,9 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_fwd(AtomFwd A)
 //   BOTTOM (with FIRST): instead of gs_out and gv_out the rows P_0 and P_2 (128
 //   slots, the first pp used) that k_sp_bwd_own takes (keep: room for g_s).
 template <int NP, int TA, bool TOP, bool BOTTOM>
-__global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A) {
+__global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
     extern __shared__ __align__(16) char lds[];
-    constexpr int CB = kRegion<NP, TA>, FF = kFragsF<TA>, E = 4 * Slice<TA>::G;
+    constexpr int CB = kRegion<NP, TA>, E = 4 * Slice<TA>::G;
     const Lane<TA> L(A.n);
     const bool two_1 = two_sums(A.n, kF), two_2 = two_sums(A.n, 2 * kF);
     char* turn = lds + CB + L.w * kTurn<TA>;
@@ -661,7 +644,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A)
         const Slice<TA> h1 = kept_slice<1>(A.h1, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            put_slice<NP>(lds, c * FF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L), true);
+            put_slice<NP>(lds, c * kKsF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L), true);
         __syncthreads();
         Sums<TA> acc[1][1];
         product<NP, 1, 1, 3 * kKsF>(acc, W, lds, 0, L);
@@ -704,8 +687,8 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A)
         for (int g = 0; g < E / 4; ++g) dot.v[g] = gs.v[g] * dot.v[g];
         if constexpr (!TOP) __syncthreads();  // W1's input is read
         put_slice<NP>(lds, 0, L, gs, true);
-        put_slice<NP>(lds, FF, L, dot, true);
-        if constexpr (!TOP) put_slice<NP>(lds, 2 * FF, L, go, true);
+        put_slice<NP>(lds, kKsF, L, dot, true);
+        if constexpr (!TOP) put_slice<NP>(lds, 2 * kKsF, L, go, true);
         const Slice<TA> a1 = kept_slice<1>(A.a1, 0, L);
         __syncthreads();
         Sums<TA> acc[1][1];
@@ -716,7 +699,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A)
     // M1^T: adjoints of s (added to gs) and of |V v|
     Slice<TA> gn;
     {
-        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.M1t, 2 * kF, L.w, kW<TA>, L, two_2);
+        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.M1t, 2 * kF, L.w, kW, L, two_2);
         __syncthreads();
         put_slice<NP>(lds, 0, L, dot, two_2);
         __syncthreads();
@@ -739,6 +722,10 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A)
             const Slice<TA> v = kept_slice<6>(A.UV, 2 * c + 1, L);
             Slice<TA> t;
             if (m == 0) {
+                if constexpr (!TOP && TA == 32) {  // read again rather than held over the products
+                    gv[c] = load_slice<3, kF>(A.gv_in, c, 0, L);
+                    if (c == 0) o = kept_slice<3>(A.pqo, 2, L);
+                }
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     nn.v[e >> 2][e & 3] = fmaf(v[e], v[e], c ? nn[e] : 1e-8f);
@@ -770,7 +757,7 @@ __global__ void __launch_bounds__(64 * kW<TA>, kWaves<TA>) k_atom_bwd(AtomBwd A)
     } else {
         // P_2 = T_2^T g_v, then P_0 = T_0^T g_s; wavefront w has the slots
         // kWF w .. of the pp ones
-        const bool on = kWF<TA> * L.w < A.pp;
+        const bool on = kWF * L.w < A.pp;
 #pragma unroll
         for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, gvo[c], false);
         {
@@ -820,7 +807,7 @@ __global__ void __launch_bounds__(256) k_pack_frags(PackFrags P, int np) {
 
 template <int NP, int TA, typename K, typename Args>
 void launch_block(K kern, const Args& a, hipStream_t s) {
-    kern<<<cdiv(a.n, TA), 64 * kW<TA>, kLdsBytes<NP, TA>, s>>>(a);
+    kern<<<cdiv(a.n, TA), 64 * kW, kLdsBytes<NP, TA>, s>>>(a);
     NNP_LAUNCH_CHECK();
 }
 
@@ -833,13 +820,13 @@ void raise_lds(K kern) {
 }
 
 // 16 atoms to a block or 32.  Measured (reverse / forward of a middle layer,
-// us): FP32, 1,536 atoms 21.7 / 19.6 with 16 against 30.5 / 27.7 with 32;
-// 4,096: 27 / 26 against 33 / 31; 5,121: 39 / 38 against 39 / 38; 6,144:
-// 41 / 43 against 41 / 42; 12,288: 72 / 75 against 69 / 69.  BF16, a third of
-// the weights: 1,536 13.3 / 12.8 against 21.8 / 20.3; 8,192 28 / 31 against
-// 39 / 38; median over an evaluation's blocks 38.5 against 40.6 at 10,200,
-// 41.9 against 43.1 at 12,288, 77.2 against 77.3 at 23,700 and 147.5 against
-// 141.8 at 48,000.  BF16 results are the same bits
+// us): FP32, 1,536 atoms 21.7 / 19.6 with 16 against 30 / 27 with 32; 4,096:
+// 27 / 26 against 32 / 30; 5,121: 39 / 38 with 16, 5,421: 39 / 37 with 32;
+// 6,144: 41 / 43 against 40 / 41; 12,288: 72 / 75 against 69 / 65.  BF16, a
+// third of the weights: 1,536 13.3 / 12.8 against 21 / 20; 8,192 28 / 31
+// against 38 / 36; over an evaluation's blocks 11,100 39 / 41 against 44 / 41,
+// 12,288 41.5 / 43.6 against 45.2 / 41.7, 23,700 77 against 72 and 48,000
+// 148 against 135.  BF16 results are the same bits
 // with both.  FP32 ones are not (the order of the six piece products): they
 // change tiles where k_gemm_x3 changed its number of sums for the widest of
 // these products, close to where the two are equal, so that replicas give the
