@@ -214,7 +214,7 @@ def measured_traffic():
     (two rocprofv3 --pmc passes, calibrated on a plain copy), or None when
     the kernel sources changed after the counters were taken."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "message_bwd_mx_water12288_traffic.md")
+    path = os.path.join(ROOT, "profiles", "message_bwd_water12288_traffic.md")
     try:
         text = open(path).read()
     except OSError:
@@ -513,7 +513,7 @@ def main():
     roof, kernels = None, {}
     if kt.get("message_bwd", (0, 0))[1] > 0:
         flops, nbytes = message_counts(F, K, s.n, g["n_edges5"], reverse=True)
-        roof = roofline_entry("k_message_bwd_mx (conservative message reverse, layers 2-3, F=128, K=16, "
+        roof = roofline_entry("k_message_bwd_send (conservative message reverse, layers 2-3, F=128, K=16, "
                               "cosine cutoff)",
                               *kt["message_bwd"], flops, nbytes, measured_traffic())
     if kt.get("message_fwd", (0, 0))[1] > 0:

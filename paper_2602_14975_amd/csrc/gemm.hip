@@ -3,8 +3,9 @@
 // C(m, n) = epi( sum_k A(m, k) B(k, n) + bias(n) ) with strided operands.
 // Two kernel families:
 //  * k_gemm_x3 (the products X W^T of the force evaluation with K of 128 or
-//    256 that are not part of the per-atom blocks): bfloat16 matrix cores, FP32 models through operands split into
-//    three bfloat16 pieces, BF16 models through rounded operands;
+//    256 that are not part of the per-atom blocks): bfloat16 matrix cores,
+//    FP32 models through operands split into three bfloat16 pieces, BF16
+//    models through rounded operands;
 //  * k_gemm / k_gemm_rk (other shapes, the weight adjoints G^T X by chunks
 //    of rows, and everything when the older kernels are selected): float32
 //    (or bfloat16-rounded) operands on the matrix cores, LDS-staged 64 x 64

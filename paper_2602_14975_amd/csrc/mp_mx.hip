@@ -21,10 +21,12 @@
 // pairs.
 //
 // Message kernels: blocks take one or two atoms in turn with four wavefronts,
-// one per block of 32 features, which share the staged edges.  The reverse is
-// bound by its vector arithmetic (34 operations per edge and feature, 59 % of
-// its time at 12,288 atoms) and by the rows it gathers through L1 (9 loads
-// per edge and feature, about half of it), the forward by the gathers; what
+// one per block of 32 features, which share the staged edges.  The reverse by
+// both messages of a pair (BF16 models; FP32 ones: one message of each edge,
+// below) is bound by its vector arithmetic (34 operations per edge and
+// feature, 59 % of its time at 12,288 atoms) and by the rows it gathers
+// through L1 (9 loads per edge and feature, about half of it), the forward by
+// the gathers; what
 // remains is the chain product -> gather -> sums of a batch with three
 // wavefronts per SIMD to hide it.  Held out of that chain: the filter operands
 // (laid out with the weights, in LDS during the kernel), the list rows of the
