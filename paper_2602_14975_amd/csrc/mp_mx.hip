@@ -31,8 +31,8 @@
 // wavefronts per SIMD to hide it.  Held out of that chain: the filter operands
 // (laid out with the weights, in LDS during the kernel), the list rows of the
 // block's atoms (in registers), the sums over lanes (no LDS).  At 12,288 atoms
-// these took the forward from 155 to 137 us (now 129) and the reverse from 255
-// to 246, at 1,536 atoms, with fewer atoms to a block, from 31 to 21 (now 19)
+// these took the forward from 155 to 137 us (now 125) and the reverse from 255
+// to 246, at 1,536 atoms, with fewer atoms to a block, from 31 to 21 (now 18.5)
 // and from 48 to 32.  An atom's edges are
 // consumed in batches of fixed size (32 forward, 16 reverse) in list order,
 // so the batch an edge falls into depends only on its rank among the atom's
@@ -61,10 +61,10 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kMxF = 128, kMxK = 16, kMxWaves = 4, kMxAtoms = 2;
-// forward: edges of a lane whose loads are issued together (eight: 40
-// loads in flight per lane, within four wavefronts per SIMD)
-constexpr int kFwdGroup = 8;
-// reverse: the same; small groups keep every variant within three
+// forward: edges of a lane in a group of loads, two groups in flight (40
+// loads per lane, within four wavefronts per SIMD)
+constexpr int kFwdGroup = 4;
+// reverse: small groups keep every variant within three
 // wavefronts per SIMD (measured: more gathers in flight per wavefront at
 // two wavefronts per SIMD are 7 % slower than fewer at three)
 template <bool L0>
@@ -427,16 +427,21 @@ struct FwdAcc {
     float s, v[3];
 };
 
-// One batch of nb <= 32 edges.  The lane's 16 edges are taken kFwdGroup at
-// a time, the loads of a group issued before its arithmetic (an edge
-// past the end of a partial batch reads the owner's rows and adds them
-// times a filter of exact zeros: with a branch around each edge instead the
-// edges' arithmetic could not overlap, 137 -> 129 us at 12,288 atoms, 20.7 ->
-// 19.3 at 1,536, and the reverse, short of registers, is no faster without).
+// One batch of up to 32 edges.  Of the lane's 16 edges two groups of kFwdGroup
+// are in flight: the loads of the first two are issued together behind the
+// filter products, those of the next where a group's registers are free
+// (left to the compiler, the first half of a batch waited for its loads in
+// three parts: 130 -> 125 us at 12,288 atoms, 323 -> 313 at 30,000, 8.0 ->
+// 7.3 at 192; with the loads before the products 128.6 and 318, and 173 with
+// two features to a lane and no barriers).  An edge past the end of a partial
+// batch reads the owner's rows and adds them times a filter of exact zeros:
+// with a branch around each edge instead the edges' arithmetic could not
+// overlap (137 -> 129 us at 12,288 atoms, 20.7 -> 19.3 at 1,536; the reverse,
+// short of registers, is no faster without).
 template <bool L0>
-__device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, const BatchBuf<32>& buf, int nb, int f,
-                                          int h, const uint4* fl, FwdAcc& acc) {
-    constexpr int F = kMxF, E = 16;
+__device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, const BatchBuf<32>& buf, int f, int h,
+                                          const uint4* fl, FwdAcc& acc) {
+    constexpr int F = kMxF, E = 16, G = kFwdGroup;
     const EdgeRec* rec = buf.rec;
     const int r = threadIdx.x & 31;  // A row: edge r (zero past nb: staged as zeros)
     const half8_t ah = as_half8(buf.a[r][h]), al = as_half8(buf.a[r][2 + h]);
@@ -454,47 +459,50 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
     load_channel(fl, 2, bh, bl, bb);
     const floatx16_t wc = mma3(ab, bb, ah, al, bh, bl);
     const uint32_t fo = uint32_t(f) * 4u;
+    // the b channel enters only as phi_b v_j, read as one product; rows
+    // of phi and pv are 3F floats: one byte offset per edge serves both
+    float pa[2][G], pc[2][G], pv[2][G][3];
+    auto gather = [&](int g0) {
+        const int d = g0 / G % 2;
 #pragma unroll
-    for (int g0 = 0; g0 < E; g0 += kFwdGroup) {
-        // the b channel enters only as phi_b v_j, read as one product; rows
-        // of phi and pv are 3F floats: one byte offset per edge serves both
-        float pa[kFwdGroup], pc[kFwdGroup], pv[kFwdGroup][3];
-#pragma unroll
-        for (int g = 0; g < kFwdGroup; ++g) {
+        for (int g = 0; g < G; ++g) {
             const int q = g0 + g;
-            const int te = 8 * (q / 4) + 4 * h + q % 4;
-            const EdgeRec& s = rec[te];
+            const EdgeRec& s = rec[8 * (q / 4) + 4 * h + q % 4];
             if (L0) {
                 const float* phj = ptab + s.t * 3 * F + f;
-                pa[g] = phj[0];
-                pc[g] = phj[2 * F];
+                pa[d][g] = phj[0];
+                pc[d][g] = phj[2 * F];
             } else {
                 const uint32_t off = (uint32_t(s.j) << 10) + ((uint32_t(s.j) << 9) + fo);
-                pa[g] = ld_off(a.phi, off);
-                pc[g] = ld_off<2 * F * 4>(a.phi, off);
-                pv[g][0] = ld_off(a.pv, off);
-                pv[g][1] = ld_off<F * 4>(a.pv, off);
-                pv[g][2] = ld_off<2 * F * 4>(a.pv, off);
+                pa[d][g] = ld_off(a.phi, off);
+                pc[d][g] = ld_off<2 * F * 4>(a.phi, off);
+                pv[d][g][0] = ld_off(a.pv, off);
+                pv[d][g][1] = ld_off<F * 4>(a.pv, off);
+                pv[d][g][2] = ld_off<2 * F * 4>(a.pv, off);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    gather(0);
+    gather(G);
 #pragma unroll
-        for (int g = 0; g < kFwdGroup; ++g) {
+    for (int g0 = 0; g0 < E; g0 += G) {
+        const int d = g0 / G % 2;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
             const int q = g0 + g;
-            const int te = 8 * (q / 4) + 4 * h + q % 4;
-            const EdgeRec& s = rec[te];
-            const float w_a = wa[q];
-            const float c = pc[g] * wc[q];
-            acc.s = fmaf(pa[g], w_a, acc.s);
-            if (L0) {
-                acc.v[0] = fmaf(s.u[0], c, acc.v[0]);
-                acc.v[1] = fmaf(s.u[1], c, acc.v[1]);
-                acc.v[2] = fmaf(s.u[2], c, acc.v[2]);
-            } else {
-                const float b = wb[q];
-                acc.v[0] = fmaf(s.u[0], c, fmaf(b, pv[g][0], acc.v[0]));
-                acc.v[1] = fmaf(s.u[1], c, fmaf(b, pv[g][1], acc.v[1]));
-                acc.v[2] = fmaf(s.u[2], c, fmaf(b, pv[g][2], acc.v[2]));
+            const EdgeRec& s = rec[8 * (q / 4) + 4 * h + q % 4];
+            const float c = pc[d][g] * wc[q];
+            acc.s = fmaf(pa[d][g], wa[q], acc.s);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                if (L0) acc.v[x] = fmaf(s.u[x], c, acc.v[x]);
+                else acc.v[x] = fmaf(s.u[x], c, fmaf(wb[q], pv[d][g][x], acc.v[x]));
             }
+        }
+        if (g0 + 2 * G < E) {
+            __builtin_amdgcn_sched_barrier(0);
+            gather(g0 + 2 * G);
         }
     }
 }
@@ -534,7 +542,7 @@ __global__ void __launch_bounds__(64 * kMxWaves, 4) k_message_fwd_mx(MpGeom mg, 
             __syncthreads();  // the batch is staged; the other buffer's batch is done
             nx = next_batch<BATCH>(rows, ai, b0, cnt);
             piece = stage.fetch(nx.p0, nx.nb, i0 + nx.ai);
-            fwd_batch<L0>(a, ptab_s, b, min(BATCH, cnt - b0), f, h, fl, acc);
+            fwd_batch<L0>(a, ptab_s, b, f, h, fl, acc);
         }
         // both halves of the wavefront hold partial sums of feature f
         acc.s = add_half(acc.s);
