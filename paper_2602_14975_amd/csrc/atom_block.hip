@@ -46,6 +46,7 @@
 #include <algorithm>
 #include <numeric>
 
+#include "atom_block_addr.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -53,17 +54,19 @@ namespace nnp {
 
 namespace {
 
+using namespace atom_block;
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kF = 128;
+constexpr int kF = kFeatures;
 constexpr int kFrag = 1024;      // bytes of one operand fragment (64 lanes x 16)
 constexpr int kKsF = kF / 32;    // steps of a product over one width: 32 k each
-constexpr int kW = 8;            // wavefronts of a block
-constexpr int kWF = kF / kW;     // features of a wavefront's slice
+constexpr int kW = kWaves;
+constexpr int kWF = kSliceFeatures;
 template <int TA>
 constexpr int kTurn = TA * kWF * 4;  // bytes of LDS that turn one slice around
 template <int TA>
@@ -116,7 +119,8 @@ struct Sums {
 // Global memory through buffer descriptors: a uniform base, a uniform offset
 // and one 32-bit lane offset per row stride, so that addresses take no
 // vector registers (plain pointers cost these kernels about 60), and rows
-// past the last atom are read as zero and not stored.
+// past the last atom, which are out of the bound by the lane offset, are read
+// as zero and not stored (atom_block_addr.h).
 struct Buf {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ Buf(const void* p, uint32_t bytes)
@@ -154,10 +158,11 @@ struct Lane {
 template <int C, int ld, int TA>
 __device__ __forceinline__ Slice<TA> load_slice(const float* p, int c, int c0, const Lane<TA>& L) {
     const Buf b(p + L.t0 * (C * ld), uint32_t(L.rows * (C * ld * 4)));
-    const uint32_t lo = uint32_t(L.a * (C * ld * 4) + 16 * L.h), o = uint32_t((c * ld + c0 + kWF * L.w) * 4);
+    const uint32_t o = row_uniform_offset<C, ld>(c, c0, L.w);
     Slice<TA> s;
 #pragma unroll
-    for (int g = 0; g < s.G; ++g) s.v[g] = __builtin_bit_cast(f32x4_t, b.load(lo, o + g * (16 * C * ld * 4)));
+    for (int g = 0; g < s.G; ++g)
+        s.v[g] = __builtin_bit_cast(f32x4_t, b.load(row_lane_offset<C, ld>(L.a, g, L.h), o));
     return s;
 }
 // The slice into row-major rows, turned around through kTurn bytes of LDS
@@ -242,27 +247,25 @@ __device__ __forceinline__ void put_slice(char* buf, int at, const Lane<TA>& L, 
 // those of put_slice, of slice f % NT (a ring of whole steps of three slices
 // does not fit 128 registers: at 4,800 atoms, where two blocks share CUs, the
 // kernels took 41.7 us instead of 39.1).
-template <int NP, int NT, int KS, int D, int TA>
+// KN: steps of 32 k that the product takes (the first of the matrix's KS).
+template <int NP, int NT, int KN, int KS, int D, int TA>
 struct Weights {
-    static constexpr uint32_t kRow = 64 * kWF * KS;  // bytes of a slice per piece
+    static constexpr uint32_t kRow = slice_bytes(KS);
+    static_assert(KN <= KS, "steps of the matrix");
     Buf b;
     uint32_t ps, off, step, lo;  // bytes: piece, first slice, slice step; lane
     bool apart;
     bf16x8_t r[D][NP];
     // mat: the matrix's pieces, N its rows; slices t0, t0 + st, ...
     __device__ __forceinline__ Weights(const uint16_t* mat, int N, int t0, int st, const Lane<TA>& L, bool two)
-        : b(mat, uint32_t(N) * (KS * 64 * NP)), ps(uint32_t(N) * (KS * 64)), off(t0 * kRow), step(st * kRow),
-          apart(NP == 1 && two) {
-        const int q = L.h;  // quarter of the fragment
-        lo = uint32_t((apart ? 4 * (q >> 1) + 2 * (q & 1) : 2 * (q & 1) + (q >> 1)) * 16 + L.a) * 16u;
+        : b(mat, NP * piece_bytes(N, KS)), ps(piece_bytes(N, KS)), off(t0 * kRow), step(st * kRow),
+          lo(unit_offset(L.h, L.a, NP == 1 && two)), apart(NP == 1 && two) {
 #pragma unroll
         for (int d = 0; d < D - 1; ++d) load(d, d);
     }
-    // step f into ring slot d (past the last step: unused data, bounded by
-    // the descriptor)
+    // step f into ring slot d
     __device__ __forceinline__ void load(int f, int d) {
-        const int ks = f / NT;
-        const uint32_t at = apart ? (ks >> 1) * 2048 + (ks & 1) * 256 : ks * 1024;
+        const uint32_t at = step_offset(f, NT, KN, apart);
 #pragma unroll
         for (int p = 0; p < NP; ++p)
             r[d][p] = __builtin_bit_cast(bf16x8_t, b.load(lo, off + (f % NT) * step + p * ps + at));
@@ -279,7 +282,6 @@ constexpr int kDepth = NP == 1 ? 4 * NT : NT == 2 ? 2 : TA == 16 ? 4 : 2;
 // waits for L2 at every step).  A loop over turns of a few steps rather than
 // straight-line code: a block walks through its code once, so that code is
 // fetched as slowly as data.
-// KN: steps of 32 k taken (the first of the matrix's KS).
 //
 // FP32 models: where registers allow, the products of the leading pieces are
 // summed apart from the five small ones (in `sep`, added by the caller's
@@ -293,7 +295,7 @@ constexpr bool kApart = NP == 3 && (TA == 16 || (NT <= 2 && NT * NB <= 3));
 
 template <int NP, int NT, int NB, int KN, int KS, int D, int TA>
 __device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Sums<TA> (&sep)[NT][NB],
-                                        Weights<NP, NT, KS, D, TA>& W, const char* buf, int stride,
+                                        Weights<NP, NT, KN, KS, D, TA>& W, const char* buf, int stride,
                                         const Lane<TA>& L) {
     constexpr int G = Sums<TA>::G;
     constexpr int S = KN * NT;                      // steps taken
@@ -303,7 +305,7 @@ __device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Sums<TA> (&sep)
     constexpr int XD = NB == 1 ? 2 : 1, XB = G > 1 ? 1 : NB;
     constexpr int R0 = std::lcm(D, G > 1 ? NT : XD * NT);  // steps of a turn: whole rings of weights and of x,
     constexpr int R = R0 / NT % 2 ? 2 * R0 : R0;           // an even number of k steps
-    static_assert(S % R == 0 && KN <= KS, "whole rings");
+    static_assert(S % R == 0, "whole rings");
     const char* bl = buf + L.lane * 16;
     bf16x8_t x[XD][XB][NP];
     auto load_x = [&](int k, int u, int d) {  // u: the step's b and g (16 atoms: all b)
@@ -377,10 +379,10 @@ __device__ __forceinline__ void fold(Sums<TA> (&acc)[NT][NB], const Sums<TA> (&s
 }
 // acc = W x
 template <int NP, int NT, int NB, int KN, int KS, int D, int TA>
-__device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Weights<NP, NT, KS, D, TA>& W, const char* buf,
+__device__ __forceinline__ void product(Sums<TA> (&acc)[NT][NB], Weights<NP, NT, KN, KS, D, TA>& W, const char* buf,
                                         int stride, const Lane<TA>& L) {
     Sums<TA> sep[NT][NB];
-    product<NP, NT, NB, KN>(acc, sep, W, buf, stride, L);
+    product<NP, NT, NB>(acc, sep, W, buf, stride, L);
     if (NP == 1 || kApart<NP, NT, NB, TA>) fold(acc, sep);
 }
 
@@ -440,9 +442,9 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
             // v = T_2 U, then s = T_0 E, by way of the same regions
             {
                 Sums<TA> sums[1][3];
-                Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.T2, kF, L.w, 1, L, false);
+                Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W(A.T2, kF, L.w, 1, L, false);
                 __syncthreads();
-                product<NP, 1, 3, kKsF>(sums, W, lds, CB, L);
+                product<NP, 1, 3>(sums, W, lds, CB, L);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) v0[c] = as_slice(sums[0][c]);
             }
@@ -451,13 +453,13 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
                 for (int c = 0; c < 3; ++c) keep_slice<3>(A.v_keep, c, L, v0[c]);
             }
             Sums<TA> sums[1][1];
-            Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.T0, kF, L.w, 1, L, false);
+            Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W(A.T0, kF, L.w, 1, L, false);
             __syncthreads();  // the rows of U are read
             put_slice<NP>(lds, 0, L, s0, false);
 #pragma unroll
             for (int c = 1; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, v0[c], two_uv);
             __syncthreads();
-            product<NP, 1, 1, kKsF>(sums, W, lds, 0, L);
+            product<NP, 1, 1>(sums, W, lds, 0, L);
             s0 = as_slice(sums[0][0]);
             __syncthreads();  // the rows of E are read
             put_slice<NP>(lds, 0, L, v0[0], two_uv);
@@ -467,9 +469,9 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
     // U v, V v: slices w of U and of V, of the adjacent matrices
     Sums<TA> uv[2][3];
     {
-        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.U, 2 * kF, L.w, kW, L, two_uv);
+        Weights<NP, 2, kKsF, kKsF, kDepth<NP, 2, TA>, TA> W(A.U, 2 * kF, L.w, kW, L, two_uv);
         __syncthreads();
-        product<NP, 2, 3, kKsF>(uv, W, lds, CB, L);
+        product<NP, 2, 3>(uv, W, lds, CB, L);
     }
     Slice<TA> nrm, dot;
 #pragma unroll
@@ -495,12 +497,12 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
     Slice<TA> z;
     {
         Sums<TA> acc[1][1];
-        Weights<NP, 1, 2 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M1, kF, L.w, 1, L, true);
+        Weights<NP, 1, 2 * kKsF, 2 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M1, kF, L.w, 1, L, true);
         __syncthreads();  // the vector fragments are read
         put_slice<NP>(lds, 0, L, s0, true);
         put_slice<NP>(lds, kKsF, L, nrm, true);
         __syncthreads();
-        product<NP, 1, 1, 2 * kKsF>(acc, W, lds, 0, L);
+        product<NP, 1, 1>(acc, W, lds, 0, L);
         const Slice<TA> a1 = added(acc[0][0], load_feat(A.m1, L));
         keep_slice<1>(A.a1, 0, L, a1);
 #pragma unroll
@@ -513,9 +515,9 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
     Slice<TA> v1[3];
     {
         Sums<TA> acc[NQ][1];
-        Weights<NP, NQ, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, kW, L, two_3);
+        Weights<NP, NQ, kKsF, kKsF, kDepth<NP, NQ, TA>, TA> W(A.M2, 3 * kF, L.w, kW, L, two_3);
         __syncthreads();
-        product<NP, NQ, 1, kKsF>(acc, W, lds + 2 * CB, 0, L);
+        product<NP, NQ, 1>(acc, W, lds + 2 * CB, 0, L);
         Slice<TA> h[NQ];
 #pragma unroll
         for (int c = 0; c < NQ; ++c) h[c] = added(acc[c][0], load_feat(A.m2 + c * kF, L));
@@ -541,9 +543,9 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
     // the s fragments of M1 are read (the barrier before M2's product)
     put_slice<NP>(lds, 0, L, s1, two_1);
     Sums<TA> acc1[1][1];
-    Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1, kF, L.w, 1, L, two_1);
+    Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1, kF, L.w, 1, L, two_1);
     __syncthreads();
-    product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
+    product<NP, 1, 1>(acc1, W1, lds, 0, L);
     const Slice<TA> h1 = added(acc1[0][0], load_feat(A.b1, L));
     if constexpr (!LAST) {
         keep_slice<1>(A.h1, 0, L, h1);
@@ -551,9 +553,9 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
         for (int e = 0; e < E; ++e) z.v[e >> 2][e & 3] = silu(h1[e]);
         put_slice<NP>(lds + CB, 0, L, z, two_3);
         Sums<TA> acc[3][1];
-        Weights<NP, 3, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, kW, L, two_3);
+        Weights<NP, 3, kKsF, kKsF, kDepth<NP, 3, TA>, TA> W2(A.W2, 3 * kF, L.w, kW, L, two_3);
         __syncthreads();
-        product<NP, 3, 1, kKsF>(acc, W2, lds + CB, 0, L);
+        product<NP, 3, 1>(acc, W2, lds + CB, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const Slice<TA> ph = added(acc[c][0], load_feat(A.b2 + c * kF, L));
@@ -599,7 +601,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
             }
         }
         put_slice<NP>(lds + CB, 0, L, z, two_1);
-        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W2(A.W2, kF, L.w, 1, L, two_1);
+        Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W2(A.W2, kF, L.w, 1, L, two_1);
         __syncthreads();
         if (L.w & 1) {
 #pragma unroll
@@ -610,7 +612,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_fwd(AtomFwd A) {
             }
         }
         Sums<TA> acc[1][1];
-        product<NP, 1, 1, kKsF>(acc, W2, lds + CB, 0, L);
+        product<NP, 1, 1>(acc, W2, lds + CB, 0, L);
         __syncthreads();
         const int r = L.lane, i = int(L.t0) + r;
         if (L.w == 0 && r < L.rows) {
@@ -640,15 +642,15 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
     char* turn = lds + CB + L.w * kTurn<TA>;
     Slice<TA> gs = load_slice<1, kF>(A.gs_in, 0, 0, L);
     if constexpr (!TOP) {
-        Weights<NP, 1, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.W2t, kF, L.w, 1, L, true);
+        Weights<NP, 1, 3 * kKsF, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.W2t, kF, L.w, 1, L, true);
         const Slice<TA> h1 = kept_slice<1>(A.h1, 0, L);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
             put_slice<NP>(lds, c * kKsF, L, load_slice<1, 3 * kF>(A.gphi, 0, c * kF, L), true);
         __syncthreads();
         Sums<TA> acc[1][1];
-        product<NP, 1, 1, 3 * kKsF>(acc, W, lds, 0, L);
-        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1t, kF, L.w, 1, L, two_1);
+        product<NP, 1, 1>(acc, W, lds, 0, L);
+        Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W1(A.W1t, kF, L.w, 1, L, two_1);
         Slice<TA> g;
 #pragma unroll
         for (int e = 0; e < E; ++e) g.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(h1[e]);
@@ -656,7 +658,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
         put_slice<NP>(lds, 0, L, g, two_1);
         __syncthreads();
         Sums<TA> acc1[1][1];
-        product<NP, 1, 1, kKsF>(acc1, W1, lds, 0, L);
+        product<NP, 1, 1>(acc1, W1, lds, 0, L);
         gs = added(acc1[0][0], gs);
     }
     // adjoints of p, q (and o): gs, gs (U v . V v), sum gv U v
@@ -664,7 +666,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
     Slice<TA> gv[3];
     {
         constexpr int KN = (TOP ? 2 : 3) * kKsF;
-        Weights<NP, 1, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M2t, kF, L.w, 1, L, true);
+        Weights<NP, 1, KN, 3 * kKsF, kDepth<NP, 1, TA>, TA> W(A.M2t, kF, L.w, 1, L, true);
         const Slice<TA> q = kept_slice<3>(A.pqo, 1, L);
         if constexpr (!TOP) o = kept_slice<3>(A.pqo, 2, L);
 #pragma unroll
@@ -692,19 +694,19 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
         const Slice<TA> a1 = kept_slice<1>(A.a1, 0, L);
         __syncthreads();
         Sums<TA> acc[1][1];
-        product<NP, 1, 1, KN>(acc, W, lds, 0, L);
+        product<NP, 1, 1>(acc, W, lds, 0, L);
 #pragma unroll
         for (int e = 0; e < E; ++e) dot.v[e >> 2][e & 3] = acc[0][0][e] * silu_grad(a1[e]);
     }
     // M1^T: adjoints of s (added to gs) and of |V v|
     Slice<TA> gn;
     {
-        Weights<NP, 2, kKsF, kDepth<NP, 2, TA>, TA> W(A.M1t, 2 * kF, L.w, kW, L, two_2);
+        Weights<NP, 2, kKsF, kKsF, kDepth<NP, 2, TA>, TA> W(A.M1t, 2 * kF, L.w, kW, L, two_2);
         __syncthreads();
         put_slice<NP>(lds, 0, L, dot, two_2);
         __syncthreads();
         Sums<TA> acc[2][1];
-        product<NP, 2, 1, kKsF>(acc, W, lds, 0, L);
+        product<NP, 2, 1>(acc, W, lds, 0, L);
         gn = as_slice(acc[1][0]);
         if constexpr (BOTTOM) keep_slice<3>(A.keep, 0, L, added(acc[0][0], gs));
         else store_slice<1, kF>(A.gs_out, 0, 0, L, added(acc[0][0], gs), turn);
@@ -714,7 +716,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
     Sums<TA> sums[1][3], sep[1][3];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(m ? A.Vt : A.Ut, kF, L.w, 1, L, true);
+        Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W(m ? A.Vt : A.Ut, kF, L.w, 1, L, true);
         __syncthreads();
         Slice<TA> nn;
 #pragma unroll
@@ -743,7 +745,7 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
             for (int e = 0; e < E; ++e) gn.v[e >> 2][e & 3] = gn[e] / sqrtf(nn[e]);
         }
         __syncthreads();
-        product<NP, 1, 3, kKsF>(sums, sep, W, lds, CB, L);
+        product<NP, 1, 3>(sums, sep, W, lds, CB, L);
     }
     fold(sums, sep);
     __syncthreads();
@@ -758,13 +760,14 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
         // P_2 = T_2^T g_v, then P_0 = T_0^T g_s; wavefront w has the slots
         // kWF w .. of the pp ones
         const bool on = kWF * L.w < A.pp;
+        const int t = slice_within(L.w, A.pp);
 #pragma unroll
         for (int c = 0; c < 3; ++c) put_slice<NP>(lds + c * CB, 0, L, gvo[c], false);
         {
             Sums<TA> p[1][3];
-            Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT2, A.pp, L.w, 1, L, false);
+            Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT2, A.pp, t, 1, L, false);
             __syncthreads();
-            if (on) product<NP, 1, 3, kKsF>(p, W, lds, CB, L);
+            if (on) product<NP, 1, 3>(p, W, lds, CB, L);
             __syncthreads();  // read: region 1 is the room to turn again
             if (on) {
 #pragma unroll
@@ -772,11 +775,11 @@ __global__ void __launch_bounds__(64 * kW, 4) k_atom_bwd(AtomBwd A) {
             }
         }
         Sums<TA> p[1][1];
-        Weights<NP, 1, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT0, A.pp, L.w, 1, L, false);
+        Weights<NP, 1, kKsF, kKsF, kDepth<NP, 1, TA>, TA> W(A.TT0, A.pp, t, 1, L, false);
         put_slice<NP>(lds, 0, L, kept_slice<3>(A.keep, 0, L), false);
         __syncthreads();
         if (on) {
-            product<NP, 1, 1, kKsF>(p, W, lds, 0, L);
+            product<NP, 1, 1>(p, W, lds, 0, L);
             store_slice<1, kF>(A.P0, 0, 0, L, as_slice(p[0][0]), turn);
         }
     }
