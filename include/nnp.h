@@ -486,7 +486,7 @@ nnp_status nnp_timer_read(const char* site, double* total_ms, int64_t* launches,
  * Message kernels of the conservative embedding (the message step
  * s_i += sum_j a_ij, v_i += sum_j (b_ij v_j + u_ij c_ij) of the models
  * section above, after the paper's Methods "Model architecture", and its
- * reverse), chosen process-wide for launches issued after the call:
+ * reverse), chosen process-wide for evaluations begun after the call:
  *   NNP_MP_AUTO (0): the matrix-core kernels for the shapes they cover
  *     (width 128, 16 Bessel functions, cosine cutoff, force evaluation);
  *     the radial filter runs there as split FP16 products at FP32-equivalent

@@ -424,21 +424,29 @@ static void gemm_gwt(const Model* m, int64_t off, int M, int N, int K, const flo
              m->pxT(off), m->wx_stride());
 }
 
-// The first layer of a conservative model by neighbour species (its edge
-// sums and two dense products in place of the per-edge message kernels),
-// where the model has the tables and the edges are prepared.
-static bool species_sum_on(const Model* m, const MpGeom& mg, const ModelBuf& b) {
-    return m->sp && b.sp && mg.ecnt && message_mx_active(m->desc.width, m->desc.n_rbf, 0) && species_sum_active();
-}
-
-// Width-128 conservative models run everything between two message steps in
-// one kernel each way (atom_block.hip) unless the older dense kernels were
-// selected.
-static bool atom_blocks_on(const Model* m) { return m->wf && dense_auto(); }
-
-// The dense products of the first layer by species within those kernels.
-static bool species_in_blocks(const Model* m, const MpGeom& mg, const ModelBuf& b) {
-    return b.blocks && b.edge_f && m->frag_species() && species_sum_on(m, mg, b);
+// The routes of one conservative evaluation, from the process-wide choices of
+// kernels, each read once: what the evaluation prepares and what it later reads
+// depend on them together, and another thread may change them in between.
+static void choose_routes(const Model* m, ModelBuf& b) {
+    const MessageRoute r = message_route(m->desc.width, m->desc.n_rbf, 0);
+    // Width-128 conservative models run everything between two message steps in
+    // one kernel each way (atom_block.hip) unless the older dense kernels were
+    // selected.
+    b.blocks = m->wf && dense_auto();
+    b.edges = b.ecnt && r.matrix_cores;
+    // The first layer by neighbour species (its edge sums and two dense products
+    // in place of the per-edge message kernels), where the model has the tables
+    // and the edges are prepared.
+    b.species_sum = b.edges && m->sp && b.sp && r.species_sum;
+    // FP32 models: the reverse past the first layer one message per edge
+    // (BF16 models keep the other form: with other sums the positions of
+    // a trajectory differ in the last bits, and some operands then round
+    // to other bfloat16 numbers)
+    const bool send = b.edges && b.blocks && !m->bf16();
+    b.edge_f = send ? b.gpqo : nullptr;
+    b.edge_key = send ? reinterpret_cast<int*>(b.gpqo + 4 * b.edge_cap) : nullptr;
+    // The dense products of the first layer by species within the blocks.
+    b.species_in_blocks = send && b.species_sum && m->frag_species();
 }
 
 void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, ModelBuf& b, hipStream_t s) {
@@ -473,10 +481,10 @@ void embed_forward(const Model* m, const nnp_system& sys, const MpGeom& mg, Mode
             a.phi = lb.phi;
             a.pv = lb.pv;
         }
-        const bool fused = l == 0 && species_in_blocks(m, mg, b);
+        const bool fused = l == 0 && b.species_in_blocks;
         if (fused) {
             // with the block
-        } else if (l == 0 && species_sum_on(m, mg, b)) {
+        } else if (l == 0 && b.species_sum) {
             // s = [E | species indicator] T_0^T (T_0 holds the embedding in
             // the indicator slots), v = U T_2^T: one launch over the rows
             // [s; v] where they are adjacent (FP32-equivalent split-bfloat16
@@ -572,7 +580,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     LayerBuf& lb = b.layer[l];
     const bool wg = dtheta != nullptr;
     const bool blocks = b.blocks;
-    const bool fused = l == 0 && species_in_blocks(m, mg, b);
+    const bool fused = l == 0 && b.species_in_blocks;
     if (blocks) {
         AtomBwd f{};
         f.n = n;
@@ -647,7 +655,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
         return;
     }
-    if (l == 0 && !wg && force && species_sum_on(m, mg, b)) {
+    if (l == 0 && !wg && force && b.species_sum) {
         // P_0 = g_smid T_0, P_2 = g_vmid T_2 (float32 products), then the
         // per-edge force shares
         // (one launch over the rows [g_smid; g_vmid] where they are adjacent)
@@ -672,7 +680,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
         return;
     }
     launch_message_bwd(F, K, cut, mg, a, force != nullptr, wg, s);
-    if (l == 1 && b.edge_f && !species_sum_on(m, mg, b)) launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
+    if (l == 1 && b.edge_f && !b.species_sum) launch_edge_force(mg, b.edge_f, force, vir, b.energy_sum, s);
     if (wg) {
         const int nb = mp_blocks(n, F);
         const int64_t cnt = int64_t(3) * F * (K + 1);
@@ -738,22 +746,12 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     const int F = m->desc.width;
     MpGeom mg = make_geom(m, sys, geom, nl);
     mg.perm = perm;
-    b.blocks = atom_blocks_on(m);
-    b.edge_f = nullptr;
-    b.edge_key = nullptr;
-    if (b.ecnt && message_mx_active(F, m->desc.n_rbf, 0)) {
-        // FP32 models: the reverse past the first layer one message per edge
-        // (BF16 models keep the other form: with other sums the positions of
-        // a trajectory differ in the last bits, and some operands then round
-        // to other bfloat16 numbers)
-        if (b.blocks && !m->bf16()) {
-            b.edge_f = b.gpqo;
-            b.edge_key = reinterpret_cast<int*>(b.gpqo + 4 * b.edge_cap);
-        }
+    choose_routes(m, b);
+    if (b.edges) {
         mg.edge_key = b.edge_key;
         // the edges within the cutoff, prepared once for all six message launches
         // (with the first layer by neighbour species, its edge sums in the same pass)
-        if (m->sp && b.sp && species_sum_active())
+        if (b.species_sum)
             launch_edge_prep(mg, b.ecnt, b.erec, b.ehalf, s, b.sp, b.sp + int64_t(n) * m->sp_ep, m->desc.n_species,
                              m->sp_ep);
         else
@@ -773,7 +771,7 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     // with the last kernel of the reverse where that is launch_edge_force
     const RepSum es{energy ? sys.n_rep : 0, t.rep_start, n, b.Ei, energy};
     b.energy_sum = RepSum{};
-    if (forces && b.edge_f && (L > 1 || species_sum_on(m, mg, b))) b.energy_sum = es;
+    if (forces && b.edge_f && (L > 1 || b.species_sum)) b.energy_sum = es;
     else if (energy) launch_rep_sum(es, s);
     if (!forces) return;
     if (!blocks) {

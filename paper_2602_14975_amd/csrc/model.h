@@ -123,7 +123,10 @@ struct ModelBuf {
     float* s[kMaxLayers + 1];
     float* v[kMaxLayers + 1];
     LayerBuf layer[kMaxLayers];
-    bool blocks = false;  // this evaluation runs the per-atom blocks (set once at its start)
+    // routes of this evaluation, set once at its start: the per-atom blocks;
+    // prepared edges and the matrix-core message kernels; the first layer by
+    // species; its products in the blocks
+    bool blocks = false, edges = false, species_sum = false, species_in_blocks = false;
     float *ao = nullptr, *zo = nullptr, *Ei = nullptr;
     float *QK = nullptr, *Vh = nullptr, *gQK = nullptr, *gVh = nullptr;
     float *gs = nullptr, *gs2 = nullptr, *gv = nullptr, *gv2 = nullptr, *gpqo = nullptr, *ga1 = nullptr,

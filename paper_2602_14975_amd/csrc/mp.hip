@@ -543,11 +543,14 @@ int mp_blocks(int n, int F) {
 }
 
 // The matrix-core kernels serve the shapes they cover unless the vector
-// kernels were selected (nnp_set_message_kernels).
+// kernels were selected (nnp_set_message_kernels).  The launches below take
+// the route of the evaluation, which only prepares the edges for it.
 static std::atomic<int> g_mp_mode{NNP_MP_AUTO};
-static bool mx_enabled() { return g_mp_mode.load(std::memory_order_relaxed) != NNP_MP_VECTOR; }
-bool message_mx_active(int F, int K, int cut) { return message_mx_shape(F, K, cut) && mx_enabled(); }
-bool species_sum_active() { return g_mp_mode.load(std::memory_order_relaxed) == NNP_MP_AUTO; }
+MessageRoute message_route(int F, int K, int cut) {
+    const int mode = g_mp_mode.load(std::memory_order_relaxed);
+    const bool mx = message_mx_shape(F, K, cut) && mode != NNP_MP_VECTOR;
+    return {mx, mx && mode == NNP_MP_AUTO};
+}
 
 #define NNP_DISPATCH_MP(F_, K_, CUT_, CALL)                                          \
     if (F == F_ && K == K_ && cut == CUT_) { CALL; NNP_LAUNCH_CHECK(); return; }
@@ -555,7 +558,7 @@ bool species_sum_active() { return g_mp_mode.load(std::memory_order_relaxed) == 
 void launch_message_fwd(int F, int K, int cut, const MpGeom& mg, const MpFwd& a, hipStream_t s) {
     if (mg.n <= 0) return;
     ScopedTimer timer(cut == 0 ? "message_fwd" : "nc_message_fwd", s, true);
-    if (mg.ecnt && a.mx_scale && message_mx_active(F, K, cut)) {
+    if (mg.ecnt && a.mx_scale && message_mx_shape(F, K, cut)) {
         launch_message_fwd_mx(mg, a, s, timer);
         NNP_LAUNCH_CHECK();
         return;
@@ -577,7 +580,7 @@ void launch_message_bwd(int F, int K, int cut, const MpGeom& mg, const MpBwd& a,
                         hipStream_t s) {
     if (mg.n <= 0) return;
     ScopedTimer timer(cut == 0 ? "message_bwd" : "nc_message_bwd", s, true);
-    if (geo && !wgrad && mg.ecnt && a.mx_scale && message_mx_active(F, K, cut)) {
+    if (geo && !wgrad && mg.ecnt && a.mx_scale && message_mx_shape(F, K, cut)) {
         launch_message_bwd_mx(mg, a, s, timer);
         NNP_LAUNCH_CHECK();
         return;
