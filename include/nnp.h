@@ -490,10 +490,11 @@ nnp_status nnp_timer_read(const char* site, double* total_ms, int64_t* launches,
  *   NNP_MP_AUTO (0): the matrix-core kernels for the shapes they cover
  *     (width 128, 16 Bessel functions, cosine cutoff, force evaluation);
  *     the radial filter runs there as split FP16 products at FP32-equivalent
- *     precision; the vector kernels elsewhere.  In that shape, with at most
- *     8 species, the first layer (whose neighbour features depend on the
- *     species alone and whose vector input is zero) is evaluated from
- *     per-atom sums of the radial basis by neighbour species and four dense
+ *     precision; the vector kernels elsewhere, and beyond 2,796,203 atoms
+ *     (the matrix-core kernels reach a row by a 32-bit offset).  In that
+ *     shape, with at most 8 species, the first layer (whose neighbour
+ *     features depend on the species alone and whose vector input is zero)
+ *     is evaluated from per-atom sums of the radial basis by neighbour species and four dense
  *     products instead of per-edge feature work (the same function: the
  *     filter is linear in the basis); its reverse, for forces, likewise.
  *   NNP_MP_VECTOR (1): the vector kernels (plain FP32 filter) everywhere.

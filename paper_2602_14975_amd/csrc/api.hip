@@ -427,8 +427,8 @@ static void gemm_gwt(const Model* m, int64_t off, int M, int N, int K, const flo
 // The routes of one conservative evaluation, from the process-wide choices of
 // kernels, each read once: what the evaluation prepares and what it later reads
 // depend on them together, and another thread may change them in between.
-static void choose_routes(const Model* m, ModelBuf& b) {
-    const MessageRoute r = message_route(m->desc.width, m->desc.n_rbf, 0);
+static void choose_routes(const Model* m, int64_t n, ModelBuf& b) {
+    const MessageRoute r = message_route(m->desc.width, m->desc.n_rbf, 0, n);
     // Width-128 conservative models run everything between two message steps in
     // one kernel each way (atom_block.hip) unless the older dense kernels were
     // selected.
@@ -746,7 +746,7 @@ void cons_eval(const Model* m, const nnp_system& sys, const RepGeom& geom, const
     const int F = m->desc.width;
     MpGeom mg = make_geom(m, sys, geom, nl);
     mg.perm = perm;
-    choose_routes(m, b);
+    choose_routes(m, n, b);
     if (b.edges) {
         mg.edge_key = b.edge_key;
         // the edges within the cutoff, prepared once for all six message launches

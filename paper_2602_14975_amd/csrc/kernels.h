@@ -244,13 +244,13 @@ void colsum(int M, int N, const float* G, int ldg, float* db, float* scratch, in
 int mp_blocks(int n, int F);
 // matrix-core message kernels (F = 128, K = 16, cosine cutoff; forces, no weight adjoints)
 bool message_mx_shape(int F, int K, int cut);
-// What nnp_set_message_kernels leaves an evaluation of this shape: the
-// matrix-core message kernels, and the first layer by neighbour species with
-// them.  Read once per evaluation.
+// What nnp_set_message_kernels leaves an evaluation of this shape and of n
+// atoms: the matrix-core message kernels, and the first layer by neighbour
+// species with them.  Read once per evaluation.
 struct MessageRoute {
     bool matrix_cores, species_sum;
 };
-MessageRoute message_route(int F, int K, int cut);
+MessageRoute message_route(int F, int K, int cut, int64_t n);
 // With Es, also the first conservative layer's edge sums by neighbour species
 // (rows Es [n][ep], Ev [3n][ep]; S species, S <= 8; mp_species.hip).
 void launch_edge_prep(const MpGeom& mg, int* ecnt, EdgeRec* erec, uint4* ehalf, hipStream_t s, float* Es = nullptr,

@@ -39,6 +39,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "mp_edge.h"
+#include "mp_rows.h"
 
 namespace nnp {
 
@@ -542,13 +543,13 @@ int mp_blocks(int n, int F) {
     return cdiv(n, kMpWaves / (F / G) * (64 / G));
 }
 
-// The matrix-core kernels serve the shapes they cover unless the vector
-// kernels were selected (nnp_set_message_kernels).  The launches below take
+// The matrix-core kernels serve the shapes they cover, up to the atoms their
+// row offsets reach, unless the vector kernels were selected (nnp_set_message_kernels).  The launches below take
 // the route of the evaluation, which only prepares the edges for it.
 static std::atomic<int> g_mp_mode{NNP_MP_AUTO};
-MessageRoute message_route(int F, int K, int cut) {
+MessageRoute message_route(int F, int K, int cut, int64_t n) {
     const int mode = g_mp_mode.load(std::memory_order_relaxed);
-    const bool mx = message_mx_shape(F, K, cut) && mode != NNP_MP_VECTOR;
+    const bool mx = message_mx_shape(F, K, cut) && n <= kRowOffsetAtoms && mode != NNP_MP_VECTOR;
     return {mx, mx && mode == NNP_MP_AUTO};
 }
 

@@ -51,6 +51,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "mp_edge.h"
+#include "mp_rows.h"
 
 namespace nnp {
 
@@ -60,7 +61,7 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kMxF = 128, kMxK = 16, kMxWaves = 4, kMxAtoms = 2;
+constexpr int kMxF = kRowFeatures, kMxK = 16, kMxWaves = 4, kMxAtoms = 2;
 // forward: edges of a lane in a group of loads, two groups in flight (40
 // loads per lane, within four wavefronts per SIMD)
 constexpr int kFwdGroup = 4;
@@ -158,9 +159,8 @@ __device__ __forceinline__ half4_t bias_rows(float c, int h) {
     return a;
 }
 
-// A float at a 32-bit byte offset from a wavefront-uniform base: the
-// neighbour-row gathers then take two shift-adds per edge for their
-// addresses (rows of F and of 3F floats), and the quantities of a row differ by immediate offsets.
+// A float at a 32-bit byte offset (mp_rows.h) from a wavefront-uniform base;
+// the quantities of a row differ by immediate offsets.
 template <int IMM = 0>  // added to the address, not to the offset, which might wrap
 __device__ __forceinline__ float ld_off(const float* base, uint32_t byte_off) {
     return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off + IMM);
@@ -473,7 +473,7 @@ __device__ __forceinline__ void fwd_batch(const MpFwd& a, const float* ptab, con
                 pa[d][g] = phj[0];
                 pc[d][g] = phj[2 * F];
             } else {
-                const uint32_t off = (uint32_t(s.j) << 10) + ((uint32_t(s.j) << 9) + fo);
+                const uint32_t off = row3_offset(uint32_t(s.j), fo);
                 pa[d][g] = ld_off(a.phi, off);
                 pc[d][g] = ld_off<2 * F * 4>(a.phi, off);
                 pv[d][g][0] = ld_off(a.pv, off);
@@ -633,7 +633,7 @@ __device__ __forceinline__ void bwd_batch(const MpBwd& a, const float* ptab, con
             const int q = g0 + g;
             const int te = 8 * (q / 4) + 4 * h + q % 4;
             const EdgeRec& s = rec[te];
-            const uint32_t off = (uint32_t(s.j) << 9) + fo, off3 = (uint32_t(s.j) << 10) + off;
+            const uint32_t off = row_offset(uint32_t(s.j), fo), off3 = row3_offset(uint32_t(s.j), fo);
             if (L0) {
                 const float* phj = ptab + s.t * 3 * F + f;
                 d.pa[g] = phj[0];
@@ -937,7 +937,7 @@ __device__ __forceinline__ float send_batch(const MpBwd& a, const BatchBuf<16>& 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int q = g0 + g, te = 8 * (q / 4) + 4 * h + q % 4;
-            const uint32_t off = (uint32_t(rec[te].j) << 9) + fo, off3 = (uint32_t(rec[te].j) << 10) + off;
+            const uint32_t j = uint32_t(rec[te].j), off = row_offset(j, fo), off3 = row3_offset(j, fo);
             d.gn[g][0] = ld_off(a.gvm, off3);
             d.gn[g][1] = ld_off<F * 4>(a.gvm, off3);
             d.gn[g][2] = ld_off<2 * F * 4>(a.gvm, off3);
