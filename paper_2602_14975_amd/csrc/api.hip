@@ -275,7 +275,8 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
     b.phi_tab = m->phi_tab();
     b.gphi_tab = a.take<float>(S * 3 * F);
     b.gh1_tab = a.take<float>(S * F);
-    const int64_t nt = (n + 31) / 32 * 32;  // whole tiles of the per-atom blocks
+    // whole tiles of the per-atom blocks, where the model has them
+    const int64_t nt = m->wf ? (n + 31) / 32 * 32 : n;
     for (int l = 0; l < L; ++l) {
         LayerBuf& lb = b.layer[l];
         lb.h1 = a.take<float>(nt * F);
