@@ -277,35 +277,52 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
     b.gh1_tab = a.take<float>(S * F);
     // whole tiles of the per-atom blocks, where the model has them
     const int64_t nt = m->wf ? (n + 31) / 32 * 32 : n;
+    // What only the separate dense kernels use.  FP32 models with the blocks
+    // take one piece for all of it, in which those have the sums of the edges'
+    // messages (E x [4] and the neighbours' indices).
+    const bool shared = m->wf && !m->bf16();
+    float* piece = nullptr;
+    if (shared) {
+        b.edge_room = a.take<float>(std::max<int64_t>(n * F * (16 + 3 * L), 5 * E));
+        b.edge_cap = E;
+        piece = b.edge_room;
+    }
+    auto dense = [&](int64_t count) {
+        if (!shared) return a.take<float>(count);
+        float* p = piece;
+        if (piece) piece += count;
+        return p;
+    };
     for (int l = 0; l < L; ++l) {
         LayerBuf& lb = b.layer[l];
-        lb.h1 = a.take<float>(nt * F);
+        // the first layer's phi is the species table's
+        const bool phi = l > 0 || m->desc.kind == NNP_MODEL_NC;
+        if (phi) lb.h1 = a.take<float>(nt * F);
         // only the weight gradient (one layer) reads it after its own layer
-        lb.zphi = l > 0 && m->desc.kind == NNP_MODEL_CONS ? b.layer[0].zphi : a.take<float>(n * F);
-        lb.phi = a.take<float>(n * 3 * F);
+        lb.zphi = l > 0 && m->desc.kind == NNP_MODEL_CONS ? b.layer[0].zphi : dense(n * F);
+        if (phi) lb.phi = a.take<float>(n * 3 * F);
         lb.smid = a.take<float>(n * F);
         lb.vmid = a.take<float>((l == 0 ? nt : n) * 3 * F);
         lb.UV = a.take<float>(nt * 6 * F);
-        lb.X = a.take<float>(n * 2 * F);
+        lb.X = dense(n * 2 * F);
         lb.a1 = a.take<float>(nt * F);
-        lb.z = a.take<float>(n * F);
+        lb.z = dense(n * F);
         lb.pqo = a.take<float>(nt * 3 * F);
     }
     if (m->desc.kind == NNP_MODEL_CONS) {
-        b.ao = a.take<float>(n * F);
-        b.zo = a.take<float>(n * F);
+        b.ao = dense(n * F);
+        b.zo = dense(n * F);
         b.Ei = a.take<float>(n);
         b.gs = a.take<float>(n * F);
         b.gs2 = a.take<float>(n * F);
         b.gv = a.take<float>(n * 3 * F);
         b.gv2 = a.take<float>(n * 3 * F);
-        b.gpqo = a.take<float>(std::max<int64_t>(n * 12 * F, m->wf && !m->bf16() ? 5 * E : 0));
-        b.edge_cap = E;
-        b.ga1 = b.gpqo + n * 3 * F;
-        b.gX = b.ga1 + n * F;
-        b.gUV = b.gX + n * 2 * F;
+        b.gpqo = dense(n * 3 * F);
+        b.ga1 = dense(n * F);
+        b.gX = dense(n * 2 * F);
+        b.gUV = dense(n * 6 * F);
         b.gphi = a.take<float>(n * 3 * F);
-        b.gh1 = a.take<float>(n * F);
+        b.gh1 = dense(n * F);
         if (message_mx_shape(int(F), m->desc.n_rbf, 0)) {
             b.ecnt = a.take<int>(n);
             b.erec = a.take<EdgeRec>(E);
@@ -444,8 +461,8 @@ static void choose_routes(const Model* m, int64_t n, ModelBuf& b) {
     // a trajectory differ in the last bits, and some operands then round
     // to other bfloat16 numbers)
     const bool send = b.edges && b.blocks && !m->bf16();
-    b.edge_f = send ? b.gpqo : nullptr;
-    b.edge_key = send ? reinterpret_cast<int*>(b.gpqo + 4 * b.edge_cap) : nullptr;
+    b.edge_f = send ? b.edge_room : nullptr;
+    b.edge_key = send ? reinterpret_cast<int*>(b.edge_room + 4 * b.edge_cap) : nullptr;
     // The dense products of the first layer by species within the blocks.
     b.species_in_blocks = send && b.species_sum && m->frag_species();
 }
@@ -862,10 +879,18 @@ struct CallScratch {
 
 // One layout serves every entry point: tables, neighbour scratch, the
 // integrator's snapshot and flags, then the two model scratch areas.
+//
+// The entries that a list build keeps from its count to its fill (512 bytes an
+// atom) are in the fast force's scratch, without a fast force in the
+// conservative model's: the builds and that model's evaluations follow each
+// other on one stream, also where a build runs beside a conservative
+// evaluation, and an evaluation reads nothing there that it has not written.
+// On top of the scratch they would take a tenth and more of a small model's
+// footprint, and a server's budget would hold as much less.
 void carve_all(Arena& a, const Model* cons, const Model* nc, int64_t n, int32_t n_rep, int64_t E, bool wgrad,
                CallScratch& c) {
     carve_tables(a, n_rep, c.t);
-    carve_nbr_scratch(a, n, n_rep, c.nb);
+    carve_nbr_scratch(a, n, n_rep, c.nb, !cons && !nc);
     c.rs.pos = a.take<double>(3 * n);
     c.rs.vel = a.take<double>(3 * n);
     c.rs.pos_ref = a.take<double>(3 * n);
@@ -890,6 +915,11 @@ void carve_all(Arena& a, const Model* cons, const Model* nc, int64_t n, int32_t 
     c.spare_species = a.take<int>(n);
     if (cons) carve_model(a, cons, n, E, false, c.cons);
     if (nc) carve_model(a, nc, n, E, wgrad, c.nc);
+    // Behind the virial shares, which are kept over a step: s and v before and
+    // after a layer and its own buffers are at least 26 floats an atom and
+    // feature, of 8 features or more.
+    if (cons || nc) c.nb.hits = reinterpret_cast<int*>((nc ? c.nc : c.cons).s[0]);
+    static_assert(kKeptEntries <= 26 * 8, "room for the kept entries");
 }
 
 size_t call_scratch_bytes(const Model* cons, const Model* nc, int64_t n, int32_t n_rep, int64_t E) {
@@ -925,7 +955,7 @@ extern "C" nnp_status nnp_neighbors(const nnp_system* sys, nnp_nlist* nl, void* 
     SysTables t;
     carve_tables(a, sys->n_rep, t);
     NbrScratch nb;
-    carve_nbr_scratch(a, sys->n_atoms, sys->n_rep, nb);
+    carve_nbr_scratch(a, sys->n_atoms, sys->n_rep, nb, true);
     const CellPlan plan = plan_cells(*sys, nl->cutoff);
     const int run = 1;
     Uploads up(s);

@@ -77,13 +77,17 @@ struct RowOrder {
 struct NbrScratch {
     int *grid_m, *grid_base, *cell_code, *cell_lex, *cell_of_atom, *slot_of_atom, *cell_count, *cell_start,
         *cell_atoms, *counts, *tmp_off, *status;
-    int* hits;         // [n][128] entries of each row as the count found them (cell positions)
+    int* hits;         // [n][kKeptEntries] entries of each row as the count found them (cell positions)
     double* cell_pos;  // [3][n] positions in cell order
 };
 
 CellPlan plan_cells(const nnp_system& sys, double radius);
 int64_t max_cells(int64_t n_atoms, int32_t n_rep);
-void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s);
+// Entries of a row that the fill takes as the count found them.
+constexpr int kKeptEntries = 128;
+// hits: take room for the kept entries too (else the caller gives it some that
+// nothing else uses from a build's count to its fill)
+void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s, bool hits);
 // The plan's tables through `up` (flushed), then the cell numbers on the device
 void upload_cell_plan(const CellPlan& plan, NbrScratch& s, Uploads& up, hipStream_t stream);
 // cell_rows: rows and entries in the cell order of this list build (s.cell_atoms

@@ -115,7 +115,8 @@ struct Model {
 };
 
 struct LayerBuf {
-    float *h1, *zphi, *phi, *smid, *vmid, *UV, *X, *a1, *z, *pqo;
+    float *h1 = nullptr, *phi = nullptr;  // of NC models, and of layers past the first
+    float *zphi, *smid, *vmid, *UV, *X, *a1, *z, *pqo;
     float* pv = nullptr;  // phi_b * v_in (matrix-core message kernels, layers past the first)
 };
 
@@ -148,10 +149,11 @@ struct ModelBuf {
     uint4* ehalf = nullptr;
     // [E][4] feature sums of the messages past the first layer, and [E] the
     // caller's index of each edge's neighbour (FP32 models with the per-atom
-    // blocks), in the room of gpqo, ga1, gX and gUV, which those do not use;
+    // blocks), in the room of what only the separate dense kernels use;
     // nullptr: not used in this evaluation
     float* edge_f = nullptr;
     int* edge_key = nullptr;
+    float* edge_room = nullptr;
     RepSum energy_sum;  // sums that launch_edge_force takes along
     int64_t edge_cap = 0;  // E
     // first layer per species: pre-activation, hidden, phi, and adjoints

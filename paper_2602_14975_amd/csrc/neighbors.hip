@@ -230,8 +230,7 @@ __device__ __forceinline__ void for_candidates(const Stencil& st, int i, int r, 
     }
 }
 
-// Entries a row may have for the fill to take them as the count found them.
-constexpr int kKeep = 128;
+constexpr int kKeep = kKeptEntries;
 
 // cell_rows: row p is the atom at cell position p (else row i is atom i).
 // The entries (their cell positions, in the order found) are kept for the
@@ -639,7 +638,7 @@ CellPlan plan_cells(const nnp_system& sys, double radius) {
 
 int64_t max_cells(int64_t n_atoms, int32_t n_rep) { return 2 * n_atoms + 27 * int64_t(n_rep) + 1; }
 
-void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s) {
+void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s, bool hits) {
     int64_t C = max_cells(n, n_rep);
     s.grid_m = a.take<int>(n_rep);
     s.grid_base = a.take<int>(n_rep);
@@ -652,7 +651,7 @@ void carve_nbr_scratch(Arena& a, int64_t n, int32_t n_rep, NbrScratch& s) {
     s.cell_atoms = a.take<int>(n);
     s.cell_pos = a.take<double>(3 * n);
     s.counts = a.take<int>(n);
-    s.hits = a.take<int>(n * kKeep);
+    if (hits) s.hits = a.take<int>(n * kKeep);
     s.tmp_off = a.take<int>(n + 1);
     s.status = a.take<int>(8);
 }
