@@ -353,7 +353,7 @@ void carve_model(Arena& a, const Model* m, int64_t n, int64_t E, bool for_wgrad,
             b.gphi = a.take<float>(n * 3 * F);
             b.gh1 = a.take<float>(n * F);
             const int64_t maxNK = std::max<int64_t>({3 * F * F, HC * F, 3 * F * S});
-            b.chunk_part = a.take<float>(int64_t(cdiv(3 * n, kChunk) + 1) * maxNK);
+            b.chunk_part = a.take<float>(int64_t(cdiv(3 * n, grad_chunk(3 * n)) + 1) * maxNK);
             b.mp_part = a.take<float>(int64_t(mp_blocks(int(n), int(F))) * 3 * F * (m->desc.n_rbf + 1));
             b.filt_sum = a.take<float>(3 * F * (m->desc.n_rbf + 1));
         }
@@ -597,6 +597,7 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     const LayerOff& lo = m->loff[l];
     LayerBuf& lb = b.layer[l];
     const bool wg = dtheta != nullptr;
+    const int chunk = grad_chunk(3 * int64_t(n));
     const bool blocks = b.blocks;
     const bool fused = l == 0 && b.species_in_blocks;
     if (blocks) {
@@ -631,17 +632,17 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
     } else {
         launch_update_combine_bwd(n, F, lb.UV, lb.pqo, b.gs, gv_zero ? nullptr : b.gv, b.gpqo, b.gUV, s);
         if (wg) {
-            gemm_wgrad(n, 3 * F, F, b.gpqo, 3 * F, lb.z, F, dtheta + lo.M2, b.chunk_part, kChunk, false, s);
-            colsum(n, 3 * F, b.gpqo, 3 * F, dtheta + lo.m2, b.chunk_part, kChunk, false, s);
+            gemm_wgrad(n, 3 * F, F, b.gpqo, 3 * F, lb.z, F, dtheta + lo.M2, b.chunk_part, chunk, false, s);
+            colsum(n, 3 * F, b.gpqo, 3 * F, dtheta + lo.m2, b.chunk_part, chunk, false, s);
     }
     gemm_gwt(m, lo.M2, n, 3 * F, F, b.gpqo, 3 * F, b.ga1, F, EPI_DSILU, lb.a1, F, false, s);
     if (wg) {
-        gemm_wgrad(n, F, 2 * F, b.ga1, F, lb.X, 2 * F, dtheta + lo.M1, b.chunk_part, kChunk, false, s);
-        colsum(n, F, b.ga1, F, dtheta + lo.m1, b.chunk_part, kChunk, false, s);
+        gemm_wgrad(n, F, 2 * F, b.ga1, F, lb.X, 2 * F, dtheta + lo.M1, b.chunk_part, chunk, false, s);
+        colsum(n, F, b.ga1, F, dtheta + lo.m1, b.chunk_part, chunk, false, s);
     }
     gemm_gwt(m, lo.M1, n, F, 2 * F, b.ga1, F, b.gX, 2 * F, EPI_NONE, nullptr, 0, false, s);
     launch_norm_bwd(n, F, b.gs, b.gX, lb.X, lb.UV, b.gs2, b.gUV, s);  // gs2 = g_smid
-    if (wg) gemm_wgrad(3 * n, 2 * F, F, b.gUV, 2 * F, lb.vmid, F, dtheta + lo.U, b.chunk_part, kChunk, false, s);
+    if (wg) gemm_wgrad(3 * n, 2 * F, F, b.gUV, 2 * F, lb.vmid, F, dtheta + lo.U, b.chunk_part, chunk, false, s);
     gemm_gwt(m, lo.U, 3 * n, 2 * F, F, b.gUV, 2 * F, b.gv, F, EPI_NONE, nullptr, 0, !gv_zero, s);  // gv = g_vmid
     }
     MpBwd a{};
@@ -711,26 +712,26 @@ void layer_backward(const Model* m, int l, const MpGeom& mg, ModelBuf& b, float*
             // differentiate the table; the embedding gets the pass-through
             // adjoint of s plus the perceptron path.
             const int S = m->desc.n_species;
-            launch_emb_grad(n, 3 * F, S, mg.species, b.gphi, b.gphi_tab, b.chunk_part, kChunk, s);
-            gemm_wgrad(S, 3 * F, F, b.gphi_tab, 3 * F, b.z_tab, F, dtheta + lo.W2, b.chunk_part, kChunk, false, s);
-            colsum(S, 3 * F, b.gphi_tab, 3 * F, dtheta + lo.b2, b.chunk_part, kChunk, false, s);
+            launch_emb_grad(n, 3 * F, S, mg.species, b.gphi, b.gphi_tab, b.chunk_part, chunk, s);
+            gemm_wgrad(S, 3 * F, F, b.gphi_tab, 3 * F, b.z_tab, F, dtheta + lo.W2, b.chunk_part, chunk, false, s);
+            colsum(S, 3 * F, b.gphi_tab, 3 * F, dtheta + lo.b2, b.chunk_part, chunk, false, s);
             gemm_gw(S, 3 * F, F, b.gphi_tab, 3 * F, m->p(lo.W2), b.gh1_tab, F, EPI_DSILU, b.h1_tab, F, false, s);
-            gemm_wgrad(S, F, F, b.gh1_tab, F, m->p(m->off_emb), F, dtheta + lo.W1, b.chunk_part, kChunk, false, s);
-            colsum(S, F, b.gh1_tab, F, dtheta + lo.b1, b.chunk_part, kChunk, false, s);
-            launch_emb_grad(n, F, S, mg.species, b.gs2, dtheta + m->off_emb, b.chunk_part, kChunk, s);
+            gemm_wgrad(S, F, F, b.gh1_tab, F, m->p(m->off_emb), F, dtheta + lo.W1, b.chunk_part, chunk, false, s);
+            colsum(S, F, b.gh1_tab, F, dtheta + lo.b1, b.chunk_part, chunk, false, s);
+            launch_emb_grad(n, F, S, mg.species, b.gs2, dtheta + m->off_emb, b.chunk_part, chunk, s);
             gemm_gw(S, F, F, b.gh1_tab, F, m->p(lo.W1), dtheta + m->off_emb, F, EPI_NONE, nullptr, 0, true, s);
         }
         return;
     }
     if (blocks) return;  // the rest comes with the block of the layer below
     if (wg) {
-        gemm_wgrad(n, 3 * F, F, b.gphi, 3 * F, lb.zphi, F, dtheta + lo.W2, b.chunk_part, kChunk, false, s);
-        colsum(n, 3 * F, b.gphi, 3 * F, dtheta + lo.b2, b.chunk_part, kChunk, false, s);
+        gemm_wgrad(n, 3 * F, F, b.gphi, 3 * F, lb.zphi, F, dtheta + lo.W2, b.chunk_part, chunk, false, s);
+        colsum(n, 3 * F, b.gphi, 3 * F, dtheta + lo.b2, b.chunk_part, chunk, false, s);
     }
     gemm_gwt(m, lo.W2, n, 3 * F, F, b.gphi, 3 * F, b.gh1, F, EPI_DSILU, lb.h1, F, false, s);
     if (wg) {
-        gemm_wgrad(n, F, F, b.gh1, F, b.s[l], F, dtheta + lo.W1, b.chunk_part, kChunk, false, s);
-        colsum(n, F, b.gh1, F, dtheta + lo.b1, b.chunk_part, kChunk, false, s);
+        gemm_wgrad(n, F, F, b.gh1, F, b.s[l], F, dtheta + lo.W1, b.chunk_part, chunk, false, s);
+        colsum(n, F, b.gh1, F, dtheta + lo.b1, b.chunk_part, chunk, false, s);
     }
     gemm_gwt(m, lo.W1, n, F, F, b.gh1, F, b.gs2, F, EPI_NONE, nullptr, 0, true, s);  // g_s_in
     std::swap(b.gs, b.gs2);
@@ -838,6 +839,7 @@ void nc_wgrad(const Model* m, const nnp_system& sys, const RepGeom& geom, const 
     const int F = m->desc.width;
     const int nl_ = m->desc.n_l;
     const int HC = 2 * (m->desc.n_s + m->desc.n_l) * m->desc.n_c;
+    const int chunk = grad_chunk(3 * int64_t(n));
     MpGeom mg = make_geom(m, sys, geom, nl);
     embed_forward(m, sys, mg, b, s);
     gemm_xwt(n, HC, F, b.s[1], F, m->p(m->off_Wq), nullptr, b.QK, HC, EPI_NONE, nullptr, 0, false, s, m->bf16(),
@@ -845,9 +847,9 @@ void nc_wgrad(const Model* m, const nnp_system& sys, const RepGeom& geom, const 
     gemm_xwt(3 * n, nl_, F, b.v[1], F, m->p(m->off_WV), nullptr, b.Vh, nl_, EPI_NONE, nullptr, 0, false, s, m->bf16(),
              m->px(m->off_WV), m->wx_stride());
     launch_head_bwd(mg, b.QK, b.Vh, dl_df, b.gQK, b.gVh, s);
-    gemm_wgrad(n, HC, F, b.gQK, HC, b.s[1], F, dtheta + m->off_Wq, b.chunk_part, kChunk, false, s);
+    gemm_wgrad(n, HC, F, b.gQK, HC, b.s[1], F, dtheta + m->off_Wq, b.chunk_part, chunk, false, s);
     gemm_gwt(m, m->off_Wq, n, HC, F, b.gQK, HC, b.gs, F, EPI_NONE, nullptr, 0, false, s);
-    gemm_wgrad(3 * n, nl_, F, b.gVh, nl_, b.v[1], F, dtheta + m->off_WV, b.chunk_part, kChunk, false, s);
+    gemm_wgrad(3 * n, nl_, F, b.gVh, nl_, b.v[1], F, dtheta + m->off_WV, b.chunk_part, chunk, false, s);
     gemm_gwt(m, m->off_WV, 3 * n, nl_, F, b.gVh, nl_, b.gv, F, EPI_NONE, nullptr, 0, false, s);
     layer_backward(m, 0, mg, b, nullptr, false, dtheta, s);
 }

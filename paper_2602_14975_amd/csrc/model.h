@@ -2,16 +2,12 @@
 #pragma once
 
 #include "common.h"
+#include "grad_chunk.h"
 #include "kernels.h"
 
 namespace nnp {
 
 constexpr int kMaxLayers = 4;
-// rows per partial sum in weight adjoints: the outputs are small (at most a
-// few 64 x 64 tiles), so the chunks of rows are what fills the chip.  24,576
-// frames' rows: 96 chunks; with 2,048 rows, 12 to 36 blocks per product took
-// 53 us each and the column sums 100 us.
-constexpr int kChunk = 256;
 
 struct LayerOff {
     int64_t W1, b1, W2, b2, Wr, br, U, V, M1, m1, M2, m2;
