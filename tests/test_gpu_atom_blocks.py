@@ -1,6 +1,7 @@
-"""Per-atom blocks of width-128 conservative models (tiles of 32 atoms) at the
-edges of their tiles: parity with the FP64 oracle and with the older dense
-kernels, one to four layers, packed replicas, and the same bits every time."""
+"""Per-atom blocks of width-128 conservative models at sizes in tiles of 16
+atoms, around multiples of 32: parity with the FP64 oracle and with the older
+dense kernels, one to four layers, packed replicas, and the same bits every
+time.  (Tiles of 32 atoms: test_gpu_atom_tiles.py, test_gpu_atom_last_tiles.py.)"""
 
 import numpy as np
 import pytest
