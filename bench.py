@@ -74,7 +74,7 @@ def message_counts(F, K, n_atoms, n_edges, reverse):
 # while the other launches of the step run untimed, so that the host keeps
 # ahead of the device as in production (the dominant kernel alone first)
 TIMER_GROUPS = (("message_bwd",), ("message_fwd",), ("message_fwd_first", "message_bwd_first"),
-                ("nc_message_fwd", "nc_update", "head_fwd", "baoa"), ("gemm",))
+                ("nc_message_fwd", "head_fwd", "baoa"), ("gemm",))
 
 
 def run_gpu(args):
@@ -520,7 +520,7 @@ def main():
         flops, nbytes = message_counts(F, K, s.n, g["n_edges5"], reverse=False)
         kernels["message_fwd"] = roofline_entry("k_message_fwd_mx (conservative message forward, layers 2-3)",
                                                 *kt["message_fwd"], flops, nbytes)
-    for site in ("message_fwd_first", "message_bwd_first", "nc_message_fwd", "nc_update", "head_fwd", "baoa", "gemm"):
+    for site in ("message_fwd_first", "message_bwd_first", "nc_message_fwd", "head_fwd", "baoa", "gemm"):
         if kt.get(site, (0, 0))[1] > 0:
             tot, cnt = kt[site]
             kernels[site] = {"avg_launch_us": round(tot / cnt * 1e3, 2), "launches": cnt,
