@@ -402,17 +402,19 @@ void Model::refresh_tables(hipStream_t s) {
             auto add = [&](int64_t off, int id, int tr) {
                 P.m[c++] = {p(off), frag(l, id), kFragRows[id], kFragK[id], tr};
             };
+            if (l > 0) {
+                add(ll.W1, kW1, 0);
+                add(ll.W2, kW2, 0);
+                add(ll.W1, kW1t, 1);
+                add(ll.W2, kW2t, 1);
+            }
             add(ll.U, kUV, 0);
             add(ll.M1, kM1, 0);
             add(ll.M2, kM2, 0);
-            add(ll.W1, kW1, 0);
-            add(ll.W2, kW2, 0);
             add(ll.U, kUt, 1);
             add(ll.V, kVt, 1);
             add(ll.M1, kM1t, 1);
             add(ll.M2, kM2t, 1);
-            add(ll.W1, kW1t, 1);
-            add(ll.W2, kW2t, 1);
             launch_pack_frags(P, c, frag_pieces(), s);
         }
         PackFrags P{};

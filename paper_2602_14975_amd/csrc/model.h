@@ -78,25 +78,28 @@ struct Model {
     }
     // Conservative models of width 128: the matrices of the per-atom blocks
     // as operand fragments (launch_pack_frags), three bfloat16 pieces for
-    // FP32 models and one for BF16 models.
+    // FP32 models and one for BF16 models.  Those of the phi perceptron come
+    // first, and the first layer, whose phi is the species table's, has none.
     uint16_t* wf = nullptr;
-    enum Frag { kUV, kM1, kM2, kW1, kW2, kUt, kVt, kM1t, kM2t, kW1t, kW2t, kFrags };
-    static constexpr int kFragRows[kFrags] = {256, 128, 384, 128, 384, 128, 128, 256, 128, 128, 128};
-    static constexpr int kFragK[kFrags] = {128, 256, 128, 128, 128, 128, 128, 128, 384, 128, 384};
+    enum Frag { kW1, kW2, kW1t, kW2t, kUV, kM1, kM2, kUt, kVt, kM1t, kM2t, kFrags };
+    static constexpr int kFragRows[kFrags] = {128, 384, 128, 128, 256, 128, 384, 128, 128, 256, 128};
+    static constexpr int kFragK[kFrags] = {128, 128, 128, 384, 128, 256, 128, 128, 128, 128, 384};
     int frag_pieces() const { return bf16() ? 1 : 3; }
     static int64_t frag_prefix(int id) {
         int64_t o = 0;
         for (int k = 0; k < id; ++k) o += int64_t(kFragRows[k]) * kFragK[k];
         return o;
     }
+    int64_t frag_layers() const { return n_layers() * frag_prefix(kFrags) - frag_prefix(kUV); }
     int64_t frag_count() const {
-        return frag_pieces() * (n_layers() * frag_prefix(kFrags) + 2 * int64_t(desc.width) * desc.width +
-                                (frag_species() ? sp_count() : 0));
+        return frag_pieces() *
+               (frag_layers() + 2 * int64_t(desc.width) * desc.width + (frag_species() ? sp_count() : 0));
     }
-    uint16_t* frag(int l, int id) const { return wf + frag_pieces() * (l * frag_prefix(kFrags) + frag_prefix(id)); }
+    uint16_t* frag(int l, int id) const {
+        return wf + frag_pieces() * (l * frag_prefix(kFrags) + frag_prefix(id) - frag_prefix(kUV));
+    }
     uint16_t* frag_Wo(bool transposed) const {
-        return wf + frag_pieces() * (n_layers() * frag_prefix(kFrags) +
-                                     (transposed ? int64_t(desc.width) * desc.width : 0));
+        return wf + frag_pieces() * (frag_layers() + (transposed ? int64_t(desc.width) * desc.width : 0));
     }
     // FP32 models with up to 128 slots of species: the tables of the first
     // layer for its blocks, T_c [F][128] and their transposes [pp][F]
