@@ -1103,15 +1103,18 @@ __global__ void __launch_bounds__(256) k_edge_force(MpGeom mg, const float4* __r
     for (int e = lane; e < cnt; e += 64) {
         const EdgeRec rec = mg.erec[start + e];
         const float4 own = edge_f[start + e];
-        int lo = mg.off[rec.j];
-        const int end = lo + mg.ecnt[rec.j];
+        const int row = mg.off[rec.j], end = row + mg.ecnt[rec.j];
+        int lo = row;
         for (int hi = end; lo < hi;) {
             const int mid = (lo + hi) >> 1;
             if (mg.edge_key[mid] < key) lo = mid + 1;
             else hi = mid;
         }
+        // a caller's list whose rows do not ascend: entry by entry
+        if (lo >= end || mg.edge_key[lo] != key)
+            for (lo = row; lo < end && mg.edge_key[lo] != key;) ++lo;
         float4 got = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (lo < end && mg.edge_key[lo] == key) got = edge_f[lo];
+        if (lo < end) got = edge_f[lo];
         const float S = own.x + got.x;
         const float tx = own.y - got.y, ty = own.z - got.z, tz = own.w - got.w;
         const float tu = fmaf(tz, rec.u[2], fmaf(ty, rec.u[1], tx * rec.u[0]));
