@@ -47,9 +47,9 @@ constexpr int kMpWaves = 4;
 
 // Stages one batch of edges of atom i (lane l of its group takes entry e)
 // into LDS; returns the number of surviving edges of this group.
-template <int G, int K, int CUT, bool DERIV>
+template <int G, int K, int CUT, bool DERIV, typename Slot>
 __device__ __forceinline__ int stage_batch(const MpGeom& mg, bool active, int e, int e_end, int l, int g, double xi,
-                                           double yi, double zi, double L, double inv, EdgeSlot<K>* slots,
+                                           double yi, double zi, double L, double inv, Slot* slots,
                                            const int* species) {
     bool ok = false;
     double dx = 0, dy = 0, dz = 0;
@@ -64,7 +64,7 @@ __device__ __forceinline__ int stage_batch(const MpGeom& mg, bool active, int e,
     const uint64_t mine = bal & gmask;
     const int pre = __popcll(mine & ((1ull << (g * G + l)) - 1ull));
     if (ok) {
-        EdgeSlot<K>& s = slots[pre];
+        Slot& s = slots[pre];
         if constexpr (CUT == 1 && !DERIV) {
             // NC forward: radial values in float32
             const float r = sqrtf(float((dx * dx + dy * dy) + dz * dz));
@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(64 * kMpWaves)
 k_message_fwd(MpGeom mg, MpFwd a) {
     using S = MpShape<F>;
     constexpr int G = S::G, APW = S::APW, WPA = S::WPA, FPL = 1;
-    __shared__ EdgeSlot<K> slots_all[S::SLOT_SETS][APW][G];
+    __shared__ EdgeSlot<K, false> slots_all[S::SLOT_SETS][APW][G];
     __shared__ int batch_cnt[S::SLOT_SETS];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = lane / G, l = lane % G;
@@ -159,7 +159,7 @@ k_message_fwd(MpGeom mg, MpFwd a) {
     const bool active = i < mg.n;
     const int n = mg.n;
     const int f0 = (w % WPA) * 64 + l;
-    EdgeSlot<K>* slots = slots_all[S::SHARED ? w / WPA : w][g];
+    EdgeSlot<K, false>* slots = slots_all[S::SHARED ? w / WPA : w][g];
 
     float wr[3][FPL][K], bb[3][FPL];
 #pragma unroll
@@ -198,7 +198,7 @@ k_message_fwd(MpGeom mg, MpFwd a) {
         }
 #pragma unroll 1
         for (int t = 0; t < cnt; ++t) {
-            const EdgeSlot<K>& s = slots[t];
+            const EdgeSlot<K, false>& s = slots[t];
             const float* phj = L0 ? a.phi_tab + s.t * 3 * F + f0 : a.phi + int64_t(s.j) * 3 * F + f0;
             const Vec<FPL> pa = ldv<FPL>(phj), pb = ldv<FPL>(phj + F), pc = ldv<FPL>(phj + 2 * F);
             Vec<FPL> v0{}, v1{}, v2{};
@@ -259,7 +259,7 @@ k_message_bwd(MpGeom mg, MpBwd a) {
     using S = MpShape<F>;
     constexpr int G = S::G, APW = S::APW, WPA = S::WPA, FPL = 1;
     static_assert(!WGRAD || WPA == 1, "filter weight adjoints need one wavefront per atom");
-    __shared__ EdgeSlot<K> slots_all[S::SLOT_SETS][APW][G];
+    __shared__ EdgeSlot<K, true> slots_all[S::SLOT_SETS][APW][G];
     __shared__ int batch_cnt[S::SLOT_SETS];
     __shared__ float fpart[kMpWaves][APW][4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -269,7 +269,7 @@ k_message_bwd(MpGeom mg, MpBwd a) {
     const bool active = i < mg.n;
     const int n = mg.n;
     const int f0 = (w % WPA) * 64 + l;
-    EdgeSlot<K>* slots = slots_all[S::SHARED ? w / WPA : w][g];
+    EdgeSlot<K, true>* slots = slots_all[S::SHARED ? w / WPA : w][g];
 
     float wr[3][FPL][K], bb[3][FPL];
 #pragma unroll
@@ -336,7 +336,7 @@ k_message_bwd(MpGeom mg, MpBwd a) {
         }
 #pragma unroll 1
         for (int t = 0; t < cnt; ++t) {
-            const EdgeSlot<K>& s = slots[t];
+            const EdgeSlot<K, true>& s = slots[t];
             const int j = s.j;
             const float* phj = L0 ? a.phi_tab + s.t * 3 * F + f0 : a.phi + int64_t(j) * 3 * F + f0;
             const float* gvj = a.gvm + int64_t(j) * 3 * F + f0;
