@@ -987,6 +987,8 @@ namespace nnp {
 static void check_list(const nnp_nlist* nl, const nnp_system* sys, double min_cutoff) {
     NNP_REQUIRE(nl && nl->offsets && nl->nbr, NNP_EINVAL, "incomplete neighbour list");
     NNP_REQUIRE(nl->n_atoms == sys->n_atoms, NNP_EINVAL, "list rows must equal n_atoms");
+    // the room for what is kept per entry is reckoned from it
+    NNP_REQUIRE(nl->capacity >= 0, NNP_EINVAL, "list capacity must not be negative");
     NNP_REQUIRE(nl->cutoff >= min_cutoff, NNP_EINVAL, "list radius is below the model cutoff");
 }
 
