@@ -26,9 +26,8 @@
 // below) is bound by its vector arithmetic (34 operations per edge and
 // feature, 59 % of its time at 12,288 atoms) and by the rows it gathers
 // through L1 (9 loads per edge and feature, about half of it), the forward by
-// the gathers; what
-// remains is the chain product -> gather -> sums of a batch with three
-// wavefronts per SIMD to hide it.  Held out of that chain: the filter operands
+// the gathers; what remains is the chain product -> gather -> sums of a batch
+// with three wavefronts per SIMD (forward: four) to hide it.  Held out of that chain: the filter operands
 // (laid out with the weights, in LDS during the kernel), the list rows of the
 // block's atoms (in registers), the sums over lanes (no LDS).  At 12,288 atoms
 // these took the forward from 155 to 137 us (now 125) and the reverse from 255
@@ -866,8 +865,9 @@ __global__ void __launch_bounds__(64 * kMxWaves, 3) k_message_bwd_mx(MpGeom mg, 
 // 9 operations per edge and feature (all four sums of a batch's edges in one
 // exchange that halves the values at every step), the rest 20 instead of 34;
 // vector arithmetic keeps the SIMDs three quarters busy.  At 12,288 atoms a
-// layer takes 185 us instead of 240, at 1,536 26 instead of 32, and the first
-// layer in the same form (k_sp_bwd_own) with k_edge_force no more than
+// layer takes 185 us instead of 240, at 1,536 26 instead of 32 (rows in the
+// caller's order; in cell order, in which a trajectory has them, 165 instead of
+// 214 at 12,288), and the first layer in the same form (k_sp_bwd_own) with k_edge_force no more than
 // k_sp_bwd did (35 + 24 us instead of 66; 7.6 + 5.2 instead of 11.6): energy
 // and forces 1,184 -> 1,086 us and 258 -> 249.  Forces are 2 % closer to
 // float64.  The adjoints of phi and of the vector input are as above, bit for
@@ -1179,13 +1179,17 @@ __global__ void __launch_bounds__(256) k_phib_v(int n, const float* __restrict__
 }
 
 // Atoms of a block: one or two, whichever takes fewer turns (an atom's time)
-// of the 3 x 256 blocks that are in flight at once, two where that is equal
-// (half as many starts).  A block's atoms follow one another, so that with
-// fewer blocks than the chip holds the longest block is the time: reverse at
-// 192 atoms 12.6 us with one, 21.0 with two, 37 with four; at 768 21.5 / 30 /
-// 48; at 1,536 33.9 / 32.3 / 45.5 (forward 22.6 / 21.0 / 31.0); at 2,100
-// 47 / 51 / 56; at 12,288 254 / 246 / 245; at 89,373 1,822 / 1,772 / 1,785.
-// An atom's sums do not depend on it.
+// of the 3 x 256 blocks of the two-message reverse that are in flight at once,
+// two where that is equal (half as many starts).  A block's atoms follow one
+// another, so that with fewer blocks than the chip holds the longest block is
+// the time.  Measured with one and two atoms, us, rows in random order (forward;
+// reverse by one message; by both): 192 atoms 9.7 14.5; 12.1 19.4; 14.6 23.5.
+// 768: 13.5 16.4; 16.2 21.5; 19.0 26.0.  1,536: 22.1 21.5; 29.9 26.6; 34.9 33.6.
+// 2,100: 28.7 31.2; 37.6 42.5; 50.0 55.7.  3,000: 42.3 42.3; 49.9 52.6; 79.4 78.7.
+// 12,288: 215 218; 199 197; 407 416.  The forward and the reverse by one message
+// have up to 4 x 256 blocks in flight, and from 769 to 1,024 atoms one atom is
+// the faster for them (1,000: 15.4 16.7; 19.7 22.4, against 27.9 27.3): the line
+// is the two-message reverse's there.  An atom's sums do not depend on it.
 constexpr int kMxSlots = 3 * 256;
 int mx_atoms(int n) { return cdiv(n, kMxSlots) < 2 * cdiv(cdiv(n, 2), kMxSlots) ? 1 : kMxAtoms; }
 
